@@ -215,7 +215,7 @@ __global__ void k_transpose_blocks(int64_t nb, int64_t ld, const double2 *A, dou
 int mbj_transpose_run(mbem_op *op, hipStream_t s) {
     if (!op->d_minv || op->nb == 0 || op->d_minv_t) return MBEM_OK;
     const int64_t ld = 2 * (int64_t)op->B, n = (int64_t)op->nb * ld * ld;
-    MBEM_HIP(hipMalloc((void **)&op->d_minv_t, sizeof(double2) * n));
+    MBEM_HIP(dev_malloc((void **)&op->d_minv_t, sizeof(double2) * n));
     hipLaunchKernelGGL(k_transpose_blocks, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, (int64_t)op->nb, ld,
                        (const double2 *)op->d_minv, op->d_minv_t);
     MBEM_HIP(hipGetLastError());

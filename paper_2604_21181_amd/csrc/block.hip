@@ -755,10 +755,10 @@ struct BlockWork {
     double *res = nullptr;     // [ncol]
     int *flags = nullptr;
     std::vector<void *> owned;
-    ~BlockWork() { for (void *q : owned) (void)hipFree(q); }
+    ~BlockWork() { for (void *q : owned) (void)dev_free(q); }
     template <typename T>
     int get(T **p, size_t n) {
-        hipError_t e = hipMalloc((void **)p, sizeof(T) * std::max<size_t>(n, 1));
+        hipError_t e = dev_malloc((void **)p, sizeof(T) * std::max<size_t>(n, 1));
         if (e != hipSuccess) { set_error(std::string("block solve workspace: ") + hipGetErrorString(e)); return MBEM_ENOMEM; }
         owned.push_back(*p);
         return MBEM_OK;
@@ -880,7 +880,7 @@ int ensure_c64_copy(mbem_op *op, hipStream_t s) {
     if (op->prec == MBEM_MIXED || op->K32[0]) return MBEM_OK;
     const int64_t n = op->n2 * op->n2;
     for (int q = 0; q < 3; ++q) {
-        hipError_t e = hipMalloc(&op->K32[q], sizeof(float2) * n);
+        hipError_t e = dev_malloc(&op->K32[q], sizeof(float2) * n);
         if (e != hipSuccess) { set_error("complex64 operator copy: out of memory"); return MBEM_ENOMEM; }
         hipLaunchKernelGGL(k_c128_to_c64, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
                            (const double2 *)op->K[q], (float2 *)op->K32[q], n);
@@ -991,12 +991,12 @@ int block_solve_run(mbem_op *op, const double2 *B, int ncol, const mbem_block_op
     std::vector<double> bn(ncol), rn(ncol);
     // the per-iteration residual norms come back through pinned memory
     double *resh = nullptr;
-    MBEM_HIP(hipHostMalloc((void **)&resh, sizeof(double) * ncol, hipHostMallocDefault));
+    MBEM_HIP(pin_malloc((void **)&resh, sizeof(double) * ncol));
     struct PinnedFree {
         double *p;
         hipStream_t st;
         ~PinnedFree() {
-            if (p) { (void)hipStreamSynchronize(st); (void)hipHostFree(p); }
+            if (p) { (void)hipStreamSynchronize(st); (void)pin_free(p); }
         }
     } resh_guard{resh, s};
     MBEM_TRY(zero(X, (int64_t)ncol * N, s));

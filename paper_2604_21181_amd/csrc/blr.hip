@@ -42,10 +42,10 @@ struct BlrOp {
 void blr_free(BlrOp *b) {
     if (!b) return;
     for (void *p : b->store)
-        if (p) (void)hipFree(p);
+        if (p) (void)dev_free(p);
     void *ps[] = {b->d_tiles, b->d_lr, b->d_w, b->d_cl_of, b->d_z, b->d_dense};
     for (void *p : ps)
-        if (p) (void)hipFree(p);
+        if (p) (void)dev_free(p);
     delete b;
 }
 
@@ -474,12 +474,12 @@ struct Scratch {
     std::vector<void *> p;
     ~Scratch() {
         for (void *q : p)
-            if (q) (void)hipFree(q);
+            if (q) (void)dev_free(q);
     }
     template <typename T>
     int alloc(T **out, size_t n) {
         *out = nullptr;
-        hipError_t e = hipMalloc((void **)out, sizeof(T) * std::max<size_t>(n, 1));
+        hipError_t e = dev_malloc((void **)out, sizeof(T) * std::max<size_t>(n, 1));
         if (e != hipSuccess) {
             set_error(std::string("block low-rank assembly: ") + hipGetErrorString(e));
             return MBEM_ENOMEM;
@@ -618,7 +618,7 @@ int blr_fill_run(mbem_op *op, const mbem_blr_opts *o, mbem_blr_stats *bs, hipStr
     b->L = L;
     b->nc = nc;
     b->start = start;
-    if (hipMalloc((void **)&b->d_cl_of, sizeof(int32_t) * nn) != hipSuccess) {
+    if (dev_malloc((void **)&b->d_cl_of, sizeof(int32_t) * nn) != hipSuccess) {
         set_error("block low-rank tables: device allocation");
         return MBEM_ENOMEM;
     }
@@ -711,7 +711,7 @@ int blr_fill_run(mbem_op *op, const mbem_blr_opts *o, mbem_blr_stats *bs, hipStr
         }
         double2 *store = nullptr;
         if (elems > 0) {
-            hipError_t e = hipMalloc((void **)&store, sizeof(double2) * elems);
+            hipError_t e = dev_malloc((void **)&store, sizeof(double2) * elems);
             if (e != hipSuccess) {
                 set_error(std::string("block low-rank storage: ") + hipGetErrorString(e));
                 return MBEM_ENOMEM;
@@ -786,11 +786,11 @@ int blr_fill_run(mbem_op *op, const mbem_blr_opts *o, mbem_blr_stats *bs, hipStr
     }
     b->n_lr = (int32_t)lr.size();
     b->n_dense = (int32_t)dn.size();
-    hipError_t e1 = hipMalloc((void **)&b->d_tiles, sizeof(BlrTile) * b->tiles.size());
-    hipError_t e2 = hipMalloc((void **)&b->d_lr, sizeof(int32_t) * std::max<size_t>(1, lr.size()));
-    hipError_t e3 = hipMalloc((void **)&b->d_w, sizeof(double2) * std::max<int64_t>(1, w));
-    hipError_t e4 = hipMalloc((void **)&b->d_z, sizeof(double2) * std::max<int64_t>(1, zz));
-    hipError_t e5 = hipMalloc((void **)&b->d_dense, sizeof(int32_t) * std::max<size_t>(1, dn.size()));
+    hipError_t e1 = dev_malloc((void **)&b->d_tiles, sizeof(BlrTile) * b->tiles.size());
+    hipError_t e2 = dev_malloc((void **)&b->d_lr, sizeof(int32_t) * std::max<size_t>(1, lr.size()));
+    hipError_t e3 = dev_malloc((void **)&b->d_w, sizeof(double2) * std::max<int64_t>(1, w));
+    hipError_t e4 = dev_malloc((void **)&b->d_z, sizeof(double2) * std::max<int64_t>(1, zz));
+    hipError_t e5 = dev_malloc((void **)&b->d_dense, sizeof(int32_t) * std::max<size_t>(1, dn.size()));
     if (e1 != hipSuccess || e2 != hipSuccess || e3 != hipSuccess || e4 != hipSuccess || e5 != hipSuccess) {
         set_error("block low-rank tables: device allocation");
         return MBEM_ENOMEM;

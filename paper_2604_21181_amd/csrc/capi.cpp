@@ -46,7 +46,7 @@ int wait_host_tag(const unsigned long long *tag, unsigned long long seq, hipStre
 template <typename T>
 static int dalloc(T **p, size_t n) {
     if (n == 0) n = 1;
-    hipError_t e = hipMalloc((void **)p, sizeof(T) * n);
+    const hipError_t e = dev_malloc((void **)p, sizeof(T) * n);
     if (e != hipSuccess) {
         set_error(std::string("hipMalloc: ") + hipGetErrorString(e));
         return MBEM_ENOMEM;
@@ -62,7 +62,7 @@ static int upload(T **p, const std::vector<T> &v, hipStream_t s) {
 }
 
 static void dfree(void *p) {
-    if (p) (void)hipFree(p);
+    if (p) (void)dev_free(p);
 }
 
 // Frees a device allocation when the scope ends (error returns included).
@@ -92,6 +92,7 @@ struct Timer {
 static int set_device(const mbem_ctx *ctx) {
     if (!ctx) { set_error("null context"); return MBEM_EINVAL; }
     MBEM_HIP(hipSetDevice(ctx->device));
+    pool_use(ctx->pool);
     return MBEM_OK;
 }
 
@@ -116,7 +117,7 @@ static void op_free_device(mbem_op *op) {
     dfree(op->d_work);
     dfree(op->d_kconst);
     dfree(op->d_rtab);
-    if (op->h_pin) (void)hipHostFree(op->h_pin);
+    if (op->h_pin) (void)pin_free(op->h_pin);
     op->h_pin = nullptr;
     blr_free(op->blr);
     op->blr = nullptr;
@@ -160,7 +161,7 @@ struct Gmres {
             if (ev0[i]) (void)hipEventDestroy(ev0[i]);
             if (ev1[i]) (void)hipEventDestroy(ev1[i]);
         }
-        if (tpart) (void)hipFree(tpart);
+        if (tpart) (void)dev_free(tpart);
     }
     int apply(const double2 *x, double2 *y) {   // y = Z x or Z^T x
         return trans ? matvec_t_run(op, x, y, tpart, s) : matvec_run(op, x, y, tmp, s);
@@ -215,11 +216,10 @@ static int gmres_alloc(Gmres &g, const mbem_op *op, int maxit, hipStream_t s) {
     // kernels straight into fine-grained host memory, then y
     const size_t pin = 2 * (col + 1) + (size_t)maxit;
     if (op->pin_elems < pin) {
-        if (mop->h_pin) (void)hipHostFree(mop->h_pin);
+        if (mop->h_pin) (void)pin_free(mop->h_pin);
         mop->h_pin = nullptr;
         mop->pin_elems = 0;
-        MBEM_HIP(hipHostMalloc((void **)&mop->h_pin, sizeof(double2) * pin,
-                               hipHostMallocMapped | hipHostMallocCoherent));
+        MBEM_HIP(pin_malloc((void **)&mop->h_pin, sizeof(double2) * pin, true));
         mop->pin_elems = pin;
     }
     g.hpin[0] = op->h_pin;
@@ -484,11 +484,17 @@ int mbem_ctx_create(int device, void *hip_stream, mbem_ctx **out) {
     if (!c) { set_error("host allocation"); return MBEM_ENOMEM; }
     c->device = device;
     c->stream = (hipStream_t)hip_stream;
+    c->pool = pool_create(device);
+    if (!c->pool) { delete c; set_error("host allocation"); return MBEM_ENOMEM; }
     *out = c;
     return MBEM_OK;
 }
 
-void mbem_ctx_destroy(mbem_ctx *ctx) { delete ctx; }
+void mbem_ctx_destroy(mbem_ctx *ctx) {
+    if (!ctx) return;
+    pool_destroy(ctx->pool);
+    delete ctx;
+}
 
 int mbem_morton_order(const double *xyz, int64_t n_nodes, const int64_t *tri6, int64_t n_tris,
                       int64_t *node_order, int64_t *tri_order) {
@@ -551,8 +557,8 @@ int mbem_mesh_create(mbem_ctx *ctx, const double *xyz, int64_t n_nodes, const in
 
 void mbem_mesh_destroy(mbem_mesh *m) {
     if (!m) return;
-    if (m->ctx) (void)hipSetDevice(m->ctx->device);
-    if (m->ctx) (void)hipStreamSynchronize(m->ctx->stream);
+    // any context may have used the mesh: its memory is handed out again
+    if (m->ctx) { (void)hipSetDevice(m->ctx->device); (void)hipDeviceSynchronize(); }
     mesh_free_device(m);
     delete m;
 }
@@ -632,7 +638,7 @@ static int op_create(mbem_ctx *ctx, const mbem_mesh *mesh, const mbem_params *p,
     const size_t esz = op->prec == MBEM_FP64 ? 16 : 8;
     int st = MBEM_OK;
     for (int o = 0; o < 3 && st == MBEM_OK && dense; ++o) {
-        hipError_t e = hipMalloc(&op->K[o], esz * op->n2 * op->n2);
+        hipError_t e = dev_malloc(&op->K[o], esz * op->n2 * op->n2);
         if (e != hipSuccess) { set_error(std::string("operator allocation: ") + hipGetErrorString(e)); st = MBEM_ENOMEM; }
     }
     if (st == MBEM_OK) st = dalloc(&op->d_mval, 4 * mesh->m_col.size());   // 2 x 2 per node pair
@@ -707,7 +713,8 @@ int mbem_fill_compressed(mbem_ctx *ctx, const mbem_mesh *mesh, const mbem_params
 
 void mbem_op_destroy(mbem_op *op) {
     if (!op) return;
-    if (op->ctx) { (void)hipSetDevice(op->ctx->device); (void)hipStreamSynchronize(op->ctx->stream); }
+    // any context may have used the operator: its memory is handed out again
+    if (op->ctx) { (void)hipSetDevice(op->ctx->device); (void)hipDeviceSynchronize(); }
     op_free_device(op);
     delete op;
 }

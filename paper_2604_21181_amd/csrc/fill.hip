@@ -1387,10 +1387,10 @@ static int nodal_table_run(mbem_op *op, const T *qp, hipStream_t s) {
     const mbem_mesh *m = op->mesh;
     const size_t bytes = sizeof(T) * (size_t)m->nt * NQ * 24;
     if (op->rtab_bytes < bytes) {
-        if (op->d_rtab) MBEM_HIP(hipFree(op->d_rtab));
+        if (op->d_rtab) MBEM_HIP(dev_free(op->d_rtab));
         op->d_rtab = nullptr;
         op->rtab_bytes = 0;
-        MBEM_HIP(hipMalloc(&op->d_rtab, bytes));
+        MBEM_HIP(dev_malloc(&op->d_rtab, bytes));
         op->rtab_bytes = bytes;
     }
     const int64_t n = m->nt * NQ * 24;
@@ -1579,9 +1579,9 @@ void fill_state_free(FillState *f) {
     if (!f) return;
     for (auto &e : f->ev)
         if (e) (void)hipEventDestroy(e);
-    if (f->h_k) (void)hipHostFree(f->h_k);
-    if (f->h_cnt) (void)hipHostFree(f->h_cnt);
-    if (f->d_cnt) (void)hipFree(f->d_cnt);
+    if (f->h_k) (void)pin_free(f->h_k);
+    if (f->h_cnt) (void)pin_free(f->h_cnt);
+    if (f->d_cnt) (void)dev_free(f->d_cnt);
     delete f;
 }
 
@@ -1591,9 +1591,9 @@ static int fill_state(mbem_op *op, FillState **out) {
         if (!f) { set_error("host allocation"); return MBEM_ENOMEM; }
         op->fs = f;
         for (auto &e : f->ev) MBEM_HIP(hipEventCreate(&e));
-        MBEM_HIP(hipHostMalloc((void **)&f->h_k, 3 * sizeof(KernelConst), hipHostMallocDefault));
-        MBEM_HIP(hipHostMalloc((void **)&f->h_cnt, sizeof(unsigned long long), hipHostMallocDefault));
-        MBEM_HIP(hipMalloc((void **)&f->d_cnt, sizeof(unsigned long long)));
+        MBEM_HIP(pin_malloc((void **)&f->h_k, 3 * sizeof(KernelConst)));
+        MBEM_HIP(pin_malloc((void **)&f->h_cnt, sizeof(unsigned long long)));
+        MBEM_HIP(dev_malloc((void **)&f->d_cnt, sizeof(unsigned long long)));
     }
     *out = op->fs;
     return MBEM_OK;
@@ -1607,7 +1607,7 @@ int fill_prepare(mbem_op *op, hipStream_t s, bool deriv) {
     if (f->pending) MBEM_HIP(hipEventSynchronize(f->ev[5]));
     // [0]: the kernels of the regular pairs, [1]: the kernels of the singular
     // pairs, [2]: the remainders (paper's scheme)
-    if (!op->d_kconst) MBEM_HIP(hipMalloc((void **)&op->d_kconst, 3 * sizeof(KernelConst)));
+    if (!op->d_kconst) MBEM_HIP(dev_malloc((void **)&op->d_kconst, 3 * sizeof(KernelConst)));
     f->h_k[0] = make_kconst(op, deriv);
     f->h_k[1] = f->h_k[0];
     f->h_k[2] = KernelConst{};

@@ -937,8 +937,8 @@ int mbj_setup_run(mbem_op *op, int B, hipStream_t s, bool keep) {
     // the transposed inverses belong to the previous blocks (and so does the
     // complex64 copy, which is rewritten below; its allocation is kept when
     // the size matches)
-    if (op->d_minv_t) { MBEM_HIP(hipFree(op->d_minv_t)); op->d_minv_t = nullptr; }
-    if (op->d_minv_t32) { MBEM_HIP(hipFree(op->d_minv_t32)); op->d_minv_t32 = nullptr; }
+    if (op->d_minv_t) { MBEM_HIP(dev_free(op->d_minv_t)); op->d_minv_t = nullptr; }
+    if (op->d_minv_t32) { MBEM_HIP(dev_free(op->d_minv_t32)); op->d_minv_t32 = nullptr; }
     op->B = 0; op->nb = 0;
     if (B > kMaxBlock) { set_error("preconditioner block above 512 is not supported"); return MBEM_EINVAL; }
     const int64_t n2 = op->n2;
@@ -949,15 +949,15 @@ int mbj_setup_run(mbem_op *op, int B, hipStream_t s, bool keep) {
     // factors and pivots in one scratch allocation: [nb][ld][ld] + [nb][ld] + info
     const size_t lu_bytes = B > 0 ? bytes + sizeof(int32_t) * (nb * ld + 1) : 0;
     if (op->d_minv && op->minv_bytes != bytes) {
-        MBEM_HIP(hipFree(op->d_minv)); op->d_minv = nullptr; op->minv_bytes = 0;
-        if (op->d_minv32) { MBEM_HIP(hipFree(op->d_minv32)); op->d_minv32 = nullptr; }
+        MBEM_HIP(dev_free(op->d_minv)); op->d_minv = nullptr; op->minv_bytes = 0;
+        if (op->d_minv32) { MBEM_HIP(dev_free(op->d_minv32)); op->d_minv32 = nullptr; }
     }
     if (op->d_lu && op->lu_bytes != lu_bytes) {
-        MBEM_HIP(hipFree(op->d_lu)); op->d_lu = nullptr; op->lu_bytes = 0;
+        MBEM_HIP(dev_free(op->d_lu)); op->d_lu = nullptr; op->lu_bytes = 0;
     }
     if (B <= 0) return MBEM_OK;
-    if (!op->d_lu) { MBEM_HIP(hipMalloc((void **)&op->d_lu, lu_bytes)); op->lu_bytes = lu_bytes; }
-    if (!op->d_minv) { MBEM_HIP(hipMalloc((void **)&op->d_minv, bytes)); op->minv_bytes = bytes; }
+    if (!op->d_lu) { MBEM_HIP(dev_malloc((void **)&op->d_lu, lu_bytes)); op->lu_bytes = lu_bytes; }
+    if (!op->d_minv) { MBEM_HIP(dev_malloc((void **)&op->d_minv, bytes)); op->minv_bytes = bytes; }
     int32_t *piv = (int32_t *)((char *)op->d_lu + bytes);
     int32_t *info = piv + nb * ld;
     MBEM_HIP(hipMemsetAsync(info, 0, sizeof(int32_t), s));
@@ -977,11 +977,11 @@ int mbj_setup_run(mbem_op *op, int B, hipStream_t s, bool keep) {
     int32_t *swp = nullptr;
     if (ld >= kMbjGemmMin) {
         // panels on one workgroup per block, updates on the whole chip
-        MBEM_HIP(hipMalloc((void **)&UT, sizeof(double2) * nb * ld * kMbjPW + sizeof(int32_t) * nb * ld));
+        MBEM_HIP(dev_malloc((void **)&UT, sizeof(double2) * nb * ld * kMbjPW + sizeof(int32_t) * nb * ld));
         swp = (int32_t *)(UT + (int64_t)nb * ld * kMbjPW);
         const int n_last = (int)(2 * (n2 - (int64_t)(nb - 1) * B));
         const int st = mbj_factor_invert_gemm((int)ld, nb, n_last, op->d_lu, swp, piv, info, UT, op->d_minv, s);
-        if (st != MBEM_OK) { (void)hipStreamSynchronize(s); (void)hipFree(UT); return st; }
+        if (st != MBEM_OK) { (void)hipStreamSynchronize(s); (void)dev_free(UT); return st; }
     } else if (ld <= 512) {
         hipLaunchKernelGGL((k_mbj_lu<512, 8>), dim3(nb), dim3(1024), 0, s, n2, B, op->d_lu, piv, info);
         MBEM_HIP(hipGetLastError());
@@ -997,14 +997,14 @@ int mbj_setup_run(mbem_op *op, int B, hipStream_t s, bool keep) {
     int32_t h = 0;
     MBEM_HIP(hipMemcpyAsync(&h, info, sizeof(h), hipMemcpyDeviceToHost, s));
     MBEM_HIP(hipStreamSynchronize(s));
-    if (UT) MBEM_HIP(hipFree(UT));
-    if (!keep) { MBEM_HIP(hipFree(op->d_lu)); op->d_lu = nullptr; op->lu_bytes = 0; }
+    if (UT) MBEM_HIP(dev_free(UT));
+    if (!keep) { MBEM_HIP(dev_free(op->d_lu)); op->d_lu = nullptr; op->lu_bytes = 0; }
     if (h) {
         set_error("zero pivot in preconditioner block " + std::to_string(h - 1));
-        MBEM_HIP(hipFree(op->d_minv));
+        MBEM_HIP(dev_free(op->d_minv));
         op->d_minv = nullptr;
         op->minv_bytes = 0;
-        if (op->d_minv32) { MBEM_HIP(hipFree(op->d_minv32)); op->d_minv32 = nullptr; }
+        if (op->d_minv32) { MBEM_HIP(dev_free(op->d_minv32)); op->d_minv32 = nullptr; }
         return MBEM_ESINGULAR;
     }
     op->B = B;
@@ -1022,7 +1022,7 @@ __global__ void k_round_c64(const double2 *a, float2 *b, int64_t n) {
     if (i < n) b[i] = {(float)a[i].x, (float)a[i].y};
 }
 int mbj_copy_c64(const double2 *src, float2 **dst, int64_t n, hipStream_t s) {
-    if (!*dst) MBEM_HIP(hipMalloc((void **)dst, sizeof(float2) * n));
+    if (!*dst) MBEM_HIP(dev_malloc((void **)dst, sizeof(float2) * n));
     hipLaunchKernelGGL(k_round_c64, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, src, *dst, n);
     MBEM_HIP(hipGetLastError());
     return MBEM_OK;

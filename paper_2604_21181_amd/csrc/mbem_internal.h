@@ -13,6 +13,7 @@ namespace mbem {
 struct KernelConst;
 struct BlrOp;
 struct FillState;
+struct MemPool;
 
 // ---------------------------------------------------------------- errors --
 void set_error(const std::string &msg);
@@ -36,6 +37,18 @@ int wait_host_tag(const unsigned long long *tag, unsigned long long seq, hipStre
         int s_ = (call);                                                     \
         if (s_ != MBEM_OK) return s_;                                        \
     } while (0)
+
+// --------------------------------------------------------------- memory --
+// Device and pinned memory (pool.cpp): released blocks stay with the context
+// that the calling thread last named (pool_use, by every entry point) until
+// it is destroyed.  mapped: coherent host memory that kernels write.
+hipError_t dev_malloc(void **p, size_t n);
+hipError_t dev_free(void *p);
+hipError_t pin_malloc(void **p, size_t n, bool mapped = false);
+hipError_t pin_free(void *p);
+MemPool *pool_create(int device);
+void pool_use(MemPool *q);
+void pool_destroy(MemPool *q);
 
 // ------------------------------------------------------------ constants --
 constexpr int kQP = 7;          // regular rule points per triangle
@@ -88,6 +101,7 @@ struct NearView {
 struct mbem_ctx {
     int device = 0;
     hipStream_t stream = nullptr;
+    mbem::MemPool *pool = nullptr;
     // FP32 GEMM tile shape measured fastest for the block product of an
     // operator with n2 rows per block and ncol right-hand sides
     int64_t tuned_n2 = 0;

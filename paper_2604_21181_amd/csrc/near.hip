@@ -204,7 +204,7 @@ void near_free(mbem_op *op) {
     void *ps[] = {op->d_nbits, op->d_nwpre, op->d_nrptr, op->d_ncol, op->d_nval, op->d_nmask, op->d_ncount,
                   op->d_ntiles, op->d_ncursor};
     for (void *p : ps)
-        if (p) (void)hipFree(p);
+        if (p) (void)dev_free(p);
     op->d_nbits = nullptr; op->d_nwpre = op->d_nrptr = op->d_ncol = nullptr;
     op->d_nval = nullptr; op->d_nmask = nullptr; op->d_ncount = nullptr;
     op->d_ntiles = nullptr; op->d_ncursor = nullptr;
@@ -220,12 +220,12 @@ int near_build_run(mbem_op *op, double near_r, hipStream_t s) {
     const int ntc = (int)m->tcol_off.size() - 1, ncc = (int)m->ccol_off.size() - 1;
     const int64_t nlaunch = (int64_t)ntc * ncc;
     if (!op->d_nbits) {
-        MBEM_HIP(hipMalloc((void **)&op->d_nbits, sizeof(uint32_t) * nn * nw));
-        MBEM_HIP(hipMalloc((void **)&op->d_nwpre, sizeof(int32_t) * nn * nw));
-        MBEM_HIP(hipMalloc((void **)&op->d_nrptr, sizeof(int32_t) * (nn + 1)));
-        MBEM_HIP(hipMalloc((void **)&op->d_nmask, sizeof(uint8_t) * nt * nch));
-        MBEM_HIP(hipMalloc((void **)&op->d_ncount, sizeof(unsigned long long) * (2 + nlaunch)));
-        MBEM_HIP(hipMalloc((void **)&op->d_ncursor, sizeof(unsigned long long) * nlaunch));
+        MBEM_HIP(dev_malloc((void **)&op->d_nbits, sizeof(uint32_t) * nn * nw));
+        MBEM_HIP(dev_malloc((void **)&op->d_nwpre, sizeof(int32_t) * nn * nw));
+        MBEM_HIP(dev_malloc((void **)&op->d_nrptr, sizeof(int32_t) * (nn + 1)));
+        MBEM_HIP(dev_malloc((void **)&op->d_nmask, sizeof(uint8_t) * nt * nch));
+        MBEM_HIP(dev_malloc((void **)&op->d_ncount, sizeof(unsigned long long) * (2 + nlaunch)));
+        MBEM_HIP(dev_malloc((void **)&op->d_ncursor, sizeof(unsigned long long) * nlaunch));
         op->near_nw = nw;
     }
     MBEM_HIP(hipMemsetAsync(op->d_nbits, 0, sizeof(uint32_t) * nn * nw, s));
@@ -249,20 +249,20 @@ int near_build_run(mbem_op *op, double near_r, hipStream_t s) {
     for (int64_t L = 0; L < nlaunch; ++L) op->near_tile_off[L + 1] = op->near_tile_off[L] + (int64_t)h[2 + L];
     const int64_t ntile = op->near_tile_off[nlaunch];
     if (ntile > op->near_tile_cap) {
-        if (op->d_ntiles) { MBEM_HIP(hipFree(op->d_ntiles)); op->d_ntiles = nullptr; }
+        if (op->d_ntiles) { MBEM_HIP(dev_free(op->d_ntiles)); op->d_ntiles = nullptr; }
         op->near_tile_cap = 0;
-        if (hipMalloc((void **)&op->d_ntiles, sizeof(int2) * ntile) != hipSuccess) {
+        if (dev_malloc((void **)&op->d_ntiles, sizeof(int2) * ntile) != hipSuccess) {
             set_error("near store: out of device memory");
             return MBEM_ENOMEM;
         }
         op->near_tile_cap = ntile;
     }
     if (nnz > op->near_cap) {
-        if (op->d_ncol) { MBEM_HIP(hipFree(op->d_ncol)); op->d_ncol = nullptr; }
-        if (op->d_nval) { MBEM_HIP(hipFree(op->d_nval)); op->d_nval = nullptr; }
+        if (op->d_ncol) { MBEM_HIP(dev_free(op->d_ncol)); op->d_ncol = nullptr; }
+        if (op->d_nval) { MBEM_HIP(dev_free(op->d_nval)); op->d_nval = nullptr; }
         op->near_cap = 0;
-        if (hipMalloc((void **)&op->d_ncol, sizeof(int32_t) * (nnz > 0 ? nnz : 1)) != hipSuccess ||
-            hipMalloc((void **)&op->d_nval, sizeof(double2) * 12 * (nnz > 0 ? nnz : 1)) != hipSuccess) {
+        if (dev_malloc((void **)&op->d_ncol, sizeof(int32_t) * (nnz > 0 ? nnz : 1)) != hipSuccess ||
+            dev_malloc((void **)&op->d_nval, sizeof(double2) * 12 * (nnz > 0 ? nnz : 1)) != hipSuccess) {
             set_error("near store: out of device memory");
             return MBEM_ENOMEM;
         }

@@ -168,7 +168,7 @@ int farfield_run(const mbem_mesh *m, const mbem_params *p, const double2 *x, int
                  const double *rhat, int64_t ndir, double2 *F, hipStream_t s) {
     const int64_t nq = m->nt * kQP, n2 = 2 * m->nn;
     double *cur = nullptr;
-    MBEM_HIP(hipMallocAsync((void **)&cur, sizeof(double) * 12 * nq, s));
+    MBEM_HIP(dev_malloc((void **)&cur, sizeof(double) * 12 * nq));
     for (int r = 0; r < nrhs; ++r) {
         hipLaunchKernelGGL(k_currents, dim3((unsigned)((nq + 255) / 256)), dim3(256), 0, s, m->nt, n2,
                            m->d_qp, m->d_tri, m->d_frames, p->frame, x + (int64_t)r * 2 * n2, cur);
@@ -179,7 +179,7 @@ int farfield_run(const mbem_mesh *m, const mbem_params *p, const double2 *x, int
             MBEM_HIP(hipGetLastError());
         }
     }
-    MBEM_HIP(hipFreeAsync(cur, s));
+    MBEM_HIP(dev_free(cur));
     return MBEM_OK;
 }
 

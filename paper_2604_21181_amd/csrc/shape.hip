@@ -891,17 +891,17 @@ int shape_grad_run(const mbem_op *op, const mbem_params *p, const double2 *x, co
     const int64_t nt = m->nt, nq = nt * kQP, nn = m->nn;
     double *fields = nullptr, *qb = nullptr, *nodeb = nullptr, *nodeb_x = nullptr;
     auto cleanup = [&]() {
-        if (fields) (void)hipFree(fields);
-        if (qb) (void)hipFree(qb);
-        if (nodeb) (void)hipFree(nodeb);
-        if (nodeb_x) (void)hipFree(nodeb_x);
+        if (fields) (void)dev_free(fields);
+        if (qb) (void)dev_free(qb);
+        if (nodeb) (void)dev_free(nodeb);
+        if (nodeb_x) (void)dev_free(nodeb_x);
     };
     const bool nodal = op->p.frame == MBEM_FRAME_NODAL;
     const int kS = nodal ? kQBN : kQB;
-    if (hipMalloc((void **)&fields, sizeof(double) * 16 * nq) != hipSuccess ||
-        hipMalloc((void **)&qb, sizeof(double) * kS * nq) != hipSuccess ||
-        hipMalloc((void **)&nodeb, sizeof(double) * 9 * nn) != hipSuccess ||
-        hipMalloc((void **)&nodeb_x, sizeof(double) * 9 * nn) != hipSuccess) {
+    if (dev_malloc((void **)&fields, sizeof(double) * 16 * nq) != hipSuccess ||
+        dev_malloc((void **)&qb, sizeof(double) * kS * nq) != hipSuccess ||
+        dev_malloc((void **)&nodeb, sizeof(double) * 9 * nn) != hipSuccess ||
+        dev_malloc((void **)&nodeb_x, sizeof(double) * 9 * nn) != hipSuccess) {
         cleanup();
         set_error("shape gradient workspace: out of memory");
         return MBEM_ENOMEM;
