@@ -100,7 +100,9 @@ static void mesh_free_device(mbem_mesh *m) {
     void *ps[] = {m->d_xyz, m->d_tri, m->d_inc_ptr, m->d_inc, m->d_spairs, m->d_frames,
                   m->d_qp, m->d_qp32, m->d_elem, m->d_mptr, m->d_mcol, m->d_mslot,
                   m->d_chunks, m->d_tcol, m->d_ccol, m->d_tcolour, m->d_ccolour, m->d_qp12, m->d_qp12_32,
-                  m->d_rng_off, m->d_rng_rec, m->d_row_first, m->d_col_first};
+                  m->d_rng_off, m->d_rng_rec, m->d_row_first,
+                  m->d_pair_rec, m->d_pair_sptr, m->d_pair_srow, m->d_pair_cb,
+                  m->d_pair_rows};
     for (void *p : ps) dfree(p);
 }
 
@@ -529,6 +531,13 @@ int mbem_mesh_create(mbem_ctx *ctx, const double *xyz, int64_t n_nodes, const in
     m->nrng = (int64_t)T.rng_off.size() - 1;
     m->ccol_off = T.ccol_off;
     m->tcol_list = T.tcol_list;
+    m->pair_batches = (int32_t)(T.pair_rec.size() / kPairRec);
+    m->pair_slots = T.pair_sptr.back();
+    m->pair_band = T.pair_band;
+    m->pair_band_rows = T.pair_band_rows;
+    m->pair_row0 = T.pair_row0;
+    m->pair_ncb = (int32_t)T.pair_cb.size() - 1;
+    m->pair_rows_off = T.pair_rows_off;
     m->spairs = T.spairs;
     const int64_t nq = m->nt * kQP;
     std::vector<int32_t> tcolour(m->nt), ccolour(T.ccol_list.size());
@@ -544,7 +553,9 @@ int mbem_mesh_create(mbem_ctx *ctx, const double *xyz, int64_t n_nodes, const in
         (st = upload(&m->d_chunks, T.chunks, s)) || (st = upload(&m->d_tcol, T.tcol_list, s)) ||
         (st = upload(&m->d_ccol, T.ccol_list, s)) || (st = upload(&m->d_rng_off, T.rng_off, s)) ||
         (st = upload(&m->d_rng_rec, T.rng_rec, s)) || (st = upload(&m->d_row_first, T.row_first, s)) ||
-        (st = upload(&m->d_col_first, T.col_first, s)) ||
+        (st = upload(&m->d_pair_rec, T.pair_rec, s)) ||
+        (st = upload(&m->d_pair_sptr, T.pair_sptr, s)) || (st = upload(&m->d_pair_cb, T.pair_cb, s)) ||
+        (st = upload(&m->d_pair_srow, T.pair_srow, s)) || (st = upload(&m->d_pair_rows, T.pair_rows, s)) ||
         (st = dalloc(&m->d_frames, 9 * m->nn)) || (st = dalloc(&m->d_qp, kQPF * nq)) ||
         (st = dalloc(&m->d_qp32, kQPF * nq)) || (st = dalloc(&m->d_elem, 4 * m->nt)) ||
         (st = dalloc(&m->d_qp12, kQPF * m->nt * kQP12)) || (st = dalloc(&m->d_qp12_32, kQPF * m->nt * kQP12)))

@@ -5,10 +5,11 @@
 //    twelve weighted kernel values of every point pair go to LDS and are
 //    contracted with the shape functions in two steps (trial side, then test
 //    side after the triangles are merged by node) before being added to Z.
-//    FP64 (k_regular): one workgroup per (test triangle, chunk of 4
-//    Morton-consecutive trial triangles), one launch per (test colour, chunk
-//    colour) so that the workgroups of a launch own disjoint rows x columns
-//    of Z.  complex64 (k_regular_range): one workgroup per (test triangle,
+//    FP64 dense blocks: pairs.hip.  Compressed bands, the near store and
+//    the other complex64 fills (k_regular): one workgroup per (test
+//    triangle, chunk of 4 Morton-consecutive trial triangles), one launch per
+//    (test colour, chunk colour) so that the workgroups of a launch own
+//    disjoint rows x columns of Z.  complex64 (k_regular_range): one workgroup per (test triangle,
 //    range of 64 consecutive trial nodes), one launch per test colour, the
 //    node sums held in registers over all trial triangles of the range so
 //    that each entry is updated once per test triangle;
@@ -26,6 +27,7 @@
 #include "kappa.h"
 #include "near_store.h"
 #include "p2_device.h"
+#include "pairs.h"
 #include "ssq_map.h"
 
 namespace mbem {
@@ -82,11 +84,6 @@ struct RegArgs {
     const int2 *tiles;      // mode 4: this launch's (test triangle, chunk) tiles
     const KernelConst *K;   // device copy, staged in LDS by every workgroup
     const int32_t *row_map; // null, or node -> row node of a band buffer
-    // FP64 dense fill: the first writer (in launch order) of an entry loads
-    // nothing and stores its sum, so Z needs no clearing; first_on = 0
-    // elsewhere
-    const int32_t *row_first, *col_first;
-    int first_on;
     TS *Z[3];
 };
 
@@ -122,46 +119,6 @@ constexpr int kPairLanes = 49 * kChunk;   // 196
 // the kernel evaluations.
 constexpr int kItemsMax = 6 * 2 * 24;
 
-// P2 shape functions at the points of the 7-point rule (rule7: centroid,
-// then the two three-point orbits with (6 -+ sqrt 15)/21), evaluated at
-// compile time: n7(q, j) = N_j(xi_q, eta_q).  The literal is sqrt(15)
-// rounded to double, so the values equal those of rule7 + p2_shape.
-__host__ __device__ constexpr double n7(int q, int j) {
-    const double r15 = 3.8729833462074168851792653997824;
-    const double s = q == 0 ? 1.0 / 3.0 : (q <= 3 ? (6.0 - r15) / 21.0 : (6.0 + r15) / 21.0);
-    const int r = q == 0 ? 0 : (q - 1) % 3;
-    const double xi = q == 0 ? s : (r == 1 ? 1.0 - 2.0 * s : s);
-    const double eta = q == 0 ? s : (r == 2 ? 1.0 - 2.0 * s : s);
-    const double L0 = 1.0 - xi - eta, L1 = xi, L2 = eta;
-    return j == 0 ? L0 * (2.0 * L0 - 1.0) : j == 1 ? L1 * (2.0 * L1 - 1.0)
-         : j == 2 ? L2 * (2.0 * L2 - 1.0) : j == 3 ? 4.0 * L0 * L1
-         : j == 4 ? 4.0 * L1 * L2 : 4.0 * L2 * L0;
-}
-
-// out[j] = sum_q n7(q, j) v[q] through the symmetry of the rule: the three
-// points of an orbit carry the same weight pattern, so with the orbit sums
-// S_a = v1 + v2 + v3, S_b = v4 + v5 + v6 every vertex function is
-// N(centroid) v0 + B_a S_a + B_b S_b plus (A - B) times the value at the
-// orbit point nearest that vertex, and every mid-edge function
-// N(centroid) v0 + E_a S_a + E_b S_b plus (F - E) times the value at the
-// orbit point nearest the opposite vertex (A, B, E, F: the shape-function
-// values at the orbit points).  44 real operations instead of 84.
-template <typename T>
-__host__ __device__ inline void contract7(const cx<T> v[7], cx<T> out[6]) {
-    constexpr double c0v = n7(0, 0), c0e = n7(0, 3);
-    constexpr double Ba = n7(2, 0), Bb = n7(5, 0), Da = n7(1, 0) - Ba, Db = n7(4, 0) - Bb;
-    constexpr double Ea = n7(1, 3), Eb = n7(4, 3), Ga = n7(3, 3) - Ea, Gb = n7(6, 3) - Eb;
-    const cx<T> Sa = v[1] + v[2] + v[3], Sb = v[4] + v[5] + v[6];
-    const cx<T> V = (T)c0v * v[0] + (T)Ba * Sa + (T)Bb * Sb;
-    const cx<T> E = (T)c0e * v[0] + (T)Ea * Sa + (T)Eb * Sb;
-    out[0] = V + (T)Da * v[1] + (T)Db * v[4];
-    out[1] = V + (T)Da * v[2] + (T)Db * v[5];
-    out[2] = V + (T)Da * v[3] + (T)Db * v[6];
-    out[3] = E + (T)Ga * v[3] + (T)Gb * v[6];    // edge 0-1, opposite vertex 2
-    out[4] = E + (T)Ga * v[1] + (T)Gb * v[4];    // edge 1-2, opposite vertex 0
-    out[5] = E + (T)Ga * v[2] + (T)Gb * v[5];    // edge 2-0, opposite vertex 1
-}
-
 // component-major kernel-value buffer: entry (c, lane) at c * kR1Stride + lane;
 // the stride (= 1 mod 16) spreads consecutive components over the banks
 constexpr int kR1Stride = 209;
@@ -174,7 +131,7 @@ constexpr int kR1Stride = 209;
 // STORE (mode 4): the near pairs of a MIXED operator in FP64, their blocks
 // added to the FP64 near store instead of Z (the store's slots of one
 // launch are disjoint like its rows x columns).
-template <typename T, typename TS, bool DK = false, bool NODAL = false, bool STORE = false>
+template <typename T, typename TS, bool NODAL = false, bool STORE = false>
 __global__ __launch_bounds__(256) void k_regular(RegArgs<T, TS> a) {
     // point-pair kernel values; the trial-side contraction is later written
     // over them in place
@@ -266,9 +223,7 @@ __global__ __launch_bounds__(256) void k_regular(RegArgs<T, TS> a) {
     int any = 0;
 #pragma unroll
     for (int k = 0; k < kChunk; ++k) any |= s_act[k];
-    // uniform over the workgroup; a first writer still stores its zeros
-    if (!any && !a.first_on) return;
-    const int rfirst = a.first_on ? a.row_first[e] : 0, cfirst = a.first_on ? a.col_first[ch] : 0;
+    if (!any) return;                          // uniform over the workgroup
     const int ns = s_rec[0];
     const int rowlen = 2 * ns;
     const int nitems = 6 * rowlen;
@@ -297,9 +252,7 @@ __global__ __launch_bounds__(256) void k_regular(RegArgs<T, TS> a) {
             for (int i = 0; i < 6; ++i) {
                 const TS *src = Z + s_row[g][i];
                 if constexpr (kF64) {
-                    const bool first = ((rfirst >> i) & (cfirst >> sl) & 1) != 0;
-                    pre[k][i] = double2{0.0, 0.0};
-                    if (on && !first) pre[k][i] = *(const double2 *)src;
+                    if (on) pre[k][i] = *(const double2 *)src;
                 } else {
                     TS *dre = s_dst + (2 * i) * kItemsMax + first, *dim = s_dst + (2 * i + 1) * kItemsMax + first;
                     if (on) {
@@ -317,7 +270,7 @@ __global__ __launch_bounds__(256) void k_regular(RegArgs<T, TS> a) {
         cx<T> k[12];
         const int kind = s_act[fsl];
         if (kind == 1) {
-            kappa12<T, DK>(s_K, x, n, ta, sa, y, tb, ww, k);
+            kappa12<T>(s_K, x, n, ta, sa, y, tb, ww, k);
         } else if (!std::is_same<T, double>::value && kind == 2) {
             // near pair: FP64 kernel differences (cancellation), then rounded
             const double *q64 = a.qp64;
@@ -328,7 +281,7 @@ __global__ __launch_bounds__(256) void k_regular(RegArgs<T, TS> a) {
             const dvec3 tb[2] = {qload(q64, nq, QT1, iy), qload(q64, nq, QT2, iy)};
             const double ww = q64[(int64_t)QW * nq + ix] * q64[(int64_t)QW * nq + iy];
             cx<double> kd[12];
-            kappa12<double, DK>(s_K, x, n, ta, sa, y, tb, ww, kd);
+            kappa12<double>(s_K, x, n, ta, sa, y, tb, ww, kd);
 #pragma unroll
             for (int c = 0; c < 12; ++c) k[c] = cx<T>{(T)kd[c].re, (T)kd[c].im};
         } else {
@@ -942,10 +895,8 @@ __global__ __launch_bounds__(256) void k_regular12(RegArgs<T, TS> a) {
     constexpr int kR12 = kQP12 * 24;
     __shared__ T s_ra[NODAL ? kR12 : 1];
     __shared__ T s_rb[NODAL ? kChunk * kR12 : 1];
-    constexpr bool kF64 = std::is_same<TS, double>::value;
-    __shared__ __align__(16) TS s_dst[kF64 ? 1 : 2 * 6 * kItemsMax];
+    __shared__ __align__(16) TS s_dst[2 * 6 * kItemsMax];
     constexpr int kRounds = (kItemsMax + 255) / 256;
-    double2 pre[kF64 ? kRounds : 1][6];
     __shared__ int64_t s_row[6][6];
     __shared__ int32_t s_rec[kChunkRec];
     __shared__ int s_act[kChunk];
@@ -1015,16 +966,12 @@ __global__ __launch_bounds__(256) void k_regular12(RegArgs<T, TS> a) {
 #pragma unroll
             for (int i = 0; i < 6; ++i) {
                 const TS *src = Z + s_row[g][i];
-                if constexpr (kF64) {
-                    if (on) pre[k][i] = *(const double2 *)src;
-                } else {
-                    TS *dre = s_dst + (2 * i) * kItemsMax + first, *dim = s_dst + (2 * i + 1) * kItemsMax + first;
-                    if (on) {
-                        __builtin_amdgcn_global_load_lds((const void *)src,
-                                                         (__attribute__((address_space(3))) void *)dre, 4, 0, 0);
-                        __builtin_amdgcn_global_load_lds((const void *)(src + 1),
-                                                         (__attribute__((address_space(3))) void *)dim, 4, 0, 0);
-                    }
+                TS *dre = s_dst + (2 * i) * kItemsMax + first, *dim = s_dst + (2 * i + 1) * kItemsMax + first;
+                if (on) {
+                    __builtin_amdgcn_global_load_lds((const void *)src,
+                                                     (__attribute__((address_space(3))) void *)dre, 4, 0, 0);
+                    __builtin_amdgcn_global_load_lds((const void *)(src + 1),
+                                                     (__attribute__((address_space(3))) void *)dim, 4, 0, 0);
                 }
             }
         }
@@ -1044,7 +991,7 @@ __global__ __launch_bounds__(256) void k_regular12(RegArgs<T, TS> a) {
                 const vec3<T> tb[2] = {qload(a.qp, nq, QT1, iy), qload(a.qp, nq, QT2, iy)};
                 const T ww = a.qp[(int64_t)QW * nq + ix] * a.qp[(int64_t)QW * nq + iy];
                 kappa12<T>(s_K, x, n, ta, sa, y, tb, ww, k);
-            } else if (!std::is_same<T, double>::value && kind == 2) {
+            } else if (kind == 2) {
                 const double *q64 = a.qp64;
                 const dvec3 x = qload(q64, nq, QX, ix), n = qload(q64, nq, QN, ix);
                 const dvec3 ta[2] = {qload(q64, nq, QT1, ix), qload(q64, nq, QT2, ix)};
@@ -1144,16 +1091,8 @@ __global__ __launch_bounds__(256) void k_regular12(RegArgs<T, TS> a) {
 #pragma unroll
         for (int i = 0; i < 6; ++i) {
             TS *dst = Z + s_row[g][i];
-            TS ore, oim;
-            if constexpr (kF64) {
-                ore = pre[k][i].x;
-                oim = pre[k][i].y;
-            } else {
-                ore = s_dst[(2 * i) * kItemsMax + it];
-                oim = s_dst[(2 * i + 1) * kItemsMax + it];
-            }
-            dst[0] = ore + (TS)out[i].re;
-            dst[1] = oim + (TS)out[i].im;
+            dst[0] = s_dst[(2 * i) * kItemsMax + it] + (TS)out[i].re;
+            dst[1] = s_dst[(2 * i + 1) * kItemsMax + it] + (TS)out[i].im;
         }
     }
 }
@@ -1400,6 +1339,11 @@ static int nodal_table_run(mbem_op *op, const T *qp, hipStream_t s) {
     return MBEM_OK;
 }
 
+int nodal_table_f64(mbem_op *op, bool with12, hipStream_t s) {
+    return with12 ? nodal_table_run<double, kQP12>(op, op->mesh->d_qp12, s)
+                  : nodal_table_run<double, kQP>(op, op->mesh->d_qp, s);
+}
+
 // Near radius of the mixed path: params.near_radius, or 1.89 / sqrt|k_a^2 -
 // k_i^2| (the gap below which FP32 cancellation of the R^-3 terms reaches
 // about 1e-7).
@@ -1409,7 +1353,7 @@ static double near_radius_of(const mbem_op *op) {
     return op->p.near_radius > 0 ? op->p.near_radius : (dk2 > 0 ? 1.89 / std::sqrt(dk2) : 0.0);
 }
 
-template <typename T, typename TS, bool DK = false, bool P12 = false, bool NODAL = false, bool STORE = false>
+template <typename T, typename TS, bool P12 = false, bool NODAL = false, bool STORE = false>
 static int launch_regular(mbem_op *op, int mode, const T *qp, unsigned long long *cnt,
                           hipStream_t s, const FillBand *band = nullptr) {
     const mbem_mesh *m = op->mesh;
@@ -1436,9 +1380,6 @@ static int launch_regular(mbem_op *op, int mode, const T *qp, unsigned long long
     a.K = op->d_kconst;
     a.near_r = near_radius_of(op);
     a.row_map = band ? band->row_map : nullptr;
-    a.row_first = m->d_row_first;
-    a.col_first = m->d_col_first;
-    a.first_on = std::is_same<TS, double>::value && !DK && !P12 && !NODAL && !STORE && !band && mode == 0;
     for (int o = 0; o < 3; ++o) a.Z[o] = (TS *)(band ? band->Z[o] : op->K[o]);
     const std::vector<int32_t> &toff = band ? band->tcol_off : m->tcol_off;
     const int32_t *tlist = band ? band->tcol : m->d_tcol;
@@ -1449,7 +1390,7 @@ static int launch_regular(mbem_op *op, int mode, const T *qp, unsigned long long
             a.tiles = op->d_ntiles + op->near_tile_off[L];
             a.total = op->near_tile_off[L + 1] - op->near_tile_off[L];
             if (a.total == 0) continue;
-            hipLaunchKernelGGL((k_regular<T, TS, DK, NODAL, true>), dim3((unsigned)a.total), dim3(256), 0, s, a);
+            hipLaunchKernelGGL((k_regular<T, TS, NODAL, true>), dim3((unsigned)a.total), dim3(256), 0, s, a);
             MBEM_HIP(hipGetLastError());
         }
         return MBEM_OK;
@@ -1466,7 +1407,7 @@ static int launch_regular(mbem_op *op, int mode, const T *qp, unsigned long long
             if constexpr (P12)
                 hipLaunchKernelGGL((k_regular12<T, TS, NODAL>), dim3((unsigned)a.total), dim3(256), 0, s, a);
             else
-                hipLaunchKernelGGL((k_regular<T, TS, DK, NODAL, STORE>), dim3((unsigned)a.total), dim3(256), 0, s, a);
+                hipLaunchKernelGGL((k_regular<T, TS, NODAL, STORE>), dim3((unsigned)a.total), dim3(256), 0, s, a);
             MBEM_HIP(hipGetLastError());
         }
     return MBEM_OK;
@@ -1625,7 +1566,7 @@ int fill_band_run(mbem_op *op, const FillBand &band, hipStream_t s) {
         return MBEM_EINVAL;
     }
     if (op->p.frame == MBEM_FRAME_NODAL) {
-        MBEM_TRY((launch_regular<double, double, false, false, true>(op, 0, op->mesh->d_qp, nullptr, s, &band)));
+        MBEM_TRY((launch_regular<double, double, false, true>(op, 0, op->mesh->d_qp, nullptr, s, &band)));
         MBEM_TRY((launch_ssq<double, false, false, true>(op, s, &band)));
     } else {
         MBEM_TRY((launch_regular<double, double>(op, 0, op->mesh->d_qp, nullptr, s, &band)));
@@ -1653,10 +1594,10 @@ int fill_enqueue(mbem_op *op, hipStream_t s, bool deriv, bool geom) {
     const int64_t n_reg = m->nt * m->nt - m->n_spairs;
     const bool mixed_chunks = op->prec == MBEM_MIXED && !deriv && !paper && !nodal && !op->p.near_store &&
                               n_reg > 0 && op->n_near > 0.3 * (double)n_reg;
-    // the default-scheme fills (FP64 by chunks, complex64 by column ranges)
-    // write every entry themselves; the others add to a cleared Z
-    const bool range_fill = !deriv && !paper && !nodal && !mixed_chunks;
-    if (!range_fill)
+    // the FP64 fills and the complex64 fill by column ranges write every
+    // entry themselves; the others add to a cleared Z
+    const bool range_fill = !paper && !nodal && !mixed_chunks;
+    if (op->prec != MBEM_FP64 && !range_fill)
         for (int o = 0; o < 3; ++o) MBEM_HIP(hipMemsetAsync(op->K[o], 0, esz * op->n2 * op->n2, s));
     f->counted = op->prec != MBEM_FP64 && !deriv && !(op->p.near_store && !paper && !nodal);
     if (f->counted) MBEM_HIP(hipMemsetAsync(f->d_cnt, 0, sizeof(unsigned long long), s));
@@ -1668,22 +1609,15 @@ int fill_enqueue(mbem_op *op, hipStream_t s, bool deriv, bool geom) {
     else if (op->near_on) near_free(op);
     MBEM_HIP(hipEventRecord(ev[1], s));
     unsigned long long *cnt = f->counted ? f->d_cnt : nullptr;
-    if (paper && op->prec == MBEM_FP64) {
-        if (nodal) MBEM_TRY((launch_regular<double, double, false, true, true>(op, 0, m->d_qp12, nullptr, s)));
-        else MBEM_TRY((launch_regular<double, double, false, true>(op, 0, m->d_qp12, nullptr, s)));
+    if (op->prec == MBEM_FP64) {
+        MBEM_TRY(pair_fill_run(op, deriv, s));
     } else if (paper) {
-        if (nodal) MBEM_TRY((launch_regular<float, float, false, true, true>(op, 1, m->d_qp12_32, cnt, s)));
-        else MBEM_TRY((launch_regular<float, float, false, true>(op, 1, m->d_qp12_32, cnt, s)));
-    } else if (deriv) {
-        if (nodal) MBEM_TRY((launch_regular<double, double, true, false, true>(op, 0, m->d_qp, nullptr, s)));
-        else MBEM_TRY((launch_regular<double, double, true>(op, 0, m->d_qp, nullptr, s)));
-    } else if (op->prec == MBEM_FP64) {
-        if (nodal) MBEM_TRY((launch_regular<double, double, false, false, true>(op, 0, m->d_qp, nullptr, s)));
-        else MBEM_TRY((launch_regular<double, double>(op, 0, m->d_qp, nullptr, s)));
+        if (nodal) MBEM_TRY((launch_regular<float, float, true, true>(op, 1, m->d_qp12_32, cnt, s)));
+        else MBEM_TRY((launch_regular<float, float, true>(op, 1, m->d_qp12_32, cnt, s)));
     } else if (store) {
         MBEM_TRY((launch_regular_range<float, float>(op, 3, m->d_qp32, nullptr, s)));
     } else if (nodal) {
-        MBEM_TRY((launch_regular<float, float, false, false, true>(op, 1, m->d_qp32, cnt, s)));
+        MBEM_TRY((launch_regular<float, float, false, true>(op, 1, m->d_qp32, cnt, s)));
     } else if (mixed_chunks) {
         MBEM_TRY((launch_regular<float, float>(op, 1, m->d_qp32, cnt, s)));
     } else {
@@ -1692,7 +1626,7 @@ int fill_enqueue(mbem_op *op, hipStream_t s, bool deriv, bool geom) {
     MBEM_HIP(hipEventRecord(ev[2], s));
     // near pairs: inside the regular launches, or with the near store in a
     // launch of their own in FP64
-    if (store) MBEM_TRY((launch_regular<double, double, false, false, false, true>(op, 4, m->d_qp, nullptr, s)));
+    if (store) MBEM_TRY((launch_regular<double, double, false, false, true>(op, 4, m->d_qp, nullptr, s)));
     MBEM_HIP(hipEventRecord(ev[3], s));
     if (paper && op->prec == MBEM_FP64 && nodal) MBEM_TRY((launch_ssq<double, false, true, true>(op, s)));
     else if (paper && op->prec == MBEM_FP64) MBEM_TRY((launch_ssq<double, false, true>(op, s)));

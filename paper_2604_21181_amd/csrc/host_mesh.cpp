@@ -209,6 +209,21 @@ namespace mbem {
 // perm code: three 2-bit local vertex indices (re-indexed order)
 static inline int32_t pack_perm(int a, int b, int c) { return a | (b << 2) | (c << 4); }
 
+// Test batches per band of the FP64 regular-pair fill.  The two band buffers
+// together stay below kPairScratch, so that they are written and read back
+// while in the 256 MB last-level cache; within that a band takes whole rounds
+// of the workgroups that run at a time (three per compute unit).
+constexpr int64_t kPairScratch = (int64_t)224 << 20, kPairRound = 768;
+
+static int64_t pair_band(int64_t nbatch, int64_t nslots) {
+    const int64_t per = 6 * 2 * 16 * nslots * nslots / nbatch;      // bytes per test batch, on average
+    if (nbatch * per <= kPairScratch / 2) return nbatch;            // a single band
+    int64_t band = std::max<int64_t>(1, kPairScratch / 2 / per);
+    const int64_t rounds = band * nbatch / kPairRound;
+    if (rounds > 0) band = std::max<int64_t>(1, rounds * kPairRound / nbatch);
+    return band;
+}
+
 int build_tables(const mbem_mesh *m, MeshTables &T) {
     const int64_t nn = m->nn, nt = m->nt;
     const int32_t *tri = m->tri.data();
@@ -226,8 +241,9 @@ int build_tables(const mbem_mesh *m, MeshTables &T) {
     // singular pairs: for every test triangle e, all triangles f sharing at
     // least one vertex node, with both re-indexed so that the shared
     // vertices come first, ordered along e's counter-clockwise edge.
+    std::vector<int32_t> cand;
     for (int64_t e = 0; e < nt; ++e) {
-        std::vector<int32_t> cand;
+        cand.clear();
         for (int a = 0; a < 3; ++a) {
             int32_t v = tri[6 * e + a];
             for (int32_t s = T.inc_ptr[v]; s < T.inc_ptr[v + 1]; ++s)
@@ -262,20 +278,23 @@ int build_tables(const mbem_mesh *m, MeshTables &T) {
         }
     }
     // mass pattern: nodes sharing a triangle
-    std::vector<std::vector<int32_t>> rows(nn);
-    for (int64_t t = 0; t < nt; ++t)
-        for (int k = 0; k < 6; ++k)
-            for (int l = 0; l < 6; ++l) rows[tri[6 * t + k]].push_back(tri[6 * t + l]);
     T.m_ptr.assign(nn + 1, 0);
-    for (int64_t v = 0; v < nn; ++v) {
-        auto &r = rows[v];
-        std::sort(r.begin(), r.end());
-        r.erase(std::unique(r.begin(), r.end()), r.end());
-        T.m_ptr[v + 1] = T.m_ptr[v] + (int32_t)r.size();
+    T.m_col.clear();
+    {
+        std::vector<int32_t> seen(nn, -1);
+        for (int64_t v = 0; v < nn; ++v) {
+            const size_t at = T.m_col.size();
+            for (int32_t s = T.inc_ptr[v]; s < T.inc_ptr[v + 1]; ++s)
+                for (int l = 0; l < 6; ++l) {
+                    const int32_t u = tri[6 * (int64_t)(T.inc[s] >> 3) + l];
+                    if (seen[u] == v) continue;
+                    seen[u] = (int32_t)v;
+                    T.m_col.push_back(u);
+                }
+            std::sort(T.m_col.begin() + at, T.m_col.end());
+            T.m_ptr[v + 1] = (int32_t)T.m_col.size();
+        }
     }
-    T.m_col.resize(T.m_ptr[nn]);
-    for (int64_t v = 0; v < nn; ++v)
-        std::copy(rows[v].begin(), rows[v].end(), T.m_col.begin() + T.m_ptr[v]);
     T.m_slot.resize(36 * nt);
     for (int64_t t = 0; t < nt; ++t)
         for (int k = 0; k < 6; ++k)
@@ -354,6 +373,150 @@ int build_tables(const mbem_mesh *m, MeshTables &T) {
             off[r + 1] = (int32_t)(recs.size() / L.rec());
         }
     }
+    // Trial batches of the FP64 regular-pair fill: grown from the first free
+    // triangle (Morton order) by the free neighbour that shares the most
+    // nodes with the batch, and among those the one with the fewest free
+    // neighbours of its own, so that few triangles are left alone; without a
+    // neighbour that fits, the next free triangle that fits.  About 18 nodes
+    // per 5 triangles (20.4 for runs of the Morton order).
+    {
+        std::vector<char> used(nt, 0);
+        // per node and slot: its place in the records, its row of the scratch
+        std::vector<std::vector<std::pair<int32_t, int32_t>>> places(nn);
+        int32_t nodes = 0;
+        // edge neighbours, and the batch that last held a node / listed a triangle
+        std::vector<int32_t> nbr(3 * nt), in_batch(nn, -1), listed(nt, -1);
+        for (int64_t t = 0; t < nt; ++t)
+            for (int k = 0; k < 3; ++k) {
+                const int32_t mid = tri[6 * t + 3 + k];
+                nbr[3 * t + k] = (int32_t)t;
+                for (int32_t q = T.inc_ptr[mid]; q < T.inc_ptr[mid + 1]; ++q)
+                    if ((T.inc[q] >> 3) != t) nbr[3 * t + k] = T.inc[q] >> 3;
+            }
+        std::vector<int32_t> bt, bn, cand;     // the batch's triangles and nodes, triangles around them
+        int32_t id = 0;
+        auto shared = [&](int32_t f) {
+            int n = 0;
+            for (int k = 0; k < 6; ++k) n += in_batch[tri[6 * (int64_t)f + k]] == id;
+            return n;
+        };
+        auto fits = [&](int n) { return (int)bn.size() + 6 - n <= kPairNS; };
+        auto add = [&](int32_t f) {
+            used[f] = 1;
+            bt.push_back(f);
+            for (int k = 0; k < 6; ++k) {
+                const int32_t v = tri[6 * (int64_t)f + k];
+                if (in_batch[v] == id) continue;
+                in_batch[v] = id;
+                bn.push_back(v);
+                for (int32_t s = T.inc_ptr[v]; s < T.inc_ptr[v + 1]; ++s) {
+                    const int32_t c = T.inc[s] >> 3;
+                    if (used[c] || listed[c] == id) continue;
+                    listed[c] = id;
+                    cand.push_back(c);
+                }
+            }
+        };
+        for (int64_t first = 0;; ++id) {
+            while (first < nt && used[first]) ++first;
+            if (first == nt) break;
+            bt.clear();
+            bn.clear();
+            cand.clear();
+            add((int32_t)first);
+            while ((int)bt.size() < kPairNB) {
+                int32_t best = -1;
+                int best_score = -1;
+                for (int32_t f : cand) {
+                    if (used[f]) continue;
+                    const int n = shared(f);
+                    if (!fits(n)) continue;
+                    const int score = 4 * n + used[nbr[3 * f]] + used[nbr[3 * f + 1]] + used[nbr[3 * f + 2]];
+                    if (score > best_score || (score == best_score && f < best)) { best_score = score; best = f; }
+                }
+                if (best < 0)
+                    for (int64_t f = first + 1; f < std::min(nt, first + 64) && best < 0; ++f)
+                        if (!used[f] && fits(shared((int32_t)f))) best = (int32_t)f;
+                if (best < 0) break;
+                add(best);
+            }
+            std::sort(bt.begin(), bt.end());
+            // nodes by falling number of incidences in the batch
+            auto uses = [&](int32_t v) {
+                int n = 0;
+                for (int32_t f : bt)
+                    for (int l = 0; l < 6; ++l) n += tri[6 * (int64_t)f + l] == v;
+                return n;
+            };
+            std::vector<std::pair<int, int32_t>> order;
+            for (int32_t v : bn) order.push_back({-uses(v), v});
+            std::sort(order.begin(), order.end());
+            for (size_t q = 0; q < bn.size(); ++q) bn[q] = order[q].second;
+            const size_t base = T.pair_rec.size();
+            T.pair_rec.resize(base + kPairRec, 0);
+            int32_t *rec = T.pair_rec.data() + base;
+            rec[0] = (int32_t)bt.size();
+            rec[1] = (int32_t)bn.size();
+            rec[2] = nodes;
+            T.pair_row0.push_back(nodes);
+            for (size_t k = 0; k < bt.size(); ++k) rec[kPairTri + k] = bt[k];
+            int ni = 0;
+            for (size_t q = 0; q < bn.size(); ++q) {
+                rec[kPairOff + q] = ni;
+                bool seen = false;
+                for (size_t k = 0; k < bt.size(); ++k)
+                    for (int l = 0; l < 6; ++l)
+                        if (tri[6 * (int64_t)bt[k] + l] == bn[q]) {
+                            rec[kPairInc + ni++] = (int32_t)(8 * k + l);
+                            rec[kPairLoc + 6 * k + l] = (int32_t)q + (seen ? 0 : 256);
+                            seen = true;
+                        }
+                places[bn[q]].push_back({(int32_t)(base + kPairPos + q), nodes + (int32_t)q});
+            }
+            rec[kPairOff + bn.size()] = ni;
+            nodes += (int32_t)bn.size();
+        }
+        T.pair_sptr.assign(nn + 1, 0);
+        for (int64_t v = 0; v < nn; ++v) {
+            int32_t slot = T.pair_sptr[v];
+            for (const auto &at : places[v]) {
+                T.pair_rec[at.first] = slot++;
+                T.pair_srow.push_back(at.second);
+            }
+            T.pair_sptr[v + 1] = slot;
+        }
+        T.pair_cb.assign(1, 0);
+        for (int64_t v = 0; v < nn; ++v)
+            if (v > T.pair_cb.back() && T.pair_sptr[v + 1] - T.pair_sptr[T.pair_cb.back()] > kPairCols)
+                T.pair_cb.push_back((int32_t)v);
+        T.pair_cb.push_back((int32_t)nn);
+        const int64_t nbatch = (int64_t)T.pair_row0.size();
+        T.pair_row0.push_back(nodes);
+        T.pair_band = pair_band(nbatch, nodes);
+        const int64_t nbands = (nbatch + T.pair_band - 1) / T.pair_band;
+        std::vector<int32_t> band_end;       // first node row after each band
+        for (int64_t b = 0; b < nbands; ++b) {
+            const int32_t r0 = T.pair_row0[b * T.pair_band];
+            band_end.push_back(T.pair_row0[std::min(nbatch, (b + 1) * T.pair_band)]);
+            T.pair_band_rows = std::max<int64_t>(T.pair_band_rows, band_end.back() - r0);
+        }
+        std::vector<std::vector<int32_t>> tasks(nbands);
+        for (int64_t v = 0; v < nn; ++v) {
+            const int32_t s1 = T.pair_sptr[v + 1];
+            for (int32_t s = T.pair_sptr[v]; s < s1;) {
+                const int64_t b = std::upper_bound(band_end.begin(), band_end.end(), T.pair_srow[s]) - band_end.begin();
+                int32_t q = s;
+                while (q < s1 && T.pair_srow[q] < band_end[b]) ++q;
+                for (int32_t x : {(int32_t)v, s, q, (int32_t)(s == T.pair_sptr[v])}) tasks[b].push_back(x);
+                s = q;
+            }
+        }
+        T.pair_rows_off.assign(1, 0);
+        for (auto &t : tasks) {
+            T.pair_rows.insert(T.pair_rows.end(), t.begin(), t.end());
+            T.pair_rows_off.push_back((int64_t)T.pair_rows.size() / 4);
+        }
+    }
     // Colour classes (greedy in Morton order, then balanced) so that the
     // regular-pair fill can add to Z with plain read-modify-write: inside one
     // launch no two test triangles share a node (disjoint rows) and no two
@@ -365,14 +528,15 @@ int build_tables(const mbem_mesh *m, MeshTables &T) {
         std::vector<std::vector<int32_t>> users(nn);
         std::vector<std::vector<int32_t>> item_nodes(nitems);
         std::vector<int32_t> col(nitems, -1);
+        std::vector<int64_t> used(1, -1);    // colour -> the last item (or pass and item) that met it
         int ncol = 0;
         for (int64_t it = 0; it < nitems; ++it) {
             nodes_of(it, item_nodes[it]);
-            std::vector<char> used(ncol + 1, 0);
             for (int32_t v : item_nodes[it])
-                for (int32_t o : users[v]) used[col[o]] = 1;
+                for (int32_t o : users[v]) used[col[o]] = it;
             int c = 0;
-            while (c < ncol && used[c]) ++c;
+            while (c < ncol && used[c] == it) ++c;
+            if (c == ncol) used.push_back(-1);
             col[it] = c;
             ncol = std::max(ncol, c + 1);
             for (int32_t v : item_nodes[it]) users[v].push_back((int32_t)it);
@@ -385,13 +549,13 @@ int build_tables(const mbem_mesh *m, MeshTables &T) {
             for (int64_t it = 0; it < nitems; ++it) {
                 const int c = col[it];
                 if (size[c] <= target) continue;
-                std::vector<char> used(ncol, 0);
+                const int64_t mark = (round + 1) * nitems + it;
                 for (int32_t v : item_nodes[it])
                     for (int32_t o : users[v])
-                        if (o != it) used[col[o]] = 1;
+                        if (o != it) used[col[o]] = mark;
                 int best = -1;
                 for (int d = 0; d < ncol; ++d)
-                    if (!used[d] && size[d] < target && (best < 0 || size[d] < size[best])) best = d;
+                    if (used[d] != mark && size[d] < target && (best < 0 || size[d] < size[best])) best = d;
                 if (best >= 0) { col[it] = best; --size[c]; ++size[best]; ++moved; }
             }
             if (!moved) break;

@@ -72,6 +72,22 @@ struct RngLayout {
     constexpr int rec() const { return inc() + 6 * nb; }
 };
 constexpr RngLayout kRng = {64, 5};
+// Batches of the FP64 regular-pair fill: up to kPairNB triangles with at most
+// kPairNS distinct nodes (by falling number of incidences).  A (batch, node)
+// pair is a slot, numbered by node, then batch.  One record of kPairRec ints
+// per batch: triangles, nodes, nodes of all earlier batches, then
+//   kPairTri  triangles [kPairNB]
+//   kPairPos  the nodes' slots [kPairNS]
+//   kPairOff  per node the offsets [kPairNS + 1] into
+//   kPairInc  the incidences [6 kPairNB], batch-local triangle * 8 + local node
+//   kPairLoc  per (triangle, local node) the batch-local node, + 256 at the
+//             node's first triangle of the batch [6 kPairNB]
+constexpr int kPairNB = 5, kPairNS = 21;
+constexpr int kPairTri = 3, kPairPos = kPairTri + kPairNB, kPairOff = kPairPos + kPairNS,
+              kPairInc = kPairOff + kPairNS + 1, kPairLoc = kPairInc + 6 * kPairNB,
+              kPairRec = kPairLoc + 6 * kPairNB;
+// The gather takes runs of nodes with at most kPairCols slots (or one node).
+constexpr int kPairCols = 170;
 // quadrature-point table fields (structure of arrays, each n_tris*7 long)
 enum QpField {
     QX = 0, QW = 3, QN = 4, QT1 = 7, QT2 = 10, QS1 = 13, QS2 = 16
@@ -140,12 +156,20 @@ struct mbem_mesh {
     int64_t nrng = 0;
     int32_t *d_rng_off = nullptr, *d_rng_rec = nullptr;
     int32_t *d_row_first = nullptr;   // per triangle: first writer of its nodes' rows
-    int32_t *d_col_first = nullptr;   // per trial chunk: first writer of its slots' columns
     // colour classes of the race-free regular-pair fill, and the class of
     // every test triangle and trial chunk
     std::vector<int32_t> tcol_off, ccol_off;
     int32_t *d_tcol = nullptr, *d_ccol = nullptr;
     int32_t *d_tcolour = nullptr, *d_ccolour = nullptr;
+    // FP64 regular-pair fill (pairs.hip): batches, node -> first slot, slot ->
+    // batch node, blocks of nodes, and per band of pair_band test batches its
+    // row tasks (4 ints each)
+    int32_t pair_batches = 0, pair_ncb = 0;
+    int64_t pair_slots = 0, pair_band = 0, pair_band_rows = 0;   // most nodes in a band's batches
+    std::vector<int64_t> pair_rows_off;
+    std::vector<int32_t> pair_row0;       // batch -> nodes of the batches before it
+    int32_t *d_pair_rec = nullptr, *d_pair_sptr = nullptr, *d_pair_srow = nullptr, *d_pair_cb = nullptr,
+            *d_pair_rows = nullptr;
     // host copies for band fills: the test colour lists and singular pairs
     std::vector<int32_t> tcol_list, spairs;
 };
@@ -230,6 +254,12 @@ struct MeshTables {
     // per trial chunk, bit sl: the chunk is the first of its colour order to
     // write the columns of its slot node sl
     std::vector<int32_t> col_first;
+    // FP64 regular-pair fill: batch records, node -> first slot, slot -> batch
+    // node, the gather's blocks of nodes, and the row tasks {node, first, last
+    // + 1 slot, first band of the node} of the bands of pair_band test batches
+    std::vector<int32_t> pair_rec, pair_sptr, pair_srow, pair_cb, pair_rows, pair_row0;
+    std::vector<int64_t> pair_rows_off;
+    int64_t pair_band = 0, pair_band_rows = 0;
     // colour classes: test triangles sharing no node, trial chunks sharing
     // no node (offsets into the concatenated lists, one more than classes)
     std::vector<int32_t> tcol_list, tcol_off, ccol_list, ccol_off;
@@ -262,6 +292,11 @@ int fill_prepare(mbem_op *op, hipStream_t s, bool deriv);
 int fill_enqueue(mbem_op *op, hipStream_t s, bool deriv, bool geom);
 int fill_collect(mbem_op *op, double *t_total_ms);
 void fill_state_free(FillState *f);
+// The regular pairs of an FP64 dense operator (pairs.hip): every entry of
+// its blocks is stored (nothing needs clearing first).
+int pair_fill_run(mbem_op *op, bool deriv, hipStream_t s);
+// the node-attached tangents' table of op in FP64 (12: the 12-point rule)
+int nodal_table_f64(mbem_op *op, bool with12, hipStream_t s);
 // A band of test rows (compressed fill): every regular and singular pair
 // whose test triangle is listed, added into band buffers whose rows are
 // numbered by row_map.

@@ -262,19 +262,23 @@ __device__ inline float exp_t(float x) { return expf(x); }
 template <typename T>
 __device__ __forceinline__ KScal<T> kernel_scalars_closed(const KernelConst &K, T R);
 
+// The Taylor series alone (max|k| R < 1/2).
+template <typename T>
+__device__ __forceinline__ KScal<T> kernel_scalars_series(const KernelConst &K, T R) {
+    const T inv4pi = (T)0.079577471545947667884;   // 1 / (4 pi)
+    const T r1 = inv4pi / R, r2 = r1 / R, r3 = r2 / R;
+    KScal<T> o;
+    o.D0 = r1 * horner<T>(K.cD, R);
+    o.df = r3 * horner<T>(K.cF, R);
+    o.dg = r3 * horner<T>(K.cG, R);
+    o.Ge = r2 * horner<T>(K.cE, R);
+    o.Gm = r2 * horner<T>(K.cM, R);
+    return o;
+}
+
 template <typename T>
 __device__ __forceinline__ KScal<T> kernel_scalars(const KernelConst &K, T R) {
-    const T inv4pi = (T)0.079577471545947667884;   // 1 / (4 pi)
-    KScal<T> o;
-    if ((T)K.kmax * R < (T)kSeriesRho) {
-        const T r1 = inv4pi / R, r2 = r1 / R, r3 = r2 / R;
-        o.D0 = r1 * horner<T>(K.cD, R);
-        o.df = r3 * horner<T>(K.cF, R);
-        o.dg = r3 * horner<T>(K.cG, R);
-        o.Ge = r2 * horner<T>(K.cE, R);
-        o.Gm = r2 * horner<T>(K.cM, R);
-        return o;
-    }
+    if ((T)K.kmax * R < (T)kSeriesRho) return kernel_scalars_series<T>(K, R);
     return kernel_scalars_closed<T>(K, R);
 }
 
