@@ -18,8 +18,8 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmbem.so")
 BUILD = os.path.join(HERE, "_build")
 
-SOURCES = ["host_mesh.cpp", "capi.cpp", "pool.cpp", "geom.hip", "fill.hip", "pairs.hip", "linalg.hip", "post.hip",
-           "gemm.hip", "block.hip", "adjoint.hip", "shape.hip", "blr.hip", "near.hip"]
+SOURCES = ["host_mesh.cpp", "capi.cpp", "pool.cpp", "geom.hip", "fill.hip", "pairs.hip", "ssq.hip", "linalg.hip",
+           "post.hip", "gemm.hip", "block.hip", "adjoint.hip", "shape.hip", "blr.hip", "near.hip"]
 ARCH = os.environ.get("MBEM_OFFLOAD_ARCH", "gfx950")
 
 
@@ -37,7 +37,7 @@ def _flags(src: str):
     if src.endswith(".hip"):
         f += ["-x", "hip", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
               "-ffp-contract=fast"]
-    if src in ("fill.hip", "pairs.hip"):
+    if src in ("fill.hip", "pairs.hip", "ssq.hip"):
         # machine-level loop-invariant code motion hoists every constant of
         # the Sauter-Schwab kernels' point loops into registers (248 instead
         # of 222 VGPRs), which measured 10 % slower, and those of the FP64

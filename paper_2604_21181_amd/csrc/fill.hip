@@ -13,9 +13,7 @@
 //    range of 64 consecutive trial nodes), one launch per test colour, the
 //    node sums held in registers over all trial triangles of the range so
 //    that each entry is updated once per test triangle;
-//  * singular pairs (coincident, common edge, common vertex): Sauter-Schwab
-//    quadrature, 6 / 5 / 2 regions x n^4 Gauss points, two wavefronts per
-//    pair, FP64;
+//  * singular pairs (coincident, common edge, common vertex): ssq.hip;
 //  * MIXED precision: far regular pairs in FP32, near regular pairs and all
 //    singular pairs in FP64, everything accumulated into complex64 Z.
 #include <complex>
@@ -28,17 +26,12 @@
 #include "near_store.h"
 #include "p2_device.h"
 #include "pairs.h"
-#include "ssq_map.h"
 
 namespace mbem {
 
 constexpr int kWave = 64;
 
 // -------------------------------------------------------------- helpers --
-__device__ inline void atomic_add(double *p, double v) { unsafeAtomicAdd(p, v); }
-__device__ inline void atomic_add(float *p, double v) { unsafeAtomicAdd(p, (float)v); }
-__device__ inline void atomic_add(float *p, float v) { unsafeAtomicAdd(p, v); }
-
 // Map a linear workgroup id so that each of the 8 XCDs (which receive
 // workgroups round-robin) works on one contiguous range of tiles.
 __device__ inline int64_t xcd_remap(int64_t bid, int64_t total) {
@@ -636,230 +629,9 @@ __global__ __launch_bounds__(THREADS, WAVES) void k_regular_range(RngArgs<T, TS>
     if (jglob < a.nn) add_to_z(Y);
 }
 
-// --------------------------------------------- Sauter-Schwab pairs ---
-// (maps of the four-dimensional rule: ssq_map.h)
-
-template <typename TS>
-struct SsqArgs {
-    int64_t n2, npairs;
-    const int32_t *pairs;   // e, f, class, perm codes
-    const int32_t *tri;
-    const double *xyz, *frames;
-    int order;
-    double glx[kMaxSSQ], glw[kMaxSSQ];   // Gauss-Legendre on [0,1]
-    const KernelConst *K;   // device copy
-    const int32_t *row_map; // null, or node -> row node of a band buffer
-    TS *Z[3];
-    NearView near;          // MIXED with the near store: added there in FP64
-};
-
-// Two wavefronts per pair.  Every lane evaluates one quadrature point per
-// batch (kernel values and the six test / trial shape functions) into LDS;
-// then 120 consumer lanes, one real component (2 c + re/im) of the twelve
-// kernel values each, split the batch's points into kStreams interleaved
-// streams and accumulate the 6 x 6 outer products N_i(x) N_j(y) kappa in
-// registers.  The streams are summed through the same LDS buffer at the end.
-constexpr int kSsqThreads = 128;
-constexpr int kStreams = 5;
-constexpr int kPtStride = 37;   // 24 kernel reals, N_i(x), N_j(y); padded
-// node-attached tangents: 24 kernel reals, then per test node i the 2 x 2
-// N_i(x) t_alpha,i . t_gamma(x) and per trial node j N_j(y) t_beta,j . t_delta(y)
-constexpr int kPtStrideNodal = 73;
-
-// Launch shape of the singular-pair kernels.  NODAL: rows of 73 doubles put
-// 75 KB of LDS on a workgroup (two per compute unit), and the 2 x 2
-// contractions make the consumers the larger part: four wavefronts per
-// workgroup, the first two producing, all of them consuming (ten streams).
-template <bool NODAL>
-struct SsqShape {
-    static constexpr int threads = NODAL ? 2 * kSsqThreads : kSsqThreads;
-    static constexpr int streams = NODAL ? 2 * kStreams : kStreams;
-    static constexpr int stride = NODAL ? kPtStrideNodal : kPtStride;
-    static_assert(streams * 36 * 24 <= kSsqThreads * stride, "reduction buffer");
-};
-
-// NODAL: the tangents of the two triangles' nodes, s_tn[side][k][b][3]
-__device__ __forceinline__ void ssq_stage_tangents(const double *frames, const int32_t *tri, int32_t e,
-                                                   int32_t f, double *s_tn, int tid) {
-    if (tid < 72) {
-        const int side = tid / 36, r = tid % 36, k = r / 6, b = (r / 3) % 2, d = r % 3;
-        s_tn[tid] = frames[9 * (int64_t)tri[6 * (side ? f : e) + k] + 3 + 3 * b + d];
-    }
-}
-
-// One LDS row: the twelve kernel values, then the shape data of the point
-// pair (shape functions, or with node-attached tangents their products
-// with the nodal tangents' components in the two point frames).
-template <bool NODAL>
-__device__ __forceinline__ void ssq_row(double *pt, const cx<double> k[12], const P2Point &X, const P2Point &Y,
-                                        const double *s_tn) {
-#pragma unroll
-    for (int q = 0; q < 12; ++q) { pt[2 * q] = k[q].re; pt[2 * q + 1] = k[q].im; }
-    if constexpr (!NODAL) {
-#pragma unroll
-        for (int q = 0; q < 6; ++q) { pt[24 + q] = X.N[q]; pt[30 + q] = Y.N[q]; }
-    } else {
-        const dvec3 tx[2] = {X.t1, X.t2}, ty[2] = {Y.t1, Y.t2};
-#pragma unroll
-        for (int q = 0; q < 6; ++q)
-#pragma unroll
-            for (int b = 0; b < 2; ++b) {
-                const double *ue = s_tn + 6 * q + 3 * b, *uf = s_tn + 36 + 6 * q + 3 * b;
-                const dvec3 te = {ue[0], ue[1], ue[2]}, tf = {uf[0], uf[1], uf[2]};
-#pragma unroll
-                for (int g = 0; g < 2; ++g) {
-                    pt[24 + 4 * q + 2 * b + g] = X.N[q] * dot(te, tx[g]);
-                    pt[48 + 4 * q + 2 * b + g] = Y.N[q] * dot(tf, ty[g]);
-                }
-            }
-    }
-}
-
-// Consumer lane (component comp = 2 c + re/im, stream): accumulate its
-// stream's rows of the batch into acc[i][j].
-template <bool NODAL>
-__device__ __forceinline__ void ssq_consume(const double *s_pt, int stream, int comp, double acc[36]) {
-    using Sh = SsqShape<NODAL>;
-    if constexpr (!NODAL) {
-        for (int r = stream; r < kSsqThreads; r += Sh::streams) {
-            const double *row = s_pt + r * Sh::stride;
-            const double kv = row[comp];
-            double u[6];
-#pragma unroll
-            for (int j = 0; j < 6; ++j) u[j] = row[30 + j] * kv;
-#pragma unroll
-            for (int i = 0; i < 6; ++i) {
-                const double nx = row[24 + i];
-#pragma unroll
-                for (int j = 0; j < 6; ++j) acc[6 * i + j] += nx * u[j];
-            }
-        }
-    } else {
-        // lane (c = 4 op + 2 alpha + beta, re / im): acc[i][j] +=
-        // sum_{gamma,delta} A_i[alpha][gamma] B_j[beta][delta] k[op,gamma,delta]
-        const int c = comp >> 1, ri = comp & 1;
-        const int op = c >> 2, al = (c >> 1) & 1, be = c & 1;
-        for (int r = stream; r < kSsqThreads; r += Sh::streams) {
-            const double *row = s_pt + r * Sh::stride;
-            const double k00 = row[2 * (4 * op) + ri], k01 = row[2 * (4 * op + 1) + ri];
-            const double k10 = row[2 * (4 * op + 2) + ri], k11 = row[2 * (4 * op + 3) + ri];
-            double u0[6], u1[6];
-#pragma unroll
-            for (int j = 0; j < 6; ++j) {
-                const double b0 = row[48 + 4 * j + 2 * be], b1 = row[48 + 4 * j + 2 * be + 1];
-                u0[j] = b0 * k00 + b1 * k01;
-                u1[j] = b0 * k10 + b1 * k11;
-            }
-#pragma unroll
-            for (int i = 0; i < 6; ++i) {
-                const double a0 = row[24 + 4 * i + 2 * al], a1 = row[24 + 4 * i + 2 * al + 1];
-#pragma unroll
-                for (int j = 0; j < 6; ++j) acc[6 * i + j] += a0 * u0[j] + a1 * u1[j];
-            }
-        }
-    }
-}
-
-// Sum the consumer streams through LDS in a fixed order and add the pair's
-// 6 x 6 x 12 block to Z (atomics: a node pair collects several element pairs).
-template <typename TS, bool NODAL>
-__device__ __forceinline__ void ssq_flush(const SsqArgs<TS> &a, int32_t e, int32_t f, double *s_pt,
-                                          const double acc[36], int tid) {
-    using Sh = SsqShape<NODAL>;
-    const int comp = tid % 24, stream = tid / 24;
-    if (tid < 24 * Sh::streams) {
-#pragma unroll
-        for (int k = 0; k < 36; ++k) s_pt[(stream * 36 + k) * 24 + comp] = acc[k];
-    }
-    __syncthreads();
-    const int32_t *te = a.tri + 6 * e, *tf = a.tri + 6 * f;
-    for (int it = tid; it < 36 * 12; it += Sh::threads) {
-        const int k = it / 12, cc = it % 12;
-        double re = 0, im = 0;
-#pragma unroll
-        for (int s = 0; s < Sh::streams; ++s) {
-            re += s_pt[(s * 36 + k) * 24 + 2 * cc];
-            im += s_pt[(s * 36 + k) * 24 + 2 * cc + 1];
-        }
-        const int i = k / 6, j = k % 6;
-        const int op = cc / 4, al = (cc / 2) % 2, be = cc % 2;
-        if (a.near.bits) {
-            // every node pair of a singular element pair is in the pattern
-            double *dst = (double *)(a.near.val + 12 * near_slot(a.near, te[i], tf[j]) + cc);
-            atomic_add(dst, re);
-            atomic_add(dst + 1, im);
-            continue;
-        }
-        const int64_t tn = a.row_map ? a.row_map[te[i]] : te[i];
-        const int64_t row = 2 * tn + al, col = 2 * (int64_t)tf[j] + be;
-        TS *dst = zblock(a.Z, op) + 2 * (row * a.n2 + col);
-        atomic_add(dst, re);
-        atomic_add(dst + 1, im);
-    }
-}
-
-template <typename TS, bool DK = false, bool NODAL = false>
-__global__ __launch_bounds__(SsqShape<NODAL>::threads) __attribute__((amdgpu_waves_per_eu(2, 8)))
-void k_ssq(SsqArgs<TS> a) {
-    using Sh = SsqShape<NODAL>;
-    __shared__ double s_pt[kSsqThreads * Sh::stride];
-    __shared__ double s_tn[NODAL ? 72 : 1];
-    const int tid = threadIdx.x;
-    const int64_t pid = blockIdx.x;
-    const int32_t e = a.pairs[4 * pid], f = a.pairs[4 * pid + 1];
-    if constexpr (NODAL) {
-        ssq_stage_tangents(a.frames, a.tri, e, f, s_tn, tid);
-        __syncthreads();
-    }
-    const int cls = a.pairs[4 * pid + 2], code = a.pairs[4 * pid + 3];
-    const int n = a.order, n4 = n * n * n * n;
-    const int nreg = cls == 3 ? 6 : (cls == 2 ? 5 : 2);
-    const int npts = nreg * n4;
-    const int comp = tid % 24, stream = tid / 24;    // consumer role
-    const bool consumer = tid < 24 * Sh::streams;
-    double acc[36];
-#pragma unroll
-    for (int k = 0; k < 36; ++k) acc[k] = 0.0;
-    for (int base = 0; base < npts; base += kSsqThreads) {
-        const int idx = base + tid;
-        if (tid < kSsqThreads) {
-            double *pt = s_pt + tid * Sh::stride;
-            if (idx < npts) {
-                const int r = idx / n4;
-                int g = idx % n4;
-                const int i3 = g % n; g /= n;
-                const int i2 = g % n; g /= n;
-                const int i1 = g % n; g /= n;
-                const int i0 = g;
-                double s1, t1, s2, t2;
-                const double jac = ss_region(cls, r, a.glx[i0], a.glx[i1], a.glx[i2], a.glx[i3], s1, t1, s2, t2);
-                const double wg = jac * a.glw[i0] * a.glw[i1] * a.glw[i2] * a.glw[i3];
-                double xe, ye, xf, yf;
-                ss_local(code & 63, s1, t1, xe, ye);
-                ss_local(code >> 6, s2, t2, xf, yf);
-                P2Point X, Y;
-                p2_point(a.xyz, a.frames, a.tri + 6 * e, xe, ye, X);
-                p2_point(a.xyz, a.frames, a.tri + 6 * f, xf, yf, Y);
-                const dvec3 ta[2] = {X.t1, X.t2}, sa[2] = {X.s1, X.s2}, tb[2] = {Y.t1, Y.t2};
-                cx<double> k[12];
-                kappa12<double, DK>(*a.K, X.x, X.n, ta, sa, Y.x, tb, wg * X.J * Y.J, k);
-                ssq_row<NODAL>(pt, k, X, Y, s_tn);
-            } else {
-#pragma unroll
-                for (int q = 0; q < (NODAL ? 72 : 36); ++q) pt[q] = 0.0;
-            }
-        }
-        __syncthreads();
-        if (consumer) ssq_consume<NODAL>(s_pt, stream, comp, acc);
-        __syncthreads();
-    }
-    ssq_flush<TS, NODAL>(a, e, f, s_pt, acc, tid);
-}
-
 // ------------------------------------- the paper's own scheme ---
-// Regular pairs on the 12-point rule (144 point pairs per element pair) and
-// singular pairs as Sauter-Schwab on kappa^s plus the 12-point rule on the
-// remainder kappa - kappa^s.  Same tiles, colour classes and chunk records
+// complex64 blocks: regular pairs on the 12-point rule (144 point pairs per
+// element pair).  Same tiles, colour classes and chunk records
 // as k_regular; the chunk's four trial triangles are taken one at a time:
 //  A: 144 lanes, one point pair each: kernel values into s_k[c][pair];
 //  B: 144 lanes (c, p): the trial-side contraction of the 12 values of
@@ -1095,80 +867,6 @@ __global__ __launch_bounds__(256) void k_regular12(RegArgs<T, TS> a) {
             dst[1] = s_dst[(2 * i + 1) * kItemsMax + it] + (TS)out[i].im;
         }
     }
-}
-
-// Singular pairs of the paper's scheme, one launch: per pair the Sauter-
-// Schwab points with the singular kernels kappa^s, then the 144 point pairs
-// of the 12-point rule with the remainders (constants a.K[0] = the kernels,
-// a.K[1] = the shifted truncated series of the remainders); the
-// accumulation into the pair's 6 x 6 x 12 block is that of k_ssq.
-template <typename TS, bool NODAL = false>
-__global__ __launch_bounds__(SsqShape<NODAL>::threads) __attribute__((amdgpu_waves_per_eu(2, 8)))
-void k_ssq_paper(SsqArgs<TS> a) {
-    using Sh = SsqShape<NODAL>;
-    __shared__ double s_pt[kSsqThreads * Sh::stride];
-    __shared__ double s_tn[NODAL ? 72 : 1];
-    const int tid = threadIdx.x;
-    const int64_t pid = blockIdx.x;
-    const int32_t e = a.pairs[4 * pid], f = a.pairs[4 * pid + 1];
-    if constexpr (NODAL) {
-        ssq_stage_tangents(a.frames, a.tri, e, f, s_tn, tid);
-        __syncthreads();
-    }
-    const int cls = a.pairs[4 * pid + 2], code = a.pairs[4 * pid + 3];
-    const int n = a.order, n4 = n * n * n * n;
-    const int nreg = cls == 3 ? 6 : (cls == 2 ? 5 : 2);
-    const int nssq = nreg * n4, npts = nssq + kPP12;
-    const int comp = tid % 24, stream = tid / 24;
-    const bool consumer = tid < 24 * Sh::streams;
-    double acc[36];
-#pragma unroll
-    for (int k = 0; k < 36; ++k) acc[k] = 0.0;
-    for (int base = 0; base < npts; base += kSsqThreads) {
-        const int idx = base + tid;
-        if (tid < kSsqThreads) {
-            double *pt = s_pt + tid * Sh::stride;
-            if (idx < npts) {
-                P2Point X, Y;
-                cx<double> k[12];
-                if (idx < nssq) {
-                    const int r = idx / n4;
-                    int g = idx % n4;
-                    const int i3 = g % n; g /= n;
-                    const int i2 = g % n; g /= n;
-                    const int i1 = g % n; g /= n;
-                    const int i0 = g;
-                    double s1, t1, s2, t2;
-                    const double jac = ss_region(cls, r, a.glx[i0], a.glx[i1], a.glx[i2], a.glx[i3], s1, t1, s2, t2);
-                    const double wg = jac * a.glw[i0] * a.glw[i1] * a.glw[i2] * a.glw[i3];
-                    double xe, ye, xf, yf;
-                    ss_local(code & 63, s1, t1, xe, ye);
-                    ss_local(code >> 6, s2, t2, xf, yf);
-                    p2_point(a.xyz, a.frames, a.tri + 6 * e, xe, ye, X);
-                    p2_point(a.xyz, a.frames, a.tri + 6 * f, xf, yf, Y);
-                    const dvec3 ta[2] = {X.t1, X.t2}, sa[2] = {X.s1, X.s2}, tb[2] = {Y.t1, Y.t2};
-                    kappa12_sing(a.K[0], X.x, X.n, ta, sa, Y.x, tb, wg * X.J * Y.J, k);
-                } else {
-                    const int rr = idx - nssq, p = rr / kQP12, q = rr % kQP12;
-                    double xe, ye, we, xf, yf, wf;
-                    rule12(p, xe, ye, we);
-                    rule12(q, xf, yf, wf);
-                    p2_point(a.xyz, a.frames, a.tri + 6 * e, xe, ye, X);
-                    p2_point(a.xyz, a.frames, a.tri + 6 * f, xf, yf, Y);
-                    const dvec3 ta[2] = {X.t1, X.t2}, sa[2] = {X.s1, X.s2}, tb[2] = {Y.t1, Y.t2};
-                    kappa12_rem(a.K[0], a.K[1], X.x, X.n, ta, sa, Y.x, tb, we * wf * X.J * Y.J, k);
-                }
-                ssq_row<NODAL>(pt, k, X, Y, s_tn);
-            } else {
-#pragma unroll
-                for (int q = 0; q < (NODAL ? 72 : 36); ++q) pt[q] = 0.0;
-            }
-        }
-        __syncthreads();
-        if (consumer) ssq_consume<NODAL>(s_pt, stream, comp, acc);
-        __syncthreads();
-    }
-    ssq_flush<TS, NODAL>(a, e, f, s_pt, acc, tid);
 }
 
 // ---------------------------------------------------------- mass ---
@@ -1463,38 +1161,6 @@ static int launch_regular_range(mbem_op *op, int mode, const T *qp, unsigned lon
     return MBEM_OK;
 }
 
-template <typename TS, bool DK = false, bool PAPER = false, bool NODAL = false>
-static int launch_ssq(mbem_op *op, hipStream_t s, const FillBand *band = nullptr) {
-    const mbem_mesh *m = op->mesh;
-    SsqArgs<TS> a;
-    a.n2 = op->n2;
-    a.npairs = band ? band->n_spairs : m->n_spairs;
-    a.pairs = band ? band->spairs : m->d_spairs;
-    a.row_map = band ? band->row_map : nullptr;
-    a.tri = m->d_tri;
-    a.xyz = m->d_xyz;
-    a.frames = m->d_frames;
-    a.order = op->p.ssq_order > 0 ? op->p.ssq_order : 4;
-    if (a.order > kMaxSSQ) { set_error("ssq_order above 8 is not supported"); return MBEM_EINVAL; }
-    double x[kMaxSSQ], w[kMaxSSQ];
-    gauss_legendre(a.order, x, w);
-    for (int i = 0; i < kMaxSSQ; ++i) {
-        a.glx[i] = i < a.order ? 0.5 * (1.0 + x[a.order - 1 - i]) : 0.0;
-        a.glw[i] = i < a.order ? 0.5 * w[a.order - 1 - i] : 0.0;
-    }
-    a.K = PAPER ? op->d_kconst + 1 : op->d_kconst;   // paper: the kernels, then the remainders
-    for (int o = 0; o < 3; ++o) a.Z[o] = (TS *)(band ? band->Z[o] : op->K[o]);
-    a.near = band ? NearView{} : op->near_view();
-    if (a.npairs == 0) return MBEM_OK;
-    if constexpr (PAPER)
-        hipLaunchKernelGGL((k_ssq_paper<TS, NODAL>), dim3((unsigned)a.npairs), dim3(SsqShape<NODAL>::threads), 0, s,
-                           a);
-    else
-        hipLaunchKernelGGL((k_ssq<TS, DK, NODAL>), dim3((unsigned)a.npairs), dim3(SsqShape<NODAL>::threads), 0, s, a);
-    MBEM_HIP(hipGetLastError());
-    return MBEM_OK;
-}
-
 int mass_run(mbem_op *op, hipStream_t s) {
     const mbem_mesh *m = op->mesh;
     MBEM_HIP(hipMemsetAsync(op->d_mval, 0, sizeof(double) * 4 * m->m_col.size(), s));
@@ -1567,12 +1233,10 @@ int fill_band_run(mbem_op *op, const FillBand &band, hipStream_t s) {
     }
     if (op->p.frame == MBEM_FRAME_NODAL) {
         MBEM_TRY((launch_regular<double, double, false, true>(op, 0, op->mesh->d_qp, nullptr, s, &band)));
-        MBEM_TRY((launch_ssq<double, false, false, true>(op, s, &band)));
     } else {
         MBEM_TRY((launch_regular<double, double>(op, 0, op->mesh->d_qp, nullptr, s, &band)));
-        MBEM_TRY(launch_ssq<double>(op, s, &band));
     }
-    return MBEM_OK;
+    return ssq_fill_run(op, false, &band, s);
 }
 
 int fill_enqueue(mbem_op *op, hipStream_t s, bool deriv, bool geom) {
@@ -1628,16 +1292,7 @@ int fill_enqueue(mbem_op *op, hipStream_t s, bool deriv, bool geom) {
     // launch of their own in FP64
     if (store) MBEM_TRY((launch_regular<double, double, false, false, true>(op, 4, m->d_qp, nullptr, s)));
     MBEM_HIP(hipEventRecord(ev[3], s));
-    if (paper && op->prec == MBEM_FP64 && nodal) MBEM_TRY((launch_ssq<double, false, true, true>(op, s)));
-    else if (paper && op->prec == MBEM_FP64) MBEM_TRY((launch_ssq<double, false, true>(op, s)));
-    else if (paper && nodal) MBEM_TRY((launch_ssq<float, false, true, true>(op, s)));
-    else if (paper) MBEM_TRY((launch_ssq<float, false, true>(op, s)));
-    else if (deriv && nodal) MBEM_TRY((launch_ssq<double, true, false, true>(op, s)));
-    else if (deriv) MBEM_TRY((launch_ssq<double, true>(op, s)));
-    else if (op->prec == MBEM_FP64 && nodal) MBEM_TRY((launch_ssq<double, false, false, true>(op, s)));
-    else if (op->prec == MBEM_FP64) MBEM_TRY(launch_ssq<double>(op, s));
-    else if (nodal) MBEM_TRY((launch_ssq<float, false, false, true>(op, s)));
-    else MBEM_TRY(launch_ssq<float>(op, s));
+    MBEM_TRY(ssq_fill_run(op, deriv, nullptr, s));
     MBEM_HIP(hipEventRecord(ev[4], s));
     MBEM_TRY(mass_run(op, s));
     if (f->counted)

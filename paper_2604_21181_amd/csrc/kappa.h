@@ -3,11 +3,7 @@
 // kappa2_alpha_beta):
 //   kappa1_ab = (D0 - dg)(s_a.t_b) + df (s_a.R)(R.t_b)
 //   kappa2_ab = G_chi [(t_a.t_b)(n.R) - (t_a.R)(n.t_b)],  R = (x - y)/|x - y|
-// output order c = 4 op + 2 a + b, op: K1, K2^eps, K2^mu.  The scalars are
-// those of the full kernels (kappa12), of their derivative in eps_i
-// (kappa12<.., true>), of the singular parts kappa^s (kappa12_sing) or of
-// the remainders kappa - kappa^s (kappa12_rem, which accepts x = y: the
-// direction R is then taken as 0, so the terms along it drop out).
+// output order c = 4 op + 2 a + b, op: K1, K2^eps, K2^mu.
 #pragma once
 
 #include "p2_device.h"
@@ -38,7 +34,7 @@ __device__ __forceinline__ void kappa_combine(const KScal<T> &s, vec3<T> Rh, vec
     }
 }
 
-template <typename T, bool DK = false>
+template <typename T>
 __device__ __forceinline__ void kappa12(const KernelConst &K, vec3<T> x, vec3<T> n,
                                         const vec3<T> ta[2], const vec3<T> sa[2],
                                         vec3<T> y, const vec3<T> tb[2], T ww,
@@ -46,27 +42,7 @@ __device__ __forceinline__ void kappa12(const KernelConst &K, vec3<T> x, vec3<T>
     vec3<T> Rv = x - y;
     const T R = sqrt(dot(Rv, Rv));
     const vec3<T> Rh = ((T)1 / R) * Rv;
-    KScal<T> s;
-    if constexpr (DK) s = kernel_scalars_deps(K, R);
-    else s = kernel_scalars<T>(K, R);
-    kappa_combine<T>(s, Rh, n, ta, sa, tb, ww, out);
-}
-
-__device__ __forceinline__ void kappa12_sing(const KernelConst &K, dvec3 x, dvec3 n, const dvec3 ta[2],
-                                             const dvec3 sa[2], dvec3 y, const dvec3 tb[2], double ww,
-                                             cx<double> out[12]) {
-    const dvec3 Rv = x - y;
-    const double R = sqrt(dot(Rv, Rv));
-    kappa_combine<double>(kernel_scalars_sing(K, R), (1.0 / R) * Rv, n, ta, sa, tb, ww, out);
-}
-
-__device__ __forceinline__ void kappa12_rem(const KernelConst &K, const KernelConst &Kr, dvec3 x, dvec3 n,
-                                            const dvec3 ta[2], const dvec3 sa[2], dvec3 y,
-                                            const dvec3 tb[2], double ww, cx<double> out[12]) {
-    const dvec3 Rv = x - y;
-    const double R = sqrt(dot(Rv, Rv));
-    const dvec3 Rh = R > 0.0 ? (1.0 / R) * Rv : dvec3{0.0, 0.0, 0.0};
-    kappa_combine<double>(kernel_scalars_rem(K, Kr, R), Rh, n, ta, sa, tb, ww, out);
+    kappa_combine<T>(kernel_scalars<T>(K, R), Rh, n, ta, sa, tb, ww, out);
 }
 
 }  // namespace mbem

@@ -308,6 +308,9 @@ struct FillBand {
     const int32_t *row_map = nullptr;     // device [nn]: node -> band row node
     void *Z[3] = {nullptr, nullptr, nullptr};   // band buffers, leading dimension 2 nn
 };
+// The singular pairs (ssq.hip) of a fill, or of a band, added to the blocks,
+// the near store or the band buffers.
+int ssq_fill_run(mbem_op *op, bool deriv, const FillBand *band, hipStream_t s);
 // FP64, default scheme; the geometry tables and kernel constants are current.
 int fill_band_run(mbem_op *op, const FillBand &band, hipStream_t s);
 

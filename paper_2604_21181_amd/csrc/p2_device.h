@@ -190,11 +190,11 @@ struct KScal {
     cx<T> D0, df, dg, Ge, Gm;
 };
 
-template <typename T>
+template <typename T, int TERMS = kSeriesTerms>
 __device__ __forceinline__ cx<T> horner(const double *c, T R) {
-    cx<T> s = {(T)c[2 * kSeriesTerms], (T)c[2 * kSeriesTerms + 1]};
+    cx<T> s = {(T)c[2 * TERMS], (T)c[2 * TERMS + 1]};
 #pragma unroll
-    for (int n = kSeriesTerms - 1; n >= 0; --n) s = cx<T>{s.re * R + (T)c[2 * n], s.im * R + (T)c[2 * n + 1]};
+    for (int n = TERMS - 1; n >= 0; --n) s = cx<T>{s.re * R + (T)c[2 * n], s.im * R + (T)c[2 * n + 1]};
     return s;
 }
 
@@ -328,32 +328,6 @@ __device__ __forceinline__ KScal<double> kernel_scalars_sing(const KernelConst &
     o.dg = o.df;
     o.Ge = (-r2) * cx<double>{K.eps_a_re - K.eps_i_re, K.eps_a_im - K.eps_i_im};
     o.Gm = (-r2) * cx<double>{K.mu_a_re - K.mu_i_re, K.mu_a_im - K.mu_i_im};
-    return o;
-}
-
-// Remainders kernel - kernel^s.  Below max|k| R = 1/2 (and at R = 0): the
-// expansions without their singular terms, whose coefficients the host
-// shifts into Kr so that only non-negative powers of R remain (D0 by one
-// power, df and dg by three, G by two; truncated after n = 6); otherwise the
-// closed forms minus the singular parts.
-__device__ __forceinline__ KScal<double> kernel_scalars_rem(const KernelConst &K, const KernelConst &Kr,
-                                                           double R) {
-    const double inv4pi = 0.079577471545947667884;
-    KScal<double> o;
-    if (R > 0.0 && K.kmax * R >= kSeriesRho) {
-        const KScal<double> c = kernel_scalars_closed<double>(K, R), s = kernel_scalars_sing(K, R);
-        o.D0 = c.D0 - s.D0;
-        o.df = c.df - s.df;
-        o.dg = c.dg - s.dg;
-        o.Ge = c.Ge - s.Ge;
-        o.Gm = c.Gm - s.Gm;
-        return o;
-    }
-    o.D0 = inv4pi * horner<double>(Kr.cD, R);
-    o.df = inv4pi * horner<double>(Kr.cF, R);
-    o.dg = inv4pi * horner<double>(Kr.cG, R);
-    o.Ge = inv4pi * horner<double>(Kr.cE, R);
-    o.Gm = inv4pi * horner<double>(Kr.cM, R);
     return o;
 }
 

@@ -6,14 +6,10 @@
 #include <cmath>
 
 #include "mbem_internal.h"
+#include "kappa64.h"
 #include "p2_device.h"
 
 namespace mbem {
-
-// closed-form kernel constants, passed by value (uniform operands)
-struct PairConst {
-    double ka, ki_re, ki_im, eps_re, eps_im, mu_re, mu_im, kmax;
-};
 
 struct PairArgs {
     int64_t nt, n2;
