@@ -746,11 +746,13 @@ int mbem_matvec(mbem_ctx *ctx, const mbem_op *op, const mbem_c128 *x, int32_t nr
     if (!op || !x || !y || nrhs < 1) { set_error("bad argument"); return MBEM_EINVAL; }
     MBEM_TRY(set_device(ctx));
     double2 *tmp = nullptr;
-    MBEM_TRY(dalloc(&tmp, 4 * op->n2));
+    const int chunk = matvecs_chunk(op, nrhs);
+    MBEM_TRY(dalloc(&tmp, (size_t)4 * op->n2 * chunk));
     const int64_t N = 2 * op->n2;
     int st = MBEM_OK;
-    for (int r = 0; r < nrhs && st == MBEM_OK; ++r)
-        st = matvec_run(op, (const double2 *)x + r * N, (double2 *)y + r * N, tmp, ctx->stream);
+    for (int r = 0; r < nrhs && st == MBEM_OK; r += chunk)
+        st = matvecs_run(op, (const double2 *)x + r * N, (double2 *)y + r * N, std::min(chunk, nrhs - r), tmp,
+                         ctx->stream);
     (void)hipStreamSynchronize(ctx->stream);
     dfree(tmp);
     return st;

@@ -7,6 +7,7 @@
 //   y_j  = (i/w) K1 x_j + K2^eps x_m + c_eps (M (x) I2) x_m
 //   y_m  = K2^mu x_j + c_mu (M (x) I2) x_j - (i/w) K1 x_m
 // so every dense entry is read once per product; K1 feeds two dot products.
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -152,6 +153,119 @@ __global__ __launch_bounds__(256) void k_gemv3(int64_t n2, const TS *K1, const T
     }
 }
 
+// ------------------------------------------------ several vectors at once --
+// t[v] = the four products of k_gemv3 for nv vectors (x: [nv][2 n2]) in one
+// pass over the blocks, on the FP64 matrix cores.  A workgroup takes 16 rows of
+// one block, its four wavefronts every fourth run of 8 columns, and their sums
+// meet in LDS.  Every lane loads two neighbouring columns of one row (c64: 16
+// bytes) and of one vector; they are the k of two instructions.
+//   COLS = 4   (4x4x4: four groups of 4 rows against the same 4 vectors) is
+//              bound by the read of the blocks;
+//   COLS = 16  (16x16x4) by the matrix units, whose 16 columns count whether
+//              they hold a vector or not.
+// One run's loads are ahead of its products; two or four runs ahead cost
+// registers and with them wavefronts (4 ahead: 397 against 305 us for two
+// vectors, n2 = 5120, FP64).  us, one after the other (k_gemv3) -> this:
+//   n2 = 5120  FP64   2: 461 -> 305   4: 921 -> 344   8: 1802 -> 420   16: 3585 -> 488
+//              mixed  2: 247 -> 252   4: 496 -> 252   8:  937 -> 372   16: 1835 -> 366
+//   n2 = 1280  FP64   2:  59 ->  53   3:  80 ->  56;  mixed  2: 66 -> 50   3: 92 -> 53
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+__device__ inline void load_pair(const float2 *p, double2 &a, double2 &b) {
+    const float4 v = *reinterpret_cast<const float4 *>(p);
+    a = {(double)v.x, (double)v.y};
+    b = {(double)v.z, (double)v.w};
+}
+__device__ inline void load_pair(const double2 *p, double2 &a, double2 &b) { a = p[0]; b = p[1]; }
+
+__device__ inline double mfma_f64(double a, double b, double c) {
+    return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
+}
+__device__ inline f64x4 mfma_f64(double a, double b, f64x4 c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+template <typename ACC>
+__device__ inline void mfma_complex(double2 a, double2 b, ACC acc[2]) {
+    acc[0] = mfma_f64(a.x, b.x, acc[0]);
+    acc[1] = mfma_f64(a.x, b.y, acc[1]);
+    acc[0] = mfma_f64(-a.y, b.y, acc[0]);
+    acc[1] = mfma_f64(a.y, b.x, acc[1]);
+}
+__device__ inline double acc_at(double v, int) { return v; }
+__device__ inline double acc_at(const f64x4 &v, int e) { return v[e]; }
+
+// rows r0 .. r0 + 15 of K times NS vector sets (halves off[0], off[1] of x)
+template <typename TS, int NS, int COLS>
+__device__ inline void gemm_rows(const TS *__restrict__ K, int64_t n2, int64_t r0, const double2 *__restrict__ x,
+                                 int nv, const int64_t (&off)[2], const int (&slot)[2], double2 *t, double *s_acc) {
+    using ACC = typename std::conditional<COLS == 4, double, f64x4>::type;
+    constexpr int E = COLS == 4 ? 1 : 4;               // sums per lane and component
+    const int lane = threadIdx.x % kW, wave = threadIdx.x / kW, grp = lane / 16, col = lane % COLS;
+    const int64_t row = r0 + lane % 16 < n2 ? r0 + lane % 16 : n2 - 1;
+    const TS *a = K + row * n2;
+    const double2 *xv = x + (int64_t)(col < nv ? col : 0) * 2 * n2;
+    ACC acc[NS][2] = {};
+    // the next run's loads are in flight during this run's products
+    double2 a0, a1, b0[NS], b1[NS];
+    auto load = [&](int64_t c) {
+        const int64_t k = c + 2 * grp;
+        const bool in = k < n2;                        // n2 is even
+        const int64_t kc = in ? k : 0;
+        load_pair(a + kc, a0, a1);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            b0[s] = xv[off[s] + kc];
+            b1[s] = xv[off[s] + kc + 1];
+            if (!in || col >= nv) b0[s] = b1[s] = double2{0.0, 0.0};
+        }
+        if (!in) a0 = a1 = double2{0.0, 0.0};          // 0 x NaN would spread
+    };
+    load(8 * wave);
+    for (int64_t c = 8 * wave; c < n2; c += 32) {
+        const double2 p0 = a0, p1 = a1;
+        double2 q0[NS], q1[NS];
+#pragma unroll
+        for (int s = 0; s < NS; ++s) { q0[s] = b0[s]; q1[s] = b1[s]; }
+        load(c + 32);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            mfma_complex(p0, q0[s], acc[s]);
+            mfma_complex(p1, q1[s], acc[s]);
+        }
+    }
+    // accumulator: 16x16x4 (lane, e): row grp + 4 e, vector lane % 16; 4x4x4
+    // (lane): row 4 (lane / 4 % 4) + grp, vector lane % 4
+    double *mine = s_acc + wave * (2 * E * NS * kW) + lane;
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+#pragma unroll
+        for (int e = 0; e < 2 * E; ++e) mine[(2 * E * s + e) * kW] = acc_at(acc[s][e / E], e % E);
+    __syncthreads();
+    for (int it = threadIdx.x; it < E * NS * kW; it += 256) {
+        const int s = it / (E * kW), e = it / kW % E, ln = it % kW;
+        double re = 0.0, im = 0.0;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            re += s_acc[w * (2 * E * NS * kW) + (2 * E * s + e) * kW + ln];
+            im += s_acc[w * (2 * E * NS * kW) + (2 * E * s + E + e) * kW + ln];
+        }
+        const int64_t r = r0 + ln / 16 + 4 * (COLS == 4 ? ln / 4 % 4 : e);
+        const int v = ln % COLS;
+        if (r < n2 && v < nv) t[((int64_t)v * 4 + slot[s]) * n2 + r] = double2{re, im};
+    }
+}
+
+template <typename TS, int COLS>
+__global__ __launch_bounds__(256) void k_gemm3(int64_t n2, const TS *K1, const TS *K2e, const TS *K2m,
+                                               const double2 *x, int nv, double2 *t) {
+    __shared__ double s_acc[4 * (COLS == 4 ? 4 : 16) * kW];
+    const int64_t tiles = (n2 + 15) / 16, blk = blockIdx.x / tiles, r0 = 16 * (blockIdx.x % tiles);
+    const int64_t j = 0, m = n2;                       // current halves of a vector
+    if (blk == 0) gemm_rows<TS, 2, COLS>(K1, n2, r0, x, nv, {j, m}, {0, 1}, t, s_acc);
+    else if (blk == 1) gemm_rows<TS, 1, COLS>(K2e, n2, r0, x, nv, {m, m}, {2, 2}, t, s_acc);
+    else gemm_rows<TS, 1, COLS>(K2m, n2, r0, x, nv, {j, j}, {3, 3}, t, s_acc);
+}
+
 struct Coef { double2 iw, ce, cm; };
 
 // LANES consecutive lanes per row split the row's mass slots (a vertex
@@ -169,6 +283,11 @@ __global__ __launch_bounds__(256) void k_combine(int64_t n2, const double2 *__re
                                                  const double *__restrict__ mval, const double2 *__restrict__ xj,
                                                  const double2 *__restrict__ xm, Coef c, NearView nv,
                                                  double2 *__restrict__ y) {
+    // vector blockIdx.y
+    t += (int64_t)blockIdx.y * 4 * n2;
+    xj += (int64_t)blockIdx.y * 2 * n2;
+    xm += (int64_t)blockIdx.y * 2 * n2;
+    y += (int64_t)blockIdx.y * 2 * n2;
     const int64_t gt = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     const int64_t r = gt / LANES;
     const int l = (int)(gt % LANES);
@@ -220,6 +339,21 @@ __global__ __launch_bounds__(256) void k_combine(int64_t n2, const double2 *__re
 
 static Coef coef_of(const mbem_op *op) { return {op->iw, op->ce, op->cm}; }
 
+// y[v] from the products t[v] of nv vectors
+static int combine_run(const mbem_op *op, const double2 *x, double2 *y, int nv, const double2 *t, hipStream_t s) {
+    const int64_t n2 = op->n2;
+    const mbem_mesh *m = op->mesh;
+    const NearView near = op->near_view();
+    if (near.bits)
+        hipLaunchKernelGGL(k_combine<kCombLanesNear>, dim3((unsigned)((n2 * kCombLanesNear + 255) / 256), nv),
+                           dim3(256), 0, s, n2, t, m->d_mptr, m->d_mcol, op->d_mval, x, x + n2, coef_of(op), near, y);
+    else
+        hipLaunchKernelGGL(k_combine<kCombLanes>, dim3((unsigned)((n2 * kCombLanes + 255) / 256), nv), dim3(256), 0,
+                           s, n2, t, m->d_mptr, m->d_mcol, op->d_mval, x, x + n2, coef_of(op), near, y);
+    MBEM_HIP(hipGetLastError());
+    return MBEM_OK;
+}
+
 int matvec_run(const mbem_op *op, const double2 *x, double2 *y, double2 *tmp, hipStream_t s,
                hipEvent_t after_gemv) {
     const int64_t n2 = op->n2;
@@ -236,16 +370,35 @@ int matvec_run(const mbem_op *op, const double2 *x, double2 *y, double2 *tmp, hi
                            (const float2 *)op->K[2], x, x + n2, tmp);
     MBEM_HIP(hipGetLastError());
     if (after_gemv) MBEM_HIP(hipEventRecord(after_gemv, s));
-    const mbem_mesh *m = op->mesh;
-    const NearView nv = op->near_view();
-    if (nv.bits)
-        hipLaunchKernelGGL(k_combine<kCombLanesNear>, dim3((unsigned)((n2 * kCombLanesNear + 255) / 256)), dim3(256),
-                           0, s, n2, tmp, m->d_mptr, m->d_mcol, op->d_mval, x, x + n2, coef_of(op), nv, y);
+    return combine_run(op, x, y, 1, tmp, s);
+}
+
+// Up to four vectors go through the 4-wide instructions, more through the
+// 16-wide ones: eight as two passes of four took 688 (FP64) and 493 us (mixed)
+// against 420 and 372 us.  A single vector stays with k_gemv3 (237 us FP64,
+// 130 us mixed), a compressed operator with its own product.
+int matvecs_chunk(const mbem_op *op, int nrhs) {
+    if (op->blr) return 1;
+    return std::min(nrhs, nrhs <= 4 ? 4 : 16);
+}
+
+template <typename TS>
+static void launch_products(const mbem_op *op, const double2 *x, int nv, double2 *t, hipStream_t s) {
+    const int64_t n2 = op->n2;
+    const TS *K[3] = {(const TS *)op->K[0], (const TS *)op->K[1], (const TS *)op->K[2]};
+    const dim3 grid((unsigned)(3 * ((n2 + 15) / 16)));
+    if (nv <= 4)
+        hipLaunchKernelGGL((k_gemm3<TS, 4>), grid, dim3(256), 0, s, n2, K[0], K[1], K[2], x, nv, t);
     else
-        hipLaunchKernelGGL(k_combine<kCombLanes>, dim3((unsigned)((n2 * kCombLanes + 255) / 256)), dim3(256), 0, s,
-                           n2, tmp, m->d_mptr, m->d_mcol, op->d_mval, x, x + n2, coef_of(op), nv, y);
+        hipLaunchKernelGGL((k_gemm3<TS, 16>), grid, dim3(256), 0, s, n2, K[0], K[1], K[2], x, nv, t);
+}
+
+int matvecs_run(const mbem_op *op, const double2 *x, double2 *y, int nv, double2 *tmp, hipStream_t s) {
+    if (nv == 1) return matvec_run(op, x, y, tmp, s);
+    if (op->prec == MBEM_FP64) launch_products<double2>(op, x, nv, tmp, s);
+    else launch_products<float2>(op, x, nv, tmp, s);
     MBEM_HIP(hipGetLastError());
-    return MBEM_OK;
+    return combine_run(op, x, y, nv, tmp, s);
 }
 
 // ------------------------------------------------------- entries of Z --
@@ -1446,8 +1599,12 @@ extern "C" int mbem_matvec_noalloc(mbem_ctx *ctx, const mbem_op *op, const mbem_
     double2 *tmp = nullptr;
     MBEM_TRY(scratch_of(ctx->device, &tmp));
     const int64_t N = 2 * op->n2;
-    for (int r = 0; r < nrhs; ++r)
-        MBEM_TRY(matvec_run(op, (const double2 *)x + r * N, (double2 *)y + r * N, tmp, ctx->stream));
+    // as many vectors at a time as the scratch holds: bit for bit mbem_matvec
+    // where that is its chunk too, else equal to rounding
+    const int chunk = (int)std::min<int64_t>(matvecs_chunk(op, nrhs), kScratchN2 / op->n2);
+    for (int r = 0; r < nrhs; r += chunk)
+        MBEM_TRY(matvecs_run(op, (const double2 *)x + r * N, (double2 *)y + r * N, std::min(chunk, nrhs - r), tmp,
+                             ctx->stream));
     return MBEM_OK;
 }
 

@@ -1,0 +1,82 @@
+"""Products with several vectors at once (linalg.hip, k_gemm3) against the
+product of each vector alone and the exported blocks: every chunk edge (4 and
+16 vectors and one more), tiles of 16 rows with 4 and with 12 left over, all
+storage forms, with and without the near store, compressed operators."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+if not torch.cuda.is_available():
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+from paper_2604_21181_amd import mbem  # noqa: E402
+from workloads.meshes import icosphere_p2, uv_sphere_p2  # noqa: E402
+
+MESHES = {"ico20": lambda: icosphere_p2(20), "uv70": lambda: uv_sphere_p2(7, 6), "ico320": lambda: icosphere_p2(320)}
+FORMS = {"fp64": dict(), "mixed": dict(precision=1), "store": dict(precision=1, near_store=True)}
+COUNTS = [1, 2, 3, 4, 5, 15, 16, 17, 18, 33]
+
+
+def _vectors(n, N, device):
+    rng = np.random.default_rng(n)
+    return torch.as_tensor(rng.normal(size=(n, N)) + 1j * rng.normal(size=(n, N)), device=device)
+
+
+def _solver(mesh, **kw):
+    xyz, tri = MESHES[mesh]()
+    return mbem.Solver(xyz, tri, 1.4, 3.0 + 0.2j, **kw)
+
+
+@pytest.mark.parametrize("form", sorted(FORMS))
+@pytest.mark.parametrize("mesh", sorted(MESHES))
+def test_each_vector_as_alone(mesh, form):
+    S = _solver(mesh, **FORMS[form])
+    try:
+        S.fill()
+        Z = S.export_dense() if form == "fp64" else None
+        for n in COUNTS:
+            X = _vectors(n, S.N, S.device)
+            Y = S.matvec(X)
+            # sums of at most 1300 terms in another order: 1300 eps
+            alone = torch.stack([S.matvec(x) for x in X])
+            scale = alone.abs().amax(dim=1, keepdim=True)
+            assert bool(((Y - alone).abs() <= 3e-13 * scale).all()), n
+            if Z is not None:
+                ref = X.cpu().numpy() @ Z.cpu().numpy().T
+                assert np.abs(Y.cpu().numpy() - ref).max() <= 1e-12 * np.abs(ref).max(), n
+            noalloc = torch.empty_like(X)
+            mbem.mbem_matvec_noalloc(S.ctx, S.op, X, noalloc, n)
+            torch.cuda.synchronize()
+            assert torch.equal(noalloc, Y), n
+    finally:
+        S.close()
+
+
+@pytest.mark.parametrize("n", [3, 7])
+def test_not_a_number_stays_in_its_vector(n):
+    S = _solver("uv70")
+    try:
+        S.fill()
+        X = _vectors(n, S.N, S.device)
+        want = S.matvec(X)
+        X[1, S.N - 1] = complex(float("nan"), 0.0)
+        X[2, 0] = complex(float("inf"), 0.0)
+        Y = S.matvec(X)
+        assert bool(torch.isnan(torch.view_as_real(Y[1])).any()) and not bool(torch.isfinite(torch.view_as_real(Y[2])).all())
+        keep = [v for v in range(n) if v not in (1, 2)]
+        assert torch.equal(Y[keep], want[keep])
+    finally:
+        S.close()
+
+
+def test_compressed_operator():
+    S = _solver("ico320")
+    try:
+        S.fill_compressed()
+        X = _vectors(5, S.N, S.device)
+        Y = S.matvec(X)
+        alone = torch.stack([S.matvec(x) for x in X])
+        assert bool(((Y - alone).abs() <= 3e-13 * alone.abs().amax(dim=1, keepdim=True)).all())
+    finally:
+        S.close()
