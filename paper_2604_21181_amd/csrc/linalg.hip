@@ -163,12 +163,15 @@ __global__ __launch_bounds__(256) void k_gemv3(int64_t n2, const TS *K1, const T
 //              bound by the read of the blocks;
 //   COLS = 16  (16x16x4) by the matrix units, whose 16 columns count whether
 //              they hold a vector or not.
-// One run's loads are ahead of its products; two or four runs ahead cost
-// registers and with them wavefronts (4 ahead: 397 against 305 us for two
-// vectors, n2 = 5120, FP64).  us, one after the other (k_gemv3) -> this:
-//   n2 = 5120  FP64   2: 461 -> 305   4: 921 -> 344   8: 1802 -> 420   16: 3585 -> 488
-//              mixed  2: 247 -> 252   4: 496 -> 252   8:  937 -> 372   16: 1835 -> 366
-//   n2 = 1280  FP64   2:  59 ->  53   3:  80 ->  56;  mixed  2: 66 -> 50   3: 92 -> 53
+// One run's loads are ahead of its products; more ahead cost registers and with
+// them wavefronts.  A lane without a vector multiplies vector 0 and its sums are
+// dropped: masks are for the last 4 columns alone (masked throughout, 2 vectors
+// took 252 us in place of 177 and 8 vectors 372 in place of 293, mixed).  Tiles
+// of 32 and 64 rows were slower (16 vectors 386 and 450 us in place of 376).
+// us, one after the other (k_gemv3) -> this:
+//   n2 = 5120  FP64   2: 461 -> 289   4: 921 -> 353   8: 1802 -> 352   16: 3585 -> 447
+//              mixed  2: 247 -> 177   4: 496 -> 254   8:  937 -> 293   16: 1835 -> 376
+//   n2 = 1280  FP64   2:  59 ->  39   3:  80 ->  41;  mixed  2: 66 -> 37   3: 92 -> 38
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 __device__ inline void load_pair(const float2 *p, double2 &a, double2 &b) {
@@ -205,33 +208,43 @@ __device__ inline void gemm_rows(const TS *__restrict__ K, int64_t n2, int64_t r
     const TS *a = K + row * n2;
     const double2 *xv = x + (int64_t)(col < nv ? col : 0) * 2 * n2;
     ACC acc[NS][2] = {};
-    // the next run's loads are in flight during this run's products
-    double2 a0, a1, b0[NS], b1[NS];
-    auto load = [&](int64_t c) {
-        const int64_t k = c + 2 * grp;
-        const bool in = k < n2;                        // n2 is even
-        const int64_t kc = in ? k : 0;
-        load_pair(a + kc, a0, a1);
+    struct Run { double2 a0, a1, b0[NS], b1[NS]; };
+    auto load = [&](int64_t k) {
+        Run v;
+        load_pair(a + k, v.a0, v.a1);
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            b0[s] = xv[off[s] + kc];
-            b1[s] = xv[off[s] + kc + 1];
-            if (!in || col >= nv) b0[s] = b1[s] = double2{0.0, 0.0};
-        }
-        if (!in) a0 = a1 = double2{0.0, 0.0};          // 0 x NaN would spread
+        for (int s = 0; s < NS; ++s) load_pair(xv + off[s] + k, v.b0[s], v.b1[s]);
+        return v;
     };
-    load(8 * wave);
-    for (int64_t c = 8 * wave; c < n2; c += 32) {
-        const double2 p0 = a0, p1 = a1;
-        double2 q0[NS], q1[NS];
-#pragma unroll
-        for (int s = 0; s < NS; ++s) { q0[s] = b0[s]; q1[s] = b1[s]; }
-        load(c + 32);
+    auto add = [&](const Run &v) {
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
-            mfma_complex(p0, q0[s], acc[s]);
-            mfma_complex(p1, q1[s], acc[s]);
+            mfma_complex(v.a0, v.b0[s], acc[s]);
+            mfma_complex(v.a1, v.b1[s], acc[s]);
         }
+    };
+    // the next run's loads are in flight during this run's products
+    const int64_t full = n2 / 8 * 8;
+    int64_t c = 8 * wave;
+    if (c < full) {
+        Run u = load(c + 2 * grp);
+        for (; c + 32 < full; c += 32) {
+            const Run v = u;
+            u = load(c + 32 + 2 * grp);
+            add(v);
+        }
+        add(u);
+        c += 32;
+    }
+    if (c == full && c < n2) {                         // n2 is even
+        const bool in = c + 2 * grp < n2;
+        Run u = load(in ? c + 2 * grp : c);
+        if (!in) {                                     // both factors: 0 x NaN would spread
+            u.a0 = u.a1 = double2{0.0, 0.0};
+#pragma unroll
+            for (int s = 0; s < NS; ++s) u.b0[s] = u.b1[s] = double2{0.0, 0.0};
+        }
+        add(u);
     }
     // accumulator: 16x16x4 (lane, e): row grp + 4 e, vector lane % 16; 4x4x4
     // (lane): row 4 (lane / 4 % 4) + grp, vector lane % 4
@@ -374,8 +387,8 @@ int matvec_run(const mbem_op *op, const double2 *x, double2 *y, double2 *tmp, hi
 }
 
 // Up to four vectors go through the 4-wide instructions, more through the
-// 16-wide ones: eight as two passes of four took 688 (FP64) and 493 us (mixed)
-// against 420 and 372 us.  A single vector stays with k_gemv3 (237 us FP64,
+// 16-wide ones: eight as two passes of four take 706 (FP64) and 508 us (mixed)
+// against 352 and 293 us.  A single vector stays with k_gemv3 (237 us FP64,
 // 130 us mixed), a compressed operator with its own product.
 int matvecs_chunk(const mbem_op *op, int nrhs) {
     if (op->blr) return 1;
@@ -385,12 +398,9 @@ int matvecs_chunk(const mbem_op *op, int nrhs) {
 template <typename TS>
 static void launch_products(const mbem_op *op, const double2 *x, int nv, double2 *t, hipStream_t s) {
     const int64_t n2 = op->n2;
-    const TS *K[3] = {(const TS *)op->K[0], (const TS *)op->K[1], (const TS *)op->K[2]};
-    const dim3 grid((unsigned)(3 * ((n2 + 15) / 16)));
-    if (nv <= 4)
-        hipLaunchKernelGGL((k_gemm3<TS, 4>), grid, dim3(256), 0, s, n2, K[0], K[1], K[2], x, nv, t);
-    else
-        hipLaunchKernelGGL((k_gemm3<TS, 16>), grid, dim3(256), 0, s, n2, K[0], K[1], K[2], x, nv, t);
+    auto k = nv <= 4 ? k_gemm3<TS, 4> : k_gemm3<TS, 16>;
+    hipLaunchKernelGGL(k, dim3((unsigned)(3 * ((n2 + 15) / 16))), dim3(256), 0, s, n2, (const TS *)op->K[0],
+                       (const TS *)op->K[1], (const TS *)op->K[2], x, nv, t);
 }
 
 int matvecs_run(const mbem_op *op, const double2 *x, double2 *y, int nv, double2 *tmp, hipStream_t s) {
