@@ -88,14 +88,24 @@ int rhs_run(const mbem_mesh *m, const mbem_params *p, const double *khat, const 
     return MBEM_OK;
 }
 
-// Surface currents W j, W j_m at every quadrature point of one solution:
-// cur[i][0..5] = W j (3 complex), cur[i][6..11] = W j_m.
-__global__ void k_currents(int64_t nt, int64_t n2, const double *__restrict__ qp,
+// Surface currents W j, W j_m at every quadrature point for g solutions
+// (blockIdx.y): cur[i][12 v ..] = W j (3 complex) and W j_m of solution v, and
+// the points' coordinates pos[3][np].  Points nq .. np - 1 are zeros.
+__global__ __launch_bounds__(64) void k_currents(int64_t nt, int64_t n2, const double *__restrict__ qp,
                            const int32_t *__restrict__ tri, const double *__restrict__ frames, int frame,
-                           const double2 *__restrict__ x, double *__restrict__ cur) {
+                           const double2 *__restrict__ x, int g, int64_t np, double *__restrict__ pos,
+                           double *__restrict__ cur) {
     const int64_t nq = nt * kQP;
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= nq) return;
+    if (i >= np) return;
+    double *o = cur + 12 * (i * g + blockIdx.y);
+    if (blockIdx.y == 0)
+        for (int d = 0; d < 3; ++d) pos[d * np + i] = i < nq ? qp[(QX + d) * nq + i] : 0.0;
+    if (i >= nq) {
+        for (int d = 0; d < 12; ++d) o[d] = 0.0;
+        return;
+    }
+    x += (int64_t)blockIdx.y * 2 * n2;
     const int64_t e = i / kQP;
     const int q = (int)(i % kQP);
     const double W = qp[QW * nq + i];
@@ -116,70 +126,176 @@ __global__ void k_currents(int64_t nt, int64_t n2, const double *__restrict__ qp
             }
         }
     }
-    double *o = cur + 12 * i;
     for (int d = 0; d < 3; ++d) {
         o[2 * d] = J[d].re; o[2 * d + 1] = J[d].im;
         o[6 + 2 * d] = Jm[d].re; o[6 + 2 * d + 1] = Jm[d].im;
     }
 }
 
-// F(r) = (i k / 4 pi) r x sum_q e^{-i k r.y_q} (W j x r - W j_m); one
-// workgroup per direction.
-__global__ __launch_bounds__(256) void k_farfield(int64_t nq, const double *__restrict__ qp,
-                                                  const double *__restrict__ cur,
-                                                  const double *__restrict__ rhat, double ka,
-                                                  double2 *__restrict__ F) {
-    __shared__ double s[4][6];
-    const int64_t d = blockIdx.x;
+// F(r) = (i k / 4 pi) r x sum_q e^{-i k r.y_q} (W j x r - W j_m)
+//      = (i k / 4 pi) r x (A x r - B),  [A B] = sum_q e^{-i k r.y_q} W [j j_m]:
+// a product of the phases (directions by points) and the currents (points by
+// 12 reals per solution) on the FP64 matrix cores, the phases evaluated in the
+// registers that the instruction reads.  A wavefront takes 16 directions and
+// one run of points (a multiple of 4) for up to four solutions; lane l is
+// direction l % 16, point l / 16 and column l % 16 of each of NT tiles of
+// columns.  Cosine and sine multiply the same currents, so the complex product
+// is one exchange of neighbouring columns at the end.
+// Bound by the matrix units for four solutions (6 instructions per 4 points)
+// and by the sine and cosine for one.  2592 directions, us, a workgroup per
+// direction and solution -> this:
+//   1280 triangles  one solution 259 -> 112   four  829 -> 173
+//   5120 triangles  one          936 -> 327   four 3194 -> 549
+// and 4 solutions, 100 directions, 1280 triangles 191 -> 56.  The wavefronts per
+// SIMD (__launch_bounds__) keep the sums out of the accumulation registers,
+// whose copies in every turn cost 255 us in place of 198.
+typedef double f64x4p __attribute__((ext_vector_type(4)));
+constexpr int kFarDirs = 16;                  // directions of a wavefront
+constexpr int kFarGroup = 4;                  // solutions of a launch
+constexpr int64_t kFarSlab = 32768;           // directions of a launch
+
+template <int NT>
+__global__ __launch_bounds__(256, 2) void k_farfield(int64_t np, const double *__restrict__ pos,
+                                                     const double *__restrict__ cur, int nc,
+                                                     const double *__restrict__ rhat, int64_t ndir, double ka,
+                                                     int tiles, int run, double *__restrict__ part) {
+    const int64_t wave = blockIdx.x * (int64_t)4 + __builtin_amdgcn_readfirstlane(threadIdx.x / kW2);
+    const int lane = threadIdx.x % kW2, grp = lane / 16, l16 = lane % 16;
+    const int64_t tile = wave % tiles, split = wave / tiles, p0 = split * run;
+    if (p0 >= np) return;
+    const int n = (int)(p0 + run < np ? run : np - p0);       // a multiple of 4
+    const int64_t d = tile * kFarDirs + l16 < ndir ? tile * kFarDirs + l16 : ndir - 1;
     const dvec3 r = {rhat[3 * d], rhat[3 * d + 1], rhat[3 * d + 2]};
-    double acc[6] = {0, 0, 0, 0, 0, 0};
-    for (int64_t i = threadIdx.x; i < nq; i += blockDim.x) {
-        const dvec3 y = {qp[QX * nq + i], qp[(QX + 1) * nq + i], qp[(QX + 2) * nq + i]};
-        const cx<double> ph = cexpi(-ka * dot(r, y));
-        const double *c = cur + 12 * i;
-        const cx<double> J[3] = {{c[0], c[1]}, {c[2], c[3]}, {c[4], c[5]}};
-        const cx<double> Jm[3] = {{c[6], c[7]}, {c[8], c[9]}, {c[10], c[11]}};
-        // j x r - j_m
-        const cx<double> v[3] = {r.z * J[1] - r.y * J[2] - Jm[0], r.x * J[2] - r.z * J[0] - Jm[1],
-                                 r.y * J[0] - r.x * J[1] - Jm[2]};
-        for (int k = 0; k < 3; ++k) {
-            const cx<double> t = ph * v[k];
-            acc[2 * k] += t.re;
-            acc[2 * k + 1] += t.im;
+    const double *px = pos + p0, *py = px + np, *pz = py + np, *pc = cur + p0 * nc;
+    uint32_t col[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) col[t] = grp * nc + (16 * t + l16 < nc ? 16 * t + l16 : 0);
+    f64x4p ac[NT], as[NT];
+    // returns whether a phase is beyond the short reduction's range
+    auto sums = [&](auto exact) {
+        bool far = false;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) ac[t] = as[t] = f64x4p{0.0, 0.0, 0.0, 0.0};
+        struct Points { double x, y, z, b[NT]; };
+        auto load = [&](int p) {                       // 4 points; p < n + 4
+            Points v;
+            v.x = px[(uint32_t)(p + grp)];
+            v.y = py[(uint32_t)(p + grp)];
+            v.z = pz[(uint32_t)(p + grp)];
+#pragma unroll
+            for (int t = 0; t < NT; ++t) v.b[t] = pc[(uint32_t)(p * nc) + col[t]];
+            return v;
+        };
+        auto add = [&](const Points &v) {
+            const double ph = -ka * dot(r, dvec3{v.x, v.y, v.z});
+            double sn, cs;
+            if constexpr (decltype(exact)::value) {
+                sincos(ph, &sn, &cs);
+            } else {
+                far |= !(fabs(ph) < 1048576.0);
+                sincos_t(ph, &sn, &cs);
+            }
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                ac[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(cs, v.b[t], ac[t], 0, 0, 0);
+                as[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(sn, v.b[t], as[t], 0, 0, 0);
+            }
+        };
+        Points a = load(0);                            // the next points are loaded ahead of these
+        int p = 0;
+        for (; p + 8 <= n; p += 8) {
+            const Points b = load(p + 4);
+            add(a);
+            a = load(p + 8);
+            add(b);
         }
+        if (p < n) add(a);
+        return far;
+    };
+    if (__any(sums(std::false_type{}))) sums(std::true_type{});
+    // (lane, e): direction grp + 4 e, column l16; even columns are real parts
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const double o = __shfl_xor(as[t][e], 1, kW2);
+            const double v = ac[t][e] + (l16 & 1 ? o : -o);
+            const int64_t dir = tile * kFarDirs + grp + 4 * e;
+            if (dir < ndir && 16 * t + l16 < nc) part[(split * ndir + dir) * nc + 16 * t + l16] = v;
+        }
+}
+
+// sums the runs and applies F = (i k / 4 pi) r x (A x r - B): one thread per
+// (direction, solution, component of A or B), 16 of the first two a workgroup
+__global__ __launch_bounds__(192) void k_farfield_sum(const double *__restrict__ part, int64_t ndir, int g,
+                                                      int splits, const double *__restrict__ rhat, double ka,
+                                                      int64_t stride, double2 *__restrict__ F) {
+    __shared__ double s[16][12];
+    const int64_t n = ndir * g, item = blockIdx.x * (int64_t)16 + threadIdx.x / 12;
+    const int c = threadIdx.x % 12;
+    double a = 0.0;
+    if (item < n) {
+#pragma unroll 8
+        for (int k = 0; k < splits; ++k) a += part[(k * n + item) * 12 + c];
     }
-    for (int k = 0; k < 6; ++k) acc[k] = wsum(acc[k]);
-    if (threadIdx.x % kW2 == 0)
-        for (int k = 0; k < 6; ++k) s[threadIdx.x / kW2][k] = acc[k];
+    s[threadIdx.x / 12][c] = a;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        cx<double> a[3];
-        for (int k = 0; k < 3; ++k)
-            a[k] = {s[0][2 * k] + s[1][2 * k] + s[2][2 * k] + s[3][2 * k],
-                    s[0][2 * k + 1] + s[1][2 * k + 1] + s[2][2 * k + 1] + s[3][2 * k + 1]};
-        // r x a, times i k / (4 pi)
-        const cx<double> c[3] = {r.y * a[2] - r.z * a[1], r.z * a[0] - r.x * a[2], r.x * a[1] - r.y * a[0]};
-        const double f = ka * 0.079577471545947667884;
-        for (int k = 0; k < 3; ++k) F[3 * d + k] = {-f * c[k].im, f * c[k].re};
-    }
+    const int64_t it = blockIdx.x * (int64_t)16 + threadIdx.x;
+    if (threadIdx.x >= 16 || it >= n) return;
+    const double *q = s[threadIdx.x];
+    const int64_t d = it / g, v = it % g;
+    const dvec3 r = {rhat[3 * d], rhat[3 * d + 1], rhat[3 * d + 2]};
+    const cx<double> A[3] = {{q[0], q[1]}, {q[2], q[3]}, {q[4], q[5]}};
+    const cx<double> B[3] = {{q[6], q[7]}, {q[8], q[9]}, {q[10], q[11]}};
+    const cx<double> w[3] = {r.z * A[1] - r.y * A[2] - B[0], r.x * A[2] - r.z * A[0] - B[1],
+                             r.y * A[0] - r.x * A[1] - B[2]};
+    const cx<double> o[3] = {r.y * w[2] - r.z * w[1], r.z * w[0] - r.x * w[2], r.x * w[1] - r.y * w[0]};
+    const double f = ka * 0.079577471545947667884;
+    for (int k = 0; k < 3; ++k) F[v * stride + 3 * d + k] = {-f * o[k].im, f * o[k].re};
+}
+
+// Points of a run (a multiple of 4): enough wavefronts for four a SIMD, at most
+// 64 runs, since the sum over them is a serial chain, none below 64 points, and
+// none so long that a 32-bit offset would not reach its end.
+static int64_t far_run(int64_t np, int64_t tiles) {
+    const int64_t want = std::max<int64_t>(std::min<int64_t>({(4096 + tiles - 1) / tiles, 64, (np + 63) / 64}),
+                                           (np >> 20) + 1);
+    const int64_t run = (np + want - 1) / want;
+    return (run + 3) / 4 * 4;
 }
 
 int farfield_run(const mbem_mesh *m, const mbem_params *p, const double2 *x, int nrhs,
                  const double *rhat, int64_t ndir, double2 *F, hipStream_t s) {
-    const int64_t nq = m->nt * kQP, n2 = 2 * m->nn;
-    double *cur = nullptr;
-    MBEM_HIP(dev_malloc((void **)&cur, sizeof(double) * 12 * nq));
-    for (int r = 0; r < nrhs; ++r) {
-        hipLaunchKernelGGL(k_currents, dim3((unsigned)((nq + 255) / 256)), dim3(256), 0, s, m->nt, n2,
-                           m->d_qp, m->d_tri, m->d_frames, p->frame, x + (int64_t)r * 2 * n2, cur);
-        MBEM_HIP(hipGetLastError());
-        if (ndir > 0) {
-            hipLaunchKernelGGL(k_farfield, dim3((unsigned)ndir), dim3(256), 0, s, nq, m->d_qp, cur, rhat,
-                               p->k0, F + (int64_t)r * ndir * 3);
-            MBEM_HIP(hipGetLastError());
+    const int64_t nq = m->nt * kQP, np = (nq + 3) / 4 * 4, n2 = 2 * m->nn, stride = 3 * ndir;
+    if (ndir <= 0) return MBEM_OK;
+    const int gmax = std::min(nrhs, kFarGroup);
+    int64_t room = 0;
+    for (int64_t d0 = 0; d0 < ndir; d0 += kFarSlab) {
+        const int64_t nd = std::min(kFarSlab, ndir - d0), run = far_run(np, (nd + kFarDirs - 1) / kFarDirs);
+        room = std::max(room, (np + run - 1) / run * nd);
+    }
+    // the partial sums behind the points: the loads ahead of the last points of
+    // pos and cur (4 points at most) stay inside
+    double *pos = nullptr;
+    MBEM_HIP(dev_malloc((void **)&pos, sizeof(double) * (3 * np + 12 * (np + 4 + room) * gmax)));
+    double *cur = pos + 3 * np, *part = cur + 12 * (np + 4) * gmax;
+    for (int v = 0; v < nrhs; v += kFarGroup) {
+        const int g = std::min(kFarGroup, nrhs - v), nc = 12 * g;
+        hipLaunchKernelGGL(k_currents, dim3((unsigned)((np + 63) / 64), g), dim3(64), 0, s, m->nt, n2,
+                           m->d_qp, m->d_tri, m->d_frames, p->frame, x + (int64_t)v * 2 * n2, g, np, pos, cur);
+        for (int64_t d0 = 0; d0 < ndir; d0 += kFarSlab) {
+            const int64_t nd = std::min(kFarSlab, ndir - d0), tiles = (nd + kFarDirs - 1) / kFarDirs;
+            const int64_t run = far_run(np, tiles), splits = (np + run - 1) / run;
+            auto k = g == 1 ? k_farfield<1> : g == 2 ? k_farfield<2> : k_farfield<3>;
+            hipLaunchKernelGGL(k, dim3((unsigned)((tiles * splits + 3) / 4)), dim3(256), 0, s, np, pos, cur, nc,
+                               rhat + 3 * d0, nd, p->k0, (int)tiles, (int)run, part);
+            hipLaunchKernelGGL(k_farfield_sum, dim3((unsigned)((nd * g + 15) / 16)), dim3(192), 0, s, part, nd, g,
+                               (int)splits, rhat + 3 * d0, p->k0, stride, F + v * stride + 3 * d0);
         }
     }
-    MBEM_HIP(dev_free(cur));
+    const hipError_t e = hipGetLastError();
+    MBEM_HIP(dev_free(pos));
+    MBEM_HIP(e);
     return MBEM_OK;
 }
 
