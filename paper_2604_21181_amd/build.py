@@ -37,12 +37,12 @@ def _flags(src: str):
     if src.endswith(".hip"):
         f += ["-x", "hip", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
               "-ffp-contract=fast"]
-    if src in ("fill.hip", "pairs.hip", "ssq.hip"):
+    if src in ("fill.hip", "pairs.hip", "ssq.hip", "shape.hip"):
         # machine-level loop-invariant code motion hoists every constant of
         # the Sauter-Schwab kernels' point loops into registers (248 instead
         # of 222 VGPRs), which measured 10 % slower, and those of the FP64
         # pair kernels into scalar registers that then spill (38, and 168
-        # instead of 152 VGPRs)
+        # instead of 152 VGPRs); k_shape_regular spills 28 bytes with it
         f += ["-mllvm", "-disable-machine-licm"]
     return f
 

@@ -12,10 +12,14 @@
 //                u_a = p_a x n  (= sum_alpha L s_alpha),
 //   trial point: v_j = X0 t1 + X1 t2,  v_m = X2 t1 + X3 t2  (from x).
 // The point-pair integrand of lambda^T Z x (eqs. kappa1/kappa2 summed over
-// alpha, beta with these weights) is
+// alpha, beta with these weights) is, with R the unit vector between the points,
 //   F = (i/w) [A (u1.vj - u2.vm) + df ((u1.R)(R.vj) - (u2.R)(R.vm))]
-//     + G_eps [(p1.vm)(n.R) - (p1.R)(n.vm)] + G_mu [(p2.vj)(n.R) - (p2.R)(n.vj)]
-// with A = D0 - dg.  Reverse mode: adjoints of the point quantities are
+//     + G_eps u1.(vm x R) + G_mu u2.(vj x R)
+//     = u1.S1 + u2.S2 = vj.Hj + vm.Hm
+// with A = D0 - dg (p.v (n.R) - (p.R)(n.v) = (p x n).(v x R)): linear in every
+// vector, so the adjoints of a point's vectors, normal and weight follow from
+// the sums of S (over trial points) and of H (over test points), and only the
+// position's adjoint is formed pair by pair.  Reverse mode: adjoints of the point quantities are
 // accumulated per quadrature point (regular rule) or per singular pair
 // (Sauter-Schwab points), carried back through the P2 map and the
 // Gram-Schmidt frame to node positions and nodal tangents, and through the
@@ -28,6 +32,7 @@
 #include <cmath>
 
 #include "mbem_internal.h"
+#include "kappa64.h"
 #include "p2_device.h"
 #include "ssq_map.h"
 
@@ -59,8 +64,9 @@ __device__ inline dvec3 im3(cv3 a) { return {a.x.im, a.y.im, a.z.im}; }
 __device__ inline cxd cscale(double s, cxd a) { return {s * a.re, s * a.im}; }
 
 // ------------------------------ kernel differences and their R-derivatives --
+// times i/w (a, d: A = D0 - dg and df) and d/dR of each
 struct KScalD {
-    cxd A, Ap, df, dfp, Ge, Gep, Gm, Gmp;   // A = D0 - dg; p = d/dR
+    cxd a, ap, d, dp, Ge, Gep, Gm, Gmp;
 };
 
 __device__ inline void horner_d(const double *c, double R, cxd &S, cxd &Sp) {
@@ -72,76 +78,96 @@ __device__ inline void horner_d(const double *c, double R, cxd &S, cxd &Sp) {
     }
 }
 
-// Same branches as kernel_scalars: Taylor series below max|k| R = 1/2,
-// closed forms above, with
-//   phi' = phi (i k - 1/R),  f' = e k^2 (1 - i k R) / (4 pi R^2) - 3 f / R,
-//   g' = e k^2 / (4 pi R^2) - 3 g / R.
-__device__ KScalD kernel_scalars_dr(const KernelConst &K, double R) {
-    const double inv4pi = 0.079577471545947667884;
+struct ShapeConst {
+    PairConst kc;
+    cxd iw;
+};
+
+// Same branches as kernel_scalars: Taylor series (Ks) below max|k| R = 1/2,
+// closed forms above.  Per medium, with t = k R and e = e^{it} / (4 pi R^3),
+//   g = e (1 - i t), h = e t^2, q = g t^2:  D0 = h, f = 3 g - h,
+//   R g' = -f,  R f' = q - 3 f,  R D0' = -q,
+// and (R g)' = h - 2 g in G_chi = -R (g_a - chi_i g_i).
+__device__ __forceinline__ KScalD kernel_scalars_dr(const ShapeConst &C, const KernelConst &Ks, double R,
+                                                    double rinv) {
+    const PairConst &K = C.kc;
     KScalD o;
-    const double r1 = inv4pi / R, r2 = r1 / R, r3 = r2 / R;
+    cxd A, Ap, df, dfp;
     if (K.kmax * R < kSeriesRho) {
-        cxd SD, SDp, SF, SFp, SG, SGp, SE, SEp, SM, SMp;
-        horner_d(K.cD, R, SD, SDp);
-        horner_d(K.cF, R, SF, SFp);
-        horner_d(K.cG, R, SG, SGp);
-        horner_d(K.cE, R, SE, SEp);
-        horner_d(K.cM, R, SM, SMp);
-        const cxd D0 = r1 * SD, D0p = cscale(-1.0 / R, D0) + r1 * SDp;
-        o.df = r3 * SF;
-        o.dfp = cscale(-3.0 / R, o.df) + r3 * SFp;
-        const cxd dg = r3 * SG, dgp = cscale(-3.0 / R, dg) + r3 * SGp;
-        o.Ge = r2 * SE;
-        o.Gep = cscale(-2.0 / R, o.Ge) + r2 * SEp;
-        o.Gm = r2 * SM;
-        o.Gmp = cscale(-2.0 / R, o.Gm) + r2 * SMp;
-        o.A = D0 - dg;
-        o.Ap = D0p - dgp;
-        return o;
-    }
-    const cxd k[2] = {{K.ka_re, K.ka_im}, {K.ki_re, K.ki_im}};
-    const cxd ch[2] = {{K.eps_a_re, K.eps_a_im}, {K.eps_i_re, K.eps_i_im}};
-    const cxd cm[2] = {{K.mu_a_re, K.mu_a_im}, {K.mu_i_re, K.mu_i_im}};
-    cxd D0 = {0, 0}, D0p = {0, 0}, dg = {0, 0}, dgp = {0, 0}, Eg = {0, 0}, Egp = {0, 0}, Mg = {0, 0}, Mgp = {0, 0};
-    o.df = {0, 0};
-    o.dfp = {0, 0};
-    for (int s = 0; s < 2; ++s) {
-        const double sg = s == 0 ? 1.0 : -1.0;
+        const double r1 = 0.079577471545947667884 * rinv, r2 = r1 * rinv, r3 = r2 * rinv;
+        cxd S, Sp;
+        horner_d(Ks.cD, R, S, Sp);
+        A = r1 * S;
+        Ap = r1 * Sp - rinv * A;
+        horner_d(Ks.cG, R, S, Sp);
+        const cxd dg = r3 * S;
+        A = A - dg;
+        Ap = Ap - (r3 * Sp - (3.0 * rinv) * dg);
+        horner_d(Ks.cF, R, S, Sp);
+        df = r3 * S;
+        dfp = r3 * Sp - (3.0 * rinv) * df;
+        horner_d(Ks.cE, R, S, Sp);
+        o.Ge = r2 * S;
+        o.Gep = r2 * Sp - (2.0 * rinv) * o.Ge;
+        horner_d(Ks.cM, R, S, Sp);
+        o.Gm = r2 * S;
+        o.Gmp = r2 * Sp - (2.0 * rinv) * o.Gm;
+    } else {
+        const double r3 = 0.079577471545947667884 * rinv * (rinv * rinv);
         double sn, cs;
-        sincos_t(k[s].re * R, &sn, &cs);
-        const double am = exp(-k[s].im * R);
-        const cxd e = {am * cs, am * sn};
-        const cxd ikR = {-k[s].im * R, k[s].re * R};
-        const cxd k2 = k[s] * k[s];
-        const cxd phi = r1 * e;
-        const cxd phip = phi * cxd{-k[s].im - 1.0 / R, k[s].re};
-        const cxd one_m = {1.0 - ikR.re, -ikR.im};
-        const cxd f = r3 * (e * cxd{3.0 - 3.0 * ikR.re - (k2.re * R * R), -3.0 * ikR.im - k2.im * R * R});
-        const cxd fp = r2 * (e * (k2 * one_m)) - cscale(3.0 / R, f);
-        const cxd g = r3 * (e * one_m);
-        const cxd gp = r2 * (e * k2) - cscale(3.0 / R, g);
-        D0 = D0 + cscale(sg, k2 * phi);
-        D0p = D0p + cscale(sg, k2 * phip);
-        o.df = o.df + cscale(sg, f);
-        o.dfp = o.dfp + cscale(sg, fp);
-        dg = dg + cscale(sg, g);
-        dgp = dgp + cscale(sg, gp);
-        Eg = Eg + cscale(sg, ch[s] * g);
-        Egp = Egp + cscale(sg, ch[s] * gp);
-        Mg = Mg + cscale(sg, cm[s] * g);
-        Mgp = Mgp + cscale(sg, cm[s] * gp);
+        const double ta = K.ka * R, ta2 = ta * ta;
+        sincos_t(ta, &sn, &cs);
+        const cxd ea = {r3 * cs, r3 * sn};
+        const cxd ga = {fma(ea.im, ta, ea.re), fma(-ea.re, ta, ea.im)}, ha = ta2 * ea;
+        const double tr = K.ki_re * R, ti = K.ki_im * R;
+        sincos_t(tr, &sn, &cs);
+        const double am = K.ki_im == 0.0 ? r3 : r3 * exp(-ti);
+        const cxd ei = {am * cs, am * sn};
+        const double u = 1.0 + ti;
+        const cxd gi = {fma(ei.im, tr, ei.re * u), fma(-ei.re, tr, ei.im * u)};
+        const cxd t2 = {fma(tr, tr, -(ti * ti)), 2.0 * tr * ti};
+        const cxd hi = t2 * ei, q = ta2 * ga - t2 * gi;
+        const cxd D0 = ha - hi, dg = ga - gi;
+        df = 3.0 * dg - D0;
+        dfp = rinv * (q - 3.0 * df);
+        A = D0 - dg;
+        Ap = rinv * (df - q);
+        const cxd ep = {K.eps_re, K.eps_im}, mu = {K.mu_re, K.mu_im};
+        const cxd Eg = ga - ep * gi, Mg = ga - mu * gi;
+        o.Ge = (-R) * Eg;
+        o.Gep = 2.0 * Eg - (ha - ep * hi);
+        o.Gm = (-R) * Mg;
+        o.Gmp = 2.0 * Mg - (ha - mu * hi);
     }
-    // G_chi = -R (chi_a g_a - chi_i g_i)
-    o.Ge = cscale(-R, Eg);
-    o.Gep = cscale(-1.0, Eg) + cscale(-R, Egp);
-    o.Gm = cscale(-R, Mg);
-    o.Gmp = cscale(-1.0, Mg) + cscale(-R, Mgp);
-    o.A = D0 - dg;
-    o.Ap = D0p - dgp;
+    o.a = C.iw * A;
+    o.ap = C.iw * Ap;
+    o.d = C.iw * df;
+    o.dp = C.iw * dfp;
     return o;
 }
 
 // ------------------------------------------------- point-pair adjoint ---
+// Adds S1, S2, Hj and Hm of one pair (R = x - y, h = R / |R|) and returns
+// d Im F / dR.
+__device__ __forceinline__ dvec3 pair_terms(const KScalD &s, dvec3 h, double rinv, cv3 u1, cv3 u2, cv3 vj, cv3 vm,
+                                            cv3 &S1, cv3 &S2, cv3 &Hj, cv3 &Hm) {
+    const cxd v1 = cdot(vj, h), v2 = cdot(vm, h), w1 = cdot(u1, h), w2 = cdot(u2, h);
+    const cxd dv1 = s.d * v1, dv2 = s.d * v2, dw1 = s.d * w1, dw2 = s.d * w2;
+    const cv3 xm = ccross(vm, h), xj = ccross(vj, h);
+    S1 = S1 + (s.a * vj + dv1 * h + s.Ge * xm);
+    S2 = S2 + (s.Gm * xj - (s.a * vm + dv2 * h));
+    Hj = Hj + (s.a * u1 + dw1 * h + s.Gm * ccross(h, u2));
+    Hm = Hm + (s.Ge * ccross(h, u1) - (s.a * u2 + dw2 * h));
+    const cxd al = cdot(u1, vj) - cdot(u2, vm), be = w1 * v1 - w2 * v2;
+    const cxd ee = cdot(u1, xm), mm = cdot(u2, xj);
+    // transverse part: the derivative of F by h
+    const dvec3 w = im3(dw1 * vj) + im3(dv1 * u1) - im3(dw2 * vm) - im3(dv2 * u2) + im3(ccross(s.Ge * u1, vm)) +
+                    im3(ccross(s.Gm * u2, vj));
+    const double wr = (2.0 * (s.d * be) + s.Ge * ee + s.Gm * mm).im;
+    const double gr = (s.ap * al + s.dp * be + s.Gep * ee + s.Gmp * mm).im;
+    return rinv * w + (gr - rinv * wr) * h;
+}
+
 struct TPt {
     dvec3 x, n, t1, t2;
     double W;
@@ -219,66 +245,52 @@ __device__ inline void nodal_tangent_adjoint(const int32_t *t, const double N[6]
     }
 }
 
-// Adds d Im(c) / d(point quantities) for c = -wfac W_x W_y F.
-template <bool WT, bool WS, bool NODAL = false>
-__device__ void pair_adjoint(const KernelConst &K, cxd iw, const TPt &P, const SPt &Q, double wfac, TGrad &gt,
-                             SGrad &gs) {
-    const dvec3 Rv = P.x - Q.y;
-    const double R = sqrt(dot(Rv, Rv));
-    const dvec3 Rh = (1.0 / R) * Rv;
-    const KScalD s = kernel_scalars_dr(K, R);
+// Adjoints of a test point's p1, p2, n and W for c (u1.S1 + u2.S2) / W.
+template <bool NODAL>
+__device__ inline void test_adjoint(const TPt &P, cv3 S1, cv3 S2, double c, TGrad &gt) {
     const cv3 p1 = P.L[0] * P.t1 + P.L[1] * P.t2, p2 = P.L[2] * P.t1 + P.L[3] * P.t2;
-    const cv3 u1 = ccross(p1, P.n), u2 = ccross(p2, P.n);
+    const cv3 g1 = ccross(P.n, S1), g2 = ccross(P.n, S2);
+    const double cw = c * P.W;
+    gt.n = gt.n + cw * im3(ccross(S1, p1) + ccross(S2, p2));
+    if constexpr (NODAL) {
+        gt.p1 = gt.p1 + cw * g1;
+        gt.p2 = gt.p2 + cw * g2;
+    } else {
+        gt.t1 = gt.t1 + cw * im3(P.L[0] * g1 + P.L[2] * g2);
+        gt.t2 = gt.t2 + cw * im3(P.L[1] * g1 + P.L[3] * g2);
+    }
+    // p.(n x S) = (p x n).S
+    gt.W += c * (cdot(p1, g1) + cdot(p2, g2)).im;
+}
+template <bool NODAL>
+__device__ inline void trial_adjoint(const SPt &Q, cv3 Hj, cv3 Hm, double c, SGrad &gs) {
+    const double cw = c * Q.W;
     const cv3 vj = Q.X[0] * Q.t1 + Q.X[1] * Q.t2, vm = Q.X[2] * Q.t1 + Q.X[3] * Q.t2;
-    const double nR = dot(P.n, Rh);
-    const cxd uv1 = cdot(u1, vj), uR1 = cdot(u1, Rh), Rv1 = cdot(vj, Rh);
-    const cxd uv2 = cdot(u2, vm), uR2 = cdot(u2, Rh), Rv2 = cdot(vm, Rh);
-    const cxd pv1 = cdot(p1, vm), pR1 = cdot(p1, Rh), nv1 = cdot(vm, P.n);
-    const cxd pv2 = cdot(p2, vj), pR2 = cdot(p2, Rh), nv2 = cdot(vj, P.n);
-    const cxd k1 = s.A * (uv1 - uv2) + s.df * (uR1 * Rv1 - uR2 * Rv2);
-    const cxd e2 = pv1 * cxd{nR, 0.0} - pR1 * nv1, m2 = pv2 * cxd{nR, 0.0} - pR2 * nv2;
-    const cxd F = iw * k1 + s.Ge * e2 + s.Gm * m2;
-    // complex gradients of F
-    const cv3 g_u1 = iw * (s.A * vj + (s.df * Rv1) * Rh);
-    const cv3 g_u2 = cxd{-iw.re, -iw.im} * (s.A * vm + (s.df * Rv2) * Rh);
-    const cv3 g_Rh = iw * (s.df * (uR1 * vj + Rv1 * u1 - uR2 * vm - Rv2 * u2)) +
-                     s.Ge * (pv1 * P.n - nv1 * p1) + s.Gm * (pv2 * P.n - nv2 * p2);
-    const cxd g_R = iw * (s.Ap * (uv1 - uv2) + s.dfp * (uR1 * Rv1 - uR2 * Rv2)) + s.Gep * e2 + s.Gmp * m2;
-    const cxd gRh_Rh = cdot(g_Rh, Rh);
-    const cv3 g_Rv = (1.0 / R) * (g_Rh - gRh_Rh * Rh) + g_R * Rh;
-    const double c = -wfac * P.W * Q.W;
-    if (WT) {
-        const cv3 g_p1 = s.Ge * (cxd{nR, 0.0} * vm - nv1 * Rh) + ccross(P.n, g_u1);
-        const cv3 g_p2 = s.Gm * (cxd{nR, 0.0} * vj - nv2 * Rh) + ccross(P.n, g_u2);
-        const cv3 g_n = s.Ge * (pv1 * Rh - pR1 * vm) + s.Gm * (pv2 * Rh - pR2 * vj) + ccross(g_u1, p1) +
-                        ccross(g_u2, p2);
-        gt.x = gt.x + c * im3(g_Rv);
-        gt.n = gt.n + c * im3(g_n);
-        if constexpr (NODAL) {
-            gt.p1 = gt.p1 + c * g_p1;
-            gt.p2 = gt.p2 + c * g_p2;
-        } else {
-            const cv3 g_t1 = P.L[0] * g_p1 + P.L[2] * g_p2, g_t2 = P.L[1] * g_p1 + P.L[3] * g_p2;
-            gt.t1 = gt.t1 + c * im3(g_t1);
-            gt.t2 = gt.t2 + c * im3(g_t2);
-        }
-        gt.W += -wfac * Q.W * F.im;
+    if constexpr (NODAL) {
+        gs.vj = gs.vj + cw * Hj;
+        gs.vm = gs.vm + cw * Hm;
+    } else {
+        gs.t1 = gs.t1 + cw * im3(Q.X[0] * Hj + Q.X[2] * Hm);
+        gs.t2 = gs.t2 + cw * im3(Q.X[1] * Hj + Q.X[3] * Hm);
     }
-    if (WS) {
-        const cv3 g_vj = iw * (s.A * u1 + (s.df * uR1) * Rh) + s.Gm * (cxd{nR, 0.0} * p2 - pR2 * P.n);
-        const cv3 g_vm = cxd{-iw.re, -iw.im} * (s.A * u2 + (s.df * uR2) * Rh) +
-                         s.Ge * (cxd{nR, 0.0} * p1 - pR1 * P.n);
-        gs.y = gs.y - c * im3(g_Rv);
-        if constexpr (NODAL) {
-            gs.vj = gs.vj + c * g_vj;
-            gs.vm = gs.vm + c * g_vm;
-        } else {
-            const cv3 g_t1 = Q.X[0] * g_vj + Q.X[2] * g_vm, g_t2 = Q.X[1] * g_vj + Q.X[3] * g_vm;
-            gs.t1 = gs.t1 + c * im3(g_t1);
-            gs.t2 = gs.t2 + c * im3(g_t2);
-        }
-        gs.W += -wfac * P.W * F.im;
-    }
+    gs.W += c * (cdot(vj, Hj) + cdot(vm, Hm)).im;
+}
+
+// Adds d Im(c) / d(point quantities) for c = -wfac W_x W_y F.
+template <bool NODAL>
+__device__ inline void pair_adjoint(const ShapeConst &C, const KernelConst &Ks, const TPt &P, const SPt &Q,
+                                    double wfac, TGrad &gt, SGrad &gs) {
+    const dvec3 Rv = P.x - Q.y;
+    const double d2 = dot(Rv, Rv), rinv = rsqrt64(d2);
+    const KScalD s = kernel_scalars_dr(C, Ks, d2 * rinv, rinv);
+    const cv3 u1 = ccross(P.L[0] * P.t1 + P.L[1] * P.t2, P.n), u2 = ccross(P.L[2] * P.t1 + P.L[3] * P.t2, P.n);
+    const cv3 vj = Q.X[0] * Q.t1 + Q.X[1] * Q.t2, vm = Q.X[2] * Q.t1 + Q.X[3] * Q.t2;
+    cv3 S1 = czero3(), S2 = S1, Hj = S1, Hm = S1;
+    const dvec3 g = (-wfac * P.W * Q.W) * pair_terms(s, rinv * Rv, rinv, u1, u2, vj, vm, S1, S2, Hj, Hm);
+    gt.x = gt.x + g;
+    gs.y = gs.y - g;
+    test_adjoint<NODAL>(P, S1, S2, -wfac * Q.W, gt);
+    trial_adjoint<NODAL>(Q, Hj, Hm, -wfac * P.W, gs);
 }
 
 // --------------------------------------------------- per-point fields ---
@@ -286,11 +298,13 @@ __device__ void pair_adjoint(const KernelConst &K, cxd iw, const TPt &P, const S
 // NODAL: the components in the point frame of the node-attached fields,
 // L = (m1.t1, m1.t2, m2.t1, m2.t2) with m1, m2 the fields of lambda's two
 // currents, X likewise from x, so that L0 t1 + L1 t2 = P m1 exactly.
+// tab[14][nq]: the position (3 reals and a zero), then W u1, W u2, W vj, W vm.
+constexpr int kTab = 14;
 template <bool NODAL>
 __global__ void k_qp_fields(int64_t nt, int64_t n2, const int32_t *__restrict__ tri,
                             const double *__restrict__ qp, const double *__restrict__ frames,
                             const double2 *__restrict__ lam, const double2 *__restrict__ x,
-                            double *__restrict__ fields) {
+                            double *__restrict__ fields, double2 *__restrict__ tab) {
     const int64_t nq = nt * kQP;
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i >= nq) return;
@@ -298,29 +312,36 @@ __global__ void k_qp_fields(int64_t nt, int64_t n2, const int32_t *__restrict__ 
     double xi, eta, w, N[6], d1[6], d2[6];
     rule7((int)(i % kQP), xi, eta, w);
     p2_shape(xi, eta, N, d1, d2);
+    const dvec3 t1 = {qp[QT1 * nq + i], qp[(QT1 + 1) * nq + i], qp[(QT1 + 2) * nq + i]};
+    const dvec3 t2 = {qp[QT2 * nq + i], qp[(QT2 + 1) * nq + i], qp[(QT2 + 2) * nq + i]};
+    cxd c[8];
     if constexpr (NODAL) {
-        const dvec3 t1 = {qp[QT1 * nq + i], qp[(QT1 + 1) * nq + i], qp[(QT1 + 2) * nq + i]};
-        const dvec3 t2 = {qp[QT2 * nq + i], qp[(QT2 + 1) * nq + i], qp[(QT2 + 2) * nq + i]};
-        const double2 *c[4] = {lam, lam + n2, x, x + n2};
+        const double2 *cf[4] = {lam, lam + n2, x, x + n2};
         for (int f = 0; f < 4; ++f) {
-            const cv3 m = nodal_field(frames, tri + 6 * e, N, c[f]);
-            const cxd a = cdot(m, t1), b = cdot(m, t2);
-            fields[16 * i + 4 * f] = a.re;
-            fields[16 * i + 4 * f + 1] = a.im;
-            fields[16 * i + 4 * f + 2] = b.re;
-            fields[16 * i + 4 * f + 3] = b.im;
+            const cv3 m = nodal_field(frames, tri + 6 * e, N, cf[f]);
+            c[2 * f] = cdot(m, t1);
+            c[2 * f + 1] = cdot(m, t2);
         }
-        return;
+    } else {
+        for (int k = 0; k < 8; ++k) c[k] = {0.0, 0.0};
+        for (int k = 0; k < 6; ++k) {
+            const int64_t nd = tri[6 * e + k];
+            const double2 v[8] = {lam[2 * nd], lam[2 * nd + 1], lam[n2 + 2 * nd], lam[n2 + 2 * nd + 1],
+                                  x[2 * nd], x[2 * nd + 1], x[n2 + 2 * nd], x[n2 + 2 * nd + 1]};
+            for (int j = 0; j < 8; ++j) c[j] = c[j] + cxd{N[k] * v[j].x, N[k] * v[j].y};
+        }
     }
-    double acc[16];
-    for (int c = 0; c < 16; ++c) acc[c] = 0.0;
-    for (int k = 0; k < 6; ++k) {
-        const int64_t nd = tri[6 * e + k];
-        const double2 v[8] = {lam[2 * nd], lam[2 * nd + 1], lam[n2 + 2 * nd], lam[n2 + 2 * nd + 1],
-                              x[2 * nd], x[2 * nd + 1], x[n2 + 2 * nd], x[n2 + 2 * nd + 1]};
-        for (int c = 0; c < 8; ++c) { acc[2 * c] += N[k] * v[c].x; acc[2 * c + 1] += N[k] * v[c].y; }
+    for (int k = 0; k < 8; ++k) { fields[16 * i + 2 * k] = c[k].re; fields[16 * i + 2 * k + 1] = c[k].im; }
+    const dvec3 nv = {qp[QN * nq + i], qp[(QN + 1) * nq + i], qp[(QN + 2) * nq + i]};
+    const double W = qp[QW * nq + i];
+    tab[i] = double2{qp[QX * nq + i], qp[(QX + 1) * nq + i]};
+    tab[nq + i] = double2{qp[(QX + 2) * nq + i], 0.0};
+    for (int f = 0; f < 4; ++f) {
+        const cv3 m = W * (c[2 * f] * t1 + c[2 * f + 1] * t2), v = f < 2 ? ccross(m, nv) : m;
+        tab[(2 + 3 * f) * nq + i] = double2{v.x.re, v.x.im};
+        tab[(3 + 3 * f) * nq + i] = double2{v.y.re, v.y.im};
+        tab[(4 + 3 * f) * nq + i] = double2{v.z.re, v.z.im};
     }
-    for (int c = 0; c < 16; ++c) fields[16 * i + c] = acc[c];
 }
 
 __device__ inline void load_tpt(const double *qp, const double *fields, int64_t nq, int64_t i, TPt &P) {
@@ -341,13 +362,6 @@ __device__ inline void load_spt(const double *qp, const double *fields, int64_t 
     for (int c = 0; c < 4; ++c) Q.X[c] = {f[2 * c], f[2 * c + 1]};
 }
 
-__device__ inline bool share_vertex(const int32_t *te, const int32_t *tf) {
-    bool s = false;
-    for (int a = 0; a < 3; ++a)
-        for (int b = 0; b < 3; ++b) s = s || te[a] == tf[b];
-    return s;
-}
-
 // --------------------------------------------------- regular pairs ---
 // Point adjoint table qb[i][13]: x(3), W(1), n(3), t1(3), t2(3).
 // NODAL, qb[i][31]: x(3), W(1), n(3), then the complex adjoints (re, im per
@@ -355,81 +369,111 @@ __device__ inline bool share_vertex(const int32_t *te, const int32_t *tf) {
 constexpr int kQB = 13;
 constexpr int kQBN = 31;
 template <bool NODAL> constexpr int qb_stride() { return NODAL ? kQBN : kQB; }
-constexpr int kGroups = 36;   // 36 x 7 = 252 threads
 
 __device__ inline void put_cv3(double *o, cv3 v) {
     o[0] = v.x.re; o[1] = v.x.im; o[2] = v.y.re; o[3] = v.y.im; o[4] = v.z.re; o[5] = v.z.im;
 }
 __device__ inline cv3 get_cv3(const double *o) { return {{o[0], o[1]}, {o[2], o[3]}, {o[4], o[5]}}; }
 
-// TEST = true: workgroup per test triangle e, its 7 points accumulate over
-// every regular trial point; TEST = false: the same with roles exchanged.
-template <bool TEST, bool NODAL>
-__global__ __launch_bounds__(256) void k_shape_regular(int64_t nt, const double *__restrict__ qp,
-                                                       const double *__restrict__ fields,
-                                                       const int32_t *__restrict__ tri, const KernelConst *Kp,
-                                                       cxd iw, double *__restrict__ qb) {
-    constexpr int kS = qb_stride<NODAL>();
-    __shared__ double s_red[kGroups][kQP][kS];
-    const int tid = threadIdx.x;
-    const int64_t e = blockIdx.x;
-    const int64_t nq = nt * kQP;
-    const int q = tid % kQP, grp = tid / kQP;
-    const bool active = grp < kGroups;
-    const KernelConst &K = *Kp;
-    TGrad gt;
-    SGrad gs;
-    zero(gt);
-    zero(gs);
-    const int32_t *te = tri + 6 * e;
-    if (active) {
-        TPt P;
-        SPt Q;
-        if (TEST) load_tpt(qp, fields, nq, e * kQP + q, P);
-        else load_spt(qp, fields, nq, e * kQP + q, Q);
-        for (int64_t idx = grp; idx < nq; idx += kGroups) {
-            const int64_t f = idx / kQP;
-            if (share_vertex(te, tri + 6 * f)) continue;
-            if (TEST) {
-                load_spt(qp, fields, nq, idx, Q);
-                pair_adjoint<true, false, NODAL>(K, iw, P, Q, 1.0, gt, gs);
-            } else {
-                load_tpt(qp, fields, nq, idx, P);
-                pair_adjoint<false, true, NODAL>(K, iw, P, Q, 1.0, gt, gs);
-            }
-        }
-        double v[kS];
-        for (int c = 0; c < kS; ++c) v[c] = 0.0;
-        if (TEST) {
-            v[0] = gt.x.x; v[1] = gt.x.y; v[2] = gt.x.z; v[3] = gt.W;
-            v[4] = gt.n.x; v[5] = gt.n.y; v[6] = gt.n.z;
-            if constexpr (NODAL) {
-                put_cv3(v + 7, gt.p1);
-                put_cv3(v + 13, gt.p2);
-            } else {
-                v[7] = gt.t1.x; v[8] = gt.t1.y; v[9] = gt.t1.z; v[10] = gt.t2.x; v[11] = gt.t2.y; v[12] = gt.t2.z;
-            }
-        } else {
-            v[0] = gs.y.x; v[1] = gs.y.y; v[2] = gs.y.z; v[3] = gs.W;
-            if constexpr (NODAL) {
-                put_cv3(v + 19, gs.vj);
-                put_cv3(v + 25, gs.vm);
-            } else {
-                v[7] = gs.t1.x; v[8] = gs.t1.y; v[9] = gs.t1.z; v[10] = gs.t2.x; v[11] = gs.t2.y; v[12] = gs.t2.z;
-            }
-        }
-        for (int c = 0; c < kS; ++c) s_red[grp][q][c] = v[c];
+// One wavefront per (64 test points, 64 trial points, run of steps): lane l
+// holds test point l and meets trial point (l + s) % 64 in step s, whose data
+// and sums wait in LDS, so each pair is evaluated once for both sides and no
+// sum crosses lanes.  acc[30][nq]: S1, S2 and the position's sum of the test
+// point, Hj, Hm and the position's sum of the trial point.
+// Bound by FP64 vector instructions (about 500 a pair).  Sphere of 1280
+// triangles: 7.3 ms as two passes with one side's adjoints formed pair by pair,
+// divisions and a reduction at the end -> 2.0 ms here.
+constexpr int kSide = 15;     // sums of one side
+constexpr int kShapeTile = 64;
+
+__device__ inline dvec3 tab_pos(double2 a, double2 b) { return {a.x, a.y, b.x}; }
+__device__ inline cv3 tab_vec(double2 a, double2 b, double2 c) { return {{a.x, a.y}, {b.x, b.y}, {c.x, c.y}}; }
+
+__global__ __launch_bounds__(64, 2) void k_shape_regular(int64_t nq, int tiles, int steps,
+                                                         const double2 *__restrict__ tab,
+                                                         const int32_t *__restrict__ tri, ShapeConst C,
+                                                         const KernelConst *__restrict__ Kp,
+                                                         double *__restrict__ acc) {
+    __shared__ double2 s_t[8][kShapeTile], s_a[8][kShapeTile];
+    __shared__ int32_t s_f[3][kShapeTile];
+    __shared__ KernelConst s_K;
+    const int lane = threadIdx.x;
+    const int64_t i = (int64_t)blockIdx.y * kShapeTile + lane, j = (int64_t)(blockIdx.x % tiles) * kShapeTile + lane;
+    const int s0 = (int)(blockIdx.x / tiles) * steps;
+    constexpr int nw = (int)(sizeof(KernelConst) / sizeof(double));
+    for (int k = lane; k < nw; k += 64) ((double *)&s_K)[k] = ((const double *)Kp)[k];
+    const int64_t ic = i < nq ? i : nq - 1, jc = j < nq ? j : nq - 1;
+    int32_t te[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        te[k] = tri[6 * (ic / kQP) + k];
+        s_f[k][lane] = j < nq ? tri[6 * (jc / kQP) + k] : -1;
     }
+    const dvec3 x = tab_pos(tab[ic], tab[nq + ic]);
+    const cv3 u1 = tab_vec(tab[2 * nq + ic], tab[3 * nq + ic], tab[4 * nq + ic]);
+    const cv3 u2 = tab_vec(tab[5 * nq + ic], tab[6 * nq + ic], tab[7 * nq + ic]);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        s_t[k][lane] = tab[(k < 2 ? k : 6 + k) * nq + jc];
+        s_a[k][lane] = double2{0.0, 0.0};
+    }
+    cv3 S1 = czero3(), S2 = S1;
+    dvec3 gx = {0, 0, 0};
     __syncthreads();
-    if (tid < kQP * kS) {
-        const int qq = tid / kS, c = tid % kS;
-        double acc = 0.0;
-        for (int g = 0; g < kGroups; ++g) acc += s_red[g][qq][c];
-        qb[(e * kQP + qq) * kS + c] += acc;
+    for (int s = s0; s < s0 + steps; ++s) {
+        const int k = (lane + s) % kShapeTile;
+        const int32_t f0 = s_f[0][k], f1 = s_f[1][k], f2 = s_f[2][k];
+        bool on = i < nq && f0 >= 0;                   // pairs that share a vertex are not regular
+#pragma unroll
+        for (int c = 0; c < 3; ++c) on = on && te[c] != f0 && te[c] != f1 && te[c] != f2;
+        if (on) {
+            const dvec3 Rv = x - tab_pos(s_t[0][k], s_t[1][k]);
+            const cv3 vj = tab_vec(s_t[2][k], s_t[3][k], s_t[4][k]), vm = tab_vec(s_t[5][k], s_t[6][k], s_t[7][k]);
+            const double d2 = dot(Rv, Rv), rinv = rsqrt64(d2);
+            const KScalD sc = kernel_scalars_dr(C, s_K, d2 * rinv, rinv);
+            cv3 Hj = tab_vec(s_a[0][k], s_a[1][k], s_a[2][k]), Hm = tab_vec(s_a[3][k], s_a[4][k], s_a[5][k]);
+            const dvec3 g = pair_terms(sc, rinv * Rv, rinv, u1, u2, vj, vm, S1, S2, Hj, Hm);
+            gx = gx + g;
+            s_a[0][k] = double2{Hj.x.re, Hj.x.im};
+            s_a[1][k] = double2{Hj.y.re, Hj.y.im};
+            s_a[2][k] = double2{Hj.z.re, Hj.z.im};
+            s_a[3][k] = double2{Hm.x.re, Hm.x.im};
+            s_a[4][k] = double2{Hm.y.re, Hm.y.im};
+            s_a[5][k] = double2{Hm.z.re, Hm.z.im};
+            const double2 a6 = s_a[6][k], a7 = s_a[7][k];
+            s_a[6][k] = double2{a6.x + g.x, a6.y + g.y};
+            s_a[7][k] = double2{a7.x + g.z, 0.0};
+        }
+        __syncthreads();                               // the next lane's turn at trial point k
+    }
+    if (i < nq) {
+        const double v[kSide] = {S1.x.re, S1.x.im, S1.y.re, S1.y.im, S1.z.re, S1.z.im, S2.x.re, S2.x.im,
+                                 S2.y.re, S2.y.im, S2.z.re, S2.z.im, gx.x, gx.y, gx.z};
+#pragma unroll
+        for (int c = 0; c < kSide; ++c) unsafeAtomicAdd(acc + c * nq + i, v[c]);
+    }
+    if (j < nq) {
+#pragma unroll
+        for (int c = 0; c < kSide; ++c)
+            unsafeAtomicAdd(acc + (kSide + c) * nq + j, c & 1 ? s_a[c / 2][lane].y : s_a[c / 2][lane].x);
     }
 }
 
+// What acc holds at point i, as adjoints of its quantities.
+template <bool NODAL>
+__device__ inline void regular_adjoint(const double *__restrict__ acc, int64_t nq, int64_t i, const TPt &P,
+                                       const SPt &Q, TGrad &gt, SGrad &gs) {
+    double v[2 * kSide];
+#pragma unroll
+    for (int c = 0; c < 2 * kSide; ++c) v[c] = acc[c * nq + i];
+    test_adjoint<NODAL>(P, get_cv3(v), get_cv3(v + 6), -1.0, gt);
+    trial_adjoint<NODAL>(Q, get_cv3(v + kSide), get_cv3(v + kSide + 6), -1.0, gs);
+    gt.x = gt.x - dvec3{v[12], v[13], v[14]};
+    gs.y = gs.y + dvec3{v[kSide + 12], v[kSide + 13], v[kSide + 14]};
+}
+
 // ------------------------------------------------ single-point terms ---
+// The regular pairs' sums (acc) and
 // + Im(g^T x)    far field functional, g^T x = sum_q pre W [j.e_perp - j_m.(e x r)]
 // + Im(lambda^T b)  right-hand side, sum_q W [-u1.E + u2.H]
 // - Im(lambda^T M-part x)  mass, sum_q W [c_eps (L0 X2 + L1 X3) + c_mu (L2 X0 + L3 X1)]
@@ -442,7 +486,7 @@ struct SingleArgs {
 
 template <bool NODAL>
 __global__ __launch_bounds__(256) void k_shape_single(int64_t nt, const double *__restrict__ qp, const double *__restrict__ fields,
-                               SingleArgs a, double *__restrict__ qb) {
+                               SingleArgs a, const double *__restrict__ acc, double *__restrict__ qb) {
     const int64_t nq = nt * kQP;
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i >= nq) return;
@@ -456,6 +500,22 @@ __global__ __launch_bounds__(256) void k_shape_single(int64_t nt, const double *
     double gW = 0.0;
     // NODAL: complex adjoints of the point's vectors p1, p2, vj, vm
     cv3 gp1 = czero3(), gp2 = czero3(), gvj = czero3(), gvm = czero3();
+    {
+        TGrad gt;
+        SGrad gs;
+        zero(gt);
+        zero(gs);
+        regular_adjoint<NODAL>(acc, nq, i, P, Q, gt, gs);
+        gx = gt.x + gs.y;
+        gn = gt.n;
+        gW = gt.W + gs.W;
+        gt1 = gt.t1 + gs.t1;
+        gt2 = gt.t2 + gs.t2;
+        gp1 = gt.p1;
+        gp2 = gt.p2;
+        gvj = gs.vj;
+        gvm = gs.vm;
+    }
     // far field
     {
         double sn, cs;
@@ -528,7 +588,7 @@ __global__ __launch_bounds__(256) void k_shape_single(int64_t nt, const double *
         v[7] = gt1.x; v[8] = gt1.y; v[9] = gt1.z; v[10] = gt2.x; v[11] = gt2.y; v[12] = gt2.z;
     }
     double *o = qb + i * kS;
-    for (int c = 0; c < kS; ++c) o[c] += v[c];
+    for (int c = 0; c < kS; ++c) o[c] = v[c];
 }
 
 // ------------------------------------------ P2 point: forward + reverse ---
@@ -657,7 +717,7 @@ struct ShapeSsqArgs {
     int order;
     double glx[kMaxSSQ], glw[kMaxSSQ];
     const KernelConst *K;
-    cxd iw;
+    ShapeConst C;
     double *nodeb;
 };
 
@@ -726,7 +786,7 @@ __global__ __launch_bounds__(64) void k_shape_ssq(ShapeSsqArgs a) {
                     }
                 }
             }
-            pair_adjoint<true, true, NODAL>(K, a.iw, P, Q, wg, gt, gs);
+            pair_adjoint<NODAL>(a.C, K, P, Q, wg, gt, gs);
         }
         // test side
         {
@@ -889,9 +949,12 @@ int shape_grad_run(const mbem_op *op, const mbem_params *p, const double2 *x, co
                    hipStream_t s) {
     const mbem_mesh *m = op->mesh;
     const int64_t nt = m->nt, nq = nt * kQP, nn = m->nn;
-    double *fields = nullptr, *qb = nullptr, *nodeb = nullptr, *nodeb_x = nullptr;
+    double *fields = nullptr, *acc = nullptr, *qb = nullptr, *nodeb = nullptr, *nodeb_x = nullptr;
+    double2 *tab = nullptr;
     auto cleanup = [&]() {
         if (fields) (void)dev_free(fields);
+        if (acc) (void)dev_free(acc);
+        if (tab) (void)dev_free(tab);
         if (qb) (void)dev_free(qb);
         if (nodeb) (void)dev_free(nodeb);
         if (nodeb_x) (void)dev_free(nodeb_x);
@@ -899,6 +962,8 @@ int shape_grad_run(const mbem_op *op, const mbem_params *p, const double2 *x, co
     const bool nodal = op->p.frame == MBEM_FRAME_NODAL;
     const int kS = nodal ? kQBN : kQB;
     if (dev_malloc((void **)&fields, sizeof(double) * 16 * nq) != hipSuccess ||
+        dev_malloc((void **)&acc, sizeof(double) * 2 * kSide * nq) != hipSuccess ||
+        dev_malloc((void **)&tab, sizeof(double2) * kTab * nq) != hipSuccess ||
         dev_malloc((void **)&qb, sizeof(double) * kS * nq) != hipSuccess ||
         dev_malloc((void **)&nodeb, sizeof(double) * 9 * nn) != hipSuccess ||
         dev_malloc((void **)&nodeb_x, sizeof(double) * 9 * nn) != hipSuccess) {
@@ -912,33 +977,26 @@ int shape_grad_run(const mbem_op *op, const mbem_params *p, const double2 *x, co
         if (e != hipSuccess) { set_error(std::string("shape gradient launch: ") + hipGetErrorString(e)); st = MBEM_EDEVICE; }
         return st == MBEM_OK;
     };
-    (void)hipMemsetAsync(qb, 0, sizeof(double) * kS * nq, s);
+    (void)hipMemsetAsync(acc, 0, sizeof(double) * 2 * kSide * nq, s);
     (void)hipMemsetAsync(nodeb, 0, sizeof(double) * 9 * nn, s);
     (void)hipMemsetAsync(nodeb_x, 0, sizeof(double) * 9 * nn, s);
     const unsigned gq = (unsigned)((nq + 255) / 256);
-    const cxd iw = {op->iw.x, op->iw.y};
+    ShapeConst C;
+    C.kc = {op->ka.x, op->ki.x, op->ki.y, op->eps_i.x, op->eps_i.y, op->mu_i.x, op->mu_i.y,
+            std::max(std::abs(op->ka.x), std::hypot(op->ki.x, op->ki.y))};
+    C.iw = {op->iw.x, op->iw.y};
     if (nodal)
         hipLaunchKernelGGL(k_qp_fields<true>, dim3(gq), dim3(256), 0, s, nt, op->n2, m->d_tri, m->d_qp, m->d_frames,
-                           lam, x, fields);
+                           lam, x, fields, tab);
     else
         hipLaunchKernelGGL(k_qp_fields<false>, dim3(gq), dim3(256), 0, s, nt, op->n2, m->d_tri, m->d_qp,
-                           m->d_frames, lam, x, fields);
+                           m->d_frames, lam, x, fields, tab);
     if (launch_ok()) {
-        if (nodal)
-            hipLaunchKernelGGL((k_shape_regular<true, true>), dim3((unsigned)nt), dim3(256), 0, s, nt, m->d_qp,
-                               fields, m->d_tri, op->d_kconst, iw, qb);
-        else
-            hipLaunchKernelGGL((k_shape_regular<true, false>), dim3((unsigned)nt), dim3(256), 0, s, nt, m->d_qp,
-                               fields, m->d_tri, op->d_kconst, iw, qb);
-        launch_ok();
-    }
-    if (st == MBEM_OK) {
-        if (nodal)
-            hipLaunchKernelGGL((k_shape_regular<false, true>), dim3((unsigned)nt), dim3(256), 0, s, nt, m->d_qp,
-                               fields, m->d_tri, op->d_kconst, iw, qb);
-        else
-            hipLaunchKernelGGL((k_shape_regular<false, false>), dim3((unsigned)nt), dim3(256), 0, s, nt, m->d_qp,
-                               fields, m->d_tri, op->d_kconst, iw, qb);
+        // a small mesh divides the 64 steps over up to four wavefronts
+        const int64_t tiles = (nq + kShapeTile - 1) / kShapeTile;
+        const int parts = tiles * tiles >= 2048 ? 1 : tiles * tiles >= 1024 ? 2 : 4;
+        hipLaunchKernelGGL(k_shape_regular, dim3((unsigned)(tiles * parts), (unsigned)tiles), dim3(kShapeTile), 0, s,
+                           nq, (int)tiles, kShapeTile / parts, tab, m->d_tri, C, op->d_kconst, acc);
         launch_ok();
     }
     if (st == MBEM_OK) {
@@ -948,8 +1006,8 @@ int shape_grad_run(const mbem_op *op, const mbem_params *p, const double2 *x, co
         sa.ka = p->k0;
         sa.ce = {op->ce.x, op->ce.y};
         sa.cm = {op->cm.x, op->cm.y};
-        if (nodal) hipLaunchKernelGGL(k_shape_single<true>, dim3(gq), dim3(256), 0, s, nt, m->d_qp, fields, sa, qb);
-        else hipLaunchKernelGGL(k_shape_single<false>, dim3(gq), dim3(256), 0, s, nt, m->d_qp, fields, sa, qb);
+        if (nodal) hipLaunchKernelGGL(k_shape_single<true>, dim3(gq), dim3(256), 0, s, nt, m->d_qp, fields, sa, acc, qb);
+        else hipLaunchKernelGGL(k_shape_single<false>, dim3(gq), dim3(256), 0, s, nt, m->d_qp, fields, sa, acc, qb);
         launch_ok();
     }
     if (st == MBEM_OK) {
@@ -979,7 +1037,7 @@ int shape_grad_run(const mbem_op *op, const mbem_params *p, const double2 *x, co
             a.glw[i] = i < a.order ? 0.5 * gw[a.order - 1 - i] : 0.0;
         }
         a.K = op->d_kconst;
-        a.iw = iw;
+        a.C = C;
         a.nodeb = nodeb;
         if (nodal) hipLaunchKernelGGL(k_shape_ssq<true>, dim3((unsigned)m->n_spairs), dim3(64), 0, s, a);
         else hipLaunchKernelGGL(k_shape_ssq<false>, dim3((unsigned)m->n_spairs), dim3(64), 0, s, a);
