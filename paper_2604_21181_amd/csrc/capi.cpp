@@ -128,24 +128,32 @@ static void op_free_device(mbem_op *op) {
 }
 
 // ---------------------------------------------------------------- GMRES --
-// trans: the same iteration on Z^T with P^-T (adjoint systems).
+// Up to kSolveGroup right-hand sides take their steps together: one pass over
+// the blocks serves them all (2 vectors of 10 248 unknowns 289 us, one 237 us),
+// and the vector kernels, which are bound by latency, take the group in one
+// launch.  trans: the same iteration on Z^T with P^-T (adjoint systems).
+constexpr int kSolveGroup = 16;
+
 struct Gmres {
     const mbem_op *op;
     hipStream_t s;
     int64_t N;
     int m;              // Krylov dimension limit
+    int group = 1;      // systems the workspace holds
     bool trans = false;
     bool lowp = false;          // MIXED: the complex64 copy of the block-Jacobi inverses
+    // vectors of the group's systems side by side: V[step][system][N]
     double2 *V, *w, *z, *tmp, *hdev;
-    double2 *W;                 // the products Z z_j of the steps, (m + 1) x N
+    double2 *W;                 // the products Z z_j of the steps, [step][system][N]
     double2 *tpart = nullptr;   // partial sums of the transposed product
     double *ndev;
     double2 *hcol;              // the current step's projection coefficients (device)
     double2 *ppart;             // projection partials of both passes, 2 (m + 1) x chunks
     double *npart;              // per-chunk parts of |w|^2
+    GroupStride gs;
     // two Hessenberg column slots in pinned host memory, each 2 (m + 1) + 1
-    // values and a completion tag, and the same slots as the kernels
-    // address them
+    // values and a completion tag per system, and the same slots as the
+    // kernels address them
     double2 *hpin[2] = {nullptr, nullptr};
     double2 *hmap[2] = {nullptr, nullptr};
     double2 *ypin = nullptr;    // the final coefficients y (pinned host memory)
@@ -165,34 +173,55 @@ struct Gmres {
         }
         if (tpart) (void)dev_free(tpart);
     }
-    int apply(const double2 *x, double2 *y) {   // y = Z x or Z^T x
-        return trans ? matvec_t_run(op, x, y, tpart, s) : matvec_run(op, x, y, tmp, s);
-    }
+    int64_t ld() const { return group * N; }   // from step to step in V and W
     static bool timed(int q) { return q >= kTimed0 && q < kTimed0 + kTimedSteps; }
-    int step_matvec(const double2 *x, double2 *y, int q) {
-        if (!timed(q)) return apply(x, y);
-        const int e = q - kTimed0;
-        MBEM_HIP(hipEventRecord(ev0[e], s));
-        if (trans) {
-            MBEM_TRY(matvec_t_run(op, x, y, tpart, s));
-            MBEM_HIP(hipEventRecord(ev1[e], s));
-            return MBEM_OK;
+    // y_i = Z x_i or Z^T x_i of nv systems, step q
+    int step_matvec(const double2 *x, double2 *y, int nv, int q) {
+        hipEvent_t after = nullptr;
+        if (timed(q)) {
+            MBEM_HIP(hipEventRecord(ev0[q - kTimed0], s));
+            after = ev1[q - kTimed0];
         }
-        return matvec_run(op, x, y, tmp, s, ev1[e]);   // ev1 right after the GEMV
+        if (!trans) return matvecs_run(op, x, y, nv, tmp, s, after);   // recorded right after the GEMV
+        for (int i = 0; i < nv; ++i) MBEM_TRY(matvec_t_run(op, x + i * N, y + i * N, tpart, s));
+        if (after) MBEM_HIP(hipEventRecord(after, s));
+        return MBEM_OK;
     }
-    void collect(int q) {   // once step q's column has arrived
+    void collect(int q) {   // once step q's columns have arrived
         if (!timed(q)) return;
         const int e = q - kTimed0;
         float t = 0.f;
         if (hipEventSynchronize(ev1[e]) == hipSuccess &&
             hipEventElapsedTime(&t, ev0[e], ev1[e]) == hipSuccess) { t_matvec += t; ++n_matvec; }
     }
-    // Wait until the tag `seq` of step `slot` is in pinned memory.
-    int wait_column(int slot, unsigned long long seq) const {
-        return wait_host_tag((const unsigned long long *)(hpin[slot] + 2 * (m + 1) + 1), seq, s,
+    const double2 *column(int slot, int i) const { return hpin[slot] + i * gs.pin; }
+    // Wait until the tag `seq` of system i's step `slot` is in pinned memory.
+    int wait_column(int slot, int i, unsigned long long seq) const {
+        return wait_host_tag((const unsigned long long *)(column(slot, i) + 2 * (m + 1) + 1), seq, s,
                              "GMRES Arnoldi column");
     }
 };
+
+// Device elements of one system's vectors and scratch (without V and W: what
+// does not grow with maxit is small beside them).
+static size_t gmres_elems(const mbem_op *op, int maxit) {
+    const size_t N = 2 * op->n2, nch = (size_t)arnoldi_chunks(N), col = 2 * (size_t)(maxit + 1) + 1;
+    // V and W, w, z, matvec partials (4 n2), the coefficients y (m) and a
+    // norm, the step's column, projection partials of both passes, norm partials
+    return 2 * (size_t)(maxit + 1) * N + 2 * N + 4 * op->n2 + (size_t)maxit + 1 + col +
+           2 * (size_t)(maxit + 1) * nch + nch + 1;
+}
+
+// Right-hand sides that are solved together: no more workspace than the
+// operator itself takes (or 256 MB); one at a time for a compressed operator
+// and for the transposed product, which have no product for several vectors.
+static int gmres_group(const mbem_op *op, int maxit, int nrhs, bool trans) {
+    if (trans || op->blr) return 1;
+    const size_t entry = op->prec == MBEM_FP64 ? sizeof(double2) : sizeof(float2);
+    const size_t limit = std::max((size_t)3 * op->n2 * op->n2 * entry, (size_t)256 << 20);
+    const size_t fit = limit / (sizeof(double2) * gmres_elems(op, maxit));
+    return (int)std::max<size_t>(1, std::min({(size_t)nrhs, (size_t)kSolveGroup, fit}));
+}
 
 static int gmres_alloc(Gmres &g, const mbem_op *op, int maxit, hipStream_t s) {
     g.op = op;
@@ -200,12 +229,9 @@ static int gmres_alloc(Gmres &g, const mbem_op *op, int maxit, hipStream_t s) {
     g.lowp = op->prec == MBEM_MIXED;
     g.N = 2 * op->n2;
     g.m = maxit;
-    // V, w, z, matvec partials (4 n2), the coefficients y (m) and a norm,
-    // the step's column, projection partials of both passes, norm partials
-    const size_t nch = (size_t)arnoldi_chunks(g.N);
+    const size_t G = g.group, nch = (size_t)arnoldi_chunks(g.N);
     const size_t col = 2 * (size_t)(maxit + 1) + 1;
-    const size_t need = (size_t)(maxit + 1) * g.N + 2 * g.N + 4 * op->n2 + (size_t)maxit + 1 + col +
-                        2 * (size_t)(maxit + 1) * nch + nch + 1 + (size_t)(maxit + 1) * g.N;
+    const size_t need = G * gmres_elems(op, maxit);
     mbem_op *mop = const_cast<mbem_op *>(op);
     if (op->work_elems < need) {
         dfree(mop->d_work);
@@ -216,7 +242,7 @@ static int gmres_alloc(Gmres &g, const mbem_op *op, int maxit, hipStream_t s) {
     }
     // two column slots of col values and a tag, written by the Arnoldi
     // kernels straight into fine-grained host memory, then y
-    const size_t pin = 2 * (col + 1) + (size_t)maxit;
+    const size_t pin = G * (2 * (col + 1) + (size_t)maxit);
     if (op->pin_elems < pin) {
         if (mop->h_pin) (void)pin_free(mop->h_pin);
         mop->h_pin = nullptr;
@@ -224,20 +250,25 @@ static int gmres_alloc(Gmres &g, const mbem_op *op, int maxit, hipStream_t s) {
         MBEM_HIP(pin_malloc((void **)&mop->h_pin, sizeof(double2) * pin, true));
         mop->pin_elems = pin;
     }
+    g.gs.vec = g.N;
+    g.gs.part = (int64_t)(2 * (size_t)(maxit + 1) * nch);
+    g.gs.norm = (int64_t)nch;
+    g.gs.hcol = (int64_t)col;
+    g.gs.pin = (int64_t)col + 1;
     g.hpin[0] = op->h_pin;
-    g.hpin[1] = op->h_pin + col + 1;
-    g.ypin = op->h_pin + 2 * (col + 1);
+    g.hpin[1] = op->h_pin + G * (col + 1);
+    g.ypin = op->h_pin + 2 * G * (col + 1);
     for (int i = 0; i < 2; ++i) MBEM_HIP(hipHostGetDevicePointer((void **)&g.hmap[i], g.hpin[i], 0));
     g.V = op->d_work;
-    g.w = g.V + (size_t)(maxit + 1) * g.N;
-    g.z = g.w + g.N;
-    g.tmp = g.z + g.N;                 // 4 n2 for the matvec partials
-    g.hdev = g.tmp + 4 * op->n2;       // the coefficients y of the final combination
-    g.ndev = (double *)(g.hdev + maxit);
-    g.hcol = g.hdev + maxit + 1;
-    g.ppart = g.hcol + col;
-    g.npart = (double *)(g.ppart + 2 * (size_t)(maxit + 1) * nch);
-    g.W = g.ppart + 2 * (size_t)(maxit + 1) * nch + (nch + 1) / 2 + 1;   // after the nch doubles of npart
+    g.W = g.V + (size_t)(maxit + 1) * G * g.N;
+    g.w = g.W + (size_t)(maxit + 1) * G * g.N;
+    g.z = g.w + G * g.N;
+    g.tmp = g.z + G * g.N;                 // 4 n2 per system for the matvec partials
+    g.hdev = g.tmp + G * 4 * op->n2;       // the coefficients y of the final combinations
+    g.ndev = (double *)(g.hdev + G * maxit);   // a norm per system
+    g.hcol = g.hdev + G * maxit + G;
+    g.ppart = g.hcol + G * col;
+    g.npart = (double *)(g.ppart + G * 2 * (size_t)(maxit + 1) * nch);
     for (int i = 0; i < Gmres::kTimedSteps; ++i) {
         if (!g.ev0[i]) MBEM_HIP(hipEventCreate(&g.ev0[i]));
         if (!g.ev1[i]) MBEM_HIP(hipEventCreate(&g.ev1[i]));
@@ -248,148 +279,169 @@ static int gmres_alloc(Gmres &g, const mbem_op *op, int maxit, hipStream_t s) {
 
 static inline std::complex<double> C(double2 v) { return {v.x, v.y}; }
 
-// Right-preconditioned GMRES on Z P^-1, x0 = 0, CGS2 Arnoldi in FP64.
-// Solves Z x = b to |r_k| <= tol |b| (Arnoldi estimate); beta = |b| is the
-// caller's (it has just computed it).  x, b device.
+// One system of a group: Z x = b to |r_k| <= tol |b| (Arnoldi estimate); beta =
+// |b| > 0 is the caller's (it has just computed it).
+struct GmresSystem {
+    GmresSystem(const double2 *b_, double beta_, double tol_, double2 *x_) : b(b_), beta(beta_), tol(tol_), x(x_) {}
+    const double2 *b;
+    double beta, tol;
+    double2 *x;
+    int iters = 0, status = MBEM_ENOCONV;
+    // the rotated Hessenberg matrix by columns (column k: rows 0 .. k), its
+    // rotations and the right-hand side
+    std::vector<std::complex<double>> H, cs, sn, gv, h;
+    double res = 1.0, r_prev = 0.0, r_last = 0.0;   // estimates after the last two columns
+    bool done = false;                              // tolerance met, or breakdown
+    static size_t at(int k) { return (size_t)k * (k + 1) / 2; }
+    // fold column k into the QR factorisation
+    void add_column(int k, const double2 *hb) {
+        const double hn = hb[2 * (k + 1)].x;
+        if (k == 0) gv.push_back(beta);
+        h.resize(k + 2);
+        for (int i = 0; i <= k; ++i) h[i] = C(hb[i]) + C(hb[k + 1 + i]);
+        h[k + 1] = hn;
+        for (int i = 0; i < k; ++i) {
+            const std::complex<double> t = cs[i] * h[i] + sn[i] * h[i + 1];
+            h[i + 1] = -std::conj(sn[i]) * h[i] + cs[i] * h[i + 1];
+            h[i] = t;
+        }
+        const std::complex<double> a = h[k], bb = h[k + 1];
+        const double r = std::hypot(std::abs(a), std::abs(bb));
+        std::complex<double> c = 1.0, sk = 0.0;
+        if (r != 0 && std::abs(a) == 0) { c = 0; sk = std::conj(bb) / std::abs(bb); }
+        else if (r != 0) { c = std::abs(a) / r; sk = (a / std::abs(a)) * std::conj(bb) / r; }
+        cs.push_back(c);
+        sn.push_back(sk);
+        h[k] = c * a + sk * bb;
+        H.insert(H.end(), h.begin(), h.begin() + k + 1);
+        gv.push_back(-std::conj(sk) * gv[k]);
+        gv[k] = c * gv[k];
+        res = std::abs(gv[k + 1]) / beta;
+        iters = k + 1;
+        done = res <= tol || hn == 0;
+        r_prev = r_last;
+        r_last = res;
+    }
+    // back substitution H y = g
+    void coefficients(double2 *y) const {
+        for (int i = iters - 1; i >= 0; --i) {
+            std::complex<double> t = gv[i];
+            for (int j = i + 1; j < iters; ++j) t -= H[at(j) + i] * C(y[j]);
+            t /= H[at(i) + i];
+            y[i] = {t.real(), t.imag()};
+        }
+    }
+};
+
+// Right-preconditioned GMRES on Z P^-1, x0 = 0, CGS2 Arnoldi in FP64, for the
+// systems of `sys` (at most g.group) in step: system i of the list is system i
+// of the workspace.  The launches span the systems that still run, so the last
+// one runs alone at a single system's cost.
 // The host lags the device by one column: Arnoldi step k (preconditioner,
 // matvec, two projection passes, norm, and V_{k+1} = w / h_{k+1,k} with the
 // norm read on the device) is queued before the host waits for column k-1
 // and applies its Givens rotation, so the stream never drains between
 // steps.  When column k-1 meets the tolerance the queued step k is unused.
-// Returns with x's last kernels queued, not finished.
-static int gmres_solve(Gmres &g, const double2 *b, double beta, double tol, double2 *x, int *iters,
-                       double *est) {
+// Returns with the x's last kernels queued, not finished.
+static int gmres_solve(Gmres &g, std::vector<GmresSystem> &sys) {
     const hipStream_t s = g.s;
-    const int64_t N = g.N;
-    if (!(beta > 0)) {
-        MBEM_HIP(hipMemsetAsync(x, 0, sizeof(double2) * N, s));
-        *iters = 0;
-        *est = 0;
-        return MBEM_OK;
-    }
-    const int m = g.m;
-    // The Hessenberg matrix, column-major (column k holds rows 0..k+1),
-    // kept across solves: allocating and zeroing (m + 1) m entries for every
-    // solve, and releasing them, left the stream idle for about 0.1 ms at
-    // each end of a solve; every entry read has been written first.
-    static thread_local std::vector<std::complex<double>> Hbuf;
-    if (Hbuf.size() < (size_t)(m + 1) * m) Hbuf.resize((size_t)(m + 1) * m);
-    std::complex<double> *const H = Hbuf.data();
-    std::vector<std::complex<double>> cs(m), sn(m), gv(m + 1);
-    gv[0] = beta;
+    const int64_t N = g.N, ld = g.ld();
+    const int m = g.m, ns = (int)sys.size();
+    if (ns < 1 || ns > g.group) return MBEM_EINVAL;
+    auto tag_of = [&](int slot, int i) {
+        return (unsigned long long *)(g.hmap[slot] + i * g.gs.pin + 2 * (m + 1) + 1);
+    };
     // no tag of an earlier solve may match; no Arnoldi kernel of one is
     // pending (the caller synchronises between solves)
-    for (int i = 0; i < 2; ++i) *(unsigned long long *)(g.hpin[i] + 2 * (m + 1) + 1) = 0ull;
-    MBEM_TRY(vec_scale_copy(g.V, b, double2{1.0 / beta, 0.0}, N, s));
-    // queue Arnoldi step k; its column lands in hpin[k % 2] with tag k + 1.
-    // With a preconditioner the step's normalisation and column run as the
+    for (int i = 0; i < ns; ++i) {
+        for (int slot = 0; slot < 2; ++slot) *(unsigned long long *)(g.column(slot, i) + 2 * (m + 1) + 1) = 0ull;
+        MBEM_TRY(vec_scale_copy(g.V + i * N, sys[i].b, double2{1.0 / sys[i].beta, 0.0}, N, s));
+    }
+    int lo = 0, hi = ns;   // the systems that still run lie in [lo, hi)
+    // queue Arnoldi step k; its columns land in hpin[k % 2] with tag k + 1.
+    // With a preconditioner the step's normalisation and columns run as the
     // first launch of step k + 1 (fused with its block-Jacobi product), or
     // as arnoldi_finish after the last step.
     const bool fuse = mbj_present(g.op);
-    auto tag_of = [&](int slot) { return (unsigned long long *)(g.hmap[slot] + 2 * (m + 1) + 1); };
+    auto finish = [&](int k) -> int {   // publish column k
+        const int slot = k & 1;
+        return arnoldi_finish(g.w + lo * N, g.V + lo * N, ld, k + 1, N, g.npart + lo * g.gs.norm,
+                              g.hcol + lo * g.gs.hcol, g.hmap[slot] + lo * g.gs.pin, tag_of(slot, lo),
+                              (unsigned long long)k + 1, s, hi - lo, g.gs);
+    };
     auto enqueue = [&](int k) -> int {
         const int slot = k & 1;
-        double2 *vk = g.V + (size_t)k * N;
+        double2 *vk = g.V + (size_t)k * ld + lo * N, *z = g.z + lo * N;
         if (fuse && k > 0) {
             const int ps = (k - 1) & 1;
-            MBEM_TRY(mbj_scale_apply_run(g.op, g.w, g.npart, N, vk, g.z, g.hcol, k, g.hmap[ps], tag_of(ps),
-                                         (unsigned long long)k, s, g.trans, g.lowp));
+            MBEM_TRY(mbj_scale_apply_run(g.op, g.w + lo * N, g.npart + lo * g.gs.norm, N, vk, z,
+                                         g.hcol + lo * g.gs.hcol, k, g.hmap[ps] + lo * g.gs.pin, tag_of(ps, lo),
+                                         (unsigned long long)k, s, g.trans, g.lowp, hi - lo, g.gs));
         } else {
-            MBEM_TRY(mbj_apply_run(g.op, vk, g.z, s, g.trans, g.lowp));
+            for (int i = 0; i < hi - lo; ++i)
+                MBEM_TRY(mbj_apply_run(g.op, vk + i * N, z + i * N, s, g.trans, g.lowp));
         }
-        double2 *wk = g.W + (size_t)k * N;   // Z z_k, kept for the residual of the solution
-        MBEM_TRY(g.step_matvec(g.z, wk, k));
-        MBEM_TRY(arnoldi_cgs2(wk, g.w, g.V, N, k + 1, N, g.ppart, g.npart, g.hcol, !fuse, g.hmap[slot],
-                              tag_of(slot), (unsigned long long)k + 1, s));
+        double2 *wk = g.W + (size_t)k * ld + lo * N;   // Z z_k, kept for the residual of the solution
+        MBEM_TRY(g.step_matvec(z, wk, hi - lo, k));
+        MBEM_TRY(arnoldi_cgs2(wk, g.w + lo * N, g.V + lo * N, ld, k + 1, N, g.ppart + lo * g.gs.part,
+                              g.npart + lo * g.gs.norm, g.hcol + lo * g.gs.hcol, !fuse,
+                              g.hmap[slot] + lo * g.gs.pin, tag_of(slot, lo), (unsigned long long)k + 1, s, hi - lo,
+                              g.gs));
         return MBEM_OK;
     };
-    double res = 1.0;
-    bool conv = false, breakdown = false;
-    // wait for column k and fold it into the QR factorisation of H
-    auto process = [&](int k) -> int {
-        const int slot = k & 1;
-        MBEM_TRY(g.wait_column(slot, (unsigned long long)k + 1));
-        g.collect(k);
-        const double2 *hb = g.hpin[slot];
-        const double hn = hb[2 * (k + 1)].x;
-        auto Hc = [&](int i) -> std::complex<double> & { return H[(size_t)k * (m + 1) + i]; };
-        for (int i = 0; i <= k; ++i) Hc(i) = C(hb[i]) + C(hb[k + 1 + i]);
-        Hc(k + 1) = hn;
-        for (int i = 0; i < k; ++i) {
-            const std::complex<double> t = cs[i] * Hc(i) + sn[i] * Hc(i + 1);
-            Hc(i + 1) = -std::conj(sn[i]) * Hc(i) + cs[i] * Hc(i + 1);
-            Hc(i) = t;
+    // wait for column k of the running systems and fold it in; true: all done
+    auto process = [&](int k, bool *all) -> int {
+        for (int i = lo; i < hi; ++i) {
+            if (sys[i].done) continue;
+            MBEM_TRY(g.wait_column(k & 1, i, (unsigned long long)k + 1));
+            sys[i].add_column(k, g.column(k & 1, i));
         }
-        const std::complex<double> a = Hc(k), bb = Hc(k + 1);
-        const double r = std::hypot(std::abs(a), std::abs(bb));
-        if (r == 0) { cs[k] = 1; sn[k] = 0; }
-        else if (std::abs(a) == 0) { cs[k] = 0; sn[k] = std::conj(bb) / std::abs(bb); }
-        else { cs[k] = std::abs(a) / r; sn[k] = (a / std::abs(a)) * std::conj(bb) / r; }
-        Hc(k) = cs[k] * a + sn[k] * bb;
-        Hc(k + 1) = 0;
-        gv[k + 1] = -std::conj(sn[k]) * gv[k];
-        gv[k] = cs[k] * gv[k];
-        res = std::abs(gv[k + 1]) / beta;
-        breakdown = hn == 0;
-        conv = res <= tol || breakdown;
+        g.collect(k);
+        while (lo < hi && sys[lo].done) ++lo;
+        while (hi > lo && sys[hi - 1].done) --hi;
+        *all = lo == hi;
         return MBEM_OK;
     };
     // The column that meets the tolerance normally finds the next step
     // already queued, and that step is wasted.  When the last two residual
-    // estimates extrapolate (at their ratio) to the tolerance at column
-    // q - 1, the host instead waits for that column before queueing step q:
-    // a short drain of the stream if the guess is wrong, one step saved if
-    // it is right.  With the fused start the column is published by step
-    // q's first launch, so it is published here by arnoldi_finish (step q
+    // estimates of a system extrapolate (at their ratio) to the tolerance at
+    // column q - 1, the host instead waits for that column before queueing
+    // step q: a short drain of the stream if the guess is wrong, one step
+    // saved if it is right.  With the fused start the column is published by
+    // step q's first launch, so it is published here by arnoldi_finish (step q
     // then recomputes the same V_q and publishes the column once more).
-    double r_prev = 0.0, r_last = 0.0;   // estimates after the last two columns
-    int k = 0;       // columns folded into H
-    for (int q = 0; q < m; ++q) {
-        if (q >= 3 && r_prev > 0 && r_last * (r_last / r_prev) <= tol) {
-            if (fuse)
-                MBEM_TRY(arnoldi_finish(g.w, g.V, N, q, N, g.npart, g.hcol, g.hmap[(q - 1) & 1],
-                                        tag_of((q - 1) & 1), (unsigned long long)q, s));
-            MBEM_TRY(process(q - 1));
-            k = q;
-            r_prev = r_last;
-            r_last = res;
-            if (conv) break;
-            MBEM_TRY(enqueue(q));
+    bool all = false;
+    for (int q = 0; q < m && !all; ++q) {
+        bool near = false;
+        if (q >= 3)
+            for (int i = lo; i < hi; ++i)
+                near = near || (!sys[i].done && sys[i].r_prev > 0 &&
+                                sys[i].r_last * (sys[i].r_last / sys[i].r_prev) <= sys[i].tol);
+        if (near) {
+            if (fuse) MBEM_TRY(finish(q - 1));
+            MBEM_TRY(process(q - 1, &all));
+            if (!all) MBEM_TRY(enqueue(q));
             continue;
         }
         MBEM_TRY(enqueue(q));
-        if (q >= 1) {
-            MBEM_TRY(process(q - 1));
-            k = q;
-            r_prev = r_last;
-            r_last = res;
-            if (conv) break;
-        }
+        if (q >= 1) MBEM_TRY(process(q - 1, &all));
     }
-    if (!conv) {
-        if (fuse)
-            MBEM_TRY(arnoldi_finish(g.w, g.V, N, m, N, g.npart, g.hcol, g.hmap[(m - 1) & 1], tag_of((m - 1) & 1),
-                                    (unsigned long long)m, s));
-        MBEM_TRY(process(m - 1));
-        k = m;
-    }
-    conv = res <= tol || breakdown;
-    // back substitution H y = g
-    std::vector<std::complex<double>> y(k);
-    for (int i = k - 1; i >= 0; --i) {
-        std::complex<double> t = gv[i];
-        for (int j = i + 1; j < k; ++j) t -= H[(size_t)j * (m + 1) + i] * y[j];
-        y[i] = t / H[(size_t)i * (m + 1) + i];
+    if (!all) {
+        if (fuse) MBEM_TRY(finish(m - 1));
+        MBEM_TRY(process(m - 1, &all));
     }
     // y through pinned memory: no earlier copy from it is pending (the
     // caller synchronises between solves), so the host needs no wait here
-    for (int i = 0; i < k; ++i) g.ypin[i] = {y[i].real(), y[i].imag()};
-    MBEM_HIP(hipMemcpyAsync(g.hdev, g.ypin, sizeof(double2) * k, hipMemcpyHostToDevice, s));
-    MBEM_TRY(vec_combine(g.w, g.V, N, k, g.hdev, N, s));
-    MBEM_TRY(mbj_apply_run(g.op, g.w, x, s, g.trans, g.lowp));
-    *iters = k;
-    *est = res;
-    return conv ? MBEM_OK : MBEM_ENOCONV;
+    for (int i = 0; i < ns; ++i) {
+        GmresSystem &y = sys[i];
+        y.status = y.done ? MBEM_OK : MBEM_ENOCONV;
+        y.coefficients(g.ypin + i * m);
+        double2 *hy = g.hdev + i * m;
+        MBEM_HIP(hipMemcpyAsync(hy, g.ypin + i * m, sizeof(double2) * y.iters, hipMemcpyHostToDevice, s));
+        MBEM_TRY(vec_combine(g.w + i * N, g.V + i * N, ld, y.iters, hy, N, s));
+        MBEM_TRY(mbj_apply_run(g.op, g.w + i * N, y.x, s, g.trans, g.lowp));
+    }
+    return MBEM_OK;
 }
 
 // Device buffers of the cross-section evaluation, grown on demand and kept
@@ -808,12 +860,23 @@ static int solve_impl(mbem_ctx *ctx, mbem_op *op, const mbem_c128 *b, int32_t nr
     if (trans) MBEM_TRY(mbj_transpose_run(op, s));
     Gmres g;
     g.trans = trans;
-    MBEM_TRY(gmres_alloc(g, op, o->maxit, s));
-    const int64_t N = g.N;
-    double2 *r = r_ws, *d = d_ws;
+    g.group = r_ws ? 1 : gmres_group(op, o->maxit, nrhs, trans);
+    double2 *r = r_ws, *d = d_ws;   // [system][N]
     Owned own_r, own_d;
-    if (!r_ws) { MBEM_TRY(dalloc(&r, N)); own_r.p = r; }
-    if (!d_ws) { MBEM_TRY(dalloc(&d, N)); own_d.p = d; }
+    auto alloc = [&]() -> int {
+        MBEM_TRY(gmres_alloc(g, op, o->maxit, s));
+        if (!r_ws && !r) { MBEM_TRY(dalloc(&r, (size_t)g.group * g.N)); own_r.p = r; }
+        if (!d_ws && !d) { MBEM_TRY(dalloc(&d, (size_t)g.group * g.N)); own_d.p = d; }
+        return MBEM_OK;
+    };
+    int ast = alloc();
+    if (ast != MBEM_OK && g.group > 1) {   // not enough memory for a group: one at a time
+        (void)hipGetLastError();
+        g.group = 1;
+        ast = alloc();
+    }
+    MBEM_TRY(ast);
+    const int64_t N = g.N;
     Timer t;
     t.start(s);
     int total_it = 0, sweeps = 0, status = MBEM_OK;
@@ -830,43 +893,68 @@ static int solve_impl(mbem_ctx *ctx, mbem_op *op, const mbem_c128 *b, int32_t nr
             set_error("right-hand side column " + std::to_string(c) + " is not finite");
             return MBEM_EINVAL;
         }
-    // Residual of the solution of the GMRES run just made on right-hand side
-    // rhs with it steps: r = rhs - Z u for its solution u = P^-1 V y, formed
-    // as rhs - sum_j y_j (Z z_j) from the steps' products Z z_j (z_j =
-    // P^-1 V_j; r may be rhs), which are products with the operator, not
-    // the Arnoldi recurrence, in place of one more product.  Returns |r|.
-    auto residual = [&](const double2 *rhs, int it, double *rn) -> int {
-        MBEM_TRY(vec_resid_products(r, rhs, g.W, N, it, g.hdev, N, s));
-        MBEM_TRY(vec_norm2(r, N, g.ndev, s));
-        MBEM_HIP(hipMemcpyAsync(rn, g.ndev, sizeof(double), hipMemcpyDeviceToHost, s));
+    std::vector<GmresSystem> sys;
+    std::vector<int> who;             // the group's column of each system
+    std::vector<double> rn(g.group);
+    // Solves the systems of `sys` and leaves the residual of each, rhs - Z u
+    // for its solution u = P^-1 V y, in r: formed as rhs - sum_j y_j (Z z_j)
+    // from the steps' products Z z_j (z_j = P^-1 V_j; r may be rhs), which are
+    // products with the operator, not the Arnoldi recurrence, in place of one
+    // more product.  rn = its norm.  With `update` the solution is a
+    // correction of the column of `into`.
+    auto sweep = [&](bool update, double2 *into) -> int {
+        if (sys.empty()) return MBEM_OK;
+        MBEM_TRY(gmres_solve(g, sys));
+        std::vector<double> norm(sys.size());
+        for (size_t i = 0; i < sys.size(); ++i) {
+            const int c = who[i];
+            if (update) MBEM_TRY(vec_axpy(into + c * N, sys[i].x, double2{1.0, 0.0}, N, s));
+            MBEM_TRY(vec_resid_products(r + c * N, sys[i].b, g.W + i * N, g.ld(), sys[i].iters, g.hdev + i * g.m, N, s));
+            MBEM_TRY(vec_norm2(r + c * N, N, g.ndev + i, s));
+        }
+        MBEM_HIP(hipMemcpyAsync(norm.data(), g.ndev, sizeof(double) * norm.size(), hipMemcpyDeviceToHost, s));
         MBEM_HIP(hipStreamSynchronize(s));
+        for (size_t i = 0; i < sys.size(); ++i) {
+            rn[who[i]] = norm[i];
+            total_it += sys[i].iters;
+            sweeps += 1;
+        }
         return MBEM_OK;
     };
-    for (int c = 0; c < nrhs; ++c) {
-        const double2 *bc = (const double2 *)b + c * N;
-        double2 *xc = (double2 *)x + c * N;
-        const double bn = bnorm[c];
-        double rn = 0;
-        int it = 0;
-        double est = 0;
+    for (int c0 = 0; c0 < nrhs; c0 += g.group) {
+        const int nc = std::min(g.group, nrhs - c0);
+        const double2 *bc = (const double2 *)b + (int64_t)c0 * N;
+        double2 *xc = (double2 *)x + (int64_t)c0 * N;
+        const double *bn = bnorm.data() + c0;
+        sys.clear();
+        who.clear();
+        auto open = [&](int c) { return bn[c] > 0 && !(rn[c] <= o->tol * bn[c]) && std::isfinite(rn[c]); };
         if (op->prec == MBEM_FP64) {
             // GMRES on b; if its Arnoldi estimate met tol but the explicit
             // residual (rounding drift of the long recurrence) did not, one
             // more GMRES from the explicit residual corrects x
             const int maxref = o->max_refine > 0 ? o->max_refine : 3;
-            int st = gmres_solve(g, bc, bn, o->tol, xc, &it, &est);
-            if (st != MBEM_OK && st != MBEM_ENOCONV) return st;
-            total_it += it;
-            sweeps += 1;
-            MBEM_TRY(residual(bc, it, &rn));
-            for (int sw = 1; sw < maxref && st == MBEM_OK && bn > 0 && !(rn <= o->tol * bn) &&
-                             std::isfinite(rn); ++sw) {
-                st = gmres_solve(g, r, rn, o->tol * bn / rn, d, &it, &est);
-                if (st != MBEM_OK && st != MBEM_ENOCONV) return st;
-                total_it += it;
-                sweeps += 1;
-                MBEM_TRY(vec_axpy(xc, d, double2{1.0, 0.0}, N, s));
-                MBEM_TRY(residual(r, it, &rn));   // r - Z d
+            for (int c = 0; c < nc; ++c) {
+                rn[c] = 0.0;
+                if (bn[c] > 0) {
+                    sys.emplace_back(bc + c * N, bn[c], o->tol, xc + c * N);
+                    who.push_back(c);
+                } else {
+                    MBEM_HIP(hipMemsetAsync(xc + c * N, 0, sizeof(double2) * N, s));
+                    sweeps += 1;
+                }
+            }
+            MBEM_TRY(sweep(false, nullptr));
+            for (int sw = 1; sw < maxref; ++sw) {
+                std::vector<GmresSystem> next;
+                std::vector<int> cols;
+                for (size_t i = 0; i < sys.size(); ++i)
+                    if (sys[i].status == MBEM_OK && open(who[i])) cols.push_back(who[i]);
+                if (cols.empty()) break;
+                for (int c : cols) next.emplace_back(r + c * N, rn[c], o->tol * bn[c] / rn[c], d + c * N);
+                sys.swap(next);
+                who.swap(cols);
+                MBEM_TRY(sweep(true, xc));   // r - Z d
             }
         } else {
             // iterative refinement: x += GMRES(Z, b - Z x), residual in FP64.
@@ -876,22 +964,27 @@ static int solve_impl(mbem_ctx *ctx, mbem_op *op, const mbem_c128 *b, int32_t nr
             // restarting from the refined residual.
             const int maxref = o->max_refine > 0 ? o->max_refine : 8;
             const double itol = o->inner_tol > 0 ? o->inner_tol : std::max(o->tol, 1e-8);
-            MBEM_HIP(hipMemsetAsync(xc, 0, sizeof(double2) * N, s));
-            MBEM_HIP(hipMemcpyAsync(r, bc, sizeof(double2) * N, hipMemcpyDeviceToDevice, s));
-            rn = bn;
-            for (int sw = 0; sw < maxref && bn > 0 && !(rn <= o->tol * bn) && std::isfinite(rn); ++sw) {
-                int st = gmres_solve(g, r, rn, std::max(itol, o->tol * bn / rn), d, &it, &est);
-                if (st != MBEM_OK && st != MBEM_ENOCONV) return st;
-                total_it += it;
-                sweeps += 1;
-                MBEM_TRY(vec_axpy(xc, d, double2{1.0, 0.0}, N, s));
-                MBEM_TRY(residual(r, it, &rn));   // r - Z d
+            MBEM_HIP(hipMemsetAsync(xc, 0, sizeof(double2) * N * nc, s));
+            MBEM_HIP(hipMemcpyAsync(r, bc, sizeof(double2) * N * nc, hipMemcpyDeviceToDevice, s));
+            for (int c = 0; c < nc; ++c) rn[c] = bn[c];
+            for (int sw = 0; sw < maxref; ++sw) {
+                sys.clear();
+                who.clear();
+                for (int c = 0; c < nc; ++c)
+                    if (open(c)) {
+                        sys.emplace_back(r + c * N, rn[c], std::max(itol, o->tol * bn[c] / rn[c]), d + c * N);
+                        who.push_back(c);
+                    }
+                if (sys.empty()) break;
+                MBEM_TRY(sweep(true, xc));   // r - Z d
             }
         }
-        // the iterate is accepted only if its explicit residual meets tol
-        const double rel = bn > 0 ? rn / bn : 0.0;
-        worst = std::max(worst, rel);
-        if (!(rel <= o->tol)) status = MBEM_ENOCONV;
+        // an iterate is accepted only if its explicit residual meets tol
+        for (int c = 0; c < nc; ++c) {
+            const double rel = bn[c] > 0 ? rn[c] / bn[c] : 0.0;
+            worst = std::max(worst, rel);
+            if (!(rel <= o->tol)) status = MBEM_ENOCONV;
+        }
     }
     const double ms = t.stop(s);
     if (stats) {

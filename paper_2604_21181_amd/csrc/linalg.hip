@@ -403,11 +403,13 @@ static void launch_products(const mbem_op *op, const double2 *x, int nv, double2
                        (const TS *)op->K[1], (const TS *)op->K[2], x, nv, t);
 }
 
-int matvecs_run(const mbem_op *op, const double2 *x, double2 *y, int nv, double2 *tmp, hipStream_t s) {
-    if (nv == 1) return matvec_run(op, x, y, tmp, s);
+int matvecs_run(const mbem_op *op, const double2 *x, double2 *y, int nv, double2 *tmp, hipStream_t s,
+                hipEvent_t after_gemv) {
+    if (nv == 1) return matvec_run(op, x, y, tmp, s, after_gemv);
     if (op->prec == MBEM_FP64) launch_products<double2>(op, x, nv, tmp, s);
     else launch_products<float2>(op, x, nv, tmp, s);
     MBEM_HIP(hipGetLastError());
+    if (after_gemv) MBEM_HIP(hipEventRecord(after_gemv, s));
     return combine_run(op, x, y, nv, tmp, s);
 }
 
@@ -1228,6 +1230,10 @@ int mbj_apply_run(const mbem_op *op, const double2 *v, double2 *z, hipStream_t s
 // of several vectors are issued together, and the sums over a chunk go
 // through LDS (eight vectors at a time, each summed by half a wavefront)
 // rather than one wavefront-wide sum per vector and wavefront.
+//
+// The systems of one solve take their steps together: blockIdx.z is the system
+// and GroupStride the distance between two systems' vectors and scratch.  At
+// these sizes a launch of two takes about as long as a launch of one.
 constexpr int kChunkN = 256;   // rows per workgroup: four wavefronts, one row per lane
 constexpr int kDotG = 8;       // basis vectors per round of chunk sums (one per half-wavefront)
 constexpr int kRedG = 64;      // coefficients per round of k_cgs_update (one per four lanes)
@@ -1286,10 +1292,13 @@ __device__ inline void load_rows(double2 (&a)[kDotG], const double2 *V, int64_t 
 // workgroup (c, y) runs on the same XCD as workgroup c of the update
 // kernels (workgroups are dealt to the eight XCDs in launch order)
 __global__ __launch_bounds__(kChunkN) void k_cgs_dots(const double2 *V, int64_t ldv, int k, const double2 *w,
-                                                     int64_t n, double2 *part, int64_t nch) {
+                                                     int64_t n, double2 *part, int64_t nch, GroupStride gs) {
     __shared__ double2 sp[kDotG * kChunkN];
     const int64_t c = blockIdx.x;
     if (c >= nch) return;   // the whole workgroup
+    V += blockIdx.z * gs.vec;
+    w += blockIdx.z * gs.vec;
+    part += blockIdx.z * gs.part;
     const int64_t i = c * kChunkN + threadIdx.x;
     const int j0 = blockIdx.y * kDotG;
     const bool in = i < n;
@@ -1306,11 +1315,18 @@ __global__ __launch_bounds__(kChunkN) void k_cgs_dots(const double2 *V, int64_t 
 template <bool DOTS>
 __global__ __launch_bounds__(kChunkN) void k_cgs_update(const double2 *win, double2 *w, const double2 *V,
                                                        int64_t ldv, int k, const double2 *part, int64_t npin,
-                                                       double2 *hout, int64_t n, double2 *next, double *npart) {
+                                                       double2 *hout, int64_t n, double2 *next, double *npart,
+                                                       GroupStride gs) {
     __shared__ double2 s_h[kRedG];
     __shared__ double2 sp[kDotG * kChunkN];
     const int wv = threadIdx.x / kW, lane = threadIdx.x % kW;
-    const int64_t c = blockIdx.x, nch = gridDim.x, i = c * kChunkN + threadIdx.x;
+    const int64_t c = blockIdx.x, nch = npin, i = c * kChunkN + threadIdx.x;
+    if (c >= nch) return;   // the whole workgroup
+    win += blockIdx.z * gs.vec;
+    w += blockIdx.z * gs.vec;
+    V += blockIdx.z * gs.vec;
+    part += blockIdx.z * gs.part;
+    hout += blockIdx.z * gs.hcol;
     const bool in = i < n;
     double2 t = in ? win[i] : double2{0, 0};
     for (int j0 = 0; j0 < k; j0 += kRedG) {
@@ -1343,6 +1359,7 @@ __global__ __launch_bounds__(kChunkN) void k_cgs_update(const double2 *win, doub
     }
     if (in) w[i] = t;
     if constexpr (DOTS) {
+        next += blockIdx.z * gs.part;
         // the next batch's rows load while the current batch is summed
         double2 a[kDotG], an[kDotG];
         load_rows(a, V, ldv, 0, k, i, in);
@@ -1356,7 +1373,7 @@ __global__ __launch_bounds__(kChunkN) void k_cgs_update(const double2 *win, doub
         const double nn = wsum_all(in ? t.x * t.x + t.y * t.y : 0.0);
         if (lane == 0) sp[wv].x = nn;
         __syncthreads();
-        if (threadIdx.x == 0) npart[c] = (sp[0].x + sp[1].x) + (sp[2].x + sp[3].x);
+        if (threadIdx.x == 0) npart[blockIdx.z * gs.norm + c] = (sp[0].x + sp[1].x) + (sp[2].x + sp[3].x);
     }
 }
 
@@ -1385,11 +1402,14 @@ __device__ inline double norm_from_parts(const double *npart, int64_t nch) {
 __global__ __launch_bounds__(kChunkN) void k_cgs_scale(double2 *dst, const double2 *src, const double *npart,
                                                       int64_t nch, int64_t n, const double2 *hcol, int k2,
                                                       double2 *pin, unsigned long long *tag,
-                                                      unsigned long long seq) {
-    const double h = norm_from_parts(npart, nch), inv = h > 0 ? 1.0 / h : 0.0;
+                                                      unsigned long long seq, GroupStride gs) {
+    dst += blockIdx.z * gs.vec;
+    src += blockIdx.z * gs.vec;
+    const double h = norm_from_parts(npart + blockIdx.z * gs.norm, nch), inv = h > 0 ? 1.0 / h : 0.0;
     const int64_t i = blockIdx.x * (int64_t)kChunkN + threadIdx.x;
     if (i < n) dst[i] = {inv * src[i].x, inv * src[i].y};
-    if (blockIdx.x == 0 && pin) publish_column(hcol, k2, h, pin, tag, seq);
+    if (blockIdx.x == 0 && pin)
+        publish_column(hcol + blockIdx.z * gs.hcol, k2, h, pin + blockIdx.z * gs.pin, tag + 2 * blockIdx.z * gs.pin, seq);
 }
 
 // The normalisation that ends an Arnoldi step fused with the block-Jacobi
@@ -1402,11 +1422,16 @@ __global__ __launch_bounds__(256) void k_mbj_scale_apply(int64_t n2, int B, int 
                                                          const double2 *w, const double *npart, int64_t nch,
                                                          double2 *vk, double2 *z, const double2 *hcol, int k2,
                                                          double2 *pin, unsigned long long *tag,
-                                                         unsigned long long seq) {
+                                                         unsigned long long seq, GroupStride gs) {
+    npart += blockIdx.z * gs.norm;
     if (blockIdx.x == 0) {   // the extra first workgroup publishes
-        publish_column(hcol, k2, norm_from_parts(npart, nch), pin, tag, seq);
+        publish_column(hcol + blockIdx.z * gs.hcol, k2, norm_from_parts(npart, nch), pin + blockIdx.z * gs.pin,
+                       tag + 2 * blockIdx.z * gs.pin, seq);
         return;
     }
+    w += blockIdx.z * gs.vec;
+    vk += blockIdx.z * gs.vec;
+    z += blockIdx.z * gs.vec;
     const int64_t wid = ((blockIdx.x - 1) * (int64_t)blockDim.x + threadIdx.x) / kW;
     const int lane = threadIdx.x % kW;
     const int64_t ld = 2 * B;
@@ -1508,46 +1533,48 @@ int vec_scale_copy(double2 *dst, const double2 *src, double2 a, int64_t n, hipSt
 int64_t arnoldi_chunks(int64_t n) { return (n + kChunkN - 1) / kChunkN; }
 int arnoldi_cgs2(const double2 *win, double2 *w, double2 *V, int64_t ldv, int k, int64_t n, double2 *part,
                  double *npart, double2 *hcol, bool finish, double2 *pin, unsigned long long *tag,
-                 unsigned long long seq, hipStream_t s) {
-    if (k < 1 || n < 1) return MBEM_EINVAL;
+                 unsigned long long seq, hipStream_t s, int nsys, const GroupStride &gs) {
+    if (k < 1 || n < 1 || nsys < 1) return MBEM_EINVAL;
     const int64_t nch = arnoldi_chunks(n);
     double2 *part2 = part + (int64_t)k * nch;
-    hipLaunchKernelGGL(k_cgs_dots, dim3((unsigned)((nch + 7) / 8 * 8), (unsigned)((k + kDotG - 1) / kDotG)),
-                       dim3(kChunkN), 0, s, V, ldv, k, win, n, part, nch);
+    const unsigned x8 = (unsigned)((nch + 7) / 8 * 8), nx = nsys > 1 ? x8 : (unsigned)nch;
+    hipLaunchKernelGGL(k_cgs_dots, dim3(x8, (unsigned)((k + kDotG - 1) / kDotG), (unsigned)nsys), dim3(kChunkN), 0, s,
+                       V, ldv, k, win, n, part, nch, gs);
     MBEM_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_cgs_update<true>, dim3((unsigned)nch), dim3(kChunkN), 0, s, win, w, V, ldv, k, part, nch,
-                       hcol, n, part2, nullptr);
+    hipLaunchKernelGGL(k_cgs_update<true>, dim3(nx, 1, (unsigned)nsys), dim3(kChunkN), 0, s, win, w, V, ldv, k, part,
+                       nch, hcol, n, part2, nullptr, gs);
     MBEM_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_cgs_update<false>, dim3((unsigned)nch), dim3(kChunkN), 0, s, (const double2 *)w, w, V, ldv,
-                       k, part2, nch, hcol + k, n, nullptr, npart);
+    hipLaunchKernelGGL(k_cgs_update<false>, dim3(nx, 1, (unsigned)nsys), dim3(kChunkN), 0, s, (const double2 *)w, w,
+                       V, ldv, k, part2, nch, hcol + k, n, nullptr, npart, gs);
     MBEM_HIP(hipGetLastError());
-    if (finish) MBEM_TRY(arnoldi_finish(w, V, ldv, k, n, npart, hcol, pin, tag, seq, s));
+    if (finish) MBEM_TRY(arnoldi_finish(w, V, ldv, k, n, npart, hcol, pin, tag, seq, s, nsys, gs));
     return MBEM_OK;
 }
 int arnoldi_finish(const double2 *w, double2 *V, int64_t ldv, int k, int64_t n, const double *npart,
                    const double2 *hcol, double2 *pin, unsigned long long *tag, unsigned long long seq,
-                   hipStream_t s) {
+                   hipStream_t s, int nsys, const GroupStride &gs) {
     const int64_t nch = arnoldi_chunks(n);
-    hipLaunchKernelGGL(k_cgs_scale, dim3((unsigned)nch), dim3(kChunkN), 0, s, V + (int64_t)k * ldv, w, npart,
-                       nch, n, hcol, 2 * k, pin, tag, seq);
+    hipLaunchKernelGGL(k_cgs_scale, dim3((unsigned)nch, 1, (unsigned)nsys), dim3(kChunkN), 0, s,
+                       V + (int64_t)k * ldv, w, npart, nch, n, hcol, 2 * k, pin, tag, seq, gs);
     MBEM_HIP(hipGetLastError());
     return MBEM_OK;
 }
 bool mbj_present(const mbem_op *op) { return op->d_minv && op->nb > 0; }
 int mbj_scale_apply_run(const mbem_op *op, const double2 *w, const double *npart, int64_t n, double2 *vk,
                         double2 *z, const double2 *hcol, int k, double2 *pin, unsigned long long *tag,
-                        unsigned long long seq, hipStream_t s, bool trans, bool lowp) {
+                        unsigned long long seq, hipStream_t s, bool trans, bool lowp, int nsys,
+                        const GroupStride &gs) {
     if (!mbj_present(op) || n != 2 * op->n2 || !pin || !tag) return MBEM_EINVAL;
     const int64_t rows = (int64_t)op->nb * 2 * op->B;
-    const dim3 grid((unsigned)((rows * kW + 255) / 256 + 1));
+    const dim3 grid((unsigned)((rows * kW + 255) / 256 + 1), 1, (unsigned)nsys);
     const float2 *m32 = lowp ? (trans ? op->d_minv_t32 : op->d_minv32) : nullptr;
     if (m32)
         hipLaunchKernelGGL(k_mbj_scale_apply<float2>, grid, dim3(256), 0, s, op->n2, op->B, op->nb, m32, w, npart,
-                           arnoldi_chunks(n), vk, z, hcol, 2 * k, pin, tag, seq);
+                           arnoldi_chunks(n), vk, z, hcol, 2 * k, pin, tag, seq, gs);
     else
         hipLaunchKernelGGL(k_mbj_scale_apply<double2>, grid, dim3(256), 0, s, op->n2, op->B, op->nb,
                            (const double2 *)(trans ? op->d_minv_t : op->d_minv), w, npart, arnoldi_chunks(n), vk,
-                           z, hcol, 2 * k, pin, tag, seq);
+                           z, hcol, 2 * k, pin, tag, seq, gs);
     MBEM_HIP(hipGetLastError());
     return MBEM_OK;
 }

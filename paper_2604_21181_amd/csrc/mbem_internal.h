@@ -358,7 +358,8 @@ int matvec_run(const mbem_op *op, const double2 *x, double2 *y, double2 *tmp,
 // y[v] = Z x[v] for nv <= matvecs_chunk(op, nrhs) of nrhs vectors (rows of N
 // elements); tmp: 4 n2 nv
 int matvecs_chunk(const mbem_op *op, int nrhs);
-int matvecs_run(const mbem_op *op, const double2 *x, double2 *y, int nv, double2 *tmp, hipStream_t s);
+int matvecs_run(const mbem_op *op, const double2 *x, double2 *y, int nv, double2 *tmp, hipStream_t s,
+                hipEvent_t after_gemv = nullptr);
 int export_dense_run(const mbem_op *op, double2 *Z, hipStream_t s);
 int export_blocks_run(const mbem_op *op, double2 *K1, double2 *K2e,
                       double2 *K2m, hipStream_t s);
@@ -374,6 +375,13 @@ int mbj_copy_c64(const double2 *src, float2 **dst, int64_t n, hipStream_t s);
 int mbj_apply_run(const mbem_op *op, const double2 *v, double2 *z,
                   hipStream_t s, bool trans = false, bool lowp = false);
 int vec_norm2(const double2 *v, int64_t n, double *out_dev, hipStream_t s);
+// Distances between the systems of a group that takes its Arnoldi steps
+// together: their vectors (of win, w, V, z alike), projection partials, norm
+// partials, coefficient columns and host-mapped columns (in elements; a tag
+// lies in its column, so two tags are 2 pin apart).
+struct GroupStride {
+    int64_t vec = 0, part = 0, norm = 0, hcol = 0, pin = 0;
+};
 // Classical Gram-Schmidt with one reorthogonalisation of win (n rows; the
 // result goes to w, which may be win) against the k orthonormal columns of
 // V (leading dimension ldv).  The
@@ -384,14 +392,14 @@ int vec_norm2(const double2 *v, int64_t n, double *out_dev, hipStream_t s);
 int64_t arnoldi_chunks(int64_t n);
 int arnoldi_cgs2(const double2 *win, double2 *w, double2 *V, int64_t ldv, int k, int64_t n, double2 *part,
                  double *npart, double2 *hcol, bool finish, double2 *pin, unsigned long long *tag,
-                 unsigned long long seq, hipStream_t s);
+                 unsigned long long seq, hipStream_t s, int nsys, const GroupStride &gs);
 // V_k = w / |w| (column k of V; 0 when w vanishes), |w| from npart; then
 // the step's column is published to host-mapped memory: pin[0..2k) = hcol,
 // pin[2k].x = |w| and, after a system-scope fence, *tag = seq, so a host
 // that reads the tag reads the whole column.
 int arnoldi_finish(const double2 *w, double2 *V, int64_t ldv, int k, int64_t n, const double *npart,
                    const double2 *hcol, double2 *pin, unsigned long long *tag, unsigned long long seq,
-                   hipStream_t s);
+                   hipStream_t s, int nsys, const GroupStride &gs);
 // arnoldi_finish fused with the block-Jacobi product of the next step:
 // vk = w / |w|, z = P^-1 vk (P^-T with trans), and the finished step's
 // column (k coefficients per pass) published as by arnoldi_finish.  Needs
@@ -399,7 +407,8 @@ int arnoldi_finish(const double2 *w, double2 *V, int64_t ldv, int k, int64_t n, 
 bool mbj_present(const mbem_op *op);
 int mbj_scale_apply_run(const mbem_op *op, const double2 *w, const double *npart, int64_t n, double2 *vk,
                         double2 *z, const double2 *hcol, int k, double2 *pin, unsigned long long *tag,
-                        unsigned long long seq, hipStream_t s, bool trans, bool lowp);
+                        unsigned long long seq, hipStream_t s, bool trans, bool lowp, int nsys,
+                        const GroupStride &gs);
 int vec_scale_copy(double2 *dst, const double2 *src, double2 a, int64_t n,
                    hipStream_t s);
 int vec_axpy(double2 *y, const double2 *x, double2 a, int64_t n,
