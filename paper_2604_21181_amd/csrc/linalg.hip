@@ -32,17 +32,7 @@ __device__ inline double wave_sum(double v) {
     return v;
 }
 
-// ---------------------------------------------------------------- GEMV --
-// One wavefront per R consecutive stored rows of one block; lanes stream
-// the rows with 16-byte loads, and every load of the right-hand vector(s)
-// (FP64, from L2) serves all R rows.  The c64 variant loads two entries per
-// lane and row per step and accumulates in FP64; with eight rows per
-// wavefront its vector loads no longer outweigh the matrix stream (measured
-// per product on the 1280-triangle sphere: 158 us at one row, 118 us at
-// eight, 440 us at sixteen; c128: 221 us at one row, slower at two).
-template <typename TS> constexpr int gemv_rows_per_wave();
-template <> constexpr int gemv_rows_per_wave<double2>() { return 1; }
-template <> constexpr int gemv_rows_per_wave<float2>() { return 8; }
+// ------------------------------------------------------------- product --
 typedef double nd2 __attribute__((ext_vector_type(2)));
 typedef float nf4 __attribute__((ext_vector_type(4)));
 // streaming loads of the matrix: each entry is used exactly once per product
@@ -55,42 +45,184 @@ __device__ inline float4 ntload(const float4 *p) {
     return {v.x, v.y, v.z, v.w};
 }
 
-// re/im[k][v] += row r0 + k of K (row length n) . xs[v], for k < nr
-// (nr is uniform over the wavefront)
-template <int NV, int R>
-__device__ inline void rows_dots(const double2 *__restrict__ K, int64_t n, int64_t r0, int nr,
-                                 const double2 *const xs[NV], double re[R][NV], double im[R][NV]) {
-    const int lane = threadIdx.x % kW;
-    const double2 *row[R];
+struct Coef { double2 iw, ce, cm; };
+
+// One column of two rows of the three blocks and of the vectors xj, xm, and its
+// share of the rows' results: acc[row] (electric, magnetic) += (i/w K1 xj + K2e
+// xm, K2m xj - i/w K1 xm)
+struct RowEntries {
+    double2 k1[2], e[2], m[2], xj, xm;
+};
+__device__ inline void add_rows(const RowEntries &v, double2 iw, double2 acc[2][2]) {
+    const double2 wj = cmul(iw, v.xj), wm = cmul(iw, v.xm);
 #pragma unroll
-    for (int k = 0; k < R; ++k) row[k] = K + (r0 + (k < nr ? k : 0)) * n;
-#pragma unroll 4
-    for (int64_t c = lane; c < n; c += kW) {
-        double2 x[NV];
+    for (int k = 0; k < 2; ++k) {
+        acc[k][0] = cadd(acc[k][0], cadd(cmul(v.k1[k], wj), cmul(v.e[k], v.xm)));
+        acc[k][1] = cadd(acc[k][1], csub(cmul(v.m[k], v.xj), cmul(v.k1[k], wm)));
+    }
+}
+// the columns of a workgroup's lanes: one at a time (c128) or two neighbours
+__device__ inline void stream_rows(const double2 *const (&K)[3], const int64_t (&at)[2], int64_t n,
+                                   const double2 *__restrict__ xj, const double2 *__restrict__ xm, double2 iw,
+                                   double2 acc[2][2]) {
+    for (int64_t c = threadIdx.x; c < n; c += 256) {
+        RowEntries v;
+        v.xj = xj[c];
+        v.xm = xm[c];
 #pragma unroll
-        for (int v = 0; v < NV; ++v) x[v] = xs[v][c];
-#pragma unroll
-        for (int k = 0; k < R; ++k) {
-            if (k >= nr) break;
-            const double2 z = ntload(row[k] + c);
-#pragma unroll
-            for (int v = 0; v < NV; ++v) {
-                re[k][v] += z.x * x[v].x - z.y * x[v].y;
-                im[k][v] += z.x * x[v].y + z.y * x[v].x;
-            }
+        for (int k = 0; k < 2; ++k) {
+            v.k1[k] = ntload(K[0] + at[k] + c);
+            v.e[k] = ntload(K[1] + at[k] + c);
+            v.m[k] = ntload(K[2] + at[k] + c);
         }
+        add_rows(v, iw, acc);
+    }
+}
+__device__ inline void stream_rows(const float2 *const (&K)[3], const int64_t (&at)[2], int64_t n,
+                                   const double2 *__restrict__ xj, const double2 *__restrict__ xm, double2 iw,
+                                   double2 acc[2][2]) {
+    for (int64_t c = 2 * threadIdx.x; c < n; c += 512) {   // n is even (2 unknowns per node)
+        RowEntries v, u;
+        v.xj = xj[c];
+        u.xj = xj[c + 1];
+        v.xm = xm[c];
+        u.xm = xm[c + 1];
+        auto two = [](const float4 &f, double2 &a, double2 &b) {
+            a = {(double)f.x, (double)f.y};
+            b = {(double)f.z, (double)f.w};
+        };
+        float4 z[6];
+#pragma unroll
+        for (int k = 0; k < 6; ++k) z[k] = ntload(reinterpret_cast<const float4 *>(K[k % 3] + at[k / 3] + c));
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            two(z[3 * k], v.k1[k], u.k1[k]);
+            two(z[3 * k + 1], v.e[k], u.e[k]);
+            two(z[3 * k + 2], v.m[k], u.m[k]);
+        }
+        add_rows(v, iw, acc);
+        add_rows(u, iw, acc);
     }
 }
 
-template <int NV, int R>
-__device__ inline void rows_dots(const float2 *__restrict__ K, int64_t n, int64_t r0, int nr,
-                                 const double2 *const xs[NV], double re[R][NV], double im[R][NV]) {
+// y = Z x in one launch: a workgroup takes one node, the two rows of all three
+// blocks, its lanes the columns, the node's mass entries (mval[4 s + 2 al + be])
+// and, with the FP64 near store (nv.bits non-null), the entries V[4 op + 2 al +
+// be] of its stored pairs, times x at 2 j + be; one sum over the workgroup at the
+// end.  Bound by the read of the blocks.  Two rows of three blocks share every
+// load of the vectors (one row: 5 % slower in FP64, four or eight in mixed: 1.3
+// to 3 times, for want of wavefronts), and the sums over the mass entries and
+// near pairs need no second launch.  The first entries' indices are loaded ahead
+// of the rows.  us, a wavefront per row of one block (c64: eight rows) and a
+// second kernel for the rest -> this:
+//   triangles      320          1280          2700
+//   FP64         36.5 -> 28.5   237 -> 212   1019 -> 880  (6.4 TB/s)
+//   mixed        40.5 -> 24.0   130 -> 126    542 -> 510
+//   near store   54.6 -> 27.7   207 -> 174    779 -> 701
+template <typename TS>
+__global__ __launch_bounds__(256) void k_product(int64_t n2, const TS *K1, const TS *K2e, const TS *K2m,
+                                                 const int32_t *__restrict__ mptr, const int32_t *__restrict__ mcol,
+                                                 const double *__restrict__ mval, const double2 *__restrict__ x, Coef c,
+                                                 NearView nv, double2 *__restrict__ y) {
+    __shared__ double s_sum[4][8];
+    const int tid = threadIdx.x;
+    const int64_t i = blockIdx.x;
+    const double2 *xj = x, *xm = x + n2;
+    struct Mass { int64_t col; double v[4]; };
+    auto load_mass = [&](int64_t s) {
+        Mass m;
+        m.col = 2 * (int64_t)mcol[s];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) m.v[q] = mval[4 * s + q];
+        return m;
+    };
+    const int64_t m1 = mptr[i + 1];
+    int64_t ms = mptr[i] + tid;
+    Mass mass{};
+    if (ms < m1) mass = load_mass(ms);
+    // near pairs: lane pairs (al = 0, 1), 128 stored pairs a turn
+    const int al = tid % 2;
+    int64_t ns = 0, n1 = 0, ncol = 0;
+    if (nv.bits) {
+        ns = (int64_t)nv.rptr[i] + tid / 2;
+        n1 = nv.rptr[i + 1];
+        if (ns < n1) ncol = 2 * (int64_t)nv.col[ns];
+    }
+    double2 acc[2][2] = {{{0.0, 0.0}, {0.0, 0.0}}, {{0.0, 0.0}, {0.0, 0.0}}};
+    const TS *const K[3] = {K1, K2e, K2m};
+    const int64_t at[2] = {2 * i * n2, (2 * i + 1) * n2};
+    stream_rows(K, at, n2, xj, xm, c.iw, acc);
+    while (ms < m1) {
+        const double2 j0 = xj[mass.col], j1 = xj[mass.col + 1], e0 = xm[mass.col], e1 = xm[mass.col + 1];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const double v0 = mass.v[2 * k], v1 = mass.v[2 * k + 1];
+            acc[k][0] = cadd(acc[k][0], cmul(c.ce, double2{v0 * e0.x + v1 * e1.x, v0 * e0.y + v1 * e1.y}));
+            acc[k][1] = cadd(acc[k][1], cmul(c.cm, double2{v0 * j0.x + v1 * j1.x, v0 * j0.y + v1 * j1.y}));
+        }
+        ms += 256;
+        if (ms < m1) mass = load_mass(ms);
+    }
+    if (nv.bits) {
+        double2 e = {0.0, 0.0}, h = e;
+        while (ns < n1) {
+            const double2 *V = nv.val + 12 * ns + 2 * al;
+            double2 v[6], vj[2], vm[2];
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                vj[b] = xj[ncol + b];
+                vm[b] = xm[ncol + b];
+#pragma unroll
+                for (int op = 0; op < 3; ++op) v[2 * op + b] = V[4 * op + b];
+            }
+            ns += 128;
+            if (ns < n1) ncol = 2 * (int64_t)nv.col[ns];
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                e = cadd(e, cadd(cmul(v[b], cmul(c.iw, vj[b])), cmul(v[2 + b], vm[b])));
+                h = cadd(h, csub(cmul(v[4 + b], vj[b]), cmul(v[b], cmul(c.iw, vm[b]))));
+            }
+        }
+        const double2 none = {0.0, 0.0};
+        acc[0][0] = cadd(acc[0][0], al ? none : e);
+        acc[0][1] = cadd(acc[0][1], al ? none : h);
+        acc[1][0] = cadd(acc[1][0], al ? e : none);
+        acc[1][1] = cadd(acc[1][1], al ? h : none);
+    }
+    const int lane = tid % kW, wave = tid / kW;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const double2 a = acc[q / 4][q / 2 % 2];
+        const double v = wsum_all(q % 2 ? a.y : a.x);
+        if (lane == 0) s_sum[wave][q] = v;
+    }
+    __syncthreads();
+    if (tid < 4) {       // (row, half)
+        double2 o = {0.0, 0.0};
+#pragma unroll
+        for (int w = 0; w < 4; ++w) o = cadd(o, double2{s_sum[w][2 * tid], s_sum[w][2 * tid + 1]});
+        y[(tid % 2) * n2 + 2 * i + tid / 2] = o;
+    }
+}
+
+// t = K1 x_j, K1 x_m, K2e x_m, K2m x_j of a large complex64 operator: a
+// wavefront per eight neighbouring rows of one block, which share the loads of
+// the vectors; k_combine follows.
+constexpr int kGemvRows = 8;
+template <int NV>
+__device__ inline void gemv_rows(const float2 *K, int64_t n, int64_t r0, int nr, const double2 *const xs[NV],
+                                 double2 *const ts[NV]) {
+    constexpr int R = kGemvRows;
+    double re[R][NV], im[R][NV];
+#pragma unroll
+    for (int k = 0; k < R; ++k)
+#pragma unroll
+        for (int v = 0; v < NV; ++v) re[k][v] = im[k][v] = 0.0;
     const int lane = threadIdx.x % kW;
     const int64_t n4 = n / 2;   // n is even (2 unknowns per node)
     const float4 *row[R];
 #pragma unroll
-    for (int k = 0; k < R; ++k)
-        row[k] = reinterpret_cast<const float4 *>(K + (r0 + (k < nr ? k : 0)) * n);
+    for (int k = 0; k < R; ++k) row[k] = reinterpret_cast<const float4 *>(K + (r0 + (k < nr ? k : 0)) * n);
 #pragma unroll 2
     for (int64_t c = lane; c < n4; c += kW) {
         double2 x0[NV], x1[NV];
@@ -109,19 +241,6 @@ __device__ inline void rows_dots(const float2 *__restrict__ K, int64_t n, int64_
             }
         }
     }
-}
-
-// t[0] = K1 x_j, t[1] = K1 x_m, t[2] = K2e x_m, t[3] = K2m x_j (each n2).
-template <typename TS, int NV, int R>
-__device__ inline void gemv_rows(const TS *K, int64_t n2, int64_t r0, int nr,
-                                 const double2 *const xs[NV], double2 *const ts[NV]) {
-    double re[R][NV], im[R][NV];
-#pragma unroll
-    for (int k = 0; k < R; ++k)
-#pragma unroll
-        for (int v = 0; v < NV; ++v) re[k][v] = im[k][v] = 0.0;
-    rows_dots<NV, R>(K, n2, r0, nr, xs, re, im);
-    const int lane = threadIdx.x % kW;
 #pragma unroll
     for (int k = 0; k < R; ++k)
 #pragma unroll
@@ -130,31 +249,27 @@ __device__ inline void gemv_rows(const TS *K, int64_t n2, int64_t r0, int nr,
             if (lane == 0 && k < nr) ts[v][r0 + k] = o;
         }
 }
-
-template <typename TS>
-__global__ __launch_bounds__(256) void k_gemv3(int64_t n2, const TS *K1, const TS *K2e,
-                                               const TS *K2m, const double2 *xj,
-                                               const double2 *xm, double2 *t) {
-    constexpr int R = gemv_rows_per_wave<TS>();
-    const int64_t nwr = (n2 + R - 1) / R;                    // wavefronts per block
+__global__ __launch_bounds__(256) void k_gemv_c64(int64_t n2, const float2 *K1, const float2 *K2e, const float2 *K2m,
+                                                  const double2 *xj, const double2 *xm, double2 *t) {
+    const int64_t nwr = (n2 + kGemvRows - 1) / kGemvRows;    // wavefronts per block
     const int64_t wid = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kW;
     if (wid >= 3 * nwr) return;
     const int blk = (int)(wid / nwr);
-    const int64_t r0 = (wid % nwr) * R;
-    const int nr = (int)(n2 - r0 < R ? n2 - r0 : R);
+    const int64_t r0 = (wid % nwr) * kGemvRows;
+    const int nr = (int)(n2 - r0 < kGemvRows ? n2 - r0 : kGemvRows);
     if (blk == 0) {
         const double2 *xs[2] = {xj, xm};
         double2 *ts[2] = {t, t + n2};
-        gemv_rows<TS, 2, R>(K1, n2, r0, nr, xs, ts);
+        gemv_rows<2>(K1, n2, r0, nr, xs, ts);
     } else {
         const double2 *xs[1] = {blk == 1 ? xm : xj};
         double2 *ts[1] = {t + (1 + blk) * n2};
-        gemv_rows<TS, 1, R>(blk == 1 ? K2e : K2m, n2, r0, nr, xs, ts);
+        gemv_rows<1>(blk == 1 ? K2e : K2m, n2, r0, nr, xs, ts);
     }
 }
 
 // ------------------------------------------------ several vectors at once --
-// t[v] = the four products of k_gemv3 for nv vectors (x: [nv][2 n2]) in one
+// t[v] = K1 x_j, K1 x_m, K2e x_m, K2m x_j for nv vectors (x: [nv][2 n2]) in one
 // pass over the blocks, on the FP64 matrix cores.  A workgroup takes 16 rows of
 // one block, its four wavefronts every fourth run of 8 columns, and their sums
 // meet in LDS.  Every lane loads two neighbouring columns of one row (c64: 16
@@ -168,7 +283,7 @@ __global__ __launch_bounds__(256) void k_gemv3(int64_t n2, const TS *K1, const T
 // dropped: masks are for the last 4 columns alone (masked throughout, 2 vectors
 // took 252 us in place of 177 and 8 vectors 372 in place of 293, mixed).  Tiles
 // of 32 and 64 rows were slower (16 vectors 386 and 450 us in place of 376).
-// us, one after the other (k_gemv3) -> this:
+// us, one after the other (a launch per block and vector) -> this:
 //   n2 = 5120  FP64   2: 461 -> 289   4: 921 -> 353   8: 1802 -> 352   16: 3585 -> 447
 //              mixed  2: 247 -> 177   4: 496 -> 254   8:  937 -> 293   16: 1835 -> 376
 //   n2 = 1280  FP64   2:  59 ->  39   3:  80 ->  41;  mixed  2: 66 -> 37   3: 92 -> 38
@@ -279,8 +394,6 @@ __global__ __launch_bounds__(256) void k_gemm3(int64_t n2, const TS *K1, const T
     else gemm_rows<TS, 1, COLS>(K2m, n2, r0, x, nv, {j, j}, {3, 3}, t, s_acc);
 }
 
-struct Coef { double2 iw, ce, cm; };
-
 // LANES consecutive lanes per row split the row's mass slots (a vertex
 // node has 19, each a dependent index-then-value load) and, with the near
 // store, its stored node pairs (about 70 per node on the 5120-triangle
@@ -367,29 +480,49 @@ static int combine_run(const mbem_op *op, const double2 *x, double2 *y, int nv, 
     return MBEM_OK;
 }
 
+template <typename TS>
+static void launch_product(const mbem_op *op, const double2 *x, double2 *y, hipStream_t s) {
+    const mbem_mesh *m = op->mesh;
+    hipLaunchKernelGGL(k_product<TS>, dim3((unsigned)(op->n2 / 2)), dim3(256), 0, s, op->n2, (const TS *)op->K[0],
+                       (const TS *)op->K[1], (const TS *)op->K[2], m->d_mptr, m->d_mcol, op->d_mval, x, coef_of(op),
+                       op->near_view(), y);
+}
+
+// Complex64 operators above n2 = 12 000 stream eight rows of one block per
+// wavefront and combine afterwards: there the memory takes that order better
+// at more sizes than not (one launch / two: 3072 triangles, n2 = 12 292, 649 /
+// 605 us, 5120: 1794 / 1710, 6912: 3249 / 3138, though 4332: 1264 / 1354; below,
+// 2700: 510 / 542, 320: 24 / 40).  FP64 takes one launch at every size (5120:
+// 3189 / 3832).
+constexpr int64_t kOneLaunchC64 = 12000;
+
 int matvec_run(const mbem_op *op, const double2 *x, double2 *y, double2 *tmp, hipStream_t s,
                hipEvent_t after_gemv) {
     const int64_t n2 = op->n2;
-    auto blocks = [n2](int R) { return (unsigned)((3 * ((n2 + R - 1) / R) * kW + 255) / 256); };
-    if (op->blr)
+    bool whole = false;
+    if (op->blr) {
         MBEM_TRY(blr_gemv_run(op, x, x + n2, tmp, s));
-    else if (op->prec == MBEM_FP64)
-        hipLaunchKernelGGL((k_gemv3<double2>), dim3(blocks(gemv_rows_per_wave<double2>())), dim3(256), 0, s,
-                           n2, (const double2 *)op->K[0], (const double2 *)op->K[1],
-                           (const double2 *)op->K[2], x, x + n2, tmp);
-    else
-        hipLaunchKernelGGL((k_gemv3<float2>), dim3(blocks(gemv_rows_per_wave<float2>())), dim3(256), 0, s,
-                           n2, (const float2 *)op->K[0], (const float2 *)op->K[1],
-                           (const float2 *)op->K[2], x, x + n2, tmp);
+    } else if (op->prec == MBEM_FP64) {
+        launch_product<double2>(op, x, y, s);
+        whole = true;
+    } else if (n2 <= kOneLaunchC64) {
+        launch_product<float2>(op, x, y, s);
+        whole = true;
+    } else {
+        const int64_t waves = 3 * ((n2 + kGemvRows - 1) / kGemvRows);
+        hipLaunchKernelGGL(k_gemv_c64, dim3((unsigned)((waves * kW + 255) / 256)), dim3(256), 0, s, n2,
+                           (const float2 *)op->K[0], (const float2 *)op->K[1], (const float2 *)op->K[2], x, x + n2,
+                           tmp);
+    }
     MBEM_HIP(hipGetLastError());
     if (after_gemv) MBEM_HIP(hipEventRecord(after_gemv, s));
-    return combine_run(op, x, y, 1, tmp, s);
+    return whole ? MBEM_OK : combine_run(op, x, y, 1, tmp, s);
 }
 
 // Up to four vectors go through the 4-wide instructions, more through the
 // 16-wide ones: eight as two passes of four take 706 (FP64) and 508 us (mixed)
-// against 352 and 293 us.  A single vector stays with k_gemv3 (237 us FP64,
-// 130 us mixed), a compressed operator with its own product.
+// against 352 and 293 us.  A single vector stays with k_product (212 us FP64,
+// 126 us mixed), a compressed operator with its own product.
 int matvecs_chunk(const mbem_op *op, int nrhs) {
     if (op->blr) return 1;
     return std::min(nrhs, nrhs <= 4 ? 4 : 16);

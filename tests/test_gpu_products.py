@@ -1,7 +1,8 @@
 """Products with several vectors at once (linalg.hip, k_gemm3) against the
-product of each vector alone and the exported blocks: every chunk edge (4 and
-16 vectors and one more), tiles of 16 rows with 4 and with 12 left over, all
-storage forms, with and without the near store, compressed operators."""
+product of each vector alone (k_product) and the exported blocks: every chunk
+edge (4 and 16 vectors and one more), tiles of 16 rows with 4 and with 12 left
+over, nodes with more mass entries (256) and near pairs (128) than one turn,
+all storage forms, with and without the near store, compressed operators."""
 import numpy as np
 import pytest
 
@@ -13,7 +14,8 @@ if not torch.cuda.is_available():
 from paper_2604_21181_amd import mbem  # noqa: E402
 from workloads.meshes import icosphere_p2, uv_sphere_p2  # noqa: E402
 
-MESHES = {"ico20": lambda: icosphere_p2(20), "uv70": lambda: uv_sphere_p2(7, 6), "ico320": lambda: icosphere_p2(320)}
+MESHES = {"ico20": lambda: icosphere_p2(20), "uv70": lambda: uv_sphere_p2(7, 6), "ico320": lambda: icosphere_p2(320),
+          "uv540": lambda: uv_sphere_p2(90, 4)}
 FORMS = {"fp64": dict(), "mixed": dict(precision=1), "store": dict(precision=1, near_store=True)}
 COUNTS = [1, 2, 3, 4, 5, 15, 16, 17, 18, 33]
 
@@ -38,10 +40,10 @@ def test_each_vector_as_alone(mesh, form):
         for n in COUNTS:
             X = _vectors(n, S.N, S.device)
             Y = S.matvec(X)
-            # sums of at most 1300 terms in another order: 1300 eps
+            # sums of at most 2200 terms in another order: 2200 eps
             alone = torch.stack([S.matvec(x) for x in X])
             scale = alone.abs().amax(dim=1, keepdim=True)
-            assert bool(((Y - alone).abs() <= 3e-13 * scale).all()), n
+            assert bool(((Y - alone).abs() <= 5e-13 * scale).all()), n
             if Z is not None:
                 ref = X.cpu().numpy() @ Z.cpu().numpy().T
                 assert np.abs(Y.cpu().numpy() - ref).max() <= 1e-12 * np.abs(ref).max(), n
