@@ -205,8 +205,12 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void k_cgemm_f32(CgemmL
 // (y + 1) kchunk) and writes its partial product at C + y * split_stride.
 // The product is scaled by alpha; with rmw it is added to what C holds
 // (one split only).
+// Two wavefronts per SIMD as the bound: with one, the sums sat in accumulation
+// registers and were copied out and back in every stage (48 moves and a wait).
+// Block solve, 1280 triangles, 128 right-hand sides: basis products 58.7 -> 51.4
+// us each, residual products 2.87 -> 2.61 ms.
 template <typename TA, typename TB, bool CONJ>
-__global__ __launch_bounds__(256) void k_cgemm_f64(CgemmList L, int64_t kchunk, int64_t split_stride, double alpha,
+__global__ __launch_bounds__(256, 2) void k_cgemm_f64(CgemmList L, int64_t kchunk, int64_t split_stride, double alpha,
                                                    int rmw) {
     constexpr int BM = 64, BC = 32, WM = 32, WC = 16;
     constexpr int LD = 10;   // 8 complex k + pad, in doubles
