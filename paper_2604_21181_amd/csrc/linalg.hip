@@ -1372,16 +1372,6 @@ constexpr int kDotG = 8;       // basis vectors per round of chunk sums (one per
 constexpr int kRedG = 64;      // coefficients per round of k_cgs_update (one per four lanes)
 static_assert(kDotG * 32 == kChunkN && kRedG * 4 == kChunkN, "one thread group per vector");
 
-// Sum over each row of 16 lanes, returned to every lane of the row (all
-// lanes active): the first four steps of wsum_all.
-__device__ inline double rsum16(double v) {
-    v += dpp_move(v, 0);
-    v += dpp_move(v, 1);
-    v += dpp_move(v, 2);
-    v += dpp_move(v, 3);
-    return v;
-}
-
 // part[(j0 + g) nch + c] = sum over the workgroup's threads of conj(a[g]) b,
 // for j0 + g < k.  sp: kDotG x kChunkN complex of LDS.  Thread t sums the
 // products of vector g = t / 32 from threads t % 32 + 32 i (i < 8), then

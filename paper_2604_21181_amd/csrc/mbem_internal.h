@@ -311,6 +311,9 @@ struct FillBand {
 // The singular pairs (ssq.hip) of a fill, or of a band, added to the blocks,
 // the near store or the band buffers.
 int ssq_fill_run(mbem_op *op, bool deriv, const FillBand *band, hipStream_t s);
+// Device table of the Sauter-Schwab points at order n, fields s1, t1, s2, t2,
+// |weight| of *np points each, regions as table_region; the caller frees it
+int ssq_table(int n, double **tab, int64_t *np, hipStream_t s);
 // FP64, default scheme; the geometry tables and kernel constants are current.
 int fill_band_run(mbem_op *op, const FillBand &band, hipStream_t s);
 

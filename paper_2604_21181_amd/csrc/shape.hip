@@ -35,6 +35,7 @@
 #include "kappa64.h"
 #include "p2_device.h"
 #include "ssq_map.h"
+#include "wave.h"
 
 namespace mbem {
 
@@ -274,23 +275,6 @@ __device__ inline void trial_adjoint(const SPt &Q, cv3 Hj, cv3 Hm, double c, SGr
         gs.t2 = gs.t2 + cw * im3(Q.X[1] * Hj + Q.X[3] * Hm);
     }
     gs.W += c * (cdot(vj, Hj) + cdot(vm, Hm)).im;
-}
-
-// Adds d Im(c) / d(point quantities) for c = -wfac W_x W_y F.
-template <bool NODAL>
-__device__ inline void pair_adjoint(const ShapeConst &C, const KernelConst &Ks, const TPt &P, const SPt &Q,
-                                    double wfac, TGrad &gt, SGrad &gs) {
-    const dvec3 Rv = P.x - Q.y;
-    const double d2 = dot(Rv, Rv), rinv = rsqrt64(d2);
-    const KScalD s = kernel_scalars_dr(C, Ks, d2 * rinv, rinv);
-    const cv3 u1 = ccross(P.L[0] * P.t1 + P.L[1] * P.t2, P.n), u2 = ccross(P.L[2] * P.t1 + P.L[3] * P.t2, P.n);
-    const cv3 vj = Q.X[0] * Q.t1 + Q.X[1] * Q.t2, vm = Q.X[2] * Q.t1 + Q.X[3] * Q.t2;
-    cv3 S1 = czero3(), S2 = S1, Hj = S1, Hm = S1;
-    const dvec3 g = (-wfac * P.W * Q.W) * pair_terms(s, rinv * Rv, rinv, u1, u2, vj, vm, S1, S2, Hj, Hm);
-    gt.x = gt.x + g;
-    gs.y = gs.y - g;
-    test_adjoint<NODAL>(P, S1, S2, -wfac * Q.W, gt);
-    trial_adjoint<NODAL>(Q, Hj, Hm, -wfac * P.W, gs);
 }
 
 // --------------------------------------------------- per-point fields ---
@@ -704,155 +688,308 @@ __global__ __launch_bounds__(256) void k_qp_backprop(int64_t nt, int64_t n2, con
 }
 
 // ------------------------------------------------- singular pairs ---
-// One wavefront per coincident / common-edge / common-vertex pair, the
-// Sauter-Schwab points of the fill, one point per lane and batch.  After
-// each batch the 6 x 9 test-node adjoints of every lane go through LDS and
-// lane c < 54 adds column c over the 64 points (then the same for the trial
-// nodes), so each lane keeps two running sums and the workgroup 28 KB of LDS.
+// One wavefront per (coincident / common-edge / common-vertex pair, two
+// regions): the Sauter-Schwab points of the fill, one per lane and batch.  Every
+// field of a triangle is a polynomial in LDS (as node data in registers they
+// spilled 436 scalars): position, nodal tangents and current coefficients;
+// NODAL: position and the node-attached vectors m of two currents.  A point's
+// geometry is formed twice, for the pair and again for its reverse, to end its
+// registers' lives in between.  The adjoints of the six nodes are summed over
+// the points by the matrix cores: a 4x4x4 instruction whose first factor has
+// ones in row r alone adds a lane value over the four groups of 16 lanes into
+// row r, so four columns share one register of sums and nothing crosses lanes
+// until the end (before: every batch through LDS and 64 reads a column).
+// Columns per side: 6 x 3 positions, 6 x 3 of each tangent; NODAL: 6 x 12 of the
+// adjoints of m, which the tangents' follow from at the end.
+// Bound by FP64 vector instructions at two wavefronts per SIMD.  1280 triangles:
+// 3.80 -> 1.67 ms, node-attached tangents 2.13 (one wavefront per SIMD, nothing
+// spilled: 2.23 and 2.15; all of a point kept live: 108 spills in place of 48).
 struct ShapeSsqArgs {
     int64_t n2, npairs;
     const int32_t *pairs, *tri;
     const double *xyz, *frames;
     const double2 *lam, *x;
     int order;
-    double glx[kMaxSSQ], glw[kMaxSSQ];
+    int64_t np;             // table points
+    const double *tab;
     const KernelConst *K;
     ShapeConst C;
     double *nodeb;
 };
 
+// Position, normal, metric and first derivatives of a triangle's polynomials
+// (F fields, coefficient k of field f at co[F k + f]).
+struct SsqGeom {
+    dvec3 x, a1, a2, n;
+    double J, Ji;
+};
+template <int F>
+__device__ __forceinline__ SsqGeom ssq_geom(const double *co, double xi, double eta) {
+    double v[3], d1[3], d2[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const double c3 = co[3 * F + d], c4 = co[4 * F + d], c5 = co[5 * F + d];
+        const double t = fma(c3, xi, fma(c4, eta, co[F + d])), s = fma(c5, eta, co[2 * F + d]);
+        v[d] = fma(xi, t, fma(eta, s, co[d]));
+        d1[d] = fma(c3, xi, t);
+        d2[d] = fma(c4, xi, fma(c5, eta, s));
+    }
+    SsqGeom g;
+    g.x = {v[0], v[1], v[2]};
+    g.a1 = {d1[0], d1[1], d1[2]};
+    g.a2 = {d2[0], d2[1], d2[2]};
+    const dvec3 c = cross(g.a1, g.a2);
+    const double c2 = dot(c, c);
+    g.Ji = rsqrt64(c2);
+    g.J = c2 * g.Ji;
+    g.n = g.Ji * c;
+    return g;
+}
+template <int F>
+__device__ __forceinline__ double ssq_field(const double *co, int f, double xi, double eta) {
+    const double t = fma(co[3 * F + f], xi, fma(co[4 * F + f], eta, co[F + f])), s = fma(co[5 * F + f], eta, co[2 * F + f]);
+    return fma(xi, t, fma(eta, s, co[f]));
+}
+template <int F>
+__device__ __forceinline__ dvec3 ssq_vec(const double *co, int f, double xi, double eta) {
+    return {ssq_field<F>(co, f, xi, eta), ssq_field<F>(co, f + 1, xi, eta), ssq_field<F>(co, f + 2, xi, eta)};
+}
+template <int F>
+__device__ __forceinline__ cv3 ssq_cvec(const double *co, int f, double xi, double eta) {
+    const dvec3 a = {ssq_field<F>(co, f, xi, eta), ssq_field<F>(co, f + 2, xi, eta), ssq_field<F>(co, f + 4, xi, eta)};
+    const dvec3 b = {ssq_field<F>(co, f + 1, xi, eta), ssq_field<F>(co, f + 3, xi, eta),
+                     ssq_field<F>(co, f + 5, xi, eta)};
+    return {{a.x, b.x}, {a.y, b.y}, {a.z, b.z}};
+}
+// the Gram-Schmidt frame of a point from the nodal tangents' fields 3 .. 8
+struct SsqFrame {
+    dvec3 u1, u2, t1, t2, w2;
+    double l1i, l3i;
+};
+template <int F>
+__device__ __forceinline__ SsqFrame ssq_frame(const double *co, double xi, double eta, dvec3 n) {
+    SsqFrame f;
+    f.u1 = ssq_vec<F>(co, 3, xi, eta);
+    f.u2 = ssq_vec<F>(co, 6, xi, eta);
+    const dvec3 w1 = f.u1 - dot(n, f.u1) * n;
+    f.l1i = rsqrt64(dot(w1, w1));
+    f.t1 = f.l1i * w1;
+    f.w2 = f.u2 - dot(n, f.u2) * n;
+    const dvec3 w3 = f.w2 - dot(f.t1, f.w2) * f.t1;
+    f.l3i = rsqrt64(dot(w3, w3));
+    f.t2 = f.l3i * w3;
+    return f;
+}
+
+// What the pair leaves to one side's reverse: the adjoints of position and
+// metric, and c S1, c S2 (test side) or c Hj, c Hm (trial side).
+struct SideAdj {
+    dvec3 bx;
+    double bJ;
+    cv3 g1, g2;
+};
+
+// Back through the point's vectors, map and frame; put(column, value).
+template <bool TEST, bool NODAL, int F, typename PUT>
+__device__ __forceinline__ void ssq_reverse(const double *co, double xi, double eta, const SideAdj &a, PUT put) {
+    const SsqGeom g = ssq_geom<F>(co, xi, eta);
+    double N[6], Nxi[6], Neta[6];
+    p2_shape(xi, eta, N, Nxi, Neta);
+    dvec3 bn = {0, 0, 0};
+    // adjoints of the side's two vectors; u = p x n on the test side
+    cv3 G1 = a.g1, G2 = a.g2;
+    if constexpr (TEST) {
+        G1 = ccross(g.n, a.g1);
+        G2 = ccross(g.n, a.g2);
+    }
+    if constexpr (NODAL) {
+#pragma unroll
+        for (int f = 0; f < 2; ++f) {
+            const cv3 m = ssq_cvec<F>(co, 3 + 6 * f, xi, eta);
+            if constexpr (TEST) bn = bn + im3(ccross(f ? a.g2 : a.g1, m - cdot(m, g.n) * g.n));
+            const cv3 gm = proj_reverse(f ? G2 : G1, m, g.n, bn);
+            const double v[6] = {gm.x.re, gm.x.im, gm.y.re, gm.y.im, gm.z.re, gm.z.im};
+#pragma unroll
+            for (int k = 0; k < 6; ++k)
+#pragma unroll
+                for (int d = 0; d < 6; ++d) put(18 + 12 * k + 6 * f + d, N[k] * v[d]);
+        }
+    } else {
+        const SsqFrame fr = ssq_frame<F>(co, xi, eta, g.n);
+        cxd L[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            L[k] = {ssq_field<F>(co, 9 + 2 * k, xi, eta), ssq_field<F>(co, 10 + 2 * k, xi, eta)};
+        if constexpr (TEST)
+            bn = im3(ccross(a.g1, L[0] * fr.t1 + L[1] * fr.t2) + ccross(a.g2, L[2] * fr.t1 + L[3] * fr.t2));
+        const dvec3 b1 = im3(L[0] * G1 + L[2] * G2), b2 = im3(L[1] * G1 + L[3] * G2);
+        // t2 = w3 / |w3|, w3 = w2 - (t1.w2) t1, w2 = u2 - (n.u2) n
+        const dvec3 bw3 = fr.l3i * (b2 - dot(b2, fr.t2) * fr.t2);
+        const double s = dot(fr.t1, fr.w2), bs = dot(bw3, fr.t1);
+        const dvec3 bw2 = bw3 - bs * fr.t1;
+        const dvec3 bt1 = b1 - bs * fr.w2 - s * bw3;
+        const double bwn2 = dot(bw2, g.n);
+        const dvec3 bu2 = bw2 - bwn2 * g.n;
+        bn = bn - bwn2 * fr.u2 - dot(g.n, fr.u2) * bw2;
+        // t1 = w1 / |w1|, w1 = u1 - (n.u1) n
+        const dvec3 bw1 = fr.l1i * (bt1 - dot(bt1, fr.t1) * fr.t1);
+        const double bwn1 = dot(bw1, g.n);
+        const dvec3 bu1 = bw1 - bwn1 * g.n;
+        bn = bn - bwn1 * fr.u1 - dot(g.n, fr.u1) * bw1;
+        const double v[6] = {bu1.x, bu1.y, bu1.z, bu2.x, bu2.y, bu2.z};
+#pragma unroll
+        for (int k = 0; k < 6; ++k)
+#pragma unroll
+            for (int d = 0; d < 6; ++d) put(18 + 6 * k + d, N[k] * v[d]);
+    }
+    // n = c / J, J = |c|, c = a1 x a2
+    const dvec3 bc = g.Ji * (bn - dot(bn, g.n) * g.n) + a.bJ * g.n;
+    const dvec3 ba1 = cross(g.a2, bc), ba2 = cross(bc, g.a1);
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        const dvec3 v = N[k] * a.bx + Nxi[k] * ba1 + Neta[k] * ba2;
+        put(3 * k, v.x);
+        put(3 * k + 1, v.y);
+        put(3 * k + 2, v.z);
+    }
+}
+
 template <bool NODAL>
-__global__ __launch_bounds__(64) void k_shape_ssq(ShapeSsqArgs a) {
-    constexpr int kCols = 54, kStride = 55;
-    __shared__ double s_buf[64 * kStride];
+__global__ __launch_bounds__(64, 2) void k_shape_ssq(ShapeSsqArgs a) {
+    constexpr int F = NODAL ? 15 : 17;                 // fields of a triangle
+    constexpr int NCOL = NODAL ? 90 : 54, NACC = (NCOL + 3) / 4;
+    __shared__ double s_co[2][6 * F];
+    __shared__ KernelConst s_K;
+    __shared__ double s_col[2][4 * NACC];
     const int lane = threadIdx.x;
-    const int64_t pid = blockIdx.x;
+    const int64_t pid = blockIdx.x % a.npairs;
+    const int part = (int)(blockIdx.x / a.npairs);
     const int32_t e = a.pairs[4 * pid], f = a.pairs[4 * pid + 1];
     const int cls = a.pairs[4 * pid + 2], code = a.pairs[4 * pid + 3];
-    const int n = a.order, n4 = n * n * n * n;
     const int nreg = cls == 3 ? 6 : (cls == 2 ? 5 : 2);
-    const int npts = nreg * n4;
-    const int32_t *te = a.tri + 6 * e, *tf = a.tri + 6 * f;
-    const KernelConst &K = *a.K;
-    double accT = 0.0, accS = 0.0;       // column `lane` of the test / trial adjoints
-    double *row = s_buf + lane * kStride;
-    for (int base = 0; base < npts; base += 64) {
-        const int idx = base + lane;
-        const bool on = idx < npts;
-        P2Fwd X, Y;
-        TGrad gt;
-        SGrad gs;
-        zero(gt);
-        zero(gs);
-        if (on) {
-            const int r = idx / n4;
-            int g = idx % n4;
-            const int i3 = g % n; g /= n;
-            const int i2 = g % n; g /= n;
-            const int i1 = g % n; g /= n;
-            const int i0 = g;
-            double s1, t1, s2, t2;
-            const double jac = ss_region(cls, r, a.glx[i0], a.glx[i1], a.glx[i2], a.glx[i3], s1, t1, s2, t2);
-            const double wg = jac * a.glw[i0] * a.glw[i1] * a.glw[i2] * a.glw[i3];
-            double xe, ye, xf, yf;
-            ss_local(code & 63, s1, t1, xe, ye);
-            ss_local(code >> 6, s2, t2, xf, yf);
-            p2_forward(a.xyz, a.frames, te, xe, ye, X);
-            p2_forward(a.xyz, a.frames, tf, xf, yf, Y);
-            TPt P;
-            SPt Q;
-            P.x = X.x; P.n = X.n; P.t1 = X.t1; P.t2 = X.t2; P.W = X.J;
-            Q.y = Y.x; Q.t1 = Y.t1; Q.t2 = Y.t2; Q.W = Y.J;
-            if constexpr (NODAL) {
-                // components of the node-attached fields in the point frames
-                const double2 *cl[2] = {a.lam, a.lam + a.n2}, *cx_[2] = {a.x, a.x + a.n2};
-                for (int f = 0; f < 2; ++f) {
-                    const cv3 m = nodal_field(a.frames, te, X.N, cl[f]), v = nodal_field(a.frames, tf, Y.N, cx_[f]);
-                    P.L[2 * f] = cdot(m, X.t1);
-                    P.L[2 * f + 1] = cdot(m, X.t2);
-                    Q.X[2 * f] = cdot(v, Y.t1);
-                    Q.X[2 * f + 1] = cdot(v, Y.t2);
-                }
+    if (2 * part >= nreg) return;
+    const int32_t *te = a.tri + 6 * (int64_t)e, *tf = a.tri + 6 * (int64_t)f;
+    constexpr int nw = (int)(sizeof(KernelConst) / sizeof(double));
+    for (int k = lane; k < nw; k += 64) ((double *)&s_K)[k] = ((const double *)a.K)[k];
+    for (int it = lane; it < 2 * F; it += 64) {
+        const int side = it / F, d = it % F;
+        const int32_t *t = side ? tf : te;
+        const double2 *c = side ? a.x : a.lam;
+        double v[6];
+        for (int q = 0; q < 6; ++q) {
+            const int64_t nd = t[q];
+            if (d < 3) {
+                v[q] = a.xyz[3 * nd + d] - a.xyz[3 * (int64_t)te[0] + d];
+            } else if (NODAL) {
+                // m_f = c_f0 t1 + c_f1 t2, component d' (re, im)
+                const int fld = (d - 3) / 6, comp = (d - 3) % 6 / 2, im = (d - 3) % 2;
+                const double2 c0 = c[fld * a.n2 + 2 * nd], c1 = c[fld * a.n2 + 2 * nd + 1];
+                const double *fr = a.frames + 9 * nd;
+                v[q] = (im ? c0.y : c0.x) * fr[3 + comp] + (im ? c1.y : c1.x) * fr[6 + comp];
+            } else if (d < 9) {
+                v[q] = a.frames[9 * nd + d];
             } else {
-                for (int c = 0; c < 4; ++c) { P.L[c] = {0, 0}; Q.X[c] = {0, 0}; }
-                for (int k = 0; k < 6; ++k) {
-                    const int64_t ne = te[k], nf = tf[k];
-                    const double2 l[4] = {a.lam[2 * ne], a.lam[2 * ne + 1], a.lam[a.n2 + 2 * ne],
-                                          a.lam[a.n2 + 2 * ne + 1]};
-                    const double2 u[4] = {a.x[2 * nf], a.x[2 * nf + 1], a.x[a.n2 + 2 * nf], a.x[a.n2 + 2 * nf + 1]};
-                    for (int c = 0; c < 4; ++c) {
-                        P.L[c] = P.L[c] + cxd{X.N[k] * l[c].x, X.N[k] * l[c].y};
-                        Q.X[c] = Q.X[c] + cxd{Y.N[k] * u[c].x, Y.N[k] * u[c].y};
-                    }
-                }
-            }
-            pair_adjoint<NODAL>(a.C, K, P, Q, wg, gt, gs);
-        }
-        // test side
-        {
-            dvec3 gX[6], gT1[6], gT2[6];
-            if (on) {
-                if constexpr (NODAL) {
-                    const double2 *cl[2] = {a.lam, a.lam + a.n2};
-                    dvec3 bn = gt.n;
-                    const cv3 gm[2] = {proj_reverse(gt.p1, nodal_field(a.frames, te, X.N, cl[0]), X.n, bn),
-                                       proj_reverse(gt.p2, nodal_field(a.frames, te, X.N, cl[1]), X.n, bn)};
-                    p2_reverse(X, gt.x, gt.W, bn, {0, 0, 0}, {0, 0, 0}, gX, gT1, gT2);
-                    nodal_tangent_adjoint<2>(te, X.N, cl, gm, gT1, gT2);
-                } else {
-                    p2_reverse(X, gt.x, gt.W, gt.n, gt.t1, gt.t2, gX, gT1, gT2);
-                }
-            }
-            for (int k = 0; k < 6; ++k) {
-                double *o = row + 9 * k;
-                if (on) {
-                    o[0] = gX[k].x; o[1] = gX[k].y; o[2] = gX[k].z;
-                    o[3] = gT1[k].x; o[4] = gT1[k].y; o[5] = gT1[k].z;
-                    o[6] = gT2[k].x; o[7] = gT2[k].y; o[8] = gT2[k].z;
-                } else {
-                    for (int c = 0; c < 9; ++c) o[c] = 0.0;
-                }
+                const int k = (d - 9) / 2;
+                const double2 w = c[(k / 2) * a.n2 + 2 * nd + k % 2];
+                v[q] = d % 2 ? w.x : w.y;
             }
         }
-        __syncthreads();
-        if (lane < kCols)
-            for (int l = 0; l < 64; ++l) accT += s_buf[l * kStride + lane];
-        __syncthreads();
-        // trial side
-        {
-            dvec3 gX[6], gT1[6], gT2[6];
-            if (on) {
-                if constexpr (NODAL) {
-                    const double2 *cx_[2] = {a.x, a.x + a.n2};
-                    dvec3 bn = {0, 0, 0};
-                    const cv3 gm[2] = {proj_reverse(gs.vj, nodal_field(a.frames, tf, Y.N, cx_[0]), Y.n, bn),
-                                       proj_reverse(gs.vm, nodal_field(a.frames, tf, Y.N, cx_[1]), Y.n, bn)};
-                    p2_reverse(Y, gs.y, gs.W, bn, {0, 0, 0}, {0, 0, 0}, gX, gT1, gT2);
-                    nodal_tangent_adjoint<2>(tf, Y.N, cx_, gm, gT1, gT2);
-                } else {
-                    p2_reverse(Y, gs.y, gs.W, {0, 0, 0}, gs.t1, gs.t2, gX, gT1, gT2);
-                }
-            }
-            for (int k = 0; k < 6; ++k) {
-                double *o = row + 9 * k;
-                if (on) {
-                    o[0] = gX[k].x; o[1] = gX[k].y; o[2] = gX[k].z;
-                    o[3] = gT1[k].x; o[4] = gT1[k].y; o[5] = gT1[k].z;
-                    o[6] = gT2[k].x; o[7] = gT2[k].y; o[8] = gT2[k].z;
-                } else {
-                    for (int c = 0; c < 9; ++c) o[c] = 0.0;
-                }
-            }
-        }
-        __syncthreads();
-        if (lane < kCols)
-            for (int l = 0; l < 64; ++l) accS += s_buf[l * kStride + lane];
-        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 6; ++k) s_co[side][F * k + d] = p2_coef(k, v);
     }
-    if (lane < kCols) {
-        const int k = lane / 9, comp = lane % 9;
-        unsafeAtomicAdd(&a.nodeb[9 * (int64_t)te[k] + comp], accT);
-        unsafeAtomicAdd(&a.nodeb[9 * (int64_t)tf[k] + comp], accS);
+    __syncthreads();
+    double accT[NACC], accS[NACC], one[4];
+#pragma unroll
+    for (int k = 0; k < NACC; ++k) accT[k] = accS[k] = 0.0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) one[k] = lane % 4 == k ? 1.0 : 0.0;
+    const int64_t n4 = (int64_t)a.order * a.order * a.order * a.order, r0 = table_region(cls);
+    const int64_t p0 = (r0 + 2 * part) * n4, p1 = (r0 + min(2 * part + 2, nreg)) * n4;
+    for (int64_t base = p0; base < p1; base += 64) {
+        const int64_t id = base + lane < p1 ? base + lane : p1 - 1;
+        const double *q = a.tab + id;
+        const double wg = base + lane < p1 ? fabs(q[4 * a.np]) : 0.0;
+        double xe, ye, xf, yf;
+        ss_local(code & 63, q[0], q[a.np], xe, ye);
+        ss_local(code >> 6, q[2 * a.np], q[3 * a.np], xf, yf);
+        SideAdj aT, aS;
+        {
+            const SsqGeom X = ssq_geom<F>(s_co[0], xe, ye), Y = ssq_geom<F>(s_co[1], xf, yf);
+            const dvec3 Rv = X.x - Y.x;
+            const double d2 = dot(Rv, Rv), rinv = rsqrt64(d2), c = -wg * X.J * Y.J;
+            const KScalD sc = kernel_scalars_dr(a.C, s_K, d2 * rinv, rinv);
+            cv3 u1, u2, vj, vm;
+            auto vectors = [](const double *co, double xi, double eta, dvec3 n, cv3 &p, cv3 &q) {
+                if constexpr (NODAL) {
+                    p = ssq_cvec<F>(co, 3, xi, eta);
+                    q = ssq_cvec<F>(co, 9, xi, eta);
+                    p = p - cdot(p, n) * n;
+                    q = q - cdot(q, n) * n;
+                } else {
+                    cxd L[4];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        L[k] = {ssq_field<F>(co, 9 + 2 * k, xi, eta), ssq_field<F>(co, 10 + 2 * k, xi, eta)};
+                    const SsqFrame fr = ssq_frame<F>(co, xi, eta, n);
+                    p = L[0] * fr.t1 + L[1] * fr.t2;
+                    q = L[2] * fr.t1 + L[3] * fr.t2;
+                }
+            };
+            vectors(s_co[0], xe, ye, X.n, u1, u2);
+            vectors(s_co[1], xf, yf, Y.n, vj, vm);
+            u1 = ccross(u1, X.n);
+            u2 = ccross(u2, X.n);
+            cv3 S1 = czero3(), S2 = S1, Hj = S1, Hm = S1;
+            aT.bx = c * pair_terms(sc, rinv * Rv, rinv, u1, u2, vj, vm, S1, S2, Hj, Hm);
+            aS.bx = dvec3{0, 0, 0} - aT.bx;
+            const double Fi = -wg * (cdot(u1, S1) + cdot(u2, S2)).im;
+            aT.bJ = Y.J * Fi;
+            aS.bJ = X.J * Fi;
+            aT.g1 = c * S1;
+            aT.g2 = c * S2;
+            aS.g1 = c * Hj;
+            aS.g2 = c * Hm;
+        }
+        asm volatile("" ::: "memory");                 // the geometry is formed anew
+        ssq_reverse<true, NODAL, F>(s_co[0], xe, ye, aT, [&](int k, double v) {
+            accT[k / 4] = __builtin_amdgcn_mfma_f64_4x4x4f64(one[k % 4], v, accT[k / 4], 0, 0, 0);
+        });
+        asm volatile("" ::: "memory");
+        ssq_reverse<false, NODAL, F>(s_co[1], xf, yf, aS, [&](int k, double v) {
+            accS[k / 4] = __builtin_amdgcn_mfma_f64_4x4x4f64(one[k % 4], v, accS[k / 4], 0, 0, 0);
+        });
+    }
+    // row r of register k: column 4 k + r in 16 parts
+#pragma unroll
+    for (int k = 0; k < NACC; ++k) {
+        const double t = rsum16(accT[k]), s = rsum16(accS[k]);
+        if (lane % 16 == 0) {
+            s_col[0][4 * k + lane / 16] = t;
+            s_col[1][4 * k + lane / 16] = s;
+        }
+    }
+    __syncthreads();
+    for (int it = lane; it < 108; it += 64) {
+        const int side = it / 54, k = it % 54 / 9, comp = it % 9;
+        const double *c = s_col[side];
+        const int64_t nd = (side ? tf : te)[k];
+        double v;
+        if (comp < 3) {
+            v = c[3 * k + comp];
+        } else if constexpr (NODAL) {
+            // Im of the current's coefficient times the adjoint of m
+            const int b = comp / 3 - 1, d = comp % 3;
+            const double2 *cf = side ? a.x : a.lam;
+            v = 0.0;
+            for (int fld = 0; fld < 2; ++fld) {
+                const double2 w = cf[fld * a.n2 + 2 * nd + b];
+                const double *g = c + 18 + 12 * k + 6 * fld + 2 * d;
+                v += w.x * g[1] + w.y * g[0];
+            }
+        } else {
+            v = c[18 + 6 * k + comp - 3];
+        }
+        unsafeAtomicAdd(&a.nodeb[9 * nd + comp], v);
     }
 }
 
@@ -1030,18 +1167,20 @@ int shape_grad_run(const mbem_op *op, const mbem_params *p, const double2 *x, co
         a.lam = lam;
         a.x = x;
         a.order = op->p.ssq_order > 0 ? op->p.ssq_order : 4;
-        double gx[kMaxSSQ], gw[kMaxSSQ];
-        gauss_legendre(a.order, gx, gw);
-        for (int i = 0; i < kMaxSSQ; ++i) {
-            a.glx[i] = i < a.order ? 0.5 * (1.0 + gx[a.order - 1 - i]) : 0.0;
-            a.glw[i] = i < a.order ? 0.5 * gw[a.order - 1 - i] : 0.0;
-        }
         a.K = op->d_kconst;
         a.C = C;
         a.nodeb = nodeb;
-        if (nodal) hipLaunchKernelGGL(k_shape_ssq<true>, dim3((unsigned)m->n_spairs), dim3(64), 0, s, a);
-        else hipLaunchKernelGGL(k_shape_ssq<false>, dim3((unsigned)m->n_spairs), dim3(64), 0, s, a);
-        launch_ok();
+        double *points = nullptr;
+        st = ssq_table(a.order, &points, &a.np, s);
+        if (st == MBEM_OK && 3 * a.npairs > 0x7fffffffLL) { set_error("too many singular pairs for one launch"); st = MBEM_EINVAL; }
+        if (st == MBEM_OK) {
+            a.tab = points;
+            const dim3 grid((unsigned)(3 * a.npairs));
+            if (nodal) hipLaunchKernelGGL(k_shape_ssq<true>, grid, dim3(64), 0, s, a);
+            else hipLaunchKernelGGL(k_shape_ssq<false>, grid, dim3(64), 0, s, a);
+            launch_ok();
+        }
+        if (points) (void)dev_free(points);            // its next user's work follows on the same stream
     }
     if (st == MBEM_OK) {
         // position adjoints so far, then the frame path adds to the copy

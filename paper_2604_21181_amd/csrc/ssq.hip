@@ -43,9 +43,6 @@ namespace {
 __device__ inline void atomic_add(double *p, double v) { unsafeAtomicAdd(p, v); }
 __device__ inline void atomic_add(float *p, double v) { unsafeAtomicAdd(p, (float)v); }
 
-// first region of a class in the table: 3, 2, 1, then the remainder points
-__host__ __device__ constexpr int table_region(int cls) { return cls == 3 ? 0 : cls == 2 ? 6 : 11; }
-constexpr int kTableRegions = 13;
 constexpr int kRuleCode = 0 | (1 << 2) | (2 << 4);    // identity vertex order
 constexpr int kRuleGroup = 4;                         // remainder points per group (12 share x)
 constexpr int kPaperTerms = 6;                        // highest Taylor term of the remainders
@@ -91,17 +88,6 @@ __global__ void k_ssq_table(int n, int64_t np, GaussRule gl, double *__restrict_
 // polynomials c0 + c1 xi + c2 eta + c3 xi^2 + c4 xi eta + c5 eta^2: coefficient
 // k of field d (x, t1, t2: 9) at co[9 k + d].
 constexpr int kCo = 54;
-__device__ __forceinline__ double p2_coef(int k, const double f[6]) {
-    switch (k) {
-    case 0: return f[0];
-    case 1: return 4.0 * f[3] - 3.0 * f[0] - f[1];
-    case 2: return 4.0 * f[5] - 3.0 * f[0] - f[2];
-    case 3: return 2.0 * (f[0] + f[1]) - 4.0 * f[3];
-    case 4: return 4.0 * ((f[0] - f[3]) + (f[4] - f[5]));
-    default: return 2.0 * (f[0] + f[2]) - 4.0 * f[5];
-    }
-}
-
 // P2 point and frame as p2_point, normalised without divisions, in two steps:
 // the tangents come after the kernel scalars, which need the registers.
 __device__ __forceinline__ void ssq_position(const double *co, double xi, double eta, dvec3 &x, dvec3 &n, double &J) {
@@ -473,6 +459,26 @@ static int launch(const mbem_op *op, bool deriv, SsqArgs<TS> &a, hipStream_t s) 
     return MBEM_OK;
 }
 
+int ssq_table(int n, double **tab, int64_t *np, hipStream_t s) {
+    *np = (int64_t)kTableRegions * n * n * n * n + kQP12 * kQP12;
+    double x[kMaxSSQ], w[kMaxSSQ];
+    gauss_legendre(n, x, w);
+    GaussRule gl{};
+    for (int i = 0; i < n; ++i) {
+        gl.x[i] = 0.5 * (1.0 + x[n - 1 - i]);
+        gl.w[i] = 0.5 * w[n - 1 - i];
+    }
+    const hipError_t err = dev_malloc((void **)tab, sizeof(double) * 5 * *np);
+    if (err != hipSuccess) { set_error(std::string("singular-pair table: ") + hipGetErrorString(err)); return MBEM_ENOMEM; }
+    hipLaunchKernelGGL(k_ssq_table, dim3((unsigned)((*np + 255) / 256)), dim3(256), 0, s, n, *np, gl, *tab);
+    if (hipGetLastError() != hipSuccess) {
+        (void)dev_free(*tab);
+        set_error("singular-pair table: launch failed");
+        return MBEM_EDEVICE;
+    }
+    return MBEM_OK;
+}
+
 template <typename TS>
 static int run(mbem_op *op, bool deriv, const FillBand *band, hipStream_t s) {
     const mbem_mesh *m = op->mesh;
@@ -492,21 +498,10 @@ static int run(mbem_op *op, bool deriv, const FillBand *band, hipStream_t s) {
             std::max(std::hypot(op->ka.x, op->ka.y), std::hypot(op->ki.x, op->ki.y))};
     for (int o = 0; o < 3; ++o) a.Z[o] = (TS *)(band ? band->Z[o] : op->K[o]);
     a.near = band ? NearView{} : op->near_view();
-    const int n = a.order, n4 = n * n * n * n;
-    a.np = (int64_t)kTableRegions * n4 + kQP12 * kQP12;
-    double x[kMaxSSQ], w[kMaxSSQ];
-    gauss_legendre(n, x, w);
-    GaussRule gl{};
-    for (int i = 0; i < n; ++i) {
-        gl.x[i] = 0.5 * (1.0 + x[n - 1 - i]);
-        gl.w[i] = 0.5 * w[n - 1 - i];
-    }
     double *tab = nullptr;
-    const hipError_t err = dev_malloc((void **)&tab, sizeof(double) * 5 * a.np);
-    if (err != hipSuccess) { set_error(std::string("singular-pair table: ") + hipGetErrorString(err)); return MBEM_ENOMEM; }
+    MBEM_TRY(ssq_table(a.order, &tab, &a.np, s));
     a.tab = tab;
-    hipLaunchKernelGGL(k_ssq_table, dim3((unsigned)((a.np + 255) / 256)), dim3(256), 0, s, n, a.np, gl, tab);
-    int st = hipGetLastError() == hipSuccess ? launch(op, deriv, a, s) : MBEM_EDEVICE;
+    const int st = launch(op, deriv, a, s);
     MBEM_HIP(dev_free(tab));         // its next user's work follows on the same stream
     return st;
 }

@@ -52,4 +52,21 @@ __device__ inline void ss_local(int code, double s, double t, double &xi, double
     eta = l[2];
 }
 
+// first region of a class in the table: 3, 2, 1, then the remainder points
+__host__ __device__ constexpr int table_region(int cls) { return cls == 3 ? 0 : cls == 2 ? 6 : 11; }
+constexpr int kTableRegions = 13;
+
+// Coefficient k of c0 + c1 xi + c2 eta + c3 xi^2 + c4 xi eta + c5 eta^2 of the P2
+// function with the nodal values f.
+__device__ __forceinline__ double p2_coef(int k, const double f[6]) {
+    switch (k) {
+    case 0: return f[0];
+    case 1: return 4.0 * f[3] - 3.0 * f[0] - f[1];
+    case 2: return 4.0 * f[5] - 3.0 * f[0] - f[2];
+    case 3: return 2.0 * (f[0] + f[1]) - 4.0 * f[3];
+    case 4: return 4.0 * ((f[0] - f[3]) + (f[4] - f[5]));
+    default: return 2.0 * (f[0] + f[2]) - 4.0 * f[5];
+    }
+}
+
 }  // namespace mbem

@@ -39,4 +39,14 @@ __device__ __forceinline__ double wsum_all(double v) {
     return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
 }
 
+// Sum over each row of 16 lanes, returned to every lane of the row (all
+// lanes active): the first four steps of wsum_all.
+__device__ __forceinline__ double rsum16(double v) {
+    v += dpp_move(v, 0);
+    v += dpp_move(v, 1);
+    v += dpp_move(v, 2);
+    v += dpp_move(v, 3);
+    return v;
+}
+
 }  // namespace mbem

@@ -1,7 +1,9 @@
-"""The regular pairs of the shape gradient (shape.hip, k_shape_regular: tiles of
-64 x 64 points, each pair once for both sides) on meshes that leave the last
-tile short, with the tile's steps divided over four, two and one wavefronts,
-against differences of sigma_ext along a direction of all node coordinates."""
+"""The shape gradient's pairs (shape.hip) against differences of sigma_ext along
+a direction of all node coordinates.  k_shape_regular (tiles of 64 x 64 points,
+each pair once for both sides): meshes that leave the last tile short, with the
+tile's steps divided over four, two and one wavefronts.  k_shape_ssq (batches of
+64 points of two regions): Sauter-Schwab orders that leave the last batch short
+or the only one nearly empty."""
 import numpy as np
 import pytest
 
@@ -19,8 +21,8 @@ MESHES = {"uv70": lambda: uv_sphere_p2(7, 6, (1.0, 0.8, 0.9)),        # 8 tiles,
 KH, POL = [0.0, 0.0, 1.0], [1.0, 0.0, 0.0]
 
 
-def _sigma(xyz, tri, eps, frame, grad):
-    S = mbem.Solver(xyz, tri, 1.8, eps, frame=frame)
+def _sigma(xyz, tri, eps, frame, grad, order=0):
+    S = mbem.Solver(xyz, tri, 1.8, eps, frame=frame, ssq_order=order)
     try:
         S.fill()
         S.precond_setup(100)
@@ -32,19 +34,28 @@ def _sigma(xyz, tri, eps, frame, grad):
         S.close()
 
 
-@pytest.mark.parametrize("frame", [0, 1])
-@pytest.mark.parametrize("eps", [3.0, -2.0 + 0.5j])
-@pytest.mark.parametrize("mesh", sorted(MESHES))
-def test_against_differences(mesh, eps, frame):
-    xyz, tri = MESHES[mesh]()
-    _, dx = _sigma(xyz, tri, eps, frame, True)
+def _compare(xyz, tri, eps, frame, order=0):
+    _, dx = _sigma(xyz, tri, eps, frame, True, order)
     # a smooth displacement of every node, of the size of the body
     rng = np.random.default_rng(5)
     D = np.sin(xyz @ rng.normal(size=(3, 3)) + rng.normal(size=3))
     h = 1e-3
-    f = {k: _sigma(xyz + k * h * D, tri, eps, frame, False)[0] for k in (-2, -1, 1, 2)}
+    f = {k: _sigma(xyz + k * h * D, tri, eps, frame, False, order)[0] for k in (-2, -1, 1, 2)}
     ref = (8.0 * (f[1] - f[-1]) - (f[2] - f[-2])) / (12.0 * h)
     # h^4 = 1e-12 of the fifth derivative, and 1e-12 sigma / h from rounding and
     # the solves; a wrong tile changes the sum by a part in a thousand
     scale = (np.abs(dx) * np.abs(D)).sum()
     assert abs(float((dx * D).sum()) - ref) <= 1e-7 * scale
+
+
+@pytest.mark.parametrize("frame", [0, 1])
+@pytest.mark.parametrize("eps", [3.0, -2.0 + 0.5j])
+@pytest.mark.parametrize("mesh", sorted(MESHES))
+def test_against_differences(mesh, eps, frame):
+    _compare(*MESHES[mesh](), eps, frame)
+
+
+@pytest.mark.parametrize("frame", [0, 1])
+@pytest.mark.parametrize("order", [2, 3, 5])
+def test_sauter_schwab_orders(order, frame):
+    _compare(*MESHES["uv70"](), 3.0, frame, order)
