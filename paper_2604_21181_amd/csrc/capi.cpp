@@ -129,7 +129,7 @@ static void op_free_device(mbem_op *op) {
 
 // ---------------------------------------------------------------- GMRES --
 // Up to kSolveGroup right-hand sides take their steps together: one pass over
-// the blocks serves them all (2 vectors of 10 248 unknowns 289 us, one 212 us),
+// the blocks serves them all (2 vectors of 10 248 unknowns 231 us, one 212 us),
 // and the vector kernels, which are bound by latency, take the group in one
 // launch.  trans: the same iteration on Z^T with P^-T (adjoint systems).
 constexpr int kSolveGroup = 16;

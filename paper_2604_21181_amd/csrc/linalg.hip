@@ -47,46 +47,50 @@ __device__ inline float4 ntload(const float4 *p) {
 
 struct Coef { double2 iw, ce, cm; };
 
-// One column of two rows of the three blocks and of the vectors xj, xm, and its
-// share of the rows' results: acc[row] (electric, magnetic) += (i/w K1 xj + K2e
-// xm, K2m xj - i/w K1 xm)
+// One column of two rows of the three blocks, and its share of the rows' results
+// for a vector's xj, xm: acc[row] (electric, magnetic) += (i/w K1 xj + K2e xm, K2m
+// xj - i/w K1 xm)
 struct RowEntries {
-    double2 k1[2], e[2], m[2], xj, xm;
+    double2 k1[2], e[2], m[2];
 };
-__device__ inline void add_rows(const RowEntries &v, double2 iw, double2 acc[2][2]) {
-    const double2 wj = cmul(iw, v.xj), wm = cmul(iw, v.xm);
+__device__ inline void add_rows(const RowEntries &v, double2 xj, double2 xm, double2 iw, double2 acc[2][2]) {
+    const double2 wj = cmul(iw, xj), wm = cmul(iw, xm);
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
-        acc[k][0] = cadd(acc[k][0], cadd(cmul(v.k1[k], wj), cmul(v.e[k], v.xm)));
-        acc[k][1] = cadd(acc[k][1], csub(cmul(v.m[k], v.xj), cmul(v.k1[k], wm)));
+        acc[k][0] = cadd(acc[k][0], cadd(cmul(v.k1[k], wj), cmul(v.e[k], xm)));
+        acc[k][1] = cadd(acc[k][1], csub(cmul(v.m[k], xj), cmul(v.k1[k], wm)));
     }
 }
-// the columns of a workgroup's lanes: one at a time (c128) or two neighbours
+// the columns of a workgroup's lanes, one at a time (c128) or two neighbours,
+// times NV vectors (x: [NV][2 n])
+template <int NV>
 __device__ inline void stream_rows(const double2 *const (&K)[3], const int64_t (&at)[2], int64_t n,
-                                   const double2 *__restrict__ xj, const double2 *__restrict__ xm, double2 iw,
-                                   double2 acc[2][2]) {
+                                   const double2 *__restrict__ x, double2 iw, double2 acc[NV][2][2]) {
     for (int64_t c = threadIdx.x; c < n; c += 256) {
+        double2 xj[NV], xm[NV];
+#pragma unroll
+        for (int q = 0; q < NV; ++q) { xj[q] = x[2 * q * n + c]; xm[q] = x[(2 * q + 1) * n + c]; }
         RowEntries v;
-        v.xj = xj[c];
-        v.xm = xm[c];
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
             v.k1[k] = ntload(K[0] + at[k] + c);
             v.e[k] = ntload(K[1] + at[k] + c);
             v.m[k] = ntload(K[2] + at[k] + c);
         }
-        add_rows(v, iw, acc);
+#pragma unroll
+        for (int q = 0; q < NV; ++q) add_rows(v, xj[q], xm[q], iw, acc[q]);
     }
 }
+template <int NV>
 __device__ inline void stream_rows(const float2 *const (&K)[3], const int64_t (&at)[2], int64_t n,
-                                   const double2 *__restrict__ xj, const double2 *__restrict__ xm, double2 iw,
-                                   double2 acc[2][2]) {
+                                   const double2 *__restrict__ x, double2 iw, double2 acc[NV][2][2]) {
     for (int64_t c = 2 * threadIdx.x; c < n; c += 512) {   // n is even (2 unknowns per node)
+        double2 xj[NV][2], xm[NV][2];
+#pragma unroll
+        for (int q = 0; q < NV; ++q)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) { xj[q][b] = x[2 * q * n + c + b]; xm[q][b] = x[(2 * q + 1) * n + c + b]; }
         RowEntries v, u;
-        v.xj = xj[c];
-        u.xj = xj[c + 1];
-        v.xm = xm[c];
-        u.xm = xm[c + 1];
         auto two = [](const float4 &f, double2 &a, double2 &b) {
             a = {(double)f.x, (double)f.y};
             b = {(double)f.z, (double)f.w};
@@ -100,12 +104,15 @@ __device__ inline void stream_rows(const float2 *const (&K)[3], const int64_t (&
             two(z[3 * k + 1], v.e[k], u.e[k]);
             two(z[3 * k + 2], v.m[k], u.m[k]);
         }
-        add_rows(v, iw, acc);
-        add_rows(u, iw, acc);
+#pragma unroll
+        for (int q = 0; q < NV; ++q) {
+            add_rows(v, xj[q][0], xm[q][0], iw, acc[q]);
+            add_rows(u, xj[q][1], xm[q][1], iw, acc[q]);
+        }
     }
 }
 
-// y = Z x in one launch: a workgroup takes one node, the two rows of all three
+// y = Z x for NV = 1 .. 4 vectors in one launch: a workgroup takes one node, the two rows of all three
 // blocks, its lanes the columns, the node's mass entries (mval[4 s + 2 al + be])
 // and, with the FP64 near store (nv.bits non-null), the entries V[4 op + 2 al +
 // be] of its stored pairs, times x at 2 j + be; one sum over the workgroup at the
@@ -119,15 +126,16 @@ __device__ inline void stream_rows(const float2 *const (&K)[3], const int64_t (&
 //   FP64         36.5 -> 28.5   237 -> 212   1019 -> 880  (6.4 TB/s)
 //   mixed        40.5 -> 24.0   130 -> 126    542 -> 510
 //   near store   54.6 -> 27.7   207 -> 174    779 -> 701
-template <typename TS>
+// Two vectors, one after the other before: FP64 59 -> 31, 461 -> 231, 2038 -> 952;
+// mixed 66 -> 28, 247 -> 156, 1080 -> 612; four at 1280: 921 -> 287, 496 -> 217.
+template <typename TS, int NV>
 __global__ __launch_bounds__(256) void k_product(int64_t n2, const TS *K1, const TS *K2e, const TS *K2m,
                                                  const int32_t *__restrict__ mptr, const int32_t *__restrict__ mcol,
                                                  const double *__restrict__ mval, const double2 *__restrict__ x, Coef c,
                                                  NearView nv, double2 *__restrict__ y) {
-    __shared__ double s_sum[4][8];
+    __shared__ double s_sum[4][8 * NV];
     const int tid = threadIdx.x;
     const int64_t i = blockIdx.x;
-    const double2 *xj = x, *xm = x + n2;
     struct Mass { int64_t col; double v[4]; };
     auto load_mass = [&](int64_t s) {
         Mass m;
@@ -148,60 +156,76 @@ __global__ __launch_bounds__(256) void k_product(int64_t n2, const TS *K1, const
         n1 = nv.rptr[i + 1];
         if (ns < n1) ncol = 2 * (int64_t)nv.col[ns];
     }
-    double2 acc[2][2] = {{{0.0, 0.0}, {0.0, 0.0}}, {{0.0, 0.0}, {0.0, 0.0}}};
+    double2 acc[NV][2][2];
+#pragma unroll
+    for (int q = 0; q < 4 * NV; ++q) acc[q / 4][q / 2 % 2][q % 2] = double2{0.0, 0.0};
     const TS *const K[3] = {K1, K2e, K2m};
     const int64_t at[2] = {2 * i * n2, (2 * i + 1) * n2};
-    stream_rows(K, at, n2, xj, xm, c.iw, acc);
+    stream_rows<NV>(K, at, n2, x, c.iw, acc);
     while (ms < m1) {
-        const double2 j0 = xj[mass.col], j1 = xj[mass.col + 1], e0 = xm[mass.col], e1 = xm[mass.col + 1];
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const double v0 = mass.v[2 * k], v1 = mass.v[2 * k + 1];
-            acc[k][0] = cadd(acc[k][0], cmul(c.ce, double2{v0 * e0.x + v1 * e1.x, v0 * e0.y + v1 * e1.y}));
-            acc[k][1] = cadd(acc[k][1], cmul(c.cm, double2{v0 * j0.x + v1 * j1.x, v0 * j0.y + v1 * j1.y}));
+        for (int q = 0; q < NV; ++q) {
+            const double2 *xj = x + 2 * q * n2 + mass.col, *xm = xj + n2;
+            const double2 j0 = xj[0], j1 = xj[1], e0 = xm[0], e1 = xm[1];
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const double v0 = mass.v[2 * k], v1 = mass.v[2 * k + 1];
+                acc[q][k][0] = cadd(acc[q][k][0], cmul(c.ce, double2{v0 * e0.x + v1 * e1.x, v0 * e0.y + v1 * e1.y}));
+                acc[q][k][1] = cadd(acc[q][k][1], cmul(c.cm, double2{v0 * j0.x + v1 * j1.x, v0 * j0.y + v1 * j1.y}));
+            }
         }
         ms += 256;
         if (ms < m1) mass = load_mass(ms);
     }
     if (nv.bits) {
-        double2 e = {0.0, 0.0}, h = e;
+        double2 e[NV], h[NV];
+#pragma unroll
+        for (int q = 0; q < NV; ++q) e[q] = h[q] = double2{0.0, 0.0};
         while (ns < n1) {
             const double2 *V = nv.val + 12 * ns + 2 * al;
-            double2 v[6], vj[2], vm[2];
+            double2 v[6], vj[NV][2], vm[NV][2];
 #pragma unroll
             for (int b = 0; b < 2; ++b) {
-                vj[b] = xj[ncol + b];
-                vm[b] = xm[ncol + b];
+#pragma unroll
+                for (int q = 0; q < NV; ++q) {
+                    vj[q][b] = x[2 * q * n2 + ncol + b];
+                    vm[q][b] = x[(2 * q + 1) * n2 + ncol + b];
+                }
 #pragma unroll
                 for (int op = 0; op < 3; ++op) v[2 * op + b] = V[4 * op + b];
             }
             ns += 128;
             if (ns < n1) ncol = 2 * (int64_t)nv.col[ns];
 #pragma unroll
-            for (int b = 0; b < 2; ++b) {
-                e = cadd(e, cadd(cmul(v[b], cmul(c.iw, vj[b])), cmul(v[2 + b], vm[b])));
-                h = cadd(h, csub(cmul(v[4 + b], vj[b]), cmul(v[b], cmul(c.iw, vm[b]))));
-            }
+            for (int q = 0; q < NV; ++q)
+#pragma unroll
+                for (int b = 0; b < 2; ++b) {
+                    e[q] = cadd(e[q], cadd(cmul(v[b], cmul(c.iw, vj[q][b])), cmul(v[2 + b], vm[q][b])));
+                    h[q] = cadd(h[q], csub(cmul(v[4 + b], vj[q][b]), cmul(v[b], cmul(c.iw, vm[q][b]))));
+                }
         }
         const double2 none = {0.0, 0.0};
-        acc[0][0] = cadd(acc[0][0], al ? none : e);
-        acc[0][1] = cadd(acc[0][1], al ? none : h);
-        acc[1][0] = cadd(acc[1][0], al ? e : none);
-        acc[1][1] = cadd(acc[1][1], al ? h : none);
+#pragma unroll
+        for (int q = 0; q < NV; ++q) {
+            acc[q][0][0] = cadd(acc[q][0][0], al ? none : e[q]);
+            acc[q][0][1] = cadd(acc[q][0][1], al ? none : h[q]);
+            acc[q][1][0] = cadd(acc[q][1][0], al ? e[q] : none);
+            acc[q][1][1] = cadd(acc[q][1][1], al ? h[q] : none);
+        }
     }
     const int lane = tid % kW, wave = tid / kW;
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        const double2 a = acc[q / 4][q / 2 % 2];
+    for (int q = 0; q < 8 * NV; ++q) {
+        const double2 a = acc[q / 8][q / 4 % 2][q / 2 % 2];
         const double v = wsum_all(q % 2 ? a.y : a.x);
         if (lane == 0) s_sum[wave][q] = v;
     }
     __syncthreads();
-    if (tid < 4) {       // (row, half)
+    if (tid < 4 * NV) {       // (vector, row, half)
         double2 o = {0.0, 0.0};
 #pragma unroll
         for (int w = 0; w < 4; ++w) o = cadd(o, double2{s_sum[w][2 * tid], s_sum[w][2 * tid + 1]});
-        y[(tid % 2) * n2 + 2 * i + tid / 2] = o;
+        y[(tid / 4 * 2 + tid % 2) * n2 + 2 * i + tid / 2 % 2] = o;
     }
 }
 
@@ -269,24 +293,19 @@ __global__ __launch_bounds__(256) void k_gemv_c64(int64_t n2, const float2 *K1, 
 }
 
 // ------------------------------------------------ several vectors at once --
-// t[v] = K1 x_j, K1 x_m, K2e x_m, K2m x_j for nv vectors (x: [nv][2 n2]) in one
-// pass over the blocks, on the FP64 matrix cores.  A workgroup takes 16 rows of
-// one block, its four wavefronts every fourth run of 8 columns, and their sums
-// meet in LDS.  Every lane loads two neighbouring columns of one row (c64: 16
-// bytes) and of one vector; they are the k of two instructions.
-//   COLS = 4   (4x4x4: four groups of 4 rows against the same 4 vectors) is
-//              bound by the read of the blocks;
-//   COLS = 16  (16x16x4) by the matrix units, whose 16 columns count whether
-//              they hold a vector or not.
-// One run's loads are ahead of its products; more ahead cost registers and with
-// them wavefronts.  A lane without a vector multiplies vector 0 and its sums are
-// dropped: masks are for the last 4 columns alone (masked throughout, 2 vectors
-// took 252 us in place of 177 and 8 vectors 372 in place of 293, mixed).  Tiles
-// of 32 and 64 rows were slower (16 vectors 386 and 450 us in place of 376).
-// us, one after the other (a launch per block and vector) -> this:
-//   n2 = 5120  FP64   2: 461 -> 289   4: 921 -> 353   8: 1802 -> 352   16: 3585 -> 447
-//              mixed  2: 247 -> 177   4: 496 -> 254   8:  937 -> 293   16: 1835 -> 376
-//   n2 = 1280  FP64   2:  59 ->  39   3:  80 ->  41;  mixed  2: 66 -> 37   3: 92 -> 38
+// t[v] = K1 x_j, K1 x_m, K2e x_m, K2m x_j for nv <= 16 vectors (x: [nv][2 n2]) in
+// one pass over the blocks, on the FP64 matrix cores (16x16x4).  A workgroup takes
+// 16 rows of one block, its four wavefronts every fourth run of 8 columns, and
+// their sums meet in LDS.  Every lane loads two neighbouring columns of one row
+// (c64: 16 bytes) and of one vector; they are the k of two instructions.  Bound
+// by the matrix units, whose 16 columns count whether they hold a vector or not.
+// One run's loads are ahead of its products.  A lane without a vector multiplies
+// vector 0 and its sums are dropped: masks are for the last 4 columns alone
+// (masked throughout, 8 vectors took 372 us in place of 293, mixed).  Tiles of
+// 32 and 64 rows were slower (16 vectors 386 and 450 us in place of 376).
+// n2 = 5120, us, one after the other (a launch per block and vector) -> this:
+//   FP64   8: 1802 -> 352   16: 3585 -> 447
+//   mixed  8:  937 -> 293   16: 1835 -> 376
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 __device__ inline void load_pair(const float2 *p, double2 &a, double2 &b) {
@@ -296,33 +315,26 @@ __device__ inline void load_pair(const float2 *p, double2 &a, double2 &b) {
 }
 __device__ inline void load_pair(const double2 *p, double2 &a, double2 &b) { a = p[0]; b = p[1]; }
 
-__device__ inline double mfma_f64(double a, double b, double c) {
-    return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
-}
 __device__ inline f64x4 mfma_f64(double a, double b, f64x4 c) {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
-template <typename ACC>
-__device__ inline void mfma_complex(double2 a, double2 b, ACC acc[2]) {
+__device__ inline void mfma_complex(double2 a, double2 b, f64x4 acc[2]) {
     acc[0] = mfma_f64(a.x, b.x, acc[0]);
     acc[1] = mfma_f64(a.x, b.y, acc[1]);
     acc[0] = mfma_f64(-a.y, b.y, acc[0]);
     acc[1] = mfma_f64(a.y, b.x, acc[1]);
 }
-__device__ inline double acc_at(double v, int) { return v; }
-__device__ inline double acc_at(const f64x4 &v, int e) { return v[e]; }
 
 // rows r0 .. r0 + 15 of K times NS vector sets (halves off[0], off[1] of x)
-template <typename TS, int NS, int COLS>
+template <typename TS, int NS>
 __device__ inline void gemm_rows(const TS *__restrict__ K, int64_t n2, int64_t r0, const double2 *__restrict__ x,
                                  int nv, const int64_t (&off)[2], const int (&slot)[2], double2 *t, double *s_acc) {
-    using ACC = typename std::conditional<COLS == 4, double, f64x4>::type;
-    constexpr int E = COLS == 4 ? 1 : 4;               // sums per lane and component
-    const int lane = threadIdx.x % kW, wave = threadIdx.x / kW, grp = lane / 16, col = lane % COLS;
+    constexpr int E = 4;                               // sums per lane and component
+    const int lane = threadIdx.x % kW, wave = threadIdx.x / kW, grp = lane / 16, col = lane % 16;
     const int64_t row = r0 + lane % 16 < n2 ? r0 + lane % 16 : n2 - 1;
     const TS *a = K + row * n2;
     const double2 *xv = x + (int64_t)(col < nv ? col : 0) * 2 * n2;
-    ACC acc[NS][2] = {};
+    f64x4 acc[NS][2] = {};
     struct Run { double2 a0, a1, b0[NS], b1[NS]; };
     auto load = [&](int64_t k) {
         Run v;
@@ -361,13 +373,12 @@ __device__ inline void gemm_rows(const TS *__restrict__ K, int64_t n2, int64_t r
         }
         add(u);
     }
-    // accumulator: 16x16x4 (lane, e): row grp + 4 e, vector lane % 16; 4x4x4
-    // (lane): row 4 (lane / 4 % 4) + grp, vector lane % 4
+    // accumulator (lane, e): row grp + 4 e, vector lane % 16
     double *mine = s_acc + wave * (2 * E * NS * kW) + lane;
 #pragma unroll
     for (int s = 0; s < NS; ++s)
 #pragma unroll
-        for (int e = 0; e < 2 * E; ++e) mine[(2 * E * s + e) * kW] = acc_at(acc[s][e / E], e % E);
+        for (int e = 0; e < 2 * E; ++e) mine[(2 * E * s + e) * kW] = acc[s][e / E][e % E];
     __syncthreads();
     for (int it = threadIdx.x; it < E * NS * kW; it += 256) {
         const int s = it / (E * kW), e = it / kW % E, ln = it % kW;
@@ -377,21 +388,21 @@ __device__ inline void gemm_rows(const TS *__restrict__ K, int64_t n2, int64_t r
             re += s_acc[w * (2 * E * NS * kW) + (2 * E * s + e) * kW + ln];
             im += s_acc[w * (2 * E * NS * kW) + (2 * E * s + E + e) * kW + ln];
         }
-        const int64_t r = r0 + ln / 16 + 4 * (COLS == 4 ? ln / 4 % 4 : e);
-        const int v = ln % COLS;
+        const int64_t r = r0 + ln / 16 + 4 * e;
+        const int v = ln % 16;
         if (r < n2 && v < nv) t[((int64_t)v * 4 + slot[s]) * n2 + r] = double2{re, im};
     }
 }
 
-template <typename TS, int COLS>
+template <typename TS>
 __global__ __launch_bounds__(256) void k_gemm3(int64_t n2, const TS *K1, const TS *K2e, const TS *K2m,
                                                const double2 *x, int nv, double2 *t) {
-    __shared__ double s_acc[4 * (COLS == 4 ? 4 : 16) * kW];
+    __shared__ double s_acc[4 * 16 * kW];
     const int64_t tiles = (n2 + 15) / 16, blk = blockIdx.x / tiles, r0 = 16 * (blockIdx.x % tiles);
     const int64_t j = 0, m = n2;                       // current halves of a vector
-    if (blk == 0) gemm_rows<TS, 2, COLS>(K1, n2, r0, x, nv, {j, m}, {0, 1}, t, s_acc);
-    else if (blk == 1) gemm_rows<TS, 1, COLS>(K2e, n2, r0, x, nv, {m, m}, {2, 2}, t, s_acc);
-    else gemm_rows<TS, 1, COLS>(K2m, n2, r0, x, nv, {j, j}, {3, 3}, t, s_acc);
+    if (blk == 0) gemm_rows<TS, 2>(K1, n2, r0, x, nv, {j, m}, {0, 1}, t, s_acc);
+    else if (blk == 1) gemm_rows<TS, 1>(K2e, n2, r0, x, nv, {m, m}, {2, 2}, t, s_acc);
+    else gemm_rows<TS, 1>(K2m, n2, r0, x, nv, {j, j}, {3, 3}, t, s_acc);
 }
 
 // LANES consecutive lanes per row split the row's mass slots (a vertex
@@ -480,12 +491,18 @@ static int combine_run(const mbem_op *op, const double2 *x, double2 *y, int nv, 
     return MBEM_OK;
 }
 
-template <typename TS>
+template <int NV>
 static void launch_product(const mbem_op *op, const double2 *x, double2 *y, hipStream_t s) {
     const mbem_mesh *m = op->mesh;
-    hipLaunchKernelGGL(k_product<TS>, dim3((unsigned)(op->n2 / 2)), dim3(256), 0, s, op->n2, (const TS *)op->K[0],
-                       (const TS *)op->K[1], (const TS *)op->K[2], m->d_mptr, m->d_mcol, op->d_mval, x, coef_of(op),
-                       op->near_view(), y);
+    const dim3 grid((unsigned)(op->n2 / 2));
+    if (op->prec == MBEM_FP64)
+        hipLaunchKernelGGL((k_product<double2, NV>), grid, dim3(256), 0, s, op->n2, (const double2 *)op->K[0],
+                           (const double2 *)op->K[1], (const double2 *)op->K[2], m->d_mptr, m->d_mcol, op->d_mval, x,
+                           coef_of(op), op->near_view(), y);
+    else
+        hipLaunchKernelGGL((k_product<float2, NV>), grid, dim3(256), 0, s, op->n2, (const float2 *)op->K[0],
+                           (const float2 *)op->K[1], (const float2 *)op->K[2], m->d_mptr, m->d_mcol, op->d_mval, x,
+                           coef_of(op), op->near_view(), y);
 }
 
 // Complex64 operators above n2 = 12 000 stream eight rows of one block per
@@ -495,19 +512,17 @@ static void launch_product(const mbem_op *op, const double2 *x, double2 *y, hipS
 // 2700: 510 / 542, 320: 24 / 40).  FP64 takes one launch at every size (5120:
 // 3189 / 3832).
 constexpr int64_t kOneLaunchC64 = 12000;
+static bool one_launch(const mbem_op *op) {
+    return !op->blr && (op->prec == MBEM_FP64 || op->n2 <= kOneLaunchC64);
+}
 
 int matvec_run(const mbem_op *op, const double2 *x, double2 *y, double2 *tmp, hipStream_t s,
                hipEvent_t after_gemv) {
     const int64_t n2 = op->n2;
-    bool whole = false;
-    if (op->blr) {
+    if (one_launch(op)) {
+        launch_product<1>(op, x, y, s);
+    } else if (op->blr) {
         MBEM_TRY(blr_gemv_run(op, x, x + n2, tmp, s));
-    } else if (op->prec == MBEM_FP64) {
-        launch_product<double2>(op, x, y, s);
-        whole = true;
-    } else if (n2 <= kOneLaunchC64) {
-        launch_product<float2>(op, x, y, s);
-        whole = true;
     } else {
         const int64_t waves = 3 * ((n2 + kGemvRows - 1) / kGemvRows);
         hipLaunchKernelGGL(k_gemv_c64, dim3((unsigned)((waves * kW + 255) / 256)), dim3(256), 0, s, n2,
@@ -516,13 +531,14 @@ int matvec_run(const mbem_op *op, const double2 *x, double2 *y, double2 *tmp, hi
     }
     MBEM_HIP(hipGetLastError());
     if (after_gemv) MBEM_HIP(hipEventRecord(after_gemv, s));
-    return whole ? MBEM_OK : combine_run(op, x, y, 1, tmp, s);
+    return one_launch(op) ? MBEM_OK : combine_run(op, x, y, 1, tmp, s);
 }
 
-// Up to four vectors go through the 4-wide instructions, more through the
-// 16-wide ones: eight as two passes of four take 706 (FP64) and 508 us (mixed)
-// against 352 and 293 us.  A single vector stays with k_product (212 us FP64,
-// 126 us mixed), a compressed operator with its own product.
+// Two to four vectors share a pass of k_product, more one of the matrix kernel:
+// 8 as two passes of four take 573 (FP64, n2 = 5120) and 434 us (mixed) against
+// 352 and 293 us, and 2 or 4 through the matrix kernel 289 and 353 against 231
+// and 287 (FP64), 177 and 254 against 156 and 217 (mixed).  A compressed operator
+// has its own product.
 int matvecs_chunk(const mbem_op *op, int nrhs) {
     if (op->blr) return 1;
     return std::min(nrhs, nrhs <= 4 ? 4 : 16);
@@ -531,18 +547,21 @@ int matvecs_chunk(const mbem_op *op, int nrhs) {
 template <typename TS>
 static void launch_products(const mbem_op *op, const double2 *x, int nv, double2 *t, hipStream_t s) {
     const int64_t n2 = op->n2;
-    auto k = nv <= 4 ? k_gemm3<TS, 4> : k_gemm3<TS, 16>;
-    hipLaunchKernelGGL(k, dim3((unsigned)(3 * ((n2 + 15) / 16))), dim3(256), 0, s, n2, (const TS *)op->K[0],
+    hipLaunchKernelGGL(k_gemm3<TS>, dim3((unsigned)(3 * ((n2 + 15) / 16))), dim3(256), 0, s, n2, (const TS *)op->K[0],
                        (const TS *)op->K[1], (const TS *)op->K[2], x, nv, t);
 }
 
 int matvecs_run(const mbem_op *op, const double2 *x, double2 *y, int nv, double2 *tmp, hipStream_t s,
                 hipEvent_t after_gemv) {
     if (nv == 1) return matvec_run(op, x, y, tmp, s, after_gemv);
-    if (op->prec == MBEM_FP64) launch_products<double2>(op, x, nv, tmp, s);
+    if (nv == 2) launch_product<2>(op, x, y, s);
+    else if (nv == 3) launch_product<3>(op, x, y, s);
+    else if (nv == 4) launch_product<4>(op, x, y, s);
+    else if (op->prec == MBEM_FP64) launch_products<double2>(op, x, nv, tmp, s);
     else launch_products<float2>(op, x, nv, tmp, s);
     MBEM_HIP(hipGetLastError());
     if (after_gemv) MBEM_HIP(hipEventRecord(after_gemv, s));
+    if (nv <= 4) return MBEM_OK;
     return combine_run(op, x, y, nv, tmp, s);
 }
 

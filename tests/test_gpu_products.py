@@ -1,6 +1,6 @@
-"""Products with several vectors at once (linalg.hip, k_gemm3) against the
-product of each vector alone (k_product) and the exported blocks: every chunk
-edge (4 and 16 vectors and one more), tiles of 16 rows with 4 and with 12 left
+"""Products with several vectors at once (linalg.hip: k_product up to 4, k_gemm3
+up to 16) against the product of each vector alone and the exported blocks:
+every chunk edge (4 and 16 vectors and one more), tiles of 16 rows with 4 and with 12 left
 over, nodes with more mass entries (256) and near pairs (128) than one turn,
 all storage forms, with and without the near store, compressed operators."""
 import numpy as np
