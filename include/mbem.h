@@ -172,7 +172,7 @@ typedef struct {
     int64_t n_regular_pairs; /* regular element pairs (all launches)          */
     /* mbem_grad_sigma_ext: wall times of its phases                          */
     double t_adjoint_ms;  /* Z^T lambda = g                                   */
-    double t_deps_ms;     /* dZ/deps_r fill and lambda^T dZ x                 */
+    double t_deps_ms;     /* lambda^T (dZ/deps_r) x                          */
     double t_shape_ms;    /* reverse pass over the geometry                   */
 } mbem_stats;
 

@@ -1056,7 +1056,7 @@ int mbem_grad_sigma_ext(mbem_ctx *ctx, mbem_op *op, const mbem_mesh *mesh, const
     MBEM_TRY(set_device(ctx));
     const hipStream_t s = ctx->stream;
     const int64_t N = 2 * op->n2;
-    double2 *g = nullptr, *lam = nullptr, *y = nullptr, *dots = nullptr;
+    double2 *g = nullptr, *lam = nullptr, *dots = nullptr;
     double *ddir = nullptr;
     Owned own_dir;
     if (disp_dir && dsig_dnode) {
@@ -1066,7 +1066,6 @@ int mbem_grad_sigma_ext(mbem_ctx *ctx, mbem_op *op, const mbem_mesh *mesh, const
     }
     MBEM_TRY(dalloc(&g, N));
     int st = dalloc(&lam, N);
-    if (st == MBEM_OK) st = dalloc(&y, N);
     if (st == MBEM_OK) st = dalloc(&dots, 2);
     mbem_op *dop = nullptr;
     mbem_stats sst{};
@@ -1081,16 +1080,20 @@ int mbem_grad_sigma_ext(mbem_ctx *ctx, mbem_op *op, const mbem_mesh *mesh, const
     if (st == MBEM_OK) st = solve_impl(ctx, op, (const mbem_c128 *)g, 1, o, (mbem_c128 *)lam, &sst, true);
     t_adj = tm.stop(s);
     tm.start(s);
-    if (st == MBEM_OK) st = mbem_fill_deps(ctx, mesh, p, &dop, nullptr);
     if (st == MBEM_OK) {
-        double2 *tmp = nullptr;
-        st = dalloc(&tmp, 4 * op->n2);
-        if (st == MBEM_OK) st = matvec_run(dop, (const double2 *)x, y, tmp, s);
-        if (st == MBEM_OK) st = dotu_run(g, (const double2 *)x, N, dots, s);
-        if (st == MBEM_OK) st = dotu_run(lam, y, N, dots + 1, s);
+        // the derivative's constants; lambda^T (dZ/deps) x needs no operator
+        mbem_params q = *p;
+        q.precision = MBEM_FP64;
+        st = op_create(ctx, mesh, &q, &dop, false);
+    }
+    if (st == MBEM_OK) st = fill_prepare(dop, s, true);
+    if (st == MBEM_OK) {
+        dop->ce = {0.5, 0.0};   // as mbem_fill_deps
+        dop->cm = {0.0, 0.0};
+        st = dotu_run(g, (const double2 *)x, N, dots, s);
+        if (st == MBEM_OK) st = deps_form_run(dop, (const double2 *)x, lam, dots + 1, s);
         if (st == MBEM_OK && hipMemcpyAsync(hd, dots, sizeof(hd), hipMemcpyDeviceToHost, s) != hipSuccess) st = MBEM_EDEVICE;
-        (void)hipStreamSynchronize(s);
-        dfree(tmp);
+        if (hipStreamSynchronize(s) != hipSuccess && st == MBEM_OK) st = MBEM_EDEVICE;
     }
     t_deps = tm.stop(s);
     if (st == MBEM_OK && lambda_out)
@@ -1104,7 +1107,7 @@ int mbem_grad_sigma_ext(mbem_ctx *ctx, mbem_op *op, const mbem_mesh *mesh, const
     sst.t_deps_ms = t_deps;
     sst.t_shape_ms = t_shape;
     if (dop) mbem_op_destroy(dop);
-    dfree(g); dfree(lam); dfree(y); dfree(dots);
+    dfree(g); dfree(lam); dfree(dots);
     if (st != MBEM_OK) return st;
     // C = (4 pi / k) Im(g^T x);  dC/deps = (4 pi / k) Im(s'), s' = -lambda^T (dZ/deps) x,
     // holomorphic in eps: d/dRe = Im(s'), d/dIm = Im(i s') = Re(s')

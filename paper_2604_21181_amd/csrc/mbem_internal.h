@@ -432,6 +432,9 @@ int mbj_transpose_run(mbem_op *op, hipStream_t s);
 int dotu_run(const double2 *a, const double2 *b, int64_t n, double2 *out, hipStream_t s);
 // shape.hip: d sigma / d(node positions) from x and lambda (Morton order)
 // dir: device [nn*3] displacement directions for dnode, or null (nodal normals)
+// *out = lambda^T (dZ/deps) x (device), without forming dZ/deps: dop carries its
+// constants (fill_prepare with deriv) and the coefficients of its mass terms
+int deps_form_run(const mbem_op *dop, const double2 *x, const double2 *lam, double2 *out, hipStream_t s);
 int shape_grad_run(const mbem_op *op, const mbem_params *p, const double2 *x, const double2 *lam,
                    const double *khat, const double2 *pol, const double *dir, double *dnode, double *dx,
                    hipStream_t s);

@@ -341,11 +341,12 @@ __device__ __forceinline__ KScal<double> kernel_scalars_sing(const KernelConst &
 // Below max|k| R = 1/2 the host supplies the term-by-term derivative of the
 // Taylor coefficients instead (same Horner evaluation as kernel_scalars).
 // KernelConst.ka_re/ka_im hold dk_i/deps_i in this mode.
-__device__ __forceinline__ KScal<double> kernel_scalars_deps(const KernelConst &K, double R) {
+__device__ __forceinline__ KScal<double> kernel_scalars_deps(const KernelConst &K, double R,
+                                                                     double rinv) {
     const double inv4pi = 0.079577471545947667884;
     KScal<double> o;
     if (K.kmax * R < kSeriesRho) {
-        const double r1 = inv4pi / R, r2 = r1 / R, r3 = r2 / R;
+        const double r1 = inv4pi * rinv, r2 = r1 * rinv, r3 = r2 * rinv;
         o.D0 = r1 * horner<double>(K.cD, R);
         o.df = r3 * horner<double>(K.cF, R);
         o.dg = r3 * horner<double>(K.cG, R);
@@ -353,7 +354,7 @@ __device__ __forceinline__ KScal<double> kernel_scalars_deps(const KernelConst &
         o.Gm = r2 * horner<double>(K.cM, R);
         return o;
     }
-    const double r1 = inv4pi / R;
+    const double r1 = inv4pi * rinv;
     const cx<double> k = {K.ki_re, K.ki_im}, dk = {K.ka_re, K.ka_im};
     double sn, cs;
     sincos_t(k.re * R, &sn, &cs);
@@ -363,7 +364,7 @@ __device__ __forceinline__ KScal<double> kernel_scalars_deps(const KernelConst &
     const cx<double> ikR = {-k.im * R, k.re * R};
     const cx<double> ek = r1 * (e * k);                       // e k / (4 pi R)
     const cx<double> dfk = ek * cx<double>{1.0 - ikR.re, -ikR.im};
-    const cx<double> g = (r1 / (R * R)) * (e * cx<double>{1.0 - ikR.re, -ikR.im});
+    const cx<double> g = (r1 * (rinv * rinv)) * (e * cx<double>{1.0 - ikR.re, -ikR.im});
     o.D0 = ((-1.0) * (k * phi) * cx<double>{2.0 + ikR.re, ikR.im}) * dk;
     o.df = (-1.0) * (dfk * dk);
     o.dg = (-1.0) * (ek * dk);

@@ -310,7 +310,7 @@ __global__ __launch_bounds__(256, NODAL ? 2 : 3) void k_pair_tiles(PairArgs a) {
                     KScal<double> sc;
                     double ww = w;
                     if constexpr (DK) {
-                        sc = kernel_scalars_deps(s_K, R);
+                        sc = kernel_scalars_deps(s_K, R, rinv);
                     } else if (kSeries && a.kc.kmax * R < kSeriesRho) {
                         sc = kernel_scalars_series<double>(s_K, R);
                     } else {

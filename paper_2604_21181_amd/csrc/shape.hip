@@ -702,7 +702,7 @@ __global__ __launch_bounds__(256) void k_qp_backprop(int64_t nt, int64_t n2, con
 // Columns per side: 6 x 3 positions, 6 x 3 of each tangent; NODAL: 6 x 12 of the
 // adjoints of m, which the tangents' follow from at the end.
 // Bound by FP64 vector instructions at two wavefronts per SIMD.  1280 triangles:
-// 3.80 -> 1.67 ms, node-attached tangents 2.13 (one wavefront per SIMD, nothing
+// 3.80 -> 1.57 ms, node-attached tangents 2.07 (one wavefront per SIMD, nothing
 // spilled: 2.23 and 2.15; all of a point kept live: 108 spills in place of 48).
 struct ShapeSsqArgs {
     int64_t n2, npairs;
@@ -716,6 +716,9 @@ struct ShapeSsqArgs {
     ShapeConst C;
     double *nodeb;
 };
+
+// What was read from LDS before is read again behind this (no instruction).
+__device__ __forceinline__ void reload_lds() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
 // Position, normal, metric and first derivatives of a triangle's polynomials
 // (F fields, coefficient k of field f at co[F k + f]).
@@ -805,6 +808,7 @@ __device__ __forceinline__ void ssq_reverse(const double *co, double xi, double 
     if constexpr (NODAL) {
 #pragma unroll
         for (int f = 0; f < 2; ++f) {
+            reload_lds();
             const cv3 m = ssq_cvec<F>(co, 3 + 6 * f, xi, eta);
             if constexpr (TEST) bn = bn + im3(ccross(f ? a.g2 : a.g1, m - cdot(m, g.n) * g.n));
             const cv3 gm = proj_reverse(f ? G2 : G1, m, g.n, bn);
@@ -815,7 +819,9 @@ __device__ __forceinline__ void ssq_reverse(const double *co, double xi, double 
                 for (int d = 0; d < 6; ++d) put(18 + 12 * k + 6 * f + d, N[k] * v[d]);
         }
     } else {
+        reload_lds();
         const SsqFrame fr = ssq_frame<F>(co, xi, eta, g.n);
+        reload_lds();
         cxd L[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k)
@@ -854,24 +860,11 @@ __device__ __forceinline__ void ssq_reverse(const double *co, double xi, double 
     }
 }
 
-template <bool NODAL>
-__global__ __launch_bounds__(64, 2) void k_shape_ssq(ShapeSsqArgs a) {
-    constexpr int F = NODAL ? 15 : 17;                 // fields of a triangle
-    constexpr int NCOL = NODAL ? 90 : 54, NACC = (NCOL + 3) / 4;
-    __shared__ double s_co[2][6 * F];
-    __shared__ KernelConst s_K;
-    __shared__ double s_col[2][4 * NACC];
-    const int lane = threadIdx.x;
-    const int64_t pid = blockIdx.x % a.npairs;
-    const int part = (int)(blockIdx.x / a.npairs);
-    const int32_t e = a.pairs[4 * pid], f = a.pairs[4 * pid + 1];
-    const int cls = a.pairs[4 * pid + 2], code = a.pairs[4 * pid + 3];
-    const int nreg = cls == 3 ? 6 : (cls == 2 ? 5 : 2);
-    if (2 * part >= nreg) return;
-    const int32_t *te = a.tri + 6 * (int64_t)e, *tf = a.tri + 6 * (int64_t)f;
-    constexpr int nw = (int)(sizeof(KernelConst) / sizeof(double));
-    for (int k = lane; k < nw; k += 64) ((double *)&s_K)[k] = ((const double *)a.K)[k];
-    for (int it = lane; it < 2 * F; it += 64) {
+// The polynomials of both triangles of a pair (fields of a side: NODAL 15, else 17)
+template <bool NODAL, int F>
+__device__ inline void ssq_polynomials(const ShapeSsqArgs &a, const int32_t *te, const int32_t *tf,
+                                       double (*s_co)[6 * F]) {
+    for (int it = threadIdx.x; it < 2 * F; it += 64) {
         const int side = it / F, d = it % F;
         const int32_t *t = side ? tf : te;
         const double2 *c = side ? a.x : a.lam;
@@ -897,6 +890,44 @@ __global__ __launch_bounds__(64, 2) void k_shape_ssq(ShapeSsqArgs a) {
 #pragma unroll
         for (int k = 0; k < 6; ++k) s_co[side][F * k + d] = p2_coef(k, v);
     }
+}
+// The two vectors of a side's point (p1, p2 or vj, vm).
+template <bool NODAL, int F>
+__device__ __forceinline__ void ssq_vectors(const double *co, double xi, double eta, dvec3 n, cv3 &p, cv3 &q) {
+    if constexpr (NODAL) {
+        p = ssq_cvec<F>(co, 3, xi, eta);
+        q = ssq_cvec<F>(co, 9, xi, eta);
+        p = p - cdot(p, n) * n;
+        q = q - cdot(q, n) * n;
+    } else {
+        cxd L[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            L[k] = {ssq_field<F>(co, 9 + 2 * k, xi, eta), ssq_field<F>(co, 10 + 2 * k, xi, eta)};
+        const SsqFrame fr = ssq_frame<F>(co, xi, eta, n);
+        p = L[0] * fr.t1 + L[1] * fr.t2;
+        q = L[2] * fr.t1 + L[3] * fr.t2;
+    }
+}
+
+template <bool NODAL>
+__global__ __launch_bounds__(64, 2) void k_shape_ssq(ShapeSsqArgs a) {
+    constexpr int F = NODAL ? 15 : 17;                 // fields of a triangle
+    constexpr int NCOL = NODAL ? 90 : 54, NACC = (NCOL + 3) / 4;
+    __shared__ double s_co[2][6 * F];
+    __shared__ KernelConst s_K;
+    __shared__ double s_col[2][4 * NACC];
+    const int lane = threadIdx.x;
+    const int64_t pid = blockIdx.x % a.npairs;
+    const int part = (int)(blockIdx.x / a.npairs);
+    const int32_t e = a.pairs[4 * pid], f = a.pairs[4 * pid + 1];
+    const int cls = a.pairs[4 * pid + 2], code = a.pairs[4 * pid + 3];
+    const int nreg = cls == 3 ? 6 : (cls == 2 ? 5 : 2);
+    if (2 * part >= nreg) return;
+    const int32_t *te = a.tri + 6 * (int64_t)e, *tf = a.tri + 6 * (int64_t)f;
+    constexpr int nw = (int)(sizeof(KernelConst) / sizeof(double));
+    for (int k = lane; k < nw; k += 64) ((double *)&s_K)[k] = ((const double *)a.K)[k];
+    ssq_polynomials<NODAL, F>(a, te, tf, s_co);
     __syncthreads();
     double accT[NACC], accS[NACC], one[4];
 #pragma unroll
@@ -919,24 +950,10 @@ __global__ __launch_bounds__(64, 2) void k_shape_ssq(ShapeSsqArgs a) {
             const double d2 = dot(Rv, Rv), rinv = rsqrt64(d2), c = -wg * X.J * Y.J;
             const KScalD sc = kernel_scalars_dr(a.C, s_K, d2 * rinv, rinv);
             cv3 u1, u2, vj, vm;
-            auto vectors = [](const double *co, double xi, double eta, dvec3 n, cv3 &p, cv3 &q) {
-                if constexpr (NODAL) {
-                    p = ssq_cvec<F>(co, 3, xi, eta);
-                    q = ssq_cvec<F>(co, 9, xi, eta);
-                    p = p - cdot(p, n) * n;
-                    q = q - cdot(q, n) * n;
-                } else {
-                    cxd L[4];
-#pragma unroll
-                    for (int k = 0; k < 4; ++k)
-                        L[k] = {ssq_field<F>(co, 9 + 2 * k, xi, eta), ssq_field<F>(co, 10 + 2 * k, xi, eta)};
-                    const SsqFrame fr = ssq_frame<F>(co, xi, eta, n);
-                    p = L[0] * fr.t1 + L[1] * fr.t2;
-                    q = L[2] * fr.t1 + L[3] * fr.t2;
-                }
-            };
-            vectors(s_co[0], xe, ye, X.n, u1, u2);
-            vectors(s_co[1], xf, yf, Y.n, vj, vm);
+            reload_lds();
+            ssq_vectors<NODAL, F>(s_co[0], xe, ye, X.n, u1, u2);
+            reload_lds();
+            ssq_vectors<NODAL, F>(s_co[1], xf, yf, Y.n, vj, vm);
             u1 = ccross(u1, X.n);
             u2 = ccross(u2, X.n);
             cv3 S1 = czero3(), S2 = S1, Hj = S1, Hm = S1;
@@ -950,11 +967,11 @@ __global__ __launch_bounds__(64, 2) void k_shape_ssq(ShapeSsqArgs a) {
             aS.g1 = c * Hj;
             aS.g2 = c * Hm;
         }
-        asm volatile("" ::: "memory");                 // the geometry is formed anew
+        reload_lds();                                  // the geometry is formed anew
         ssq_reverse<true, NODAL, F>(s_co[0], xe, ye, aT, [&](int k, double v) {
             accT[k / 4] = __builtin_amdgcn_mfma_f64_4x4x4f64(one[k % 4], v, accT[k / 4], 0, 0, 0);
         });
-        asm volatile("" ::: "memory");
+        reload_lds();
         ssq_reverse<false, NODAL, F>(s_co[1], xf, yf, aS, [&](int k, double v) {
             accS[k / 4] = __builtin_amdgcn_mfma_f64_4x4x4f64(one[k % 4], v, accS[k / 4], 0, 0, 0);
         });
@@ -991,6 +1008,126 @@ __global__ __launch_bounds__(64, 2) void k_shape_ssq(ShapeSsqArgs a) {
         }
         unsafeAtomicAdd(&a.nodeb[9 * nd + comp], v);
     }
+}
+
+// ------------------------------------------ lambda^T (dZ/deps) x ---
+// The same pairs with the derivatives' scalars: one complex sum, no operator.
+// 1280 triangles: 5.4 ms for the fill of dZ/deps, its product and their buffers
+// -> 1.5 ms here (the gradient 18.8 -> 14.8 ms, node-attached tangents 24.6 ->
+// 15.3).
+__device__ __forceinline__ cxd pair_form(const KScal<double> &s, cxd iw, dvec3 h, cv3 u1, cv3 u2, cv3 vj, cv3 vm) {
+    const cxd al = cdot(u1, vj) - cdot(u2, vm);
+    const cxd be = cdot(u1, h) * cdot(vj, h) - cdot(u2, h) * cdot(vm, h);
+    return iw * ((s.D0 - s.dg) * al + s.df * be) + s.Ge * cdot(u1, ccross(vm, h)) + s.Gm * cdot(u2, ccross(vj, h));
+}
+
+constexpr int kFormSlots = 256;    // partial sums: a wavefront adds to slot block % kFormSlots
+__device__ inline void form_add(double2 *slots, cxd v) {
+    const double re = wsum_all(v.re), im = wsum_all(v.im);
+    if (threadIdx.x == 0) {
+        double2 *o = slots + (blockIdx.x + blockIdx.y * (int64_t)gridDim.x) % kFormSlots;
+        unsafeAtomicAdd(&o->x, re);
+        unsafeAtomicAdd(&o->y, im);
+    }
+}
+
+// One wavefront per (64 test points, 64 trial points): a test point per lane,
+// the trial points in turn; the first tile adds the points' mass terms.
+__global__ __launch_bounds__(64, 4) void k_deps_regular(int64_t nq, const double2 *__restrict__ tab,
+                                                     const double *__restrict__ qp,
+                                                     const double *__restrict__ fields,
+                                                     const int32_t *__restrict__ tri, ShapeConst C, cxd ce, cxd cm,
+                                                     const KernelConst *__restrict__ Kp,
+                                                     double2 *__restrict__ slots) {
+    __shared__ double2 s_t[8][kShapeTile];
+    __shared__ int32_t s_f[3][kShapeTile];
+    __shared__ KernelConst s_K;
+    const int lane = threadIdx.x;
+    const int64_t i = (int64_t)blockIdx.y * kShapeTile + lane, j0 = (int64_t)blockIdx.x * kShapeTile;
+    const int64_t ic = i < nq ? i : nq - 1, jc = j0 + lane < nq ? j0 + lane : nq - 1;
+    const int nj = (int)(nq - j0 < kShapeTile ? nq - j0 : kShapeTile);
+    constexpr int nw = (int)(sizeof(KernelConst) / sizeof(double));
+    for (int k = lane; k < nw; k += 64) ((double *)&s_K)[k] = ((const double *)Kp)[k];
+    int32_t te[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        te[k] = tri[6 * (ic / kQP) + k];
+        s_f[k][lane] = tri[6 * (jc / kQP) + k];
+    }
+    const dvec3 x = tab_pos(tab[ic], tab[nq + ic]);
+    const cv3 u1 = tab_vec(tab[2 * nq + ic], tab[3 * nq + ic], tab[4 * nq + ic]);
+    const cv3 u2 = tab_vec(tab[5 * nq + ic], tab[6 * nq + ic], tab[7 * nq + ic]);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) s_t[k][lane] = tab[(k < 2 ? k : 6 + k) * nq + jc];
+    __syncthreads();
+    cxd sum = {0.0, 0.0};
+    for (int k = 0; k < nj; ++k) {
+        reload_lds();                                  // the series' coefficients stay in LDS
+        bool on = i < nq;                              // pairs that share a vertex are not regular
+#pragma unroll
+        for (int c = 0; c < 3; ++c) on = on && te[c] != s_f[0][k] && te[c] != s_f[1][k] && te[c] != s_f[2][k];
+        if (on) {
+            const dvec3 Rv = x - tab_pos(s_t[0][k], s_t[1][k]);
+            const cv3 vj = tab_vec(s_t[2][k], s_t[3][k], s_t[4][k]), vm = tab_vec(s_t[5][k], s_t[6][k], s_t[7][k]);
+            const double d2 = dot(Rv, Rv), rinv = rsqrt64(d2);
+            sum = sum + pair_form(kernel_scalars_deps(s_K, d2 * rinv, rinv), C.iw, rinv * Rv, u1, u2, vj, vm);
+        }
+    }
+    if (blockIdx.x == 0 && i < nq) {
+        const double *f = fields + 16 * i;
+        cxd v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = {f[2 * k], f[2 * k + 1]};
+        sum = sum + qp[QW * nq + i] * (ce * (v[0] * v[6] + v[1] * v[7]) + cm * (v[2] * v[4] + v[3] * v[5]));
+    }
+    form_add(slots, sum);
+}
+
+template <bool NODAL>
+__global__ __launch_bounds__(64, 3) void k_deps_ssq(ShapeSsqArgs a, double2 *__restrict__ slots) {
+    constexpr int F = NODAL ? 15 : 17;
+    __shared__ double s_co[2][6 * F];
+    __shared__ KernelConst s_K;
+    const int lane = threadIdx.x;
+    const int64_t pid = blockIdx.x % a.npairs;
+    const int part = (int)(blockIdx.x / a.npairs);
+    const int32_t e = a.pairs[4 * pid], f = a.pairs[4 * pid + 1];
+    const int cls = a.pairs[4 * pid + 2], code = a.pairs[4 * pid + 3];
+    const int nreg = cls == 3 ? 6 : (cls == 2 ? 5 : 2);
+    if (2 * part >= nreg) return;
+    constexpr int nw = (int)(sizeof(KernelConst) / sizeof(double));
+    for (int k = lane; k < nw; k += 64) ((double *)&s_K)[k] = ((const double *)a.K)[k];
+    ssq_polynomials<NODAL, F>(a, a.tri + 6 * (int64_t)e, a.tri + 6 * (int64_t)f, s_co);
+    __syncthreads();
+    const int64_t n4 = (int64_t)a.order * a.order * a.order * a.order, r0 = table_region(cls);
+    const int64_t p1 = (r0 + min(2 * part + 2, nreg)) * n4;
+    cxd sum = {0.0, 0.0};
+    for (int64_t id = (r0 + 2 * part) * n4 + lane; id < p1; id += 64) {
+        reload_lds();                                  // no coefficient stays in a register over the points
+        const double *q = a.tab + id;
+        double xe, ye, xf, yf;
+        ss_local(code & 63, q[0], q[a.np], xe, ye);
+        ss_local(code >> 6, q[2 * a.np], q[3 * a.np], xf, yf);
+        const SsqGeom X = ssq_geom<F>(s_co[0], xe, ye), Y = ssq_geom<F>(s_co[1], xf, yf);
+        const dvec3 Rv = X.x - Y.x;
+        const double d2 = dot(Rv, Rv), rinv = rsqrt64(d2), w = fabs(q[4 * a.np]) * X.J * Y.J;
+        const KScal<double> sc = kernel_scalars_deps(s_K, d2 * rinv, rinv);
+        cv3 u1, u2, vj, vm;
+        reload_lds();
+        ssq_vectors<NODAL, F>(s_co[0], xe, ye, X.n, u1, u2);
+        reload_lds();
+        ssq_vectors<NODAL, F>(s_co[1], xf, yf, Y.n, vj, vm);
+        sum = sum + w * pair_form(sc, a.C.iw, rinv * Rv, ccross(u1, X.n),
+                                  ccross(u2, X.n), vj, vm);
+    }
+    form_add(slots, sum);
+}
+
+__global__ __launch_bounds__(64) void k_form_sum(const double2 *__restrict__ slots, double2 *__restrict__ out) {
+    cxd v = {0.0, 0.0};
+    for (int k = threadIdx.x; k < kFormSlots; k += 64) v = v + cxd{slots[k].x, slots[k].y};
+    const double re = wsum_all(v.re), im = wsum_all(v.im);
+    if (threadIdx.x == 0) *out = double2{re, im};
 }
 
 // -------------------------------------------------- nodal frames ---
@@ -1081,6 +1218,78 @@ __global__ void k_shape_out(int64_t nn, double scale, const double *__restrict__
 }
 
 // --------------------------------------------------------------- host ---
+static ShapeConst shape_const(const mbem_op *op) {
+    ShapeConst C;
+    C.kc = {op->ka.x, op->ki.x, op->ki.y, op->eps_i.x, op->eps_i.y, op->mu_i.x, op->mu_i.y,
+            std::max(std::abs(op->ka.x), std::hypot(op->ki.x, op->ki.y))};
+    C.iw = {op->iw.x, op->iw.y};
+    return C;
+}
+
+// The singular pairs' arguments but for the point table.
+static ShapeSsqArgs ssq_args(const mbem_op *op, const double2 *x, const double2 *lam) {
+    const mbem_mesh *m = op->mesh;
+    ShapeSsqArgs a{};
+    a.n2 = op->n2;
+    a.npairs = m->n_spairs;
+    a.pairs = m->d_spairs;
+    a.tri = m->d_tri;
+    a.xyz = m->d_xyz;
+    a.frames = m->d_frames;
+    a.lam = lam;
+    a.x = x;
+    a.order = op->p.ssq_order > 0 ? op->p.ssq_order : 4;
+    a.K = op->d_kconst;
+    a.C = shape_const(op);
+    return a;
+}
+
+static void launch_fields(const mbem_op *op, const double2 *x, const double2 *lam, double *fields, double2 *tab,
+                          hipStream_t s) {
+    const mbem_mesh *m = op->mesh;
+    const dim3 grid((unsigned)((m->nt * kQP + 255) / 256));
+    auto k = op->p.frame == MBEM_FRAME_NODAL ? k_qp_fields<true> : k_qp_fields<false>;
+    hipLaunchKernelGGL(k, grid, dim3(256), 0, s, m->nt, op->n2, m->d_tri, m->d_qp, m->d_frames, lam, x, fields, tab);
+}
+
+int deps_form_run(const mbem_op *dop, const double2 *x, const double2 *lam, double2 *out, hipStream_t s) {
+    const mbem_mesh *m = dop->mesh;
+    const int64_t nq = m->nt * kQP, tiles = (nq + kShapeTile - 1) / kShapeTile;
+    const bool nodal = dop->p.frame == MBEM_FRAME_NODAL;
+    if (tiles > 65535 || 3 * m->n_spairs > 0x7fffffffLL) { set_error("too many pairs for one launch"); return MBEM_EINVAL; }
+    double2 *tab = nullptr;
+    if (dev_malloc((void **)&tab, sizeof(double2) * (kTab * nq + kFormSlots + 8 * nq)) != hipSuccess) {
+        set_error("permittivity gradient workspace: out of memory");
+        return MBEM_ENOMEM;
+    }
+    double2 *slots = tab + kTab * nq;
+    double *fields = (double *)(slots + kFormSlots);
+    (void)hipMemsetAsync(slots, 0, sizeof(double2) * kFormSlots, s);
+    launch_fields(dop, x, lam, fields, tab, s);
+    hipLaunchKernelGGL(k_deps_regular, dim3((unsigned)tiles, (unsigned)tiles), dim3(kShapeTile), 0, s, nq, tab, m->d_qp,
+                       fields, m->d_tri, shape_const(dop), cxd{dop->ce.x, dop->ce.y}, cxd{dop->cm.x, dop->cm.y},
+                       dop->d_kconst, slots);
+    int st = MBEM_OK;
+    double *points = nullptr;
+    if (m->n_spairs > 0) {
+        ShapeSsqArgs a = ssq_args(dop, x, lam);
+        st = ssq_table(a.order, &points, &a.np, s);
+        a.tab = points;
+        auto k = nodal ? k_deps_ssq<true> : k_deps_ssq<false>;
+        if (st == MBEM_OK) hipLaunchKernelGGL(k, dim3((unsigned)(3 * a.npairs)), dim3(64), 0, s, a, slots);
+    }
+    hipLaunchKernelGGL(k_form_sum, dim3(1), dim3(64), 0, s, slots, out);
+    const hipError_t e = hipGetLastError();
+    if (st == MBEM_OK && e != hipSuccess) {
+        set_error(std::string("permittivity gradient launch: ") + hipGetErrorString(e));
+        st = MBEM_EDEVICE;
+    }
+    // their next user's work follows on the same stream
+    if (points) (void)dev_free(points);
+    (void)dev_free(tab);
+    return st;
+}
+
 int shape_grad_run(const mbem_op *op, const mbem_params *p, const double2 *x, const double2 *lam,
                    const double *khat, const double2 *pol, const double *dir, double *dnode, double *dx,
                    hipStream_t s) {
@@ -1118,16 +1327,8 @@ int shape_grad_run(const mbem_op *op, const mbem_params *p, const double2 *x, co
     (void)hipMemsetAsync(nodeb, 0, sizeof(double) * 9 * nn, s);
     (void)hipMemsetAsync(nodeb_x, 0, sizeof(double) * 9 * nn, s);
     const unsigned gq = (unsigned)((nq + 255) / 256);
-    ShapeConst C;
-    C.kc = {op->ka.x, op->ki.x, op->ki.y, op->eps_i.x, op->eps_i.y, op->mu_i.x, op->mu_i.y,
-            std::max(std::abs(op->ka.x), std::hypot(op->ki.x, op->ki.y))};
-    C.iw = {op->iw.x, op->iw.y};
-    if (nodal)
-        hipLaunchKernelGGL(k_qp_fields<true>, dim3(gq), dim3(256), 0, s, nt, op->n2, m->d_tri, m->d_qp, m->d_frames,
-                           lam, x, fields, tab);
-    else
-        hipLaunchKernelGGL(k_qp_fields<false>, dim3(gq), dim3(256), 0, s, nt, op->n2, m->d_tri, m->d_qp,
-                           m->d_frames, lam, x, fields, tab);
+    const ShapeConst C = shape_const(op);
+    launch_fields(op, x, lam, fields, tab, s);
     if (launch_ok()) {
         // a small mesh divides the 64 steps over up to four wavefronts
         const int64_t tiles = (nq + kShapeTile - 1) / kShapeTile;
@@ -1157,18 +1358,7 @@ int shape_grad_run(const mbem_op *op, const mbem_params *p, const double2 *x, co
         launch_ok();
     }
     if (st == MBEM_OK && m->n_spairs > 0) {
-        ShapeSsqArgs a;
-        a.n2 = op->n2;
-        a.npairs = m->n_spairs;
-        a.pairs = m->d_spairs;
-        a.tri = m->d_tri;
-        a.xyz = m->d_xyz;
-        a.frames = m->d_frames;
-        a.lam = lam;
-        a.x = x;
-        a.order = op->p.ssq_order > 0 ? op->p.ssq_order : 4;
-        a.K = op->d_kconst;
-        a.C = C;
+        ShapeSsqArgs a = ssq_args(op, x, lam);
         a.nodeb = nodeb;
         double *points = nullptr;
         st = ssq_table(a.order, &points, &a.np, s);

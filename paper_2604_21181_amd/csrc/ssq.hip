@@ -286,7 +286,7 @@ void k_ssq(SsqArgs<TS> a) {
                     sc = rem ? scalars_rem64(a.kc, s_K, R, rinv, w) : scalars_sing64(a.kc, rinv, w);
                     ww = 1.0;
                 } else if constexpr (DK) {
-                    sc = kernel_scalars_deps(s_K, R);
+                    sc = kernel_scalars_deps(s_K, R, rinv);
                 } else if (a.kc.kmax * R < kSeriesRho) {
                     sc = kernel_scalars_series<double>(s_K, R);
                 } else {
