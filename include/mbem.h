@@ -248,7 +248,7 @@ int mbem_matvec(mbem_ctx *ctx, const mbem_op *op, const mbem_c128 *x,
  * (code under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc): no allocation or release of any kind and no host wait -- the
  * products are enqueued on the context's stream and the call returns; the
- * caller synchronises before reading y.  The partial sums live in a 4 MiB
+ * caller synchronises before reading y.  The partial sums live in a 12 MiB
  * array in device memory that the library holds on every device it runs
  * on until the process ends, so op must have 2 n_nodes <= 65536 (MBEM_EINVAL
  * otherwise, nothing enqueued).  Every call on one device uses that

@@ -206,9 +206,10 @@ struct Gmres {
 // does not grow with maxit is small beside them).
 static size_t gmres_elems(const mbem_op *op, int maxit) {
     const size_t N = 2 * op->n2, nch = (size_t)arnoldi_chunks(N), col = 2 * (size_t)(maxit + 1) + 1;
-    // V and W, w, z, matvec partials (4 n2), the coefficients y (m) and a
+    // V and W, w, z, matvec partials (4 n2, and 32 n2 for more than eight
+    // systems: 8 n2 covers both), the coefficients y (m) and a
     // norm, the step's column, projection partials of both passes, norm partials
-    return 2 * (size_t)(maxit + 1) * N + 2 * N + 4 * op->n2 + (size_t)maxit + 1 + col +
+    return 2 * (size_t)(maxit + 1) * N + 2 * N + 8 * op->n2 + (size_t)maxit + 1 + col +
            2 * (size_t)(maxit + 1) * nch + nch + 1;
 }
 
@@ -263,8 +264,8 @@ static int gmres_alloc(Gmres &g, const mbem_op *op, int maxit, hipStream_t s) {
     g.W = g.V + (size_t)(maxit + 1) * G * g.N;
     g.w = g.W + (size_t)(maxit + 1) * G * g.N;
     g.z = g.w + G * g.N;
-    g.tmp = g.z + G * g.N;                 // 4 n2 per system for the matvec partials
-    g.hdev = g.tmp + G * 4 * op->n2;       // the coefficients y of the final combinations
+    g.tmp = g.z + G * g.N;                 // matvecs_work
+    g.hdev = g.tmp + G * 8 * op->n2;       // the coefficients y of the final combinations
     g.ndev = (double *)(g.hdev + G * maxit);   // a norm per system
     g.hcol = g.hdev + G * maxit + G;
     g.ppart = g.hcol + G * col;
@@ -799,7 +800,7 @@ int mbem_matvec(mbem_ctx *ctx, const mbem_op *op, const mbem_c128 *x, int32_t nr
     MBEM_TRY(set_device(ctx));
     double2 *tmp = nullptr;
     const int chunk = matvecs_chunk(op, nrhs);
-    MBEM_TRY(dalloc(&tmp, (size_t)4 * op->n2 * chunk));
+    MBEM_TRY(dalloc(&tmp, (size_t)matvecs_work(op, chunk)));
     const int64_t N = 2 * op->n2;
     int st = MBEM_OK;
     for (int r = 0; r < nrhs && st == MBEM_OK; r += chunk)

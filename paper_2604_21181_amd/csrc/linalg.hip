@@ -302,10 +302,10 @@ __global__ __launch_bounds__(256) void k_gemv_c64(int64_t n2, const float2 *K1, 
 // One run's loads are ahead of its products.  A lane without a vector multiplies
 // vector 0 and its sums are dropped: masks are for the last 4 columns alone
 // (masked throughout, 8 vectors took 372 us in place of 293, mixed).  Tiles of
-// 32 and 64 rows were slower (16 vectors 386 and 450 us in place of 376).
+// 32 and 64 rows were slower (16 vectors 386 and 450 us where this took 376).
 // n2 = 5120, us, one after the other (a launch per block and vector) -> this:
-//   FP64   8: 1802 -> 352   16: 3585 -> 447
-//   mixed  8:  937 -> 293   16: 1835 -> 376
+//   FP64   8: 1802 -> 352   16: 3585 -> 376
+//   mixed  8:  937 -> 293   16: 1835 -> 296
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 __device__ inline void load_pair(const float2 *p, double2 &a, double2 &b) {
@@ -325,22 +325,37 @@ __device__ inline void mfma_complex(double2 a, double2 b, f64x4 acc[2]) {
     acc[1] = mfma_f64(a.y, b.x, acc[1]);
 }
 
+// xt[k][v] = x[v][k] for v < nv, 0 up to 16, which k_gemm3 reads in whole lines
+__global__ void k_pack_vectors(int64_t n, int nv, const double2 *__restrict__ x, double2 *__restrict__ xt) {
+    const int64_t id = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, k = id / 16;
+    const int v = (int)(id % 16);
+    if (k < n) xt[id] = v < nv ? x[v * n + k] : double2{0.0, 0.0};
+}
+
+// entry (k, v) of the vectors at p[k step + v lead]
+struct Vectors {
+    const double2 *p;
+    int64_t step, lead;
+};
 // rows r0 .. r0 + 15 of K times NS vector sets (halves off[0], off[1] of x)
 template <typename TS, int NS>
-__device__ inline void gemm_rows(const TS *__restrict__ K, int64_t n2, int64_t r0, const double2 *__restrict__ x,
+__device__ inline void gemm_rows(const TS *__restrict__ K, int64_t n2, int64_t r0, const Vectors &x,
                                  int nv, const int64_t (&off)[2], const int (&slot)[2], double2 *t, double *s_acc) {
     constexpr int E = 4;                               // sums per lane and component
     const int lane = threadIdx.x % kW, wave = threadIdx.x / kW, grp = lane / 16, col = lane % 16;
     const int64_t row = r0 + lane % 16 < n2 ? r0 + lane % 16 : n2 - 1;
     const TS *a = K + row * n2;
-    const double2 *xv = x + (int64_t)(col < nv ? col : 0) * 2 * n2;
+    const double2 *xv = x.p + (col < nv ? col : 0) * x.lead;
     f64x4 acc[NS][2] = {};
     struct Run { double2 a0, a1, b0[NS], b1[NS]; };
     auto load = [&](int64_t k) {
         Run v;
         load_pair(a + k, v.a0, v.a1);
 #pragma unroll
-        for (int s = 0; s < NS; ++s) load_pair(xv + off[s] + k, v.b0[s], v.b1[s]);
+        for (int s = 0; s < NS; ++s) {
+            v.b0[s] = xv[(off[s] + k) * x.step];
+            v.b1[s] = xv[(off[s] + k + 1) * x.step];
+        }
         return v;
     };
     auto add = [&](const Run &v) {
@@ -396,7 +411,7 @@ __device__ inline void gemm_rows(const TS *__restrict__ K, int64_t n2, int64_t r
 
 template <typename TS>
 __global__ __launch_bounds__(256) void k_gemm3(int64_t n2, const TS *K1, const TS *K2e, const TS *K2m,
-                                               const double2 *x, int nv, double2 *t) {
+                                               Vectors x, int nv, double2 *t) {
     __shared__ double s_acc[4 * 16 * kW];
     const int64_t tiles = (n2 + 15) / 16, blk = blockIdx.x / tiles, r0 = 16 * (blockIdx.x % tiles);
     const int64_t j = 0, m = n2;                       // current halves of a vector
@@ -544,11 +559,26 @@ int matvecs_chunk(const mbem_op *op, int nrhs) {
     return std::min(nrhs, nrhs <= 4 ? 4 : 16);
 }
 
+// More than eight vectors of a larger operator are packed first: their loads,
+// sixteen lines at a time otherwise, bound the kernel (n2 = 5120, FP64: 16
+// vectors 447 -> 376 us, 12: 407 -> 374, 8: 352 -> 370; mixed 16: 376 -> 296, 8:
+// 293 -> 288; n2 = 1284, 16: 46 -> 49, the launch).
+static bool packed(const mbem_op *op, int nv) { return nv > 8 && op->n2 >= 2048; }
+// the products of every vector, and the packed vectors
+int64_t matvecs_work(const mbem_op *op, int nv) { return (4 * (int64_t)nv + (packed(op, nv) ? 32 : 0)) * op->n2; }
+
 template <typename TS>
 static void launch_products(const mbem_op *op, const double2 *x, int nv, double2 *t, hipStream_t s) {
     const int64_t n2 = op->n2;
+    Vectors v = {x, 1, 2 * n2};
+    if (packed(op, nv)) {
+        double2 *xt = t + 4 * n2 * nv;
+        hipLaunchKernelGGL(k_pack_vectors, dim3((unsigned)((2 * n2 * 16 + 255) / 256)), dim3(256), 0, s, 2 * n2, nv, x,
+                           xt);
+        v = {xt, 16, 1};
+    }
     hipLaunchKernelGGL(k_gemm3<TS>, dim3((unsigned)(3 * ((n2 + 15) / 16))), dim3(256), 0, s, n2, (const TS *)op->K[0],
-                       (const TS *)op->K[1], (const TS *)op->K[2], x, nv, t);
+                       (const TS *)op->K[1], (const TS *)op->K[2], v, nv, t);
 }
 
 int matvecs_run(const mbem_op *op, const double2 *x, double2 *y, int nv, double2 *tmp, hipStream_t s,
@@ -1736,8 +1766,9 @@ int vec_axpy(double2 *y, const double2 *x, double2 a, int64_t n, hipStream_t s) 
 // device current, and the kernels receive that address (the array's name in
 // host code is not a device address).
 namespace mbem {
-constexpr int64_t kScratchN2 = 65536;                 // largest n2 = 2 n_nodes (4 MiB)
-static __device__ __align__(256) double2 scratch[4 * kScratchN2];
+constexpr int64_t kScratchN2 = 65536;                 // largest n2 = 2 n_nodes
+constexpr int64_t kScratchElems = 12 * kScratchN2;    // 12 MiB: 16 vectors up to n2 = 8192
+static __device__ __align__(256) double2 scratch[kScratchElems];
 namespace {
 constexpr int kScratchDevices = 64;
 void *g_scratch[kScratchDevices] = {};
@@ -1780,7 +1811,8 @@ extern "C" int mbem_matvec_noalloc(mbem_ctx *ctx, const mbem_op *op, const mbem_
     const int64_t N = 2 * op->n2;
     // as many vectors at a time as the scratch holds: bit for bit mbem_matvec
     // where that is its chunk too, else equal to rounding
-    const int chunk = (int)std::min<int64_t>(matvecs_chunk(op, nrhs), kScratchN2 / op->n2);
+    int chunk = matvecs_chunk(op, nrhs);
+    while (chunk > 1 && matvecs_work(op, chunk) > kScratchElems) --chunk;
     for (int r = 0; r < nrhs; r += chunk)
         MBEM_TRY(matvecs_run(op, (const double2 *)x + r * N, (double2 *)y + r * N, std::min(chunk, nrhs - r), tmp,
                              ctx->stream));

@@ -359,8 +359,9 @@ int mass_run(mbem_op *op, hipStream_t s);
 int matvec_run(const mbem_op *op, const double2 *x, double2 *y, double2 *tmp,
                hipStream_t s, hipEvent_t after_gemv = nullptr);
 // y[v] = Z x[v] for nv <= matvecs_chunk(op, nrhs) of nrhs vectors (rows of N
-// elements); tmp: 4 n2 nv
+// elements); tmp: matvecs_work(op, nv) elements
 int matvecs_chunk(const mbem_op *op, int nrhs);
+int64_t matvecs_work(const mbem_op *op, int nv);
 int matvecs_run(const mbem_op *op, const double2 *x, double2 *y, int nv, double2 *tmp, hipStream_t s,
                 hipEvent_t after_gemv = nullptr);
 int export_dense_run(const mbem_op *op, double2 *Z, hipStream_t s);

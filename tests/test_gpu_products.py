@@ -15,7 +15,7 @@ from paper_2604_21181_amd import mbem  # noqa: E402
 from workloads.meshes import icosphere_p2, uv_sphere_p2  # noqa: E402
 
 MESHES = {"ico20": lambda: icosphere_p2(20), "uv70": lambda: uv_sphere_p2(7, 6), "ico320": lambda: icosphere_p2(320),
-          "uv540": lambda: uv_sphere_p2(90, 4)}
+          "uv540": lambda: uv_sphere_p2(90, 4)}               # n2 = 2164: more than 8 vectors packed
 FORMS = {"fp64": dict(), "mixed": dict(precision=1), "store": dict(precision=1, near_store=True)}
 COUNTS = [1, 2, 3, 4, 5, 15, 16, 17, 18, 33]
 
