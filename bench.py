@@ -12,7 +12,7 @@ One step = the whole hot path, both precisions side by side:
          iterative refinement.
   GRADIENT: 1280-triangle ellipsoid (1, 0.8, 0.6), k_a = 3, eps_r = 3 + 0.1i:
          FP64 fill -> block-Jacobi setup -> GMRES to 1e-12 -> adjoint
-         (Z^T solve, dZ/deps_r fill, reverse pass over every point pair and
+         (Z^T solve, dZ/deps_r form, reverse pass over every point pair and
          the geometry) -> sigma_ext, d sigma/d eps_r, d sigma/d(normal
          displacement) of every node.
   MULTI-RHS: the same sphere at k_a = 3, eps_r = 6 with 128 plane waves
@@ -84,14 +84,13 @@ PEAK_HBM = 8000.0          # GB/s
 PEAK_FP32_MFMA = 157.3     # TFLOP/s, MI355X dense FP32 matrix cores
 
 # HBM bytes moved per launch (per fill for the regular-pair kernel: all its
-# colour-class launches), from rocprofv3 FETCH_SIZE and WRITE_SIZE counters
+# launches), from rocprofv3 FETCH_SIZE and WRITE_SIZE counters
 # scaled by a 1 GiB device copy (FETCH_SIZE x 2.0, WRITE_SIZE x 1.0).  A
 # kernel changed after its counters were taken gets None here.
 MEASURED_TRAFFIC = {
-    ("k_regular", "fp64"): 21.77e9,    # 13.83 GB read + 7.94 GB written per fill
+    ("k_pair_tiles", "fp64"): 15.27e9,  # 7.72 GB read + 7.55 GB written per fill
     ("k_regular_range", "mixed"): 3.52e9,   # 1.42 GB read + 2.10 GB written per fill
-    ("k_gemv3", "fp64"): 1.291e9,
-    ("k_gemv3", "mixed"): 0.683e9,
+    ("k_product", "fp64"): 1.313e9,
 }
 
 # Algorithmic flops of the regular-pair fill (FMA = 2 flops, every
@@ -114,7 +113,7 @@ FLOP_SSQ_POINT = 2 * 310 + 20 + 319 + 12 * 156
 
 
 def regular_fill_flops(S, tri, npairs):
-    """Algorithmic flops of one regular-pair fill (all colour-class launches)
+    """Algorithmic flops of one regular-pair fill (all its launches)
     of the solver's mesh: per element pair the point-pair work and the
     trial-side contraction, per (test triangle, trial chunk) workgroup the
     test-side contraction of its ns distinct chunk nodes."""
@@ -387,12 +386,12 @@ def spectrum_study(mbem, log):
                      # FP64: every regular pair in FP64; mixed: the FP32 kernel, which
                      # evaluates its near pairs in FP64 (on this electrically small,
                      # high-contrast body most pairs are near)
-                     "k_regular": ({"ms_per_point": t_reg, "tflops": flops / (t_reg * 1e-3) / 1e12,
+                     "regular": ({"ms_per_point": t_reg, "tflops": flops / (t_reg * 1e-3) / 1e12,
                                     "peak": peak, "frac": flops / (t_reg * 1e-3) / 1e12 / peak}
                                    if name == "fp64" else
                                    {"ms_per_point": t_reg,
                                     "near_pair_fraction": st.n_near_pairs / npts / max(1, st.n_regular_pairs)}),
-                     "k_gemv3": {"ms_per_launch": gemv_ms,
+                     "product": {"ms_per_launch": gemv_ms,
                                  "gbps": gemv_bytes / (gemv_ms * 1e-3) / 1e9,
                                  "frac": gemv_bytes / (gemv_ms * 1e-3) / 1e9 / PEAK_HBM},
                      "t_fill_ms": st.t_fill_ms, "t_setup_ms": st.t_setup_ms,
@@ -706,14 +705,14 @@ def main():
                 per_launch_ms = r["t_matvec_ms"] / max(1, r["n_matvec"])
                 achieved = traffic / (per_launch_ms * 1e-3) / 1e9
                 return {"bound": "hbm", "achieved": achieved, "peak": PEAK_HBM, "unit": "GB/s",
-                        "frac": achieved / PEAK_HBM, "traffic": MEASURED_TRAFFIC.get(("k_gemv3", kp)),
-                        "kernel": "k_gemv3", "path": kp,
+                        "frac": achieved / PEAK_HBM, "traffic": MEASURED_TRAFFIC.get(("k_product", kp)),
+                        "kernel": "k_product", "path": kp,
                         "algorithmic_bytes_per_launch": traffic, "launch_ms": per_launch_ms}
             if kname == "regular":
                 flops = regular_fill_flops(solvers[kp], tri, r["n_regular"])
                 achieved = flops / (r["t_regular_ms"] * 1e-3) / 1e12
                 peak = PEAK_FP64_VALU if kp == "fp64" else PEAK_FP32_VALU
-                kern = "k_regular" if kp == "fp64" else "k_regular_range"
+                kern = "k_pair_tiles" if kp == "fp64" else "k_regular_range"
                 return {"bound": "alu", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
                         "frac": achieved / peak, "traffic": MEASURED_TRAFFIC.get((kern, kp)),
                         "kernel": kern, "path": kp,
