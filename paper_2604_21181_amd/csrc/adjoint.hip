@@ -74,55 +74,70 @@ int ff_functional_run(const mbem_mesh *m, const mbem_params *p, const double *rh
 }
 
 // ---------------------------------------------------- Z^T product ---
-// Partial sums of K^T v over row chunks: one thread per column, reading
-// rows of the stored blocks (contiguous across the wavefront).
-//   slot 0: K1^T l1, slot 1: K1^T l2, slot 2: K2eps^T l1, slot 3: K2mu^T l2
-// Rows per chunk: 256 for the complex128 blocks (a quarter of the partial
-// sums to write and add; the adjoint solve to 1e-8 on the 1280-triangle
-// sphere 9.33 -> 8.42 ms), 64 for complex64, whose shorter loads need the
-// four times larger grid (256 rows: 6.41 -> 7.05 ms)
-template <typename TS> constexpr int rows_per_chunk() { return std::is_same<TS, double2>::value ? 256 : 64; }
-constexpr int kRowsPerChunkMin = 64;
+// Partial sums over row chunks: a thread per column (c64: two neighbours), which
+// streams the rows of all three blocks (16-byte loads, contiguous across the
+// wavefront; the rows' lambda uniform):
+//   slot 0: (i/w) K1^T l1 + K2mu^T l2, slot 1: K2eps^T l1 - (i/w) K1^T l2
+// Bound by the read of the blocks.  A step of the adjoint GMRES, us, with a
+// launch dimension per block, four slots and chunks of 256 rows (c64: 64) -> this:
+//   triangles    80           320          768          1280         2700
+//   FP64      81 -> 32    129 -> 46    199 -> 110    271 -> 248   1060 -> 1012
+//   mixed     51 -> 37     67 -> 50     93 -> 84     206 -> 153    693 -> 606
+__device__ inline double2 zm(double2 a, double2 b) { return {a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x}; }
+__device__ inline double2 za(double2 a, double2 b) { return {a.x + b.x, a.y + b.y}; }
+typedef double td2 __attribute__((ext_vector_type(2)));
+typedef float tf4 __attribute__((ext_vector_type(4)));
+__device__ inline void load_columns(const double2 *p, double2 v[1]) {
+    const td2 t = __builtin_nontemporal_load(reinterpret_cast<const td2 *>(p));
+    v[0] = {t.x, t.y};
+}
+__device__ inline void load_columns(const float2 *p, double2 v[2]) {
+    const tf4 t = __builtin_nontemporal_load(reinterpret_cast<const tf4 *>(p));
+    v[0] = {(double)t.x, (double)t.y};
+    v[1] = {(double)t.z, (double)t.w};
+}
+template <typename TS> constexpr int t_columns() { return std::is_same<TS, double2>::value ? 1 : 2; }
 template <typename TS>
 __global__ __launch_bounds__(256) void k_gemvt_part(int64_t n2, const TS *K1, const TS *K2e, const TS *K2m,
-                                                    const double2 *l1, const double2 *l2, double2 *part) {
-    const int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    const int64_t chunk = blockIdx.y;
-    const int which = blockIdx.z;
+                                                    const double2 *__restrict__ l1, const double2 *__restrict__ l2,
+                                                    double2 iw, int rows, double2 *__restrict__ part) {
+    constexpr int C = t_columns<TS>();
+    const int64_t j = C * (blockIdx.x * (int64_t)blockDim.x + threadIdx.x);   // n2 is even
     if (j >= n2) return;
-    constexpr int kRows = rows_per_chunk<TS>();
-    const int64_t r0 = chunk * kRows, r1 = min(n2, r0 + kRows);
-    const TS *K = which == 0 ? K1 : (which == 1 ? K2e : K2m);
-    double a0r = 0, a0i = 0, a1r = 0, a1i = 0;
+    const int64_t r0 = blockIdx.y * (int64_t)rows, r1 = min(n2, r0 + rows);
+    double2 aj[C], am[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) aj[c] = am[c] = double2{0.0, 0.0};
+#pragma unroll 4
     for (int64_t i = r0; i < r1; ++i) {
-        const TS kv = K[i * n2 + j];
-        const double kr = (double)kv.x, ki = (double)kv.y;
-        const double2 u = which == 2 ? l2[i] : l1[i];
-        a0r += kr * u.x - ki * u.y;
-        a0i += kr * u.y + ki * u.x;
-        if (which == 0) {
-            const double2 v = l2[i];
-            a1r += kr * v.x - ki * v.y;
-            a1i += kr * v.y + ki * v.x;
+        double2 k1[C], ke[C], km[C];
+        load_columns(K1 + i * n2 + j, k1);
+        load_columns(K2e + i * n2 + j, ke);
+        load_columns(K2m + i * n2 + j, km);
+        const double2 u = l1[i], v = l2[i], wu = zm(iw, u), wv = zm(iw, v);
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const double2 b = zm(k1[c], wv);
+            aj[c] = za(aj[c], za(zm(k1[c], wu), zm(km[c], v)));
+            am[c] = za(am[c], za(zm(ke[c], u), double2{-b.x, -b.y}));
         }
     }
-    const int64_t nch = gridDim.y;
-    double2 *o = part + chunk * 4 * n2;
-    (void)nch;
-    if (which == 0) { o[j] = {a0r, a0i}; o[n2 + j] = {a1r, a1i}; }
-    else o[(1 + which) * n2 + j] = {a0r, a0i};
+    double2 *o = part + blockIdx.y * 2 * n2 + j;
+#pragma unroll
+    for (int c = 0; c < C; ++c) { o[c] = aj[c]; o[n2 + c] = am[c]; }
 }
 
 struct TCoef { double2 iw, ce, cm; };
-__device__ inline double2 zm(double2 a, double2 b) { return {a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x}; }
 
 // y = Z^T lambda from the summed partials and the mass matrix (symmetric as
 // a matrix of unknowns, so M^T l = M l):
 //   y_j = (i/w) K1^T l1 + K2mu^T l2 + c_mu M l2
 //   y_m = K2eps^T l1 + c_eps M l1 - (i/w) K1^T l2
-// A workgroup takes 64 rows; its four wavefronts sum every fourth chunk of
-// partials and the four sums are added in a fixed order through LDS.
-constexpr int kCombRows = 64;
+// A workgroup takes 16 rows; its sixteen groups of 16 lanes split the rows' chunks
+// of partials, mass entries and near pairs (with a thread per row for the latter a
+// step with the store took 1195 us at 1280 triangles, 278 now), and their sums are
+// added in a fixed order through LDS.
+constexpr int kCombRows = 16, kCombGroups = 256 / kCombRows;
 __global__ __launch_bounds__(256) void k_combine_t(int64_t n2, int nch, const double2 *__restrict__ part,
                                                    const int32_t *__restrict__ mptr,
                                                    const int32_t *__restrict__ mcol,
@@ -130,66 +145,75 @@ __global__ __launch_bounds__(256) void k_combine_t(int64_t n2, int nch, const do
                                                    const double2 *__restrict__ l1,
                                                    const double2 *__restrict__ l2, TCoef c, NearView nv,
                                                    double2 *__restrict__ y) {
-    __shared__ double2 s_t[4][4][kCombRows];   // [group][slot][row]
+    __shared__ double2 s_t[kCombGroups][2][kCombRows];   // [group][slot][row]
     const int lr = threadIdx.x % kCombRows, grp = threadIdx.x / kCombRows;
     const int64_t r = blockIdx.x * (int64_t)kCombRows + lr;
-    double2 t[4] = {{0, 0}, {0, 0}, {0, 0}, {0, 0}};
-    if (r < n2)
-        for (int ch = grp; ch < nch; ch += 4)
-            for (int k = 0; k < 4; ++k) {
-                const double2 v = part[((int64_t)ch * 4 + k) * n2 + r];
-                t[k].x += v.x; t[k].y += v.y;
+    double2 p[2] = {{0, 0}, {0, 0}};
+    if (r < n2) {
+#pragma unroll 4
+        for (int ch = grp; ch < nch; ch += kCombGroups)
+            for (int k = 0; k < 2; ++k) p[k] = za(p[k], part[((int64_t)ch * 2 + k) * n2 + r]);
+        const int64_t i = r / 2;
+        const int al = (int)(r % 2);
+        if (nv.bits) {
+            // the near store, transposed: output row 2 i + al (column of Z)
+            // takes V(k, i)[4 op + 2 a + al] of every stored pair (k, i) times l
+            // at 2 k + a; the pattern is symmetric, so row i lists every k
+            for (int32_t s = nv.rptr[i] + grp; s < nv.rptr[i + 1]; s += kCombGroups) {
+                const int64_t k = nv.col[s];
+                const int64_t sk = near_slot(nv, k, i);
+                if (sk < 0) continue;
+                const double2 *V = nv.val + 12 * sk + al;
+                const double2 a0 = l1[2 * k], a1 = l1[2 * k + 1], b0 = l2[2 * k], b1 = l2[2 * k + 1];
+                const double2 q = zm(c.iw, za(zm(V[0], b0), zm(V[2], b1)));
+                p[0] = za(p[0], za(zm(c.iw, za(zm(V[0], a0), zm(V[2], a1))), za(zm(V[8], b0), zm(V[10], b1))));
+                p[1] = za(p[1], za(za(zm(V[4], a0), zm(V[6], a1)), double2{-q.x, -q.y}));
             }
-    for (int k = 0; k < 4; ++k) s_t[grp][k][lr] = t[k];
-    __syncthreads();
-    if (grp != 0 || r >= n2) return;
-    for (int k = 0; k < 4; ++k) {
-        t[k] = s_t[0][k][lr];
-        for (int g = 1; g < 4; ++g) { t[k].x += s_t[g][k][lr].x; t[k].y += s_t[g][k][lr].y; }
-    }
-    const int64_t i = r / 2;
-    const int al = (int)(r % 2);
-    if (nv.bits) {
-        // the near store, transposed: output row 2 i + al (column of Z)
-        // takes V(k, i)[4 op + 2 a + al] of every stored pair (k, i) times l
-        // at 2 k + a; the pattern is symmetric, so row i lists every k
-        for (int32_t s = nv.rptr[i]; s < nv.rptr[i + 1]; ++s) {
-            const int64_t k = nv.col[s];
-            const int64_t sk = near_slot(nv, k, i);
-            if (sk < 0) continue;
-            const double2 *V = nv.val + 12 * sk + al;
-            const double2 a0 = l1[2 * k], a1 = l1[2 * k + 1], b0 = l2[2 * k], b1 = l2[2 * k + 1];
-            const double2 p0 = zm(V[0], a0), p1 = zm(V[2], a1), q0 = zm(V[0], b0), q1 = zm(V[2], b1);
-            const double2 e0 = zm(V[4], a0), e1 = zm(V[6], a1), m0 = zm(V[8], b0), m1 = zm(V[10], b1);
-            t[0].x += p0.x + p1.x; t[0].y += p0.y + p1.y;
-            t[1].x += q0.x + q1.x; t[1].y += q0.y + q1.y;
-            t[2].x += e0.x + e1.x; t[2].y += e0.y + e1.y;
-            t[3].x += m0.x + m1.x; t[3].y += m0.y + m1.y;
         }
+        double2 M1 = {0, 0}, M2 = {0, 0};
+        for (int32_t s = mptr[i] + grp; s < mptr[i + 1]; s += kCombGroups) {
+            const int64_t col = 2 * (int64_t)mcol[s];
+            const double v0 = mval[4 * s + 2 * al], v1 = mval[4 * s + 2 * al + 1];
+            M1.x += v0 * l1[col].x + v1 * l1[col + 1].x; M1.y += v0 * l1[col].y + v1 * l1[col + 1].y;
+            M2.x += v0 * l2[col].x + v1 * l2[col + 1].x; M2.y += v0 * l2[col].y + v1 * l2[col + 1].y;
+        }
+        p[0] = za(p[0], zm(c.cm, M2));
+        p[1] = za(p[1], zm(c.ce, M1));
     }
-    double2 M1 = {0, 0}, M2 = {0, 0};
-    for (int32_t s = mptr[i]; s < mptr[i + 1]; ++s) {
-        const int64_t col = 2 * (int64_t)mcol[s];
-        const double v0 = mval[4 * s + 2 * al], v1 = mval[4 * s + 2 * al + 1];
-        M1.x += v0 * l1[col].x + v1 * l1[col + 1].x; M1.y += v0 * l1[col].y + v1 * l1[col + 1].y;
-        M2.x += v0 * l2[col].x + v1 * l2[col + 1].x; M2.y += v0 * l2[col].y + v1 * l2[col + 1].y;
-    }
-    const double2 a = zm(c.iw, t[0]), b = zm(c.iw, t[1]), cm = zm(c.cm, M2), ce = zm(c.ce, M1);
-    y[r] = {a.x + t[3].x + cm.x, a.y + t[3].y + cm.y};
-    y[n2 + r] = {t[2].x + ce.x - b.x, t[2].y + ce.y - b.y};
+    for (int k = 0; k < 2; ++k) s_t[grp][k][lr] = p[k];
+    __syncthreads();
+    if (grp >= 2 || r >= n2) return;
+    double2 o = {0, 0};
+#pragma unroll
+    for (int g = 0; g < kCombGroups; ++g) o = za(o, s_t[g][grp][lr]);
+    y[grp * n2 + r] = o;
+}
+
+// Rows of a chunk: a power of two of at least 8 that leaves 800 (c128) or 1200
+// workgroups (c64, whose threads take two columns) where the operator is large
+// enough, up to 128 or 64: the partial sums speak for long chunks, small operators
+// for short ones (n2 = 1284, FP64: 8 rows 53 us a step, 64 72; 5124: 128 rows 253,
+// 32 273; c64 3076: 16 rows 91, 8 103; 10 804: 64 rows 605, 128 659).
+static int t_rows(const mbem_op *op) {
+    const bool fp64 = op->prec == MBEM_FP64;
+    const int64_t columns = (op->n2 / (fp64 ? 1 : 2) + 255) / 256, want = op->n2 * columns / (fp64 ? 800 : 1200);
+    int rows = 8;
+    while (rows < (fp64 ? 128 : 64) && 2 * rows <= want) rows *= 2;
+    return rows;
 }
 
 int matvec_t_run(const mbem_op *op, const double2 *x, double2 *y, double2 *part, hipStream_t s) {
     const int64_t n2 = op->n2;
-    const int rows = op->prec == MBEM_FP64 ? rows_per_chunk<double2>() : rows_per_chunk<float2>();
-    const int nch = (int)((n2 + rows - 1) / rows);
-    const dim3 grid((unsigned)((n2 + 255) / 256), (unsigned)nch, 3);
+    const int rows = t_rows(op), nch = (int)((n2 + rows - 1) / rows);
+    auto grid = [&](int64_t c) { return dim3((unsigned)((n2 / c + 255) / 256), (unsigned)nch); };
     if (op->prec == MBEM_FP64)
-        hipLaunchKernelGGL((k_gemvt_part<double2>), grid, dim3(256), 0, s, n2, (const double2 *)op->K[0],
-                           (const double2 *)op->K[1], (const double2 *)op->K[2], x, x + n2, part);
+        hipLaunchKernelGGL((k_gemvt_part<double2>), grid(t_columns<double2>()), dim3(256), 0, s, n2,
+                           (const double2 *)op->K[0], (const double2 *)op->K[1], (const double2 *)op->K[2], x, x + n2,
+                           op->iw, rows, part);
     else
-        hipLaunchKernelGGL((k_gemvt_part<float2>), grid, dim3(256), 0, s, n2, (const float2 *)op->K[0],
-                           (const float2 *)op->K[1], (const float2 *)op->K[2], x, x + n2, part);
+        hipLaunchKernelGGL((k_gemvt_part<float2>), grid(t_columns<float2>()), dim3(256), 0, s, n2,
+                           (const float2 *)op->K[0], (const float2 *)op->K[1], (const float2 *)op->K[2], x, x + n2,
+                           op->iw, rows, part);
     MBEM_HIP(hipGetLastError());
     const mbem_mesh *m = op->mesh;
     hipLaunchKernelGGL(k_combine_t, dim3((unsigned)((n2 + kCombRows - 1) / kCombRows)), dim3(256), 0, s, n2, nch,
@@ -200,8 +224,8 @@ int matvec_t_run(const mbem_op *op, const double2 *x, double2 *y, double2 *part,
 }
 
 int64_t matvec_t_work(const mbem_op *op) {
-    const int64_t nch = (op->n2 + kRowsPerChunkMin - 1) / kRowsPerChunkMin;   // enough for either
-    return nch * 4 * op->n2;
+    const int rows = t_rows(op);
+    return (op->n2 + rows - 1) / rows * 2 * op->n2;
 }
 
 // ------------------------------------- transposed preconditioner ---
