@@ -62,6 +62,28 @@ def test_group_as_one_by_one(mesh, form, n):
         S.close()
 
 
+@pytest.mark.parametrize("block", [1, 7, 33, 512])
+@pytest.mark.parametrize("form", ["fp64", "mixed"])
+def test_block_sizes(form, block):
+    """Odd blocks, a short last block, one block: the fused preconditioner step
+    for one, two and three systems against the dense system."""
+    xyz, tri = MESHES["uv70"]()
+    S = mbem.Solver(xyz, tri, 1.4, 3.0 + 0.2j, **FORMS[form])
+    try:
+        S.fill()
+        S.precond_setup(block)
+        Z = S.export_dense()
+        B = _columns(S, 4)[:3]
+        for n in (1, 2, 3):
+            X, _, code = S.solve(B[:n], 1e-10)
+            assert code == 0
+            R = X @ Z.T.contiguous() - B[:n]
+            # the solve's own criterion, and sums of 568 terms
+            assert bool((R.norm(dim=1) <= 1.1e-10 * B[:n].norm(dim=1)).all())
+    finally:
+        S.close()
+
+
 @pytest.mark.parametrize("form", ["fp64", "mixed"])
 def test_without_preconditioner_and_at_the_limit(form):
     xyz, tri = MESHES["uv70"]()
