@@ -186,6 +186,7 @@ struct SsqArgs {
     const KernelConst *K;   // device: series of the kernels, paper's scheme: [1] of the remainders
     PairConst kc;
     const int32_t *row_map; // null, or node -> row node of a band buffer
+    int regions;            // regions of one workgroup
     TS *Z[3];
     NearView near;          // MIXED with the near store: added there in FP64
 };
@@ -210,7 +211,11 @@ struct SsqShape {
 
 // Regions of one workgroup: a coincident pair has 12 batches of points at
 // order 4 and a common-vertex pair 4; two regions per workgroup level them.
-constexpr int kSsqParts = 3;
+// Into complex64 a pair stays with one workgroup: every part's block would be
+// rounded to 32 bits by an addition of its own (mixed solve of a 300-triangle
+// body: x off by 8.8e-8 from the 64-bit solution in parts, 8.5e-8 whole), at no
+// cost on 1280 triangles (fill and product 5.23 ms in parts, 5.22 whole).
+constexpr int kSsqMaxRegions = 6, kSsqSplitRegions = 2;
 
 template <typename TS, bool DK, bool NODAL, bool PAPER>
 __global__ __launch_bounds__(SsqShape<NODAL>::threads) __attribute__((amdgpu_waves_per_eu(2, 8)))
@@ -227,7 +232,7 @@ void k_ssq(SsqArgs<TS> a) {
     const int32_t e = a.pairs[4 * pid], f = a.pairs[4 * pid + 1];
     const int cls = a.pairs[4 * pid + 2], code = a.pairs[4 * pid + 3];
     const int nreg = cls == 3 ? 6 : cls == 2 ? 5 : 2;
-    if (2 * part >= nreg) return;
+    if (a.regions * part >= nreg) return;
     const int32_t *const te = a.tri + 6 * (int64_t)e, *const tf = a.tri + 6 * (int64_t)f;
     if constexpr (NODAL) {
         if (tid < 72) {
@@ -400,7 +405,7 @@ void k_ssq(SsqArgs<TS> a) {
     };
     const int64_t n4 = (int64_t)a.order * a.order * a.order * a.order;
     const int64_t r0 = table_region(cls);
-    points((r0 + 2 * part) * n4, (r0 + min(2 * part + 2, nreg)) * n4, a.order, code, false);
+    points((r0 + a.regions * part) * n4, (r0 + min(a.regions * (part + 1), nreg)) * n4, a.order, code, false);
     if constexpr (PAPER)
         if (part == 0)
             points(kTableRegions * n4, kTableRegions * n4 + kQP12 * kQP12, kRuleGroup, kRuleCode | (kRuleCode << 6),
@@ -441,8 +446,11 @@ void k_ssq(SsqArgs<TS> a) {
 template <typename TS>
 static int launch(const mbem_op *op, bool deriv, SsqArgs<TS> &a, hipStream_t s) {
     const bool paper = op->p.quadrature == MBEM_QUAD_PAPER, nodal = op->p.frame == MBEM_FRAME_NODAL;
-    if (kSsqParts * a.npairs > 0x7fffffffLL) { set_error("too many singular pairs for one launch"); return MBEM_EINVAL; }
-    const dim3 grid((unsigned)(kSsqParts * a.npairs)), blk(nodal ? SsqShape<true>::threads : SsqShape<false>::threads);
+    // FP64 destinations: the blocks of Z, or the near store's values
+    a.regions = std::is_same<TS, double>::value || a.near.bits ? kSsqSplitRegions : kSsqMaxRegions;
+    const int64_t parts = kSsqMaxRegions / a.regions;
+    if (parts * a.npairs > 0x7fffffffLL) { set_error("too many singular pairs for one launch"); return MBEM_EINVAL; }
+    const dim3 grid((unsigned)(parts * a.npairs)), blk(nodal ? SsqShape<true>::threads : SsqShape<false>::threads);
     if (paper) {
         if (nodal) hipLaunchKernelGGL((k_ssq<TS, false, true, true>), grid, blk, 0, s, a);
         else hipLaunchKernelGGL((k_ssq<TS, false, false, true>), grid, blk, 0, s, a);
