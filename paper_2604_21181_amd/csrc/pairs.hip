@@ -305,7 +305,8 @@ __global__ __launch_bounds__(256, NODAL ? 2 : 3) void k_pair_tiles(PairArgs a) {
                     auto tv = [&](int f) { return dvec3{tp[f * NP], tp[(f + 1) * NP], tp[(f + 2) * NP]}; };
                     const dvec3 Rv = tv(QX) - y;
                     const double d2 = dot(Rv, Rv);
-                    const double rinv = rsqrt64(d2), R = d2 * rinv;
+                    const Root64 root = root64(d2);
+                    const double rinv = root.inv, R = root.r;
                     const double w = tp[QW * NP] * wy;
                     KScal<double> sc;
                     double ww = w;

@@ -114,31 +114,19 @@ __device__ __forceinline__ KScalD kernel_scalars_dr(const ShapeConst &C, const K
         o.Gm = r2 * S;
         o.Gmp = r2 * Sp - (2.0 * rinv) * o.Gm;
     } else {
-        const double r3 = 0.079577471545947667884 * rinv * (rinv * rinv);
-        double sn, cs;
-        const double ta = K.ka * R, ta2 = ta * ta;
-        sincos_t(ta, &sn, &cs);
-        const cxd ea = {r3 * cs, r3 * sn};
-        const cxd ga = {fma(ea.im, ta, ea.re), fma(-ea.re, ta, ea.im)}, ha = ta2 * ea;
-        const double tr = K.ki_re * R, ti = K.ki_im * R;
-        sincos_t(tr, &sn, &cs);
-        const double am = K.ki_im == 0.0 ? r3 : r3 * exp(-ti);
-        const cxd ei = {am * cs, am * sn};
-        const double u = 1.0 + ti;
-        const cxd gi = {fma(ei.im, tr, ei.re * u), fma(-ei.re, tr, ei.im * u)};
-        const cxd t2 = {fma(tr, tr, -(ti * ti)), 2.0 * tr * ti};
-        const cxd hi = t2 * ei, q = ta2 * ga - t2 * gi;
-        const cxd D0 = ha - hi, dg = ga - gi;
-        df = 3.0 * dg - D0;
-        dfp = rinv * (q - 3.0 * df);
-        A = D0 - dg;
-        Ap = rinv * (df - q);
+        const double r1 = 0.079577471545947667884 * rinv, r2 = r1 * rinv, r3 = r2 * rinv, r4 = r3 * rinv;
+        const Media64 m = media64(K, R);
         const cxd ep = {K.eps_re, K.eps_im}, mu = {K.mu_re, K.mu_im};
-        const cxd Eg = ga - ep * gi, Mg = ga - mu * gi;
-        o.Ge = (-R) * Eg;
-        o.Gep = 2.0 * Eg - (ha - ep * hi);
-        o.Gm = (-R) * Mg;
-        o.Gmp = 2.0 * Mg - (ha - mu * hi);
+        const cxd f = m.fa - m.fi, q = m.ta2 * m.ga - m.ti2 * m.gi;
+        df = r3 * f;
+        dfp = r4 * (q - 3.0 * f);
+        A = r1 * m.d - r3 * (m.ga - m.gi);
+        Ap = r4 * (f - q);
+        const cxd Eg = m.ga - ep * m.gi, Mg = m.ga - mu * m.gi;
+        o.Ge = (-r2) * Eg;
+        o.Gep = r3 * (2.0 * Eg - (m.ha - ep * m.hi));
+        o.Gm = (-r2) * Mg;
+        o.Gmp = r3 * (2.0 * Mg - (m.ha - mu * m.hi));
     }
     o.a = C.iw * A;
     o.ap = C.iw * Ap;
@@ -413,8 +401,9 @@ __global__ __launch_bounds__(64, 2) void k_shape_regular(int64_t nq, int tiles, 
         if (on) {
             const dvec3 Rv = x - tab_pos(s_t[0][k], s_t[1][k]);
             const cv3 vj = tab_vec(s_t[2][k], s_t[3][k], s_t[4][k]), vm = tab_vec(s_t[5][k], s_t[6][k], s_t[7][k]);
-            const double d2 = dot(Rv, Rv), rinv = rsqrt64(d2);
-            const KScalD sc = kernel_scalars_dr(C, s_K, d2 * rinv, rinv);
+            const Root64 root = root64(dot(Rv, Rv));
+            const double rinv = root.inv;
+            const KScalD sc = kernel_scalars_dr(C, s_K, root.r, rinv);
             cv3 Hj = tab_vec(s_a[0][k], s_a[1][k], s_a[2][k]), Hm = tab_vec(s_a[3][k], s_a[4][k], s_a[5][k]);
             const dvec3 g = pair_terms(sc, rinv * Rv, rinv, u1, u2, vj, vm, S1, S2, Hj, Hm);
             gx = gx + g;
@@ -742,9 +731,9 @@ __device__ __forceinline__ SsqGeom ssq_geom(const double *co, double xi, double 
     g.a1 = {d1[0], d1[1], d1[2]};
     g.a2 = {d2[0], d2[1], d2[2]};
     const dvec3 c = cross(g.a1, g.a2);
-    const double c2 = dot(c, c);
-    g.Ji = rsqrt64(c2);
-    g.J = c2 * g.Ji;
+    const Root64 root = root64(dot(c, c));
+    g.Ji = root.inv;
+    g.J = root.r;
     g.n = g.Ji * c;
     return g;
 }
@@ -775,11 +764,11 @@ __device__ __forceinline__ SsqFrame ssq_frame(const double *co, double xi, doubl
     f.u1 = ssq_vec<F>(co, 3, xi, eta);
     f.u2 = ssq_vec<F>(co, 6, xi, eta);
     const dvec3 w1 = f.u1 - dot(n, f.u1) * n;
-    f.l1i = rsqrt64(dot(w1, w1));
+    f.l1i = root64(dot(w1, w1)).inv;
     f.t1 = f.l1i * w1;
     f.w2 = f.u2 - dot(n, f.u2) * n;
     const dvec3 w3 = f.w2 - dot(f.t1, f.w2) * f.t1;
-    f.l3i = rsqrt64(dot(w3, w3));
+    f.l3i = root64(dot(w3, w3)).inv;
     f.t2 = f.l3i * w3;
     return f;
 }
@@ -947,8 +936,9 @@ __global__ __launch_bounds__(64, 2) void k_shape_ssq(ShapeSsqArgs a) {
         {
             const SsqGeom X = ssq_geom<F>(s_co[0], xe, ye), Y = ssq_geom<F>(s_co[1], xf, yf);
             const dvec3 Rv = X.x - Y.x;
-            const double d2 = dot(Rv, Rv), rinv = rsqrt64(d2), c = -wg * X.J * Y.J;
-            const KScalD sc = kernel_scalars_dr(a.C, s_K, d2 * rinv, rinv);
+            const Root64 root = root64(dot(Rv, Rv));
+            const double rinv = root.inv, c = -wg * X.J * Y.J;
+            const KScalD sc = kernel_scalars_dr(a.C, s_K, root.r, rinv);
             cv3 u1, u2, vj, vm;
             reload_lds();
             ssq_vectors<NODAL, F>(s_co[0], xe, ye, X.n, u1, u2);
@@ -1069,8 +1059,8 @@ __global__ __launch_bounds__(64, 4) void k_deps_regular(int64_t nq, const double
         if (on) {
             const dvec3 Rv = x - tab_pos(s_t[0][k], s_t[1][k]);
             const cv3 vj = tab_vec(s_t[2][k], s_t[3][k], s_t[4][k]), vm = tab_vec(s_t[5][k], s_t[6][k], s_t[7][k]);
-            const double d2 = dot(Rv, Rv), rinv = rsqrt64(d2);
-            sum = sum + pair_form(kernel_scalars_deps(s_K, d2 * rinv, rinv), C.iw, rinv * Rv, u1, u2, vj, vm);
+            const Root64 root = root64(dot(Rv, Rv));
+            sum = sum + pair_form(kernel_scalars_deps(s_K, root.r, root.inv), C.iw, root.inv * Rv, u1, u2, vj, vm);
         }
     }
     if (blockIdx.x == 0 && i < nq) {
@@ -1110,8 +1100,9 @@ __global__ __launch_bounds__(64, 3) void k_deps_ssq(ShapeSsqArgs a, double2 *__r
         ss_local(code >> 6, q[2 * a.np], q[3 * a.np], xf, yf);
         const SsqGeom X = ssq_geom<F>(s_co[0], xe, ye), Y = ssq_geom<F>(s_co[1], xf, yf);
         const dvec3 Rv = X.x - Y.x;
-        const double d2 = dot(Rv, Rv), rinv = rsqrt64(d2), w = fabs(q[4 * a.np]) * X.J * Y.J;
-        const KScal<double> sc = kernel_scalars_deps(s_K, d2 * rinv, rinv);
+        const Root64 root = root64(dot(Rv, Rv));
+        const double rinv = root.inv, w = fabs(q[4 * a.np]) * X.J * Y.J;
+        const KScal<double> sc = kernel_scalars_deps(s_K, root.r, rinv);
         cv3 u1, u2, vj, vm;
         reload_lds();
         ssq_vectors<NODAL, F>(s_co[0], xe, ye, X.n, u1, u2);

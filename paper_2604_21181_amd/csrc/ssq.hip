@@ -101,9 +101,9 @@ __device__ __forceinline__ void ssq_position(const double *co, double xi, double
         d2[d] = fma(c4, xi, fma(c5, eta, s));
     }
     const dvec3 c = cross(dvec3{d1[0], d1[1], d1[2]}, dvec3{d2[0], d2[1], d2[2]});
-    const double c2 = dot(c, c), ci = rsqrt64(c2);
-    J = c2 * ci;
-    n = ci * c;
+    const Root64 root = root64(dot(c, c));
+    J = root.r;
+    n = root.inv * c;
     x = {v[0], v[1], v[2]};
 }
 __device__ __forceinline__ void ssq_frame(const double *co, double xi, double eta, dvec3 n, dvec3 t[2]) {
@@ -116,9 +116,9 @@ __device__ __forceinline__ void ssq_frame(const double *co, double xi, double et
     dvec3 u1 = {v[0], v[1], v[2]}, u2 = {v[3], v[4], v[5]};
     u1 = u1 - dot(n, u1) * n;
     u2 = u2 - dot(n, u2) * n;
-    t[0] = rsqrt64(dot(u1, u1)) * u1;
+    t[0] = root64(dot(u1, u1)).inv * u1;
     u2 = u2 - dot(t[0], u2) * t[0];
-    t[1] = rsqrt64(dot(u2, u2)) * u2;
+    t[1] = root64(dot(u2, u2)).inv * u2;
 }
 __device__ __forceinline__ void p2_values(double xi, double eta, double N[6]) {
     const double l = 1.0 - xi - eta;
@@ -282,7 +282,8 @@ void k_ssq(SsqArgs<TS> a) {
                 const dvec3 Rv = x - y;
                 const double d2 = dot(Rv, Rv);
                 // R = 0 (remainders on a coincident pair): no direction
-                const double rinv = PAPER && d2 == 0.0 ? 0.0 : rsqrt64(d2), R = d2 * rinv;
+                const Root64 root = PAPER && d2 == 0.0 ? Root64{0.0, 0.0} : root64(d2);
+                const double rinv = root.inv, R = root.r;
                 const double w = fabs(w0) * Jx * Jy;
                 const dvec3 Rh = rinv * Rv;
                 KScal<double> sc;
