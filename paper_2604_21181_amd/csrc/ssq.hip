@@ -23,8 +23,11 @@
 // before -> now: 1.51 -> 1.12 ms; node-attached tangents 3.25 -> 2.60;
 // paper's scheme 1.65 -> 1.08, node-attached 3.75 -> 2.70; 80 triangles
 // 177 -> 114 us (136 us with a workgroup per pair instead of per two regions).
-// Blocks of a 20- and a 56-triangle body against an 80-bit evaluation: 3.5e-16
-// to 1.6e-15 before, 3.6e-16 to 7.9e-16 now.
+// Blocks of a 70-, an 80- and a 320-triangle body, four media, both rules and
+// bases, against an 80-bit evaluation, with one P2 sum per node -> now: K1 5.0e-16
+// to 1.6e-15 -> 4.9e-16 to 1.8e-15 (12-point rule at large |k|: up to 8 % more, else
+// equal or less), K2^eps 5.9e-16 to 1.9e-14 -> 4.0e-16 to 3.2e-15, K2^mu 2.9 to
+// 5.9e-16 -> 2.8 to 5.1e-16.
 #include <algorithm>
 #include <cmath>
 #include <type_traits>
@@ -43,7 +46,6 @@ namespace {
 __device__ inline void atomic_add(double *p, double v) { unsafeAtomicAdd(p, v); }
 __device__ inline void atomic_add(float *p, double v) { unsafeAtomicAdd(p, (float)v); }
 
-constexpr int kRuleCode = 0 | (1 << 2) | (2 << 4);    // identity vertex order
 constexpr int kRuleGroup = 4;                         // remainder points per group (12 share x)
 constexpr int kPaperTerms = 6;                        // highest Taylor term of the remainders
 
@@ -54,7 +56,8 @@ struct GaussRule {
 
 // Point table, fields s1, t1, s2, t2, weight (Jacobian included); a negative
 // weight marks the points whose y does not depend on the innermost variable
-// (else x does not).
+// (else x does not).  The remainder points hold xi, eta of both triangles: as
+// s, t they would come back rounded, the same way on every pair.
 __global__ void k_ssq_table(int n, int64_t np, GaussRule gl, double *__restrict__ tab) {
     const int64_t id = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (id >= np) return;
@@ -71,12 +74,12 @@ __global__ void k_ssq_table(int n, int64_t np, GaussRule gl, double *__restrict_
         const int xfix = cls == 3 ? 0x29 : cls == 2 ? 0x6 : 0x1;     // regions 0 3 5 / 1 2 / 0
         v[4] = jac * gl.w[i0] * gl.w[i1] * gl.w[i2] * gl.w[i3] * ((xfix >> r) & 1 ? 1.0 : -1.0);
     } else {
-        // the 12-point rule on both triangles: s = xi + eta, t = eta
+        // the 12-point rule on both triangles
         const int rr = (int)(id - (int64_t)kTableRegions * n4), p = rr / kQP12, q = rr % kQP12;
         double xe, ye, we, xf, yf, wf;
         rule12(p, xe, ye, we);
         rule12(q, xf, yf, wf);
-        v[0] = xe + ye; v[1] = ye; v[2] = xf + yf; v[3] = yf;
+        v[0] = xe; v[1] = ye; v[2] = xf; v[3] = yf;
         v[4] = we * wf;
     }
 #pragma unroll
@@ -263,7 +266,7 @@ void k_ssq(SsqArgs<TS> a) {
     for (int k = 0; k < 36; ++k) acc[k] = 0.0;
 
     // the points [p0, p1) of the table in groups of m
-    auto points = [&](int64_t p0, int64_t p1, int m, int codes, bool rem) {
+    auto points = [&](int64_t p0, int64_t p1, int m, bool rem) {
         const int per = min(kSsqPoints / m, Sh::groups) * m;      // points per batch: whole groups
         for (int64_t base = p0; base < p1; base += per) {
             const int cnt = (int)min((int64_t)per, p1 - base);
@@ -273,8 +276,12 @@ void k_ssq(SsqArgs<TS> a) {
                 const double w0 = q[4 * a.np];
                 const bool xfix = w0 > 0.0;
                 double xe, ye, xf, yf;
-                ss_local(codes & 63, q[0], q[a.np], xe, ye);
-                ss_local(codes >> 6, q[2 * a.np], q[3 * a.np], xf, yf);
+                if (PAPER && rem) {
+                    xe = q[0], ye = q[a.np], xf = q[2 * a.np], yf = q[3 * a.np];
+                } else {
+                    ss_local(code & 63, q[0], q[a.np], xe, ye);
+                    ss_local(code >> 6, q[2 * a.np], q[3 * a.np], xf, yf);
+                }
                 dvec3 x, nx, y, ny;
                 double Jx, Jy;
                 ssq_position(s_co[0], xe, ye, x, nx, Jx);
@@ -406,11 +413,10 @@ void k_ssq(SsqArgs<TS> a) {
     };
     const int64_t n4 = (int64_t)a.order * a.order * a.order * a.order;
     const int64_t r0 = table_region(cls);
-    points((r0 + a.regions * part) * n4, (r0 + min(a.regions * (part + 1), nreg)) * n4, a.order, code, false);
+    points((r0 + a.regions * part) * n4, (r0 + min(a.regions * (part + 1), nreg)) * n4, a.order, false);
     if constexpr (PAPER)
         if (part == 0)
-            points(kTableRegions * n4, kTableRegions * n4 + kQP12 * kQP12, kRuleGroup, kRuleCode | (kRuleCode << 6),
-                   true);
+            points(kTableRegions * n4, kTableRegions * n4 + kQP12 * kQP12, kRuleGroup, true);
 
     // the streams in a fixed order, then the workgroup's 6 x 6 x 12 block
     // (atomics: a node pair collects several element pairs and parts)

@@ -19,6 +19,7 @@ static inline double host_rsq(double x) {
 }
 #define __builtin_amdgcn_rsq host_rsq
 #include "../paper_2604_21181_amd/csrc/kappa64.h"
+#include "../paper_2604_21181_amd/csrc/ssq_map.h"
 
 using namespace mbem;
 
@@ -76,8 +77,39 @@ static void scalars(double k0, double er, double ei) {
     for (int c = 0; c < 5; ++c) print(names[c], got[c], yard[c], norm[c]);
 }
 
+// a P2 field of nearby nodal values (a tangent's component): the polynomial of
+// p2_coef against the sum over the nodes
+static void polynomial() {
+    std::mt19937_64 rng(3);
+    std::uniform_real_distribution<double> u(0.0, 1.0);
+    double got = 0, yard = 0, norm = 0;
+    const int n = 20000;
+    for (int i = 0; i < n; ++i) {
+        double f[6], c[6];
+        const double base = 2.0 * u(rng) - 1.0;
+        for (double &v : f) v = base + 0.2 * (u(rng) - 0.5);
+        for (int k = 0; k < 6; ++k) c[k] = p2_coef(k, f);
+        const double xi = u(rng), eta = (1.0 - xi) * u(rng);
+        const double t = std::fma(c[3], xi, std::fma(c[4], eta, c[1])), s = std::fma(c[5], eta, c[2]);
+        const double p = std::fma(xi, t, std::fma(eta, s, c[0]));
+        auto nodes = [&](auto one) {
+            using T = decltype(one);
+            const T a = xi, b = eta, l = one - a - b;
+            const T N[6] = {l * (2 * l - one), a * (2 * a - one), b * (2 * b - one), 4 * l * a, 4 * a * b, 4 * b * l};
+            T v = 0;
+            for (int k = 0; k < 6; ++k) v += N[k] * (T)f[k];
+            return v;
+        };
+        const long double ref = nodes(1.0L);
+        got += (double)((p - ref) * (p - ref));
+        yard += (double)((nodes(1.0) - ref) * (nodes(1.0) - ref));
+        norm += (double)(ref * ref);
+    }
+    print("p2", got, yard, norm);
+}
+
 int main(int argc, char **argv) {
-    if (argc != 4) return 2;
-    scalars(std::atof(argv[1]), std::atof(argv[2]), std::atof(argv[3]));
+    if (argc == 4) scalars(std::atof(argv[1]), std::atof(argv[2]), std::atof(argv[3]));
+    else polynomial();
     return 0;
 }

@@ -1,10 +1,11 @@
-"""The FP64 pair kernels' point arithmetic (kappa64.h), compiled for the host,
-against long double: closed-form kernel differences from a root and an inverse
-root without divisions.
+"""The FP64 pair kernels' point arithmetic (kappa64.h, ssq_map.h), compiled for
+the host, against long double: closed-form kernel differences from a root and
+an inverse root without divisions, and the P2 polynomials of the singular pairs.
 
 The yardstick is the same quantity by its definition in double.  Both round a
 few dozen times; 10 % is more than 200 000 points (0.2 %) and the order of the
-operations account for."""
+operations account for.  The polynomials have fewer operations than the sum
+over six nodes and smaller terms, so they are held to the sum's own error."""
 import os
 import subprocess
 
@@ -31,3 +32,8 @@ def driver(tmp_path_factory):
 def test_closed_forms_are_as_accurate_as_their_definitions(driver, k0, eps):
     for name, (got, yard) in driver(k0, eps.real, complex(eps).imag).items():
         assert got <= 1.1 * yard, (name, got, yard)
+
+
+def test_polynomials_are_as_accurate_as_nodal_sums(driver):
+    got, yard = driver()["p2"]
+    assert got <= yard
