@@ -912,7 +912,7 @@ static int block_residual(const mbem_op *op, BlockWork &w, const double2 *X, con
     return MBEM_OK;
 }
 
-int block_solve_run(mbem_op *op, const double2 *B, int ncol, const mbem_block_opts *o, double2 *X,
+int block_solve_run(mbem_ctx *ctx, mbem_op *op, const double2 *B, int ncol, const mbem_block_opts *o, double2 *X,
                     mbem_block_stats *st, hipStream_t s) {
     // the block product runs on complex64 entries: a near store is folded
     // into them first
@@ -966,7 +966,6 @@ int block_solve_run(mbem_op *op, const double2 *B, int ncol, const mbem_block_op
     CgemmList L32;
     MBEM_TRY(block_matvec32_list(op, w.Zt, ncol, w.T32, &L32));
     if (cfg < 0 || cfg >= kGemmConfigs) {
-        mbem_ctx *ctx = op->ctx;
         if (ctx->tuned_n2 == n2 && ctx->tuned_ncol == ncol) cfg = ctx->tuned_cfg;
         else {
             MBEM_TRY(cgemm_f32_autotune(L32, s, 2, nullptr, &cfg));

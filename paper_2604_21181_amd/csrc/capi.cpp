@@ -569,7 +569,7 @@ int mbem_mesh_create(mbem_ctx *ctx, const double *xyz, int64_t n_nodes, const in
     MBEM_TRY(set_device(ctx));
     mbem_mesh *m = new (std::nothrow) mbem_mesh;
     if (!m) { set_error("host allocation"); return MBEM_ENOMEM; }
-    m->ctx = ctx;
+    m->device = ctx->device;
     int st = build_mesh_host(xyz, n_nodes, tri6, n_tris, m);
     MeshTables T;
     if (st == MBEM_OK) st = build_tables(m, T);
@@ -622,7 +622,8 @@ int mbem_mesh_create(mbem_ctx *ctx, const double *xyz, int64_t n_nodes, const in
 void mbem_mesh_destroy(mbem_mesh *m) {
     if (!m) return;
     // any context may have used the mesh: its memory is handed out again
-    if (m->ctx) { (void)hipSetDevice(m->ctx->device); (void)hipDeviceSynchronize(); }
+    (void)hipSetDevice(m->device);
+    (void)hipDeviceSynchronize();
     mesh_free_device(m);
     delete m;
 }
@@ -694,7 +695,7 @@ static int op_create(mbem_ctx *ctx, const mbem_mesh *mesh, const mbem_params *p,
     MBEM_TRY(set_device(ctx));
     mbem_op *op = new (std::nothrow) mbem_op;
     if (!op) { set_error("host allocation"); return MBEM_ENOMEM; }
-    op->ctx = ctx;
+    op->device = ctx->device;
     op->mesh = mesh;
     op->prec = p->precision;
     op->n2 = 2 * mesh->nn;
@@ -778,7 +779,8 @@ int mbem_fill_compressed(mbem_ctx *ctx, const mbem_mesh *mesh, const mbem_params
 void mbem_op_destroy(mbem_op *op) {
     if (!op) return;
     // any context may have used the operator: its memory is handed out again
-    if (op->ctx) { (void)hipSetDevice(op->ctx->device); (void)hipDeviceSynchronize(); }
+    (void)hipSetDevice(op->device);
+    (void)hipDeviceSynchronize();
     op_free_device(op);
     delete op;
 }
@@ -1130,7 +1132,7 @@ int mbem_solve_block(mbem_ctx *ctx, mbem_op *op, const mbem_c128 *b, int32_t nrh
     MBEM_TRY(set_device(ctx));
     Timer t;
     t.start(ctx->stream);
-    const int st = block_solve_run(op, (const double2 *)b, nrhs, o, (double2 *)x, stats, ctx->stream);
+    const int st = block_solve_run(ctx, op, (const double2 *)b, nrhs, o, (double2 *)x, stats, ctx->stream);
     const double ms = t.stop(ctx->stream);
     if (stats) stats->t_solve_ms = ms;
     return st;

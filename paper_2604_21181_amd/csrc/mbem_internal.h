@@ -125,7 +125,7 @@ struct mbem_ctx {
 };
 
 struct mbem_mesh {
-    mbem_ctx *ctx = nullptr;
+    int device = 0;              // its context may be gone before it
     int64_t nn = 0, nt = 0;
     std::vector<int64_t> node_order, tri_order;  // Morton position -> caller
     std::vector<double> xyz;                     // Morton order [nn*3]
@@ -175,7 +175,7 @@ struct mbem_mesh {
 };
 
 struct mbem_op {
-    mbem_ctx *ctx = nullptr;
+    int device = 0;              // its context may be gone before it
     const mbem_mesh *mesh = nullptr;
     mbem_params p{};
     int prec = MBEM_FP64;
@@ -453,7 +453,8 @@ void near_free(mbem_op *op);
 int near_add_dense_run(const mbem_op *op, double2 *K1, double2 *K2e, double2 *K2m, hipStream_t s);
 
 // multi-right-hand-side solve (block.hip)
-int block_solve_run(mbem_op *op, const double2 *B, int ncol, const mbem_block_opts *o, double2 *X,
+// ctx: holds the tuned GEMM shape
+int block_solve_run(mbem_ctx *ctx, mbem_op *op, const double2 *B, int ncol, const mbem_block_opts *o, double2 *X,
                     mbem_block_stats *st, hipStream_t s);
 int ensure_c64_copy(mbem_op *op, hipStream_t s);
 
