@@ -235,7 +235,7 @@ static int gmres_alloc(Gmres &g, const mbem_op *op, int maxit, hipStream_t s) {
     const size_t need = G * gmres_elems(op, maxit);
     mbem_op *mop = const_cast<mbem_op *>(op);
     if (op->work_elems < need) {
-        dfree(mop->d_work);
+        if (mop->d_work) (void)dev_free_wait(mop->d_work);
         mop->d_work = nullptr;
         mop->work_elems = 0;
         MBEM_TRY(dalloc(&mop->d_work, need));
@@ -245,7 +245,7 @@ static int gmres_alloc(Gmres &g, const mbem_op *op, int maxit, hipStream_t s) {
     // kernels straight into fine-grained host memory, then y
     const size_t pin = G * (2 * (col + 1) + (size_t)maxit);
     if (op->pin_elems < pin) {
-        if (mop->h_pin) (void)pin_free(mop->h_pin);
+        if (mop->h_pin) { (void)hipDeviceSynchronize(); (void)pin_free(mop->h_pin); }   // as dev_free_wait
         mop->h_pin = nullptr;
         mop->pin_elems = 0;
         MBEM_HIP(pin_malloc((void **)&mop->h_pin, sizeof(double2) * pin, true));

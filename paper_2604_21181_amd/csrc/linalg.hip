@@ -1284,8 +1284,8 @@ int mbj_setup_run(mbem_op *op, int B, hipStream_t s, bool keep) {
     // the transposed inverses belong to the previous blocks (and so does the
     // complex64 copy, which is rewritten below; its allocation is kept when
     // the size matches)
-    if (op->d_minv_t) { MBEM_HIP(dev_free(op->d_minv_t)); op->d_minv_t = nullptr; }
-    if (op->d_minv_t32) { MBEM_HIP(dev_free(op->d_minv_t32)); op->d_minv_t32 = nullptr; }
+    if (op->d_minv_t) { MBEM_HIP(dev_free_wait(op->d_minv_t)); op->d_minv_t = nullptr; }
+    if (op->d_minv_t32) { MBEM_HIP(dev_free_wait(op->d_minv_t32)); op->d_minv_t32 = nullptr; }
     op->B = 0; op->nb = 0;
     if (B > kMaxBlock) { set_error("preconditioner block above 512 is not supported"); return MBEM_EINVAL; }
     const int64_t n2 = op->n2;
@@ -1296,7 +1296,7 @@ int mbj_setup_run(mbem_op *op, int B, hipStream_t s, bool keep) {
     // factors and pivots in one scratch allocation: [nb][ld][ld] + [nb][ld] + info
     const size_t lu_bytes = B > 0 ? bytes + sizeof(int32_t) * (nb * ld + 1) : 0;
     if (op->d_minv && op->minv_bytes != bytes) {
-        MBEM_HIP(dev_free(op->d_minv)); op->d_minv = nullptr; op->minv_bytes = 0;
+        MBEM_HIP(dev_free_wait(op->d_minv)); op->d_minv = nullptr; op->minv_bytes = 0;
         if (op->d_minv32) { MBEM_HIP(dev_free(op->d_minv32)); op->d_minv32 = nullptr; }
     }
     if (op->d_lu && op->lu_bytes != lu_bytes) {
@@ -1348,7 +1348,7 @@ int mbj_setup_run(mbem_op *op, int B, hipStream_t s, bool keep) {
     if (!keep) { MBEM_HIP(dev_free(op->d_lu)); op->d_lu = nullptr; op->lu_bytes = 0; }
     if (h) {
         set_error("zero pivot in preconditioner block " + std::to_string(h - 1));
-        MBEM_HIP(dev_free(op->d_minv));
+        MBEM_HIP(dev_free_wait(op->d_minv));
         op->d_minv = nullptr;
         op->minv_bytes = 0;
         if (op->d_minv32) { MBEM_HIP(dev_free(op->d_minv32)); op->d_minv32 = nullptr; }

@@ -44,6 +44,9 @@ int wait_host_tag(const unsigned long long *tag, unsigned long long seq, hipStre
 // it is destroyed.  mapped: coherent host memory that kernels write.
 hipError_t dev_malloc(void **p, size_t n);
 hipError_t dev_free(void *p);
+// For a part of a handle that any context may still be reading: waits for the
+// device first, as hipFree does by itself.
+hipError_t dev_free_wait(void *p);
 hipError_t pin_malloc(void **p, size_t n, bool mapped = false);
 hipError_t pin_free(void *p);
 MemPool *pool_create(int device);

@@ -296,7 +296,7 @@ int near_fold_run(mbem_op *op, hipStream_t s) {
                            op->mesh->nn, op->n2, v, op->near_nnz, (float2 *)op->K[0], (float2 *)op->K[1],
                            (float2 *)op->K[2]);
     MBEM_HIP(hipGetLastError());
-    MBEM_HIP(hipStreamSynchronize(s));
+    MBEM_HIP(hipDeviceSynchronize());    // any context may be reading the store
     near_free(op);
     return MBEM_OK;
 }

@@ -7,8 +7,9 @@
 // release, up to 1/16 of the device's memory, and hands it out again:
 //  - a block only goes back to the context it was allocated under, whose work
 //    all runs on one stream, so a new user's work follows the last one's;
-//  - handles that other contexts may have used are released after a device
-//    synchronisation (as hipFree does by itself);
+//  - handles that other contexts may have used, and the parts of them that a
+//    later call replaces, are released after a device synchronisation (as
+//    hipFree does by itself);
 //  - a failed allocation releases what every context keeps and is tried again;
 //  - destroying the context gives everything back.  Blocks still in use then
 //    are freed when their handle is.
@@ -131,6 +132,11 @@ hipError_t release(void *p) {
 
 hipError_t dev_malloc(void **p, size_t n) { return alloc(kDevice, p, std::max<size_t>(n, 1)); }
 hipError_t dev_free(void *p) { return release(p); }
+hipError_t dev_free_wait(void *p) {
+    const hipError_t e = hipDeviceSynchronize();
+    const hipError_t f = release(p);
+    return e != hipSuccess ? e : f;
+}
 hipError_t pin_malloc(void **p, size_t n, bool mapped) {
     return alloc(mapped ? kMapped : kPinned, p, std::max<size_t>(n, 1));
 }

@@ -1,4 +1,5 @@
-"""Handles that outlive their context: they keep the device, not the context."""
+"""Handles that outlive their context, and parts of a handle that one context
+replaces while another is still reading them."""
 import pytest
 
 from workloads import icosphere_p2
@@ -37,3 +38,37 @@ def test_handles_outlive_their_context():
             mbem.mbem_mesh_destroy(mesh)
     finally:
         mbem.mbem_ctx_destroy(other)
+
+
+@pytest.mark.parametrize("block", [37, 200])
+def test_preconditioner_replaced_while_another_context_reads_it(block):
+    """Inverses that another stream's queued product still reads are handed out
+    again only after it: the setup with another block size waits, as hipFree did
+    before contexts kept memory."""
+    import torch
+    from paper_2604_21181_amd import mbem
+    xyz, tri = icosphere_p2(320)
+    n = 4 * xyz.shape[0]
+    side = torch.cuda.Stream()
+    c1, c2 = mbem.mbem_ctx_create(0), mbem.mbem_ctx_create(0, side.cuda_stream)
+    x = torch.randn(n, dtype=torch.complex128, device="cuda")
+    y = torch.zeros(64, n, dtype=torch.complex128, device="cuda")
+    z = torch.zeros(65, n, dtype=torch.complex128, device="cuda")
+    try:
+        mesh = mbem.mbem_mesh_create(c1, xyz, tri)
+        op, _ = mbem.mbem_fill(c1, mesh, mbem.make_params(1.0, 3.0))
+        for _ in range(4):
+            mbem.mbem_precond_setup(c1, op, 100)
+            mbem.mbem_precond_apply(c1, op, x, z[64])
+            torch.cuda.synchronize()
+            for k in range(64):
+                mbem.mbem_matvec_noalloc(c2, op, x, y[k])       # enqueued only
+                mbem.mbem_precond_apply(c2, op, x, z[k])
+            mbem.mbem_precond_setup(c1, op, block)
+            torch.cuda.synchronize()
+            assert bool((z[:64] == z[64]).all())
+        mbem.mbem_op_destroy(op)
+        mbem.mbem_mesh_destroy(mesh)
+    finally:
+        mbem.mbem_ctx_destroy(c2)
+        mbem.mbem_ctx_destroy(c1)
