@@ -146,6 +146,7 @@ struct Gmres {
     double2 *V, *w, *z, *tmp, *hdev;
     double2 *W;                 // the products Z z_j of the steps, [step][system][N]
     double2 *tpart = nullptr;   // partial sums of the transposed product
+    double2 *group_work = nullptr;   // vectors and scratch of more than one system
     double *ndev;
     double2 *hcol;              // the current step's projection coefficients (device)
     double2 *ppart;             // projection partials of both passes, 2 (m + 1) x chunks
@@ -172,6 +173,7 @@ struct Gmres {
             if (ev1[i]) (void)hipEventDestroy(ev1[i]);
         }
         if (tpart) (void)dev_free(tpart);
+        if (group_work) (void)dev_free(group_work);
     }
     int64_t ld() const { return group * N; }   // from step to step in V and W
     static bool timed(int q) { return q >= kTimed0 && q < kTimed0 + kTimedSteps; }
@@ -234,7 +236,13 @@ static int gmres_alloc(Gmres &g, const mbem_op *op, int maxit, hipStream_t s) {
     const size_t col = 2 * (size_t)(maxit + 1) + 1;
     const size_t need = G * gmres_elems(op, maxit);
     mbem_op *mop = const_cast<mbem_op *>(op);
-    if (op->work_elems < need) {
+    // One system's workspace stays with the operator.  A group's goes back to
+    // the context with the call, so that an allocation that finds no memory can
+    // have it: up to the operator's own size, held by a live operator, kept a
+    // second fill or a block solve from fitting.
+    if (G > 1) {
+        MBEM_TRY(dalloc(&g.group_work, need));
+    } else if (op->work_elems < need) {
         if (mop->d_work) (void)dev_free_wait(mop->d_work);
         mop->d_work = nullptr;
         mop->work_elems = 0;
@@ -260,7 +268,7 @@ static int gmres_alloc(Gmres &g, const mbem_op *op, int maxit, hipStream_t s) {
     g.hpin[1] = op->h_pin + G * (col + 1);
     g.ypin = op->h_pin + 2 * G * (col + 1);
     for (int i = 0; i < 2; ++i) MBEM_HIP(hipHostGetDevicePointer((void **)&g.hmap[i], g.hpin[i], 0));
-    g.V = op->d_work;
+    g.V = G > 1 ? g.group_work : op->d_work;
     g.W = g.V + (size_t)(maxit + 1) * G * g.N;
     g.w = g.W + (size_t)(maxit + 1) * G * g.N;
     g.z = g.w + G * g.N;
@@ -868,14 +876,19 @@ static int solve_impl(mbem_ctx *ctx, mbem_op *op, const mbem_c128 *b, int32_t nr
     Owned own_r, own_d;
     auto alloc = [&]() -> int {
         MBEM_TRY(gmres_alloc(g, op, o->maxit, s));
-        if (!r_ws && !r) { MBEM_TRY(dalloc(&r, (size_t)g.group * g.N)); own_r.p = r; }
-        if (!d_ws && !d) { MBEM_TRY(dalloc(&d, (size_t)g.group * g.N)); own_d.p = d; }
+        if (!r_ws) { MBEM_TRY(dalloc(&r, (size_t)g.group * g.N)); own_r.p = r; }
+        if (!d_ws) { MBEM_TRY(dalloc(&d, (size_t)g.group * g.N)); own_d.p = d; }
         return MBEM_OK;
     };
     int ast = alloc();
-    if (ast != MBEM_OK && g.group > 1) {   // not enough memory for a group: one at a time
+    while (ast != MBEM_OK && g.group > 1) {   // not enough memory for the group
         (void)hipGetLastError();
-        g.group = 1;
+        dfree(g.group_work);
+        dfree(own_r.p);
+        dfree(own_d.p);
+        g.group_work = nullptr;
+        own_r.p = own_d.p = nullptr;
+        g.group = (g.group + 1) / 2;
         ast = alloc();
     }
     MBEM_TRY(ast);

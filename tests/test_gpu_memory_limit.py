@@ -1,0 +1,91 @@
+"""Calls with little device memory left: solves with several right-hand sides
+take smaller groups, and keep no memory that a later call needs."""
+import pytest
+
+from workloads import icosphere_p2
+
+pytestmark = pytest.mark.gpu
+
+MIB = 1 << 20
+
+
+def _take(n):
+    """Takes device memory until n bytes are free."""
+    import torch
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    held = []
+    for _ in range(2):           # a large block frees some memory of the runtime's own
+        more = torch.cuda.mem_get_info()[0] - n
+        if more > 0:
+            held.append(torch.empty(more, dtype=torch.uint8, device="cuda"))
+    assert torch.cuda.mem_get_info()[0] <= n + 4 * MIB
+    return held
+
+
+@pytest.fixture(scope="module")
+def most():
+    """All but 5 GiB, taken once: giving so much back takes the driver a while."""
+    import torch
+    held = _take(5 << 30)
+    yield
+    held.clear()
+    torch.cuda.empty_cache()
+
+
+@pytest.fixture
+def leave(most):
+    import torch
+    held = []
+    yield lambda n: held.extend(_take(n))
+    held.clear()
+    torch.cuda.empty_cache()
+
+
+def _problem(mbem, nrhs):
+    import torch
+    xyz, tri = icosphere_p2(1280)
+    ctx = mbem.mbem_ctx_create(0)
+    mesh = mbem.mbem_mesh_create(ctx, xyz, tri)
+    p = mbem.make_params(1.0, 2.0)
+    op, _ = mbem.mbem_fill(ctx, mesh, p)                 # 1202 MiB, and 224 MiB of scratch
+    mbem.mbem_precond_setup(ctx, op, 100)
+    b = torch.randn(nrhs, 4 * xyz.shape[0], dtype=torch.complex128, device="cuda")
+    return ctx, mesh, p, op, b, torch.zeros_like(b)
+
+
+def _close(mbem, ctx, mesh, *ops):
+    for op in ops:
+        mbem.mbem_op_destroy(op)
+    mbem.mbem_mesh_destroy(mesh)
+    mbem.mbem_ctx_destroy(ctx)
+
+
+@pytest.mark.parametrize("room", [1100, 500])
+def test_solve_with_little_memory(leave, room):
+    """Sixteen systems of 100 steps take 520 MiB; in 500 they need smaller
+    groups.  The solutions agree to the tolerance, for a conditioning below 100."""
+    import torch
+    from paper_2604_21181_amd import mbem
+    ctx, mesh, p, op, b, x = _problem(mbem, 16)
+    ref = torch.zeros_like(b)
+    code, _ = mbem.mbem_solve(ctx, op, b, ref, 16, 1e-9, maxit=100)
+    assert code == 0
+    leave(room * MIB)
+    code, st = mbem.mbem_solve(ctx, op, b, x, 16, 1e-9, maxit=100)
+    assert code == 0 and st.rel_resid <= 1e-9
+    assert float((x - ref).norm()) <= 1e-6 * float(ref.norm())
+    _close(mbem, ctx, mesh, op)
+
+
+def test_a_group_solve_keeps_no_memory_from_the_next_fill(leave):
+    """1700 MiB and the kept 224 hold either the workspace of sixteen systems of
+    160 steps (830 MiB) or a second operator and its scratch (1426 MiB), in turn
+    but not together."""
+    from paper_2604_21181_amd import mbem
+    ctx, mesh, p, op, b, x = _problem(mbem, 16)
+    leave(1700 * MIB)
+    code, _ = mbem.mbem_solve(ctx, op, b, x, 16, 1e-9, maxit=160)
+    assert code == 0
+    second, _ = mbem.mbem_fill(ctx, mesh, p)
+    _close(mbem, ctx, mesh, op, second)
