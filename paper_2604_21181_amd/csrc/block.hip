@@ -881,7 +881,12 @@ int ensure_c64_copy(mbem_op *op, hipStream_t s) {
     const int64_t n = op->n2 * op->n2;
     for (int q = 0; q < 3; ++q) {
         hipError_t e = dev_malloc(&op->K32[q], sizeof(float2) * n);
-        if (e != hipSuccess) { set_error("complex64 operator copy: out of memory"); return MBEM_ENOMEM; }
+        if (e != hipSuccess) {
+            // all three or none: the first block tells whether there is a copy
+            for (void *&k : op->K32) { (void)dev_free(k); k = nullptr; }
+            set_error("complex64 operator copy: out of memory");
+            return MBEM_ENOMEM;
+        }
         hipLaunchKernelGGL(k_c128_to_c64, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
                            (const double2 *)op->K[q], (float2 *)op->K32[q], n);
         MBEM_HIP(hipGetLastError());

@@ -1,5 +1,6 @@
 """Calls with little device memory left: solves with several right-hand sides
-take smaller groups, and keep no memory that a later call needs."""
+take smaller groups and keep no memory that a later call needs, and a call that
+fails leaves nothing half made."""
 import pytest
 
 from workloads import icosphere_p2
@@ -89,3 +90,22 @@ def test_a_group_solve_keeps_no_memory_from_the_next_fill(leave):
     assert code == 0
     second, _ = mbem.mbem_fill(ctx, mesh, p)
     _close(mbem, ctx, mesh, op, second)
+
+
+def test_block_solve_after_a_copy_that_did_not_fit(most):
+    """The complex64 copy of the operator takes three blocks of 200 MiB; 250 MiB
+    and the kept scratch hold at most two."""
+    import torch
+    from paper_2604_21181_amd import mbem
+    ctx, mesh, p, op, b, x = _problem(mbem, 4)
+    ref = torch.zeros_like(b)
+    room = _take(250 * MIB)
+    with pytest.raises(mbem.MbemError, match="complex64 operator copy"):
+        mbem.mbem_solve_block(ctx, op, b, x, 4, 1e-8)
+    del room[:]
+    torch.cuda.empty_cache()
+    code, st = mbem.mbem_solve_block(ctx, op, b, x, 4, 1e-8)
+    assert code == 0
+    mbem.mbem_solve(ctx, op, b, ref, 4, 1e-9)
+    assert float((x - ref).norm()) <= 1e-5 * float(ref.norm())
+    _close(mbem, ctx, mesh, op)
