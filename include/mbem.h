@@ -26,8 +26,10 @@
  *    caller memory.  "device" pointers are HIP device memory on the
  *    context's device (e.g. torch tensor data pointers), "host" pointers are
  *    ordinary host memory.  A context keeps the device memory that its handles
- *    and calls release, up to 1/16 of the device's, for the next ones; it goes
- *    back to the device when an allocation fails and with mbem_ctx_destroy().
+ *    and calls release, all contexts of a device together up to 1/16 of its
+ *    memory, for the next ones; it goes back to the device when an allocation
+ *    of the library fails and with mbem_ctx_destroy().  A context may be
+ *    destroyed before its handles.
  *  - Streams: all device work is enqueued on the context's stream (borrowed,
  *    never destroyed by the library).  Functions that write host outputs
  *    synchronise that stream before returning.

@@ -38,17 +38,23 @@ struct Block {
 
 struct MemPool {
     int device = 0;
-    size_t limit[kKinds] = {0, 0, 0}, kept[kKinds] = {0, 0, 0};
     std::multimap<size_t, void *> idle[kKinds];
 };
 
 namespace {
 
-// One lock for the table of blocks and every pool: allocations are rare.
-// Never destroyed: handles may be released during the program's exit.
+// What the contexts of a device may keep together, and what they do
+struct Kept {
+    size_t limit[kKinds] = {0, 0, 0}, now[kKinds] = {0, 0, 0};
+};
+
+// One lock for the tables, held for their updates alone: hipMalloc and hipFree,
+// which may wait for a device, run outside it.  Never destroyed: handles may be
+// released during the program's exit.
 std::mutex &g_mu = *new std::mutex;
 std::unordered_map<void *, Block> &g_blocks = *new std::unordered_map<void *, Block>;
 std::vector<MemPool *> &g_pools = *new std::vector<MemPool *>;
+std::map<int, Kept> &g_kept = *new std::map<int, Kept>;
 thread_local MemPool *t_pool = nullptr;
 
 hipError_t raw_alloc(Kind k, void **p, size_t n) {
@@ -58,52 +64,82 @@ hipError_t raw_alloc(Kind k, void **p, size_t n) {
 
 hipError_t raw_free(Kind k, void *p) { return k == kDevice ? hipFree(p) : hipHostFree(p); }
 
-void release_idle(MemPool *q) {   // g_mu held
-    int was = 0;
-    (void)hipGetDevice(&was);
-    (void)hipSetDevice(q->device);
-    for (int k = 0; k < kKinds; ++k) {
-        for (auto &b : q->idle[k]) (void)raw_free((Kind)k, b.second);
-        q->idle[k].clear();
-        q->kept[k] = 0;
+// The idle blocks of one pool, taken out of it
+struct Idle {
+    int device = 0;
+    std::multimap<size_t, void *> blocks[kKinds];
+    void take(MemPool *q) {   // g_mu held
+        device = q->device;
+        for (int k = 0; k < kKinds; ++k) {
+            blocks[k].swap(q->idle[k]);
+            for (auto &b : blocks[k]) g_kept[device].now[k] -= b.first;
+        }
     }
-    (void)hipSetDevice(was);
+    void free_all() {
+        int was = 0;
+        (void)hipGetDevice(&was);
+        (void)hipSetDevice(device);
+        for (int k = 0; k < kKinds; ++k)
+            for (auto &b : blocks[k]) (void)raw_free((Kind)k, b.second);
+        (void)hipSetDevice(was);
+    }
+};
+
+void release_all_idle() {
+    for (;;) {
+        Idle idle;
+        {
+            std::lock_guard<std::mutex> lock(g_mu);
+            auto q = std::find_if(g_pools.begin(), g_pools.end(), [](MemPool *o) {
+                return std::any_of(o->idle, o->idle + kKinds, [](auto &m) { return !m.empty(); });
+            });
+            if (q == g_pools.end()) return;
+            idle.take(*q);
+        }
+        idle.free_all();
+    }
+}
+
+MemPool *thread_pool() {   // g_mu held
+    return std::find(g_pools.begin(), g_pools.end(), t_pool) != g_pools.end() ? t_pool : nullptr;
 }
 
 hipError_t alloc(Kind k, void **p, size_t n) {
     *p = nullptr;
     try {
-        std::lock_guard<std::mutex> lock(g_mu);
-        MemPool *q = std::find(g_pools.begin(), g_pools.end(), t_pool) != g_pools.end() ? t_pool : nullptr;
-        if (q) {
-            // the smallest kept block that fits without wasting a quarter
-            auto it = q->idle[k].lower_bound(n);
-            if (it != q->idle[k].end() && it->first <= n + n / 4 + 4096) {
-                *p = it->second;
-                g_blocks[*p] = {q, it->first, k};
-                q->kept[k] -= it->first;
-                q->idle[k].erase(it);
-                return hipSuccess;
+        {
+            std::lock_guard<std::mutex> lock(g_mu);
+            if (MemPool *q = thread_pool()) {
+                // the smallest kept block that fits without wasting a quarter
+                auto it = q->idle[k].lower_bound(n);
+                if (it != q->idle[k].end() && it->first <= n + n / 4 + 4096) {
+                    g_blocks[it->second] = {q, it->first, k};
+                    *p = it->second;
+                    g_kept[q->device].now[k] -= it->first;
+                    q->idle[k].erase(it);
+                    return hipSuccess;
+                }
             }
         }
-        hipError_t e = raw_alloc(k, p, n);
+        void *b = nullptr;
+        hipError_t e = raw_alloc(k, &b, n);
         if (e != hipSuccess) {
             (void)hipGetLastError();
-            for (MemPool *o : g_pools) release_idle(o);
-            e = raw_alloc(k, p, n);
+            release_all_idle();
+            e = raw_alloc(k, &b, n);
         }
         if (e != hipSuccess) {
             (void)hipGetLastError();
-            *p = nullptr;
             return e;
         }
         try {
-            g_blocks[*p] = {q, n, k};
+            std::lock_guard<std::mutex> lock(g_mu);
+            g_blocks[b] = {thread_pool(), n, k};
         } catch (...) {
-            (void)raw_free(k, *p);
-            *p = nullptr;
+            (void)raw_free(k, b);
             throw;
         }
+        *p = b;
         return hipSuccess;
     } catch (const std::bad_alloc &) {
         return hipErrorOutOfMemory;
@@ -112,17 +148,23 @@ hipError_t alloc(Kind k, void **p, size_t n) {
 
 hipError_t release(void *p) {
     if (!p) return hipSuccess;
-    std::lock_guard<std::mutex> lock(g_mu);
-    auto it = g_blocks.find(p);
-    if (it == g_blocks.end()) return hipErrorInvalidValue;
-    const Block b = it->second;
-    g_blocks.erase(it);
-    if (b.pool && b.pool->kept[b.kind] + b.size <= b.pool->limit[b.kind]) {
-        try {
-            b.pool->idle[b.kind].emplace(b.size, p);
-            b.pool->kept[b.kind] += b.size;
-            return hipSuccess;
-        } catch (const std::bad_alloc &) {
+    Block b;
+    {
+        std::lock_guard<std::mutex> lock(g_mu);
+        auto it = g_blocks.find(p);
+        if (it == g_blocks.end()) return hipErrorInvalidValue;
+        b = it->second;
+        g_blocks.erase(it);
+        if (b.pool) {
+            Kept &kept = g_kept[b.pool->device];   // made with the pool
+            if (kept.now[b.kind] + b.size <= kept.limit[b.kind]) {
+                try {
+                    b.pool->idle[b.kind].emplace(b.size, p);
+                    kept.now[b.kind] += b.size;
+                    return hipSuccess;
+                } catch (const std::bad_alloc &) {
+                }
+            }
         }
     }
     return raw_free(b.kind, p);
@@ -147,10 +189,12 @@ MemPool *pool_create(int device) {
     if (!q) return nullptr;
     q->device = device;
     size_t total = 0;
-    if (hipDeviceTotalMem(&total, device) == hipSuccess) q->limit[kDevice] = total / 16;
-    q->limit[kPinned] = q->limit[kMapped] = (size_t)16 << 20;
+    const bool known = hipDeviceTotalMem(&total, device) == hipSuccess;
     std::lock_guard<std::mutex> lock(g_mu);
     try {
+        Kept &kept = g_kept[device];
+        if (known) kept.limit[kDevice] = total / 16;
+        kept.limit[kPinned] = kept.limit[kMapped] = (size_t)16 << 20;
         g_pools.push_back(q);
     } catch (const std::bad_alloc &) {
         delete q;
@@ -163,12 +207,16 @@ void pool_use(MemPool *q) { t_pool = q; }
 
 void pool_destroy(MemPool *q) {
     if (!q) return;
-    std::lock_guard<std::mutex> lock(g_mu);
-    release_idle(q);
-    for (auto &b : g_blocks)
-        if (b.second.pool == q) b.second.pool = nullptr;
-    g_pools.erase(std::remove(g_pools.begin(), g_pools.end(), q), g_pools.end());
-    if (t_pool == q) t_pool = nullptr;
+    Idle idle;
+    {
+        std::lock_guard<std::mutex> lock(g_mu);
+        idle.take(q);
+        for (auto &b : g_blocks)
+            if (b.second.pool == q) b.second.pool = nullptr;
+        g_pools.erase(std::remove(g_pools.begin(), g_pools.end(), q), g_pools.end());
+        if (t_pool == q) t_pool = nullptr;
+    }
+    idle.free_all();
     delete q;
 }
 

@@ -1,8 +1,9 @@
-"""Handles that outlive their context, and parts of a handle that one context
-replaces while another is still reading them."""
+"""Handles that outlive their context, parts of a handle that one context replaces
+while another is still reading them, and the memory that contexts keep."""
 import pytest
 
 from workloads import icosphere_p2
+from workloads.meshes import cubesphere_p2
 
 pytestmark = pytest.mark.gpu
 
@@ -72,3 +73,27 @@ def test_preconditioner_replaced_while_another_context_reads_it(block):
     finally:
         mbem.mbem_ctx_destroy(c2)
         mbem.mbem_ctx_destroy(c1)
+
+
+def test_contexts_keep_a_sixteenth_of_the_device_together():
+    """Two contexts release an operator of 11.6 GB each: together more than a
+    sixteenth of the device's 309 GB."""
+    import torch
+    from paper_2604_21181_amd import mbem
+    torch.cuda.synchronize()
+    before, total = torch.cuda.mem_get_info()
+    xyz, tri = cubesphere_p2(18)
+    ctxs = [mbem.mbem_ctx_create(0) for _ in range(2)]
+    try:
+        for ctx in ctxs:
+            mesh = mbem.mbem_mesh_create(ctx, xyz, tri)
+            op, _ = mbem.mbem_fill(ctx, mesh, mbem.make_params(1.0, 2.0))
+            mbem.mbem_op_destroy(op)
+            mbem.mbem_mesh_destroy(mesh)
+        kept = before - torch.cuda.mem_get_info()[0]
+        # 64 MiB: the runtime's own
+        assert 8 << 30 < kept <= total // 16 + (64 << 20)
+    finally:
+        for ctx in ctxs:
+            mbem.mbem_ctx_destroy(ctx)
+    assert before - torch.cuda.mem_get_info()[0] <= 64 << 20
