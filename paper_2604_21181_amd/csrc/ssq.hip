@@ -488,6 +488,7 @@ int ssq_table(int n, double **tab, int64_t *np, hipStream_t s) {
     hipLaunchKernelGGL(k_ssq_table, dim3((unsigned)((*np + 255) / 256)), dim3(256), 0, s, n, *np, gl, *tab);
     if (hipGetLastError() != hipSuccess) {
         (void)dev_free(*tab);
+        *tab = nullptr;
         set_error("singular-pair table: launch failed");
         return MBEM_EDEVICE;
     }
