@@ -745,7 +745,7 @@ int mbem_fill(mbem_ctx *ctx, const mbem_mesh *mesh, const mbem_params *p, mbem_o
     mbem_op *op = nullptr;
     MBEM_TRY(op_create(ctx, mesh, p, &op));
     const int st = op_fill(ctx, op, false, stats);
-    if (st != MBEM_OK) { op_free_device(op); delete op; return st; }
+    if (st != MBEM_OK) { mbem_op_destroy(op); return st; }   // after what is queued
     *out = op;
     return MBEM_OK;
 }
@@ -1037,7 +1037,7 @@ int mbem_fill_deps(mbem_ctx *ctx, const mbem_mesh *mesh, const mbem_params *p, m
     mbem_op *op = nullptr;
     MBEM_TRY(op_create(ctx, mesh, &q, &op));
     const int st = op_fill(ctx, op, true, stats);
-    if (st != MBEM_OK) { op_free_device(op); delete op; return st; }
+    if (st != MBEM_OK) { mbem_op_destroy(op); return st; }   // after what is queued
     op->ce = {0.5, 0.0};   // d((eps_i + 1) / 2) / deps_i; the mass matrix itself is fixed
     op->cm = {0.0, 0.0};
     *out = op;
