@@ -595,7 +595,6 @@ int mbem_mesh_create(mbem_ctx *ctx, const double *xyz, int64_t n_nodes, const in
     m->pair_batches = (int32_t)(T.pair_rec.size() / kPairRec);
     m->pair_slots = T.pair_sptr.back();
     m->pair_band = T.pair_band;
-    m->pair_band_rows = T.pair_band_rows;
     m->pair_row0 = T.pair_row0;
     m->pair_ncb = (int32_t)T.pair_cb.size() - 1;
     m->pair_rows_off = T.pair_rows_off;

@@ -210,9 +210,15 @@ namespace mbem {
 static inline int32_t pack_perm(int a, int b, int c) { return a | (b << 2) | (c << 4); }
 
 // Test batches per band of the FP64 regular-pair fill.  The two band buffers
-// together stay below kPairScratch, so that they are written and read back
-// while in the 256 MB last-level cache; within that a band takes whole rounds
-// of the workgroups that run at a time (three per compute unit).
+// together stay below kPairScratch where a band has more than one batch, so
+// that they are written and read back while in the 256 MB last-level cache.  A
+// band is at least one batch, whose two buffers grow with the mesh: 224 MB at
+// 9 400 triangles, 290 MB at 12 300, written through to memory from there on
+// (9 408 triangles, fill 238 ms where the colour classes took 628).  Of the bands
+// that fit, the largest is cut towards whole rounds of 768 workgroups (three
+// per compute unit; node-attached tangents run two), rounded down to whole
+// batches: 1.95 rounds at 320 triangles, 1.7 at 1280, 1.6 at 3072, what one batch
+// has from 5120 on.
 constexpr int64_t kPairScratch = (int64_t)224 << 20, kPairRound = 768;
 
 static int64_t pair_band(int64_t nbatch, int64_t nslots) {
@@ -495,11 +501,7 @@ int build_tables(const mbem_mesh *m, MeshTables &T) {
         T.pair_band = pair_band(nbatch, nodes);
         const int64_t nbands = (nbatch + T.pair_band - 1) / T.pair_band;
         std::vector<int32_t> band_end;       // first node row after each band
-        for (int64_t b = 0; b < nbands; ++b) {
-            const int32_t r0 = T.pair_row0[b * T.pair_band];
-            band_end.push_back(T.pair_row0[std::min(nbatch, (b + 1) * T.pair_band)]);
-            T.pair_band_rows = std::max<int64_t>(T.pair_band_rows, band_end.back() - r0);
-        }
+        for (int64_t b = 0; b < nbands; ++b) band_end.push_back(T.pair_row0[std::min(nbatch, (b + 1) * T.pair_band)]);
         std::vector<std::vector<int32_t>> tasks(nbands);
         for (int64_t v = 0; v < nn; ++v) {
             const int32_t s1 = T.pair_sptr[v + 1];

@@ -168,7 +168,7 @@ struct mbem_mesh {
     // batch node, blocks of nodes, and per band of pair_band test batches its
     // row tasks (4 ints each)
     int32_t pair_batches = 0, pair_ncb = 0;
-    int64_t pair_slots = 0, pair_band = 0, pair_band_rows = 0;   // most nodes in a band's batches
+    int64_t pair_slots = 0, pair_band = 0;
     std::vector<int64_t> pair_rows_off;
     std::vector<int32_t> pair_row0;       // batch -> nodes of the batches before it
     int32_t *d_pair_rec = nullptr, *d_pair_sptr = nullptr, *d_pair_srow = nullptr, *d_pair_cb = nullptr,
@@ -262,7 +262,7 @@ struct MeshTables {
     // + 1 slot, first band of the node} of the bands of pair_band test batches
     std::vector<int32_t> pair_rec, pair_sptr, pair_srow, pair_cb, pair_rows, pair_row0;
     std::vector<int64_t> pair_rows_off;
-    int64_t pair_band = 0, pair_band_rows = 0;
+    int64_t pair_band = 0;
     // colour classes: test triangles sharing no node, trial chunks sharing
     // no node (offsets into the concatenated lists, one more than classes)
     std::vector<int32_t> tcol_list, tcol_off, ccol_list, ccol_off;

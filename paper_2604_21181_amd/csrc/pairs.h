@@ -16,7 +16,7 @@ struct PairArgs {
     int64_t nslots;
     int64_t batch0, n_tiles;     // first test batch and workgroups of this launch's tiles
     int32_t n_batches;
-    int32_t row0, row0g;         // first T row (test node) of the tiles' and the gather's band
+    int32_t row0, row0g, row1g;  // first T row (test node) of the tiles' and the gather's batches, end of the latter
     const double *qp;            // [kQPF][nt * points]
     const int32_t *tri;
     const int32_t *rec;          // trial batch records, kPairRec ints each

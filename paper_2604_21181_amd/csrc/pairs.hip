@@ -98,7 +98,8 @@ __host__ __device__ constexpr double n_at(int p, int j) {
 // -------------------------------------------------------------- gather --
 // Row tasks of one band: {node, first slot, last slot + 1, 1 if no earlier
 // band wrote the node's rows} (a node's slots follow the order of the
-// batches).  One workgroup per (row task, block of nodes): the T rows of the
+// batches), of which the T rows row0g .. row1g - 1 are held: all of the band's,
+// or a part of them where memory was short.  One workgroup per (row task, block of nodes): the T rows of the
 // node's batches are read in whole runs and summed in registers, then the
 // slots of every column through LDS.  A block of a single node with more than
 // kPairCols slots takes several turns.
@@ -107,6 +108,10 @@ __device__ __forceinline__ void gather_rows(const PairArgs &a, int64_t id, doubl
     const int tid = threadIdx.x;
     const int4 task = a.rows[id / a.ncb];
     const int cb = (int)(id % a.ncb);
+    int s0 = task.y, s1 = task.z;
+    while (s0 < s1 && a.slot_row[s0] < a.row0g) ++s0;
+    while (s0 < s1 && a.slot_row[s1 - 1] >= a.row1g) --s1;
+    if (s0 == s1) return;                  // uniform over the workgroup
     const int32_t j0 = a.cblocks[cb], j1 = a.cblocks[cb + 1];
     const int32_t p1 = a.slot_ptr[j1];
     const int ncol = 2 * (j1 - j0);
@@ -116,7 +121,7 @@ __device__ __forceinline__ void gather_rows(const PairArgs &a, int64_t id, doubl
         double2 v[kPer];
 #pragma unroll
         for (int k = 0; k < kPer; ++k) v[k] = double2{0.0, 0.0};
-        for (int s = task.y; s < task.z; ++s) {
+        for (int s = s0; s < s1; ++s) {
             const double2 *__restrict__ row = a.Tg + ((a.slot_row[s] - a.row0g) * a.nslots + p0) * 12;
 #pragma unroll
             for (int k = 0; k < kPer; ++k) {
@@ -130,7 +135,7 @@ __device__ __forceinline__ void gather_rows(const PairArgs &a, int64_t id, doubl
         for (int k = 0; k < kPer; ++k)
             if (tid + 256 * k < kItems) s_v[tid + 256 * k] = v[k];
         __syncthreads();
-        const bool first = task.w && p0 == a.slot_ptr[j0];
+        const bool first = task.w && s0 == task.y && p0 == a.slot_ptr[j0];
         for (int it = tid; it < 6 * ncol; it += 256) {
             const int g = it / ncol, c = it % ncol;
             const int32_t j = j0 + (c >> 1);
@@ -422,24 +427,28 @@ __global__ __launch_bounds__(256, NODAL ? 2 : 3) void k_pair_tiles(PairArgs a) {
     }
 }
 
+// Launches of at most `part` test batches, bands in parts of that size.
 template <int NP, bool DK, bool NODAL>
-static int launch_bands(const mbem_op *op, PairArgs &a, double2 *const buf[2], hipStream_t s) {
+static int launch_bands(const mbem_op *op, PairArgs &a, int64_t part, double2 *const buf[2], hipStream_t s) {
     const mbem_mesh *m = op->mesh;
-    const int64_t nbands = (int64_t)m->pair_rows_off.size() - 1;
-    for (int64_t b = 0; b <= nbands; ++b) {
-        a.n_tiles = 0;
-        if (b < nbands) {
-            a.batch0 = b * m->pair_band;
-            a.row0 = m->pair_row0[a.batch0];
-            a.T = buf[b & 1];
-            a.n_tiles = std::min<int64_t>(m->pair_band, a.n_batches - a.batch0) * a.n_batches;
+    int64_t turn = 0, band = 0;            // launches so far, band of the gather's batches
+    for (int64_t b0 = 0, g0 = -1; g0 < a.n_batches;) {
+        // the tiles of the batches [b0, b1), the gather of those before, [g0, b0)
+        const int64_t b1 = std::min<int64_t>({b0 + part, (b0 / m->pair_band + 1) * m->pair_band, a.n_batches});
+        a.n_tiles = (b1 - b0) * a.n_batches;
+        if (a.n_tiles > 0) {
+            a.batch0 = b0;
+            a.row0 = m->pair_row0[b0];
+            a.T = buf[turn & 1];
         }
         int64_t gather = 0;
-        if (b > 0) {
-            a.rows = (const int4 *)m->d_pair_rows + m->pair_rows_off[b - 1];
-            a.row0g = m->pair_row0[(b - 1) * m->pair_band];
-            a.Tg = buf[(b - 1) & 1];
-            gather = (m->pair_rows_off[b] - m->pair_rows_off[b - 1]) * a.ncb;
+        if (g0 >= 0) {
+            band = g0 / m->pair_band;
+            a.rows = (const int4 *)m->d_pair_rows + m->pair_rows_off[band];
+            a.row0g = m->pair_row0[g0];
+            a.row1g = m->pair_row0[b0];
+            a.Tg = buf[(turn - 1) & 1];
+            gather = (m->pair_rows_off[band + 1] - m->pair_rows_off[band]) * a.ncb;
         }
         if (a.n_tiles + gather > 0x7fffffffLL) {
             set_error("too many element pairs for one launch");
@@ -447,6 +456,9 @@ static int launch_bands(const mbem_op *op, PairArgs &a, double2 *const buf[2], h
         }
         hipLaunchKernelGGL((k_pair_tiles<NP, DK, NODAL>), dim3((unsigned)(a.n_tiles + gather)), dim3(256), 0, s, a);
         MBEM_HIP(hipGetLastError());
+        g0 = b0;
+        b0 = b1;
+        ++turn;
     }
     return MBEM_OK;
 }
@@ -474,19 +486,32 @@ int pair_fill_run(mbem_op *op, bool deriv, hipStream_t s) {
         MBEM_TRY(nodal_table_f64(op, paper, s));
         a.rtab = (const double *)op->d_rtab;
     }
-    const int64_t nbands = (int64_t)m->pair_rows_off.size() - 1;
-    const size_t elems = (size_t)m->pair_band_rows * 12 * a.nslots;
-    double2 *scratch = nullptr;
-    const hipError_t err = dev_malloc((void **)&scratch, elems * sizeof(double2) * (nbands > 1 ? 2 : 1));
-    if (err != hipSuccess) { set_error(std::string("fill scratch: ") + hipGetErrorString(err)); return MBEM_ENOMEM; }
-    double2 *const buf[2] = {scratch, scratch + (nbands > 1 ? elems : 0)};
+    // two buffers of a band, one where a single band is all; where they do not
+    // fit, bands in parts, down to one batch
+    int64_t part = std::min<int64_t>(m->pair_band, a.n_batches);
+    double2 *scratch = nullptr, *buf[2];
+    for (;;) {
+        int64_t rows = 0;                  // most T rows of a part
+        for (int64_t b0 = 0, b1; b0 < a.n_batches; b0 = b1) {
+            b1 = std::min<int64_t>({b0 + part, (b0 / m->pair_band + 1) * m->pair_band, a.n_batches});
+            rows = std::max<int64_t>(rows, m->pair_row0[b1] - m->pair_row0[b0]);
+        }
+        const size_t elems = (size_t)rows * 12 * a.nslots;
+        const int nbuf = part < a.n_batches ? 2 : 1;
+        const hipError_t err = dev_malloc((void **)&scratch, elems * sizeof(double2) * nbuf);
+        buf[0] = scratch;
+        buf[1] = scratch + (nbuf - 1) * elems;
+        if (err == hipSuccess) break;
+        if (part == 1) { set_error(std::string("fill scratch: ") + hipGetErrorString(err)); return MBEM_ENOMEM; }
+        part = (part + 1) / 2;
+    }
     int st;
-    if (paper) st = nodal ? launch_bands<kQP12, false, true>(op, a, buf, s)
-                          : launch_bands<kQP12, false, false>(op, a, buf, s);
-    else if (deriv) st = nodal ? launch_bands<kQP, true, true>(op, a, buf, s)
-                               : launch_bands<kQP, true, false>(op, a, buf, s);
-    else st = nodal ? launch_bands<kQP, false, true>(op, a, buf, s)
-                    : launch_bands<kQP, false, false>(op, a, buf, s);
+    if (paper) st = nodal ? launch_bands<kQP12, false, true>(op, a, part, buf, s)
+                          : launch_bands<kQP12, false, false>(op, a, part, buf, s);
+    else if (deriv) st = nodal ? launch_bands<kQP, true, true>(op, a, part, buf, s)
+                               : launch_bands<kQP, true, false>(op, a, part, buf, s);
+    else st = nodal ? launch_bands<kQP, false, true>(op, a, part, buf, s)
+                    : launch_bands<kQP, false, false>(op, a, part, buf, s);
     MBEM_HIP(dev_free(scratch));     // its next user's work follows on the same stream
     return st;
 }

@@ -1,6 +1,6 @@
 """Calls with little device memory left: solves with several right-hand sides
-take smaller groups and keep no memory that a later call needs, and a call that
-fails leaves nothing half made."""
+take smaller groups and keep no memory that a later call needs, fills take
+smaller bands, and a call that fails leaves nothing half made."""
 import pytest
 
 from workloads import icosphere_p2
@@ -109,3 +109,28 @@ def test_block_solve_after_a_copy_that_did_not_fit(most):
     mbem.mbem_solve(ctx, op, b, ref, 4, 1e-9)
     assert float((x - ref).norm()) <= 1e-5 * float(ref.norm())
     _close(mbem, ctx, mesh, op)
+
+
+@pytest.mark.parametrize("room", [1340, 1250])
+@pytest.mark.parametrize("frame", [0, 1])
+@pytest.mark.parametrize("paper", [0, 1])
+def test_fill_with_little_memory(leave, paper, frame, room):
+    """Three blocks of 401 MiB and the tables leave 120 and 30 MiB for the bands'
+    scratch, which takes 224.  The blocks agree to the rounding of the singular
+    pairs' additions, whose order varies: 1e-16 of the blocks' scale each."""
+    import torch
+    from paper_2604_21181_amd import mbem
+    xyz, tri = icosphere_p2(1280)
+    p = mbem.make_params(1.3, 2.6 + 0.1j, quadrature=paper, frame=frame)
+    x = torch.randn(4 * xyz.shape[0], dtype=torch.complex128, device="cuda")
+    y = []
+    for n in (None, room):
+        ctx = mbem.mbem_ctx_create(0)
+        mesh = mbem.mbem_mesh_create(ctx, xyz, tri)
+        if n:
+            leave(n * MIB)
+        op, _ = mbem.mbem_fill(ctx, mesh, p)
+        y.append(torch.zeros_like(x))
+        mbem.mbem_matvec(ctx, op, x, y[-1])
+        _close(mbem, ctx, mesh, op)
+    assert float((y[0] - y[1]).norm()) <= 1e-13 * float(y[0].norm())
