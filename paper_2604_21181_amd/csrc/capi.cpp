@@ -808,10 +808,10 @@ int mbem_matvec(mbem_ctx *ctx, const mbem_op *op, const mbem_c128 *x, int32_t nr
     if (!op || !x || !y || nrhs < 1) { set_error("bad argument"); return MBEM_EINVAL; }
     MBEM_TRY(set_device(ctx));
     double2 *tmp = nullptr;
-    const int chunk = matvecs_chunk(op, nrhs);
-    MBEM_TRY(dalloc(&tmp, (size_t)matvecs_work(op, chunk)));
+    int chunk = matvecs_chunk(op, nrhs), st;
+    while ((st = dalloc(&tmp, (size_t)matvecs_work(op, chunk))) != MBEM_OK && chunk > 1) chunk = (chunk + 1) / 2;
+    MBEM_TRY(st);                          // as many vectors at a time as there is memory for
     const int64_t N = 2 * op->n2;
-    int st = MBEM_OK;
     for (int r = 0; r < nrhs && st == MBEM_OK; r += chunk)
         st = matvecs_run(op, (const double2 *)x + r * N, (double2 *)y + r * N, std::min(chunk, nrhs - r), tmp,
                          ctx->stream);
