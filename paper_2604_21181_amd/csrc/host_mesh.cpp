@@ -314,9 +314,10 @@ int build_tables(const mbem_mesh *m, MeshTables &T) {
     // pairs that touch it
     const int64_t nch = (nt + kChunk - 1) / kChunk;
     T.chunks.assign(nch * kChunkRec, 0);
+    std::vector<std::pair<int32_t, int32_t>> uses;   // (node, local triangle * 8 + loc)
     for (int64_t k = 0; k < nch; ++k) {
         int32_t *rec = T.chunks.data() + k * kChunkRec;
-        std::vector<std::pair<int32_t, int32_t>> uses;   // (node, fs*8 + loc)
+        uses.clear();
         for (int fs = 0; fs < kChunk; ++fs) {
             const int64_t f = k * kChunk + fs;
             if (f >= nt) break;
@@ -358,7 +359,7 @@ int build_tables(const mbem_mesh *m, MeshTables &T) {
                 recs.resize(base + L.rec(), 0);
                 int32_t *rec = recs.data() + base;
                 const int nb = (int)std::min<size_t>(L.nb, rtris.size() - b0);
-                std::vector<std::pair<int32_t, int32_t>> uses;   // (range-local node, fb*8 + loc)
+                uses.clear();            // (range-local node, fb*8 + loc)
                 rec[0] = nb;
                 for (int fb = 0; fb < nb; ++fb) {
                     const int32_t f = rtris[b0 + fb];
@@ -387,8 +388,11 @@ int build_tables(const mbem_mesh *m, MeshTables &T) {
     // per 5 triangles (20.4 for runs of the Morton order).
     {
         std::vector<char> used(nt, 0);
-        // per node and slot: its place in the records, its row of the scratch
-        std::vector<std::vector<std::pair<int32_t, int32_t>>> places(nn);
+        // per row of the scratch, in order: its node and its place in the records
+        std::vector<int32_t> row_node, row_place;
+        row_node.reserve(4 * nt);
+        row_place.reserve(4 * nt);
+        T.pair_rec.reserve((nt / 4 + 1) * kPairRec);
         int32_t nodes = 0;
         // edge neighbours, and the batch that last held a node / listed a triangle
         std::vector<int32_t> nbr(3 * nt), in_batch(nn, -1), listed(nt, -1);
@@ -400,6 +404,7 @@ int build_tables(const mbem_mesh *m, MeshTables &T) {
                     if ((T.inc[q] >> 3) != t) nbr[3 * t + k] = T.inc[q] >> 3;
             }
         std::vector<int32_t> bt, bn, cand;     // the batch's triangles and nodes, triangles around them
+        std::vector<std::pair<int, int32_t>> order;
         int32_t id = 0;
         auto shared = [&](int32_t f) {
             int n = 0;
@@ -448,14 +453,13 @@ int build_tables(const mbem_mesh *m, MeshTables &T) {
             }
             std::sort(bt.begin(), bt.end());
             // nodes by falling number of incidences in the batch
-            auto uses = [&](int32_t v) {
+            order.clear();
+            for (int32_t v : bn) {
                 int n = 0;
                 for (int32_t f : bt)
                     for (int l = 0; l < 6; ++l) n += tri[6 * (int64_t)f + l] == v;
-                return n;
-            };
-            std::vector<std::pair<int, int32_t>> order;
-            for (int32_t v : bn) order.push_back({-uses(v), v});
+                order.push_back({-n, v});
+            }
             std::sort(order.begin(), order.end());
             for (size_t q = 0; q < bn.size(); ++q) bn[q] = order[q].second;
             const size_t base = T.pair_rec.size();
@@ -477,19 +481,21 @@ int build_tables(const mbem_mesh *m, MeshTables &T) {
                             rec[kPairLoc + 6 * k + l] = (int32_t)q + (seen ? 0 : 256);
                             seen = true;
                         }
-                places[bn[q]].push_back({(int32_t)(base + kPairPos + q), nodes + (int32_t)q});
+                row_node.push_back(bn[q]);
+                row_place.push_back((int32_t)(base + kPairPos + q));
             }
             rec[kPairOff + bn.size()] = ni;
             nodes += (int32_t)bn.size();
         }
         T.pair_sptr.assign(nn + 1, 0);
-        for (int64_t v = 0; v < nn; ++v) {
-            int32_t slot = T.pair_sptr[v];
-            for (const auto &at : places[v]) {
-                T.pair_rec[at.first] = slot++;
-                T.pair_srow.push_back(at.second);
-            }
-            T.pair_sptr[v + 1] = slot;
+        for (int32_t v : row_node) ++T.pair_sptr[v + 1];
+        for (int64_t v = 0; v < nn; ++v) T.pair_sptr[v + 1] += T.pair_sptr[v];
+        T.pair_srow.resize(nodes);
+        std::vector<int32_t> next(T.pair_sptr.begin(), T.pair_sptr.end() - 1);
+        for (int32_t row = 0; row < nodes; ++row) {
+            const int32_t slot = next[row_node[row]]++;
+            T.pair_rec[row_place[row]] = slot;
+            T.pair_srow[slot] = row;
         }
         T.pair_cb.assign(1, 0);
         for (int64_t v = 0; v < nn; ++v)
@@ -528,20 +534,22 @@ int build_tables(const mbem_mesh *m, MeshTables &T) {
     auto colour = [&](int64_t nitems, auto nodes_of, std::vector<int32_t> &list,
                       std::vector<int32_t> &off) {
         std::vector<std::vector<int32_t>> users(nn);
-        std::vector<std::vector<int32_t>> item_nodes(nitems);
+        std::vector<int32_t> item_nodes, first(1, 0);    // an item's nodes: [first[it], first[it + 1])
+        item_nodes.reserve(6 * nt);
         std::vector<int32_t> col(nitems, -1);
         std::vector<int64_t> used(1, -1);    // colour -> the last item (or pass and item) that met it
         int ncol = 0;
         for (int64_t it = 0; it < nitems; ++it) {
-            nodes_of(it, item_nodes[it]);
-            for (int32_t v : item_nodes[it])
-                for (int32_t o : users[v]) used[col[o]] = it;
+            nodes_of(it, item_nodes);
+            first.push_back((int32_t)item_nodes.size());
+            for (int32_t k = first[it]; k < first[it + 1]; ++k)
+                for (int32_t o : users[item_nodes[k]]) used[col[o]] = it;
             int c = 0;
             while (c < ncol && used[c] == it) ++c;
             if (c == ncol) used.push_back(-1);
             col[it] = c;
             ncol = std::max(ncol, c + 1);
-            for (int32_t v : item_nodes[it]) users[v].push_back((int32_t)it);
+            for (int32_t k = first[it]; k < first[it + 1]; ++k) users[item_nodes[k]].push_back((int32_t)it);
         }
         std::vector<int64_t> size(ncol, 0);
         for (int64_t it = 0; it < nitems; ++it) size[col[it]]++;
@@ -552,8 +560,8 @@ int build_tables(const mbem_mesh *m, MeshTables &T) {
                 const int c = col[it];
                 if (size[c] <= target) continue;
                 const int64_t mark = (round + 1) * nitems + it;
-                for (int32_t v : item_nodes[it])
-                    for (int32_t o : users[v])
+                for (int32_t k = first[it]; k < first[it + 1]; ++k)
+                    for (int32_t o : users[item_nodes[k]])
                         if (o != it) used[col[o]] = mark;
                 int best = -1;
                 for (int d = 0; d < ncol; ++d)
