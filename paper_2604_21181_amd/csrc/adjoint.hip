@@ -81,8 +81,8 @@ int ff_functional_run(const mbem_mesh *m, const mbem_params *p, const double *rh
 // Bound by the read of the blocks.  A step of the adjoint GMRES, us, with a
 // launch dimension per block, four slots and chunks of 256 rows (c64: 64) -> this:
 //   triangles    80           320          768          1280         2700
-//   FP64      81 -> 32    129 -> 46    199 -> 110    271 -> 248   1060 -> 1012
-//   mixed     51 -> 37     67 -> 50     93 -> 84     206 -> 153    693 -> 606
+//   FP64      81 -> 33    129 -> 48    199 -> 112    271 -> 248   1060 -> 1023
+//   mixed     51 -> 33     67 -> 47     93 -> 82     206 -> 148    693 -> 590
 __device__ inline double2 zm(double2 a, double2 b) { return {a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x}; }
 __device__ inline double2 za(double2 a, double2 b) { return {a.x + b.x, a.y + b.y}; }
 typedef double td2 __attribute__((ext_vector_type(2)));
@@ -192,8 +192,9 @@ __global__ __launch_bounds__(256) void k_combine_t(int64_t n2, int nch, const do
 // Rows of a chunk: a power of two of at least 8 that leaves 800 (c128) or 1200
 // workgroups (c64, whose threads take two columns) where the operator is large
 // enough, up to 128 or 64: the partial sums speak for long chunks, small operators
-// for short ones (n2 = 1284, FP64: 8 rows 53 us a step, 64 72; 5124: 128 rows 253,
-// 32 273; c64 3076: 16 rows 91, 8 103; 10 804: 64 rows 605, 128 659).
+// for short ones (us a step as above; FP64 320 triangles, n2 = 1284: 8 rows 48, 64
+// 68; 1280, 5124: 128 rows 248, 32 267; c64 768, 3076: 16 rows 82, 8 89; 2700,
+// 10 804: 64 rows 592, 128 647).
 static int t_rows(const mbem_op *op) {
     const bool fp64 = op->prec == MBEM_FP64;
     const int64_t columns = (op->n2 / (fp64 ? 1 : 2) + 255) / 256, want = op->n2 * columns / (fp64 ? 800 : 1200);

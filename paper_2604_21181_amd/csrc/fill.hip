@@ -974,7 +974,6 @@ static KernelConst make_kconst(const mbem_op *op, bool deriv) {
 // dg: c_{m+3}, G: c_{m+2} multiply R^m).
 static KernelConst make_rem_kconst(const mbem_op *op) {
     using C = std::complex<double>;
-    constexpr int kPaperTerms = 6;
     KernelConst K = make_kconst(op, false);
     KernelConst R = K;
     for (int i = 0; i < 2 * (kSeriesTerms + 1); ++i) R.cD[i] = R.cF[i] = R.cG[i] = R.cE[i] = R.cM[i] = 0.0;

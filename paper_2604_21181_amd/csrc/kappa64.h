@@ -1,4 +1,5 @@
-// FP64 kernel differences of the fills without divisions or square roots.
+// FP64 kernel differences of the fills: closed forms from a root and an inverse
+// root, without divisions (the series below max|k| R = 1/2 divide, as before).
 #pragma once
 
 #include "p2_device.h"

@@ -166,6 +166,7 @@ __device__ inline dvec3 project_tangent(dvec3 t, dvec3 n) { return t - dot(t, n)
 // ------------------------------------------------- kernel differences --
 constexpr int kSeriesTerms = 16;   // Taylor terms n = 0..16
 constexpr double kSeriesRho = 0.5; // series below max|k| R = 1/2
+constexpr int kPaperTerms = 6;     // highest term of the paper's scheme's remainders
 
 // Material constants and the frequency-dependent Taylor coefficients,
 // precomputed on the host once per fill (Sec. 6.1).  With
@@ -310,24 +311,6 @@ __device__ __forceinline__ KScal<T> kernel_scalars_closed(const KernelConst &K, 
     const cx<T> ma = {(T)K.mu_a_re, (T)K.mu_a_im}, mi = {(T)K.mu_i_re, (T)K.mu_i_im};
     o.Ge = (-R) * (ea * g[0] - ei * g[1]);
     o.Gm = (-R) * (ma * g[0] - mi * g[1]);
-    return o;
-}
-
-// Singular parts of the scalars (kappa^s of the paper's scheme, Sec. 4.1
-// and 4.2): the terms of negative order in R of the expansions,
-//   D0^s = (k_a^2 - k_i^2)/(4 pi R), df^s = dg^s = (k_a^2 - k_i^2)/(8 pi R),
-//   G_chi^s = -(chi_a - chi_i)/(4 pi R^2).
-__device__ __forceinline__ KScal<double> kernel_scalars_sing(const KernelConst &K, double R) {
-    const double inv4pi = 0.079577471545947667884;
-    const cx<double> ka = {K.ka_re, K.ka_im}, ki = {K.ki_re, K.ki_im};
-    const cx<double> dk2 = ka * ka - ki * ki;
-    const double r1 = inv4pi / R, r2 = r1 / R;
-    KScal<double> o;
-    o.D0 = r1 * dk2;
-    o.df = (0.5 * r1) * dk2;
-    o.dg = o.df;
-    o.Ge = (-r2) * cx<double>{K.eps_a_re - K.eps_i_re, K.eps_a_im - K.eps_i_im};
-    o.Gm = (-r2) * cx<double>{K.mu_a_re - K.mu_i_re, K.mu_a_im - K.mu_i_im};
     return o;
 }
 

@@ -62,7 +62,6 @@ __device__ inline cv3 ccross(cv3 a, cv3 b) {
     return {a.y * b.z - a.z * b.y, a.z * b.x - a.x * b.z, a.x * b.y - a.y * b.x};
 }
 __device__ inline dvec3 im3(cv3 a) { return {a.x.im, a.y.im, a.z.im}; }
-__device__ inline cxd cscale(double s, cxd a) { return {s * a.re, s * a.im}; }
 
 // ------------------------------ kernel differences and their R-derivatives --
 // times i/w (a, d: A = D0 - dg and df) and d/dR of each

@@ -47,7 +47,6 @@ __device__ inline void atomic_add(double *p, double v) { unsafeAtomicAdd(p, v); 
 __device__ inline void atomic_add(float *p, double v) { unsafeAtomicAdd(p, (float)v); }
 
 constexpr int kRuleGroup = 4;                         // remainder points per group (12 share x)
-constexpr int kPaperTerms = 6;                        // highest Taylor term of the remainders
 
 // Gauss-Legendre points and weights on [0, 1]
 struct GaussRule {
