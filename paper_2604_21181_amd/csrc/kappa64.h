@@ -2,6 +2,9 @@
 // root, without divisions (the series below max|k| R = 1/2 divide, as before).
 #pragma once
 
+#include <algorithm>
+#include <cmath>
+
 #include "p2_device.h"
 
 namespace mbem {
@@ -9,7 +12,12 @@ namespace mbem {
 // closed-form kernel constants, passed by value (uniform operands)
 struct PairConst {
     double ka, ki_re, ki_im, eps_re, eps_im, mu_re, mu_im, kmax;
+    double ka2, ki2_re, ki2_im;    // their squares
 };
+inline PairConst pair_const(double2 ka, double2 ki, double2 eps, double2 mu) {
+    return {ka.x, ki.x, ki.y, eps.x, eps.y, mu.x, mu.y, std::max(std::hypot(ka.x, ka.y), std::hypot(ki.x, ki.y)),
+            ka.x * ka.x, std::fma(ki.x, ki.x, -(ki.y * ki.y)), 2.0 * ki.x * ki.y};
+}
 
 // sqrt(x) and 1 / sqrt(x) for x > 0: the hardware estimate y (at least 24 bits)
 // and one third-order step, y (1 + e/2 + 3 e^2/8) with e = 1 - x y^2 formed
@@ -57,8 +65,7 @@ __device__ __forceinline__ Media64 media64(const PairConst &K, double R) {
     m.fi = ei * cx<double>{fma(3.0, ti, 3.0) - m.ti2.re, fma(-3.0, tr, -m.ti2.im)};
     m.ha = m.ta2 * ea;
     m.hi = m.ti2 * ei;
-    const cx<double> ki2 = {fma(K.ki_re, K.ki_re, -(K.ki_im * K.ki_im)), 2.0 * K.ki_re * K.ki_im};
-    m.d = (K.ka * K.ka) * ea - ki2 * ei;
+    m.d = K.ka2 * ea - cx<double>{K.ki2_re, K.ki2_im} * ei;
     return m;
 }
 

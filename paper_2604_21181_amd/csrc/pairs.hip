@@ -479,8 +479,7 @@ int pair_fill_run(mbem_op *op, bool deriv, hipStream_t s) {
     a.slot_ptr = m->d_pair_sptr;
     a.slot_row = m->d_pair_srow;
     a.K = op->d_kconst;
-    a.kc = {op->ka.x, op->ki.x, op->ki.y, op->eps_i.x, op->eps_i.y, op->mu_i.x, op->mu_i.y,
-            std::max(std::hypot(op->ka.x, op->ka.y), std::hypot(op->ki.x, op->ki.y))};
+    a.kc = pair_const(op->ka, op->ki, op->eps_i, op->mu_i);
     for (int o = 0; o < 3; ++o) a.Z[o] = (double2 *)op->K[o];
     if (nodal) {
         MBEM_TRY(nodal_table_f64(op, paper, s));

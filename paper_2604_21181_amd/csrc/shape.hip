@@ -1210,8 +1210,7 @@ __global__ void k_shape_out(int64_t nn, double scale, const double *__restrict__
 // --------------------------------------------------------------- host ---
 static ShapeConst shape_const(const mbem_op *op) {
     ShapeConst C;
-    C.kc = {op->ka.x, op->ki.x, op->ki.y, op->eps_i.x, op->eps_i.y, op->mu_i.x, op->mu_i.y,
-            std::max(std::abs(op->ka.x), std::hypot(op->ki.x, op->ki.y))};
+    C.kc = pair_const(op->ka, op->ki, op->eps_i, op->mu_i);
     C.iw = {op->iw.x, op->iw.y};
     return C;
 }

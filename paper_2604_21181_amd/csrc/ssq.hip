@@ -138,7 +138,7 @@ __device__ __forceinline__ void p2_values(double xi, double eta, double N[6]) {
 //   G_chi^s = -(chi_a - chi_i)/(4 pi R^2).
 __device__ __forceinline__ KScal<double> scalars_sing64(const PairConst &K, double rinv, double w) {
     const double r1 = w * 0.079577471545947667884 * rinv, r2 = r1 * rinv;
-    const cx<double> dk2 = {K.ka * K.ka - K.ki_re * K.ki_re + K.ki_im * K.ki_im, -2.0 * K.ki_re * K.ki_im};
+    const cx<double> dk2 = {K.ka2 - K.ki2_re, -K.ki2_im};
     KScal<double> o;
     o.D0 = r1 * dk2;
     o.df = (0.5 * r1) * dk2;
@@ -509,8 +509,7 @@ static int run(mbem_op *op, bool deriv, const FillBand *band, hipStream_t s) {
     a.order = op->p.ssq_order > 0 ? op->p.ssq_order : 4;
     if (a.order > kMaxSSQ) { set_error("ssq_order above 8 is not supported"); return MBEM_EINVAL; }
     a.K = op->d_kconst + 1;
-    a.kc = {op->ka.x, op->ki.x, op->ki.y, op->eps_i.x, op->eps_i.y, op->mu_i.x, op->mu_i.y,
-            std::max(std::hypot(op->ka.x, op->ka.y), std::hypot(op->ki.x, op->ki.y))};
+    a.kc = pair_const(op->ka, op->ki, op->eps_i, op->mu_i);
     for (int o = 0; o < 3; ++o) a.Z[o] = (TS *)(band ? band->Z[o] : op->K[o]);
     a.near = band ? NearView{} : op->near_view();
     double *tab = nullptr;

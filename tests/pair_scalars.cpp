@@ -53,7 +53,7 @@ static void print(const char *name, double got, double yardstick, double norm) {
 
 static void scalars(double k0, double er, double ei) {
     std::complex<double> ki = k0 * std::sqrt(std::complex<double>(er, ei));
-    const PairConst K = {k0, ki.real(), ki.imag(), er, ei, 1.0, 0.0, std::max(k0, std::abs(ki))};
+    const PairConst K = pair_const({k0, 0.0}, {ki.real(), ki.imag()}, {er, ei}, {1.0, 0.0});
     std::mt19937_64 rng(7);
     std::uniform_real_distribution<double> u(-1.0, 1.0);
     double got[5] = {}, yard[5] = {}, norm[5] = {};
