@@ -23,8 +23,8 @@
 // valence.
 //
 // Measured on the 1280-triangle sphere (10 248 unknowns), regular pairs by
-// colour classes -> here: 6.9 -> 3.8 ms (7 points), 22.8 -> 7.0 ms (12
-// points), 9.4 -> 7.2 ms (7 points, node-attached tangents), 62.5 -> 21.8 ms
+// colour classes -> here: 6.9 -> 3.8 ms (7 points), 22.8 -> 7.1 ms (12
+// points), 9.4 -> 7.5 ms (7 points, node-attached tangents), 62.5 -> 21.9 ms
 // (12 points, node-attached).  Of the 3.8 ms the tiles alone take 2.85 ms:
 // LDS and the non-FP64 half of their vector instructions (FP64 units 22 %
 // busy); the gather alone takes 1.6 ms, of which 0.9 are not hidden.  The

@@ -690,8 +690,8 @@ __global__ __launch_bounds__(256) void k_qp_backprop(int64_t nt, int64_t n2, con
 // Columns per side: 6 x 3 positions, 6 x 3 of each tangent; NODAL: 6 x 12 of the
 // adjoints of m, which the tangents' follow from at the end.
 // Bound by FP64 vector instructions at two wavefronts per SIMD.  1280 triangles:
-// 3.80 -> 1.57 ms, node-attached tangents 2.07 (one wavefront per SIMD, nothing
-// spilled: 2.23 and 2.15; all of a point kept live: 108 spills in place of 48).
+// 3.80 -> 1.63 ms, node-attached tangents about 2.1 (one wavefront per SIMD, nothing
+// spilled: 2.23 and 2.15; all of a point kept live: 108 spills in place of 46).
 struct ShapeSsqArgs {
     int64_t n2, npairs;
     const int32_t *pairs, *tri;

@@ -20,12 +20,12 @@
 // lane.  The triangles' positions and tangents are polynomials in LDS: as
 // uniform node data they filled the scalar file (170 - 214 spills).  On the
 // 1280-triangle sphere, with one P2 sum per node and one product per point
-// before -> now: 1.51 -> 1.12 ms; node-attached tangents 3.25 -> 2.60;
-// paper's scheme 1.65 -> 1.08, node-attached 3.75 -> 2.70; 80 triangles
-// 177 -> 114 us (136 us with a workgroup per pair instead of per two regions).
+// before -> now: 1.51 -> 1.16 ms; node-attached tangents 3.25 -> 2.63;
+// paper's scheme 1.65 -> 1.09, node-attached 3.75 -> 2.67; 80 triangles
+// 177 -> 115 us (136 us with a workgroup per pair instead of per two regions).
 // Blocks of a 70-, an 80- and a 320-triangle body, four media, both rules and
 // bases, against an 80-bit evaluation, with one P2 sum per node -> now: K1 5.0e-16
-// to 1.6e-15 -> 4.9e-16 to 1.8e-15 (12-point rule at large |k|: up to 8 % more, else
+// to 1.6e-15 -> 4.9e-16 to 1.7e-15 (12-point rule at large |k|: up to 8 % more, else
 // equal or less), K2^eps 5.9e-16 to 1.9e-14 -> 4.0e-16 to 3.2e-15, K2^mu 2.9 to
 // 5.9e-16 -> 2.8 to 5.1e-16.
 #include <algorithm>
